@@ -248,6 +248,8 @@ craft_status craft_pack_weights(int32_t dtype, int32_t H, int32_t I, const void 
  *   craft_pack_weights (8 bytes per lane instead of 16), the scales appended to the buffers.
  *     gate/up codes DEVICE [I][H], down codes DEVICE [H][I]; scales [I], [I], [H]
  *     packed buffers DEVICE, 16-byte aligned, of craft_pack_weights_e4m3_bytes() bytes
+ * craft_quantize_pack_e4m3: the two in one pass over the bf16 matrices of one expert (as for
+ *   craft_pack_weights), with the same codes, scales and packed bytes and no codes kept.
  */
 craft_status craft_quantize_e4m3(const void *w, int64_t rows, int32_t K, uint8_t *codes,
                                  float *scale, void *stream);
@@ -258,6 +260,9 @@ craft_status craft_pack_weights_e4m3(int32_t H, int32_t I, const uint8_t *gate_c
                                      const float *gate_scale, const float *up_scale,
                                      const float *down_scale, void *packed_gateup,
                                      void *packed_down, void *stream);
+craft_status craft_quantize_pack_e4m3(int32_t H, int32_t I, const void *w_gate, const void *w_up,
+                                      const void *w_down, void *packed_gateup, void *packed_down,
+                                      void *stream);
 
 /* ------------------------------------------------------------------- execution
  * One rank's share of one MoE layer (Sec. 2.1) under the plan:

@@ -69,6 +69,7 @@ EXPORTS = {
     "craft_pack_weights_e4m3_bytes": (ctypes.c_int, [c_i32, c_i32, P(c_sz), P(c_sz)]),
     "craft_pack_weights_e4m3": (ctypes.c_int, [c_i32, c_i32, c_vp, c_vp, c_vp, c_vp, c_vp, c_vp, c_vp, c_vp,
                                                c_vp]),
+    "craft_quantize_pack_e4m3": (ctypes.c_int, [c_i32, c_i32, c_vp, c_vp, c_vp, c_vp, c_vp, c_vp]),
     "craft_moe_rank_forward_workspace": (ctypes.c_int, [c_vp, c_i32, c_i32, P(FwdArgs), P(c_sz)]),
     "craft_moe_rank_forward": (ctypes.c_int, [c_vp, c_i32, c_i32, P(FwdArgs), c_vp]),
     "craft_moe_rank_forward_static": (ctypes.c_int, [c_vp, c_i32, c_i32, P(FwdArgs), c_vp]),
@@ -333,15 +334,14 @@ def pack_weights_e4m3(w_gate, w_up, w_down, stream=None):
     """bf16 device matrices of one expert -> E4M3-packed (gateup, down) device buffers."""
     import torch
     I, H = w_gate.shape
-    q = [quantize_e4m3(m, stream) for m in (w_gate, w_up, w_down)]
+    for m, shape in ((w_gate, (I, H)), (w_up, (I, H)), (w_down, (H, I))):
+        assert m.dtype == torch.bfloat16 and tuple(m.shape) == shape
     a, b = c_sz(), c_sz()
     _check(lib().craft_pack_weights_e4m3_bytes(H, I, a, b), "craft_pack_weights_e4m3_bytes")
     pgu = torch.empty(a.value, dtype=torch.uint8, device=w_gate.device)
     pdn = torch.empty(b.value, dtype=torch.uint8, device=w_gate.device)
-    _check(lib().craft_pack_weights_e4m3(H, I, _dev(q[0][0]), _dev(q[1][0]), _dev(q[2][0]),
-                                         _dev(q[0][1]), _dev(q[1][1]), _dev(q[2][1]),
-                                         _dev(pgu), _dev(pdn), _stream_ptr(stream)),
-           "craft_pack_weights_e4m3")
+    _check(lib().craft_quantize_pack_e4m3(H, I, _dev(w_gate), _dev(w_up), _dev(w_down), _dev(pgu), _dev(pdn),
+                                          _stream_ptr(stream)), "craft_quantize_pack_e4m3")
     return pgu, pdn
 
 

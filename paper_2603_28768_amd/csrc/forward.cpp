@@ -415,6 +415,18 @@ craft_status craft_pack_weights_e4m3(int32_t H, int32_t I, const uint8_t *gate_c
                                                                                           : CRAFT_EHIP;
 }
 
+craft_status craft_quantize_pack_e4m3(int32_t H, int32_t I, const void *w_gate, const void *w_up,
+                                      const void *w_down, void *packed_gateup, void *packed_down,
+                                      void *stream) {
+    if (H <= 0 || I <= 0 || H % 8 || I % 8) return CRAFT_EINVAL;
+    if (!w_gate || !w_up || !w_down || !packed_gateup || !packed_down) return CRAFT_EINVAL;
+    if (!aligned(w_gate, 16) || !aligned(w_up, 16) || !aligned(w_down, 16) ||
+        !aligned(packed_gateup, 16) || !aligned(packed_down, 16))
+        return CRAFT_EINVAL;
+    return launch_quantize_pack_e4m3(H, I, w_gate, w_up, w_down, packed_gateup, packed_down, as_stream(stream)) ==
+                   hipSuccess ? CRAFT_OK : CRAFT_EHIP;
+}
+
 craft_status craft_moe_rank_forward_workspace(const craft_plan_t *plan, int32_t layer, int32_t rank,
                                               const craft_fwd_args *a, size_t *bytes) {
     if (!bytes) return CRAFT_EINVAL;

@@ -146,6 +146,8 @@ hipError_t launch_pack(int32_t H, int32_t I, const void *wg, const void *wu, con
 void packed_sizes_e4m3(int32_t H, int32_t I, size_t *gateup_bytes, size_t *down_bytes);
 hipError_t launch_quantize_e4m3(const void *w, int64_t rows, int32_t K, uint8_t *codes, float *scale,
                                 hipStream_t s);
+hipError_t launch_quantize_pack_e4m3(int32_t H, int32_t I, const void *wg, const void *wu, const void *wd,
+                                     void *pgu, void *pdn, hipStream_t s);
 hipError_t launch_pack_e4m3(int32_t H, int32_t I, const uint8_t *cg, const uint8_t *cu, const uint8_t *cd,
                             const float *sg, const float *su, const float *sd, void *pgu, void *pdn,
                             hipStream_t s);

@@ -678,3 +678,35 @@ def test_full_size_qwen3_with_e4m3_weights(torch_cuda):
     case = Case(synth.CONFIGS["qwen3"], w8=True)
     g = case.heaviest
     _check_rank(torch_cuda, case, g, packed=True, cover=True)          # every token
+
+
+@pytest.mark.parametrize("H,I,scale", [
+    (72, 40, 1.0),                   # one row block, ragged rows and steps, padding groups
+    (264, 520, 0.02),                # ragged last row block
+    (4096, 136, 30.0), (136, 2056, 1.0), (5000, 24, 1.0),      # 2, 4 and 8 step pairs per wave
+    (8200, 16, 1.0),                 # rows that do not fit the registers
+    (256, 64, 2.0 ** -75), (256, 64, 2.0 ** 90)])              # scales outside the reciprocal's range
+def test_quantize_and_pack_in_one_pass_is_the_two_steps(torch_cuda, H, I, scale):
+    # codes and scales are the checker's, and the packed bytes those of packing them
+    torch = torch_cuda
+    print(f"quantize+pack H={H} I={I} scale={scale}", flush=True)
+    g = np.random.default_rng(H * 1000 + I)
+    mats = [synth.round_to_storage((g.standard_normal(s) * scale).astype(np.float32), "bf16")
+            for s in ((I, H), (I, H), (H, I))]
+    mats[0][3] = 0.0
+    mats[1][2, 5] = np.inf
+    dev = [binding.to_device(m, "bf16") for m in mats]
+    pgu, pdn = binding.pack_weights_e4m3(*dev)
+    q = [binding.quantize_e4m3(m) for m in dev]
+    want_gu, want_dn = torch.full_like(pgu, 0xAA), torch.full_like(pdn, 0xAA)
+    ptr = binding._dev
+    assert binding.lib().craft_pack_weights_e4m3(H, I, ptr(q[0][0]), ptr(q[1][0]), ptr(q[2][0]), ptr(q[0][1]), ptr(q[1][1]),
+                                                 ptr(q[2][1]), ptr(want_gu), ptr(want_dn), binding._stream_ptr()) == 0
+    torch.cuda.synchronize()
+    for m, (codes, sc) in zip(mats, q):
+        want_c, want_s = oracle.quantize_e4m3(m)
+        finite = np.isfinite(m).all(axis=1)
+        assert np.array_equal(sc.cpu().numpy(), want_s)
+        assert np.array_equal(codes.cpu().numpy()[finite], want_c[finite])
+    assert torch.equal(pgu, want_gu)
+    assert torch.equal(pdn, want_dn)
