@@ -676,33 +676,6 @@ __global__ __launch_bounds__(256, 1) void ffn_packed_kernel(FfnArgs a) {
     }
 }
 
-// One 16-byte chunk of the packed stream per thread: chunk ((step * groups + group) * 2 + half) * 64 + lane.
-//   gate/up : group g = output columns 16g..16g+15; half 0 = gate rows 16g..16g+15, half 1 = the
-//             up rows of the same columns
-//   down    : group g = output columns 32g..32g+31; half h = down rows 32g+16h..+15
-// Lane l of 32-wide step s holds row (l & 15) of its half, contraction elements 32s + 8(l>>4) .. +7:
-// the row operand of one v_mfma_f32_16x16x32_bf16.  Rows and contraction elements past the matrix are zero.
-__global__ void pack_kernel(const unsigned short *wa, const unsigned short *wb, int rows, int K,
-                            int gc, int64_t nchunks, int ksteps, uint4 *out) {
-    const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= nchunks) return;
-    const int l = (int)(c & 63);
-    const int h = (int)(c >> 6) & 1;
-    const int64_t sg = c >> 7;                   // step-major
-    const int64_t ngroups = nchunks / 128 / ksteps;   // padded to whole tiles of 8 groups
-    const int s = (int)(sg / ngroups);
-    const int64_t g = sg % ngroups;
-    const int r = l & 15;
-    const int k0 = 32 * s + 8 * (l >> 4);
-    int64_t row;
-    const unsigned short *src;
-    if (gc == 16) { row = g * 16 + r; src = h ? wb : wa; }
-    else { row = g * 32 + 16 * h + r; src = wa; }
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if (row < rows && k0 < K) v = *reinterpret_cast<const uint4 *>(src + row * K + k0);
-    out[c] = v;
-}
-
 template <bool GATEUP>
 hipError_t launch_packed(const FfnArgs &a, hipStream_t s) {
     if (a.nslots <= 0 || a.max_rows <= 0) return hipSuccess;
@@ -721,26 +694,5 @@ hipError_t launch_packed(const FfnArgs &a, hipStream_t s) {
 
 hipError_t launch_gateup_packed(const FfnArgs &a, hipStream_t s) { return launch_packed<true>(a, s); }
 hipError_t launch_down_packed(const FfnArgs &a, hipStream_t s) { return launch_packed<false>(a, s); }
-
-void packed_sizes(int32_t H, int32_t I, size_t *gateup_bytes, size_t *down_bytes) {
-    const size_t gu_groups = ((size_t)(I + 15) / 16 + 7) / 8 * 8, gu_steps = (size_t)(H + 255) / 256 * 16;
-    const size_t dn_groups = ((size_t)(H + 31) / 32 + 7) / 8 * 8, dn_steps = (size_t)(I + 255) / 256 * 16;
-    *gateup_bytes = gu_groups * gu_steps * 1024;
-    *down_bytes = dn_groups * dn_steps * 1024;
-}
-
-hipError_t launch_pack(int32_t H, int32_t I, const void *wg, const void *wu, const void *wd,
-                       void *pgu, void *pdn, hipStream_t s) {
-    size_t gub, dnb;
-    packed_sizes(H, I, &gub, &dnb);
-    const int64_t c1 = (int64_t)(gub / 16), c2 = (int64_t)(dnb / 16);
-    hipLaunchKernelGGL(pack_kernel, dim3((unsigned)((c1 + 255) / 256)), dim3(256), 0, s,
-                       static_cast<const unsigned short *>(wg), static_cast<const unsigned short *>(wu),
-                       I, H, 16, c1, (H + 255) / 256 * 8, static_cast<uint4 *>(pgu));
-    hipLaunchKernelGGL(pack_kernel, dim3((unsigned)((c2 + 255) / 256)), dim3(256), 0, s,
-                       static_cast<const unsigned short *>(wd), static_cast<const unsigned short *>(wd),
-                       H, I, 32, c2, (I + 255) / 256 * 8, static_cast<uint4 *>(pdn));
-    return hipGetLastError();
-}
 
 }  // namespace craft

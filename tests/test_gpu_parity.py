@@ -486,6 +486,28 @@ def test_packed_weights_layout(torch_cuda):
     assert np.array_equal(pgu, gu) and np.array_equal(pdn, dn)
 
 
+@pytest.mark.parametrize("H,I", [(1024, 136), (1032, 40), (2056, 1288), (8, 8)])
+def test_packed_weights_layout_over_several_workgroups(torch_cuda, H, I):
+    # parts of the contraction: exactly one, one and a ragged second, several on both sides
+    g = np.random.default_rng(H + I)
+    mats = [synth.round_to_storage(g.standard_normal(s).astype(np.float32), "bf16")
+            for s in ((I, H), (I, H), (H, I))]
+    pgu, pdn = (synth.bf16_bits_to_f32(p.cpu().numpy().view(np.uint16))
+                for p in binding.pack_weights(*[binding.to_device(m, "bf16") for m in mats]))
+
+    def fragments(W, rows, ksteps):                 # [rows / 16][ksteps][lane][8], zero padded
+        P = np.zeros((rows, ksteps * 32), np.float32)
+        P[:W.shape[0], :W.shape[1]] = W
+        return P.reshape(rows // 16, 16, ksteps, 4, 8).transpose(0, 2, 3, 1, 4).reshape(rows // 16, ksteps, 64, 8)
+
+    gu_rows, dn_rows = (I + 127) // 128 * 128, (H + 255) // 256 * 256
+    gk, dk = (H + 255) // 256 * 8, (I + 255) // 256 * 8
+    gu = np.stack([fragments(mats[0], gu_rows, gk), fragments(mats[1], gu_rows, gk)], axis=1)   # [group][half][step]
+    assert np.array_equal(pgu, gu.transpose(2, 0, 1, 3, 4).reshape(-1))
+    dn = fragments(mats[2], dn_rows, dk).reshape(dn_rows // 32, 2, dk, 64, 8)
+    assert np.array_equal(pdn, dn.transpose(2, 0, 1, 3, 4).reshape(-1))
+
+
 def test_empty_batch(torch_cuda):
     torch = torch_cuda
     cfg = synth.scaled(synth.CONFIGS["tiny"], T=0)
