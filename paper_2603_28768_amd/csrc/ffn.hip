@@ -58,7 +58,7 @@ __global__ __launch_bounds__(256, 2) void ffn_bf16_kernel(FfnArgs a) {
     const int mf0 = wm * 64, mf1 = wm * 64 + 32;   // activation-row fragments
     const int frag_off = (lane & 31) * ROWB + (lane >> 5) * 16;
 
-    for (int64_t w = xcd_major_id(); w < total; w += gridDim.x) {
+    for (int64_t w = first_tile(total); w < total; w += gridDim.x) {
         const Tile t = decode_tile(a, mt_start, w, nt, BN, GATEUP ? a.frags_gu : a.frags_dn);
         const unsigned short *wa = static_cast<const unsigned short *>(
             GATEUP ? a.w_gate[t.slot] : a.w_down[t.slot]);
@@ -189,7 +189,7 @@ __global__ __launch_bounds__(256) void ffn_f32_kernel(FfnArgs a) {
     const int32_t lo_pos = a.slot_off[a.s_lo];
     const float *xin = static_cast<const float *>(GATEUP ? a.x : a.act);
 
-    for (int64_t w = xcd_major_id(); w < total; w += gridDim.x) {
+    for (int64_t w = ((int64_t)blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8; w < total; w += gridDim.x) {
         const Tile t = decode_tile(a, mt_start, w, nt, FN, GATEUP ? a.frags_gu : a.frags_dn);
         const float *wa = static_cast<const float *>(GATEUP ? a.w_gate[t.slot] : a.w_down[t.slot]);
         const float *wb = GATEUP ? static_cast<const float *>(a.w_up[t.slot]) : wa;

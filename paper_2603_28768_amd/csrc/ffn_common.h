@@ -101,11 +101,15 @@ static __device__ __forceinline__ Tile decode_tile(const FfnArgs &a, const TileT
     return decode_tile_in(a.nslots, tt.mt_start, tt.order, tt.slot_off, w, nt, bn, fmax, blocked);
 }
 
-// Workgroups are dealt to the 8 XCDs round-robin; give each XCD a contiguous run of the
-// tile list per sweep so that tiles sharing weights meet in one L2.
-static __device__ __forceinline__ int64_t xcd_major_id() {
+// Workgroups are dealt to the 8 XCDs round-robin; give each XCD a contiguous run of the first
+// gridDim.x tiles, so that tiles sharing weights meet in one L2.  A list shorter than the grid is
+// shared evenly: runs of gridDim.x / 8 would leave whole XCDs, and their paths to memory, without
+// a tile (two live slots of H = 7168, I = 2048 with 32 column tiles each ran on two of the eight).
+// Returns `total` or more where there is nothing to do.  The grid is a multiple of 8.
+static __device__ __forceinline__ int64_t first_tile(int64_t total) {
     const int64_t g = gridDim.x, b = blockIdx.x;
-    return (b % 8) * (g / 8) + b / 8;
+    const int64_t run = total < g ? (total + 7) / 8 : g / 8;
+    return b / 8 < run ? (b % 8) * run + b / 8 : total;
 }
 
 static __device__ __forceinline__ uint32_t bf16_rne(float f) {
@@ -125,6 +129,46 @@ typedef float f32x2_t __attribute__((ext_vector_type(2)));
 static __device__ __forceinline__ uint32_t bf16_pair(float lo, float hi) {
     const f32x2_t v = {lo, hi};
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
+}
+
+// A packed stream holds a multiple of kPackGroups column groups (whole full-width tiles).
+constexpr int kPackGroups = 8;
+typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
+// A weight fragment as it sits in registers: 8 bf16 values, or 8 E4M3 codes that are widened
+// (exactly) right in front of the MFMAs that use them.
+template <bool W8> struct WFrag { typedef bf16x8_t type; };
+template <> struct WFrag<true> { typedef u32x2_t type; };
+
+static __device__ __forceinline__ bf16x8_t widen(bf16x8_t w) { return w; }
+static __device__ __forceinline__ bf16x8_t widen(u32x2_t w) {
+    // two codes per conversion (bytes 0,1 / 2,3 of a word), then pairs of fp32 to bf16
+    const f32x2_t a = __builtin_amdgcn_cvt_pk_f32_fp8(w[0], false), b = __builtin_amdgcn_cvt_pk_f32_fp8(w[0], true);
+    const f32x2_t c = __builtin_amdgcn_cvt_pk_f32_fp8(w[1], false), d = __builtin_amdgcn_cvt_pk_f32_fp8(w[1], true);
+    typedef unsigned int u32x4v __attribute__((ext_vector_type(4)));
+    const u32x4v r = {bf16_pair(a[0], a[1]), bf16_pair(b[0], b[1]), bf16_pair(c[0], c[1]), bf16_pair(d[0], d[1])};
+    return __builtin_bit_cast(bf16x8_t, r);
+}
+
+// Every global load of the contraction loop is addressed as a wave-uniform 64-bit base (scalar
+// registers, advanced with scalar adds) plus a 32-bit byte offset per lane: no 64-bit vector
+// arithmetic per request, and half the address registers to hand to the memory pipeline.
+typedef const unsigned char *ubase_t;
+static __device__ __forceinline__ ubase_t uniform_base(const void *p) {
+    const uint64_t v = reinterpret_cast<uint64_t>(p);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+    return reinterpret_cast<ubase_t>(((uint64_t)hi << 32) | lo);
+}
+// A weight fragment that no other tile of the launch reads (a cold slot's: it has one
+// row-tile): a streaming load, which leaves the L2 to the weights and rows that are shared.
+template <bool ONCE, typename F>
+static __device__ __forceinline__ F wload(ubase_t base, uint32_t &off) {
+    // the lane's offset never changes inside a tile; widened to 64 bits once outside the loop it
+    // would no longer be recognised as the 32-bit offset of a scalar-base request
+    // (redefined in place, so that no copy is made)
+    asm volatile("" : "+v"(off));
+    const F __attribute__((address_space(1))) *p = (const F __attribute__((address_space(1))) *)(base + off);
+    if (ONCE) return __builtin_nontemporal_load(p);
+    return *p;
 }
 
 }  // namespace craft

@@ -64,7 +64,6 @@ constexpr int ring_depth(int nxa, bool gateup) { return nxa >= 3 && !gateup ? 4 
 // there its ring runs twice as far ahead as the tile's own.
 constexpr int rider_ring(int nxf, bool w8) { return w8 || nxf <= 4 ? 8 : 4; }
 constexpr int NG = 2;             // column groups per wave in a full-width tile (1 in a half-width one)
-constexpr int kPackGroups = 8;    // the packed stream is padded to whole full-width tiles
 // An LDS stage holds one 64-wide slab of up to 256 activation rows, 128 bytes per row, no
 // padding: the rows arrive by loads that write LDS directly, 64 lanes x 16 bytes to consecutive
 // addresses.  So that the fragment reads (16 rows at one contraction offset) still spread over
@@ -74,21 +73,6 @@ constexpr int XROWB = 64 * 2;
 constexpr int XSTAGEB = kBM_packed * XROWB;
 constexpr int kStages = 4;
 
-typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
-// A weight fragment as it sits in the ring: 8 bf16 values, or 8 E4M3 codes that are widened
-// (exactly) right in front of the MFMAs that use them.
-template <bool W8> struct WFrag { typedef bf16x8_t type; };
-template <> struct WFrag<true> { typedef u32x2_t type; };
-
-static __device__ __forceinline__ bf16x8_t widen(bf16x8_t w) { return w; }
-static __device__ __forceinline__ bf16x8_t widen(u32x2_t w) {
-    // two codes per conversion (bytes 0,1 / 2,3 of a word), then pairs of fp32 to bf16
-    const f32x2_t a = __builtin_amdgcn_cvt_pk_f32_fp8(w[0], false), b = __builtin_amdgcn_cvt_pk_f32_fp8(w[0], true);
-    const f32x2_t c = __builtin_amdgcn_cvt_pk_f32_fp8(w[1], false), d = __builtin_amdgcn_cvt_pk_f32_fp8(w[1], true);
-    typedef unsigned int u32x4v __attribute__((ext_vector_type(4)));
-    const u32x4v r = {bf16_pair(a[0], a[1]), bf16_pair(b[0], b[1]), bf16_pair(c[0], c[1]), bf16_pair(d[0], d[1])};
-    return __builtin_bit_cast(bf16x8_t, r);
-}
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));      // native vector: stays in VGPRs
 template <bool W8> static __device__ __forceinline__ typename WFrag<W8>::type zero_fragment();
 template <> __device__ __forceinline__ bf16x8_t zero_fragment<false>() {
@@ -98,15 +82,6 @@ template <> __device__ __forceinline__ bf16x8_t zero_fragment<false>() {
 template <> __device__ __forceinline__ u32x2_t zero_fragment<true>() {
     const u32x2_t z = {0u, 0u};
     return z;
-}
-// Every global load of the contraction loop is addressed as a wave-uniform 64-bit base (scalar
-// registers, advanced with scalar adds) plus a 32-bit byte offset per lane: no 64-bit vector
-// arithmetic per request, and half the address registers to hand to the memory pipeline.
-typedef const unsigned char *ubase_t;
-static __device__ __forceinline__ ubase_t uniform_base(const void *p) {
-    const uint64_t v = reinterpret_cast<uint64_t>(p);
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-    return reinterpret_cast<ubase_t>(((uint64_t)hi << 32) | lo);
 }
 // 16 bytes per lane from base + off straight into LDS at lds + 16 * lane (lds: the byte address
 // of the wave's 1 KiB destination, wave-uniform; it goes through M0, which the compiler keeps
@@ -135,19 +110,6 @@ static __device__ __forceinline__ int lane_index() {
     asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
     return lane;
 }
-// A weight fragment that no other tile of the launch reads (a cold slot's: it has one
-// row-tile): a streaming load, which leaves the L2 to the weights and rows that are shared.
-template <bool ONCE, typename F>
-static __device__ __forceinline__ F wload(ubase_t base, uint32_t &off) {
-    // the lane's offset never changes inside a tile; widened to 64 bits once outside the loop it
-    // would no longer be recognised as the 32-bit offset of a scalar-base request
-    // (redefined in place, so that no copy is made)
-    asm volatile("" : "+v"(off));
-    const F __attribute__((address_space(1))) *p = (const F __attribute__((address_space(1))) *)(base + off);
-    if (ONCE) return __builtin_nontemporal_load(p);
-    return *p;
-}
-
 // Where a tile's operands come from.  The bases are wave-uniform; the weight offsets woff /
 // wroff are the ring's next refill (the step that many ahead, held at the last step of the
 // stream once it is reached) and move on by one step's worth of fragments per step.
@@ -614,7 +576,7 @@ __global__ __launch_bounds__(256, 1) void ffn_packed_kernel(FfnArgs a) {
         return t;
     };
 
-    int64_t w = xcd_major_id();                    // first tile by position, the rest on demand
+    int64_t w = first_tile(total);                    // first tile by position, the rest on demand
     while (w < total) {
         int32_t claimed = 0;                       // thread 0: the counter's answer, fetched inside the tile
         if (w < hot_tiles) {

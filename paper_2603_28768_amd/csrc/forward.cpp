@@ -21,7 +21,7 @@ inline size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // ---- workspace layout of one forward -------------------------------------------------
 struct Layout {
-    size_t ctrl, ids, w, lrank, dest, src, hist, chunk_tot, chunk_base, gate_logits, gate_ws, gate_ws_bytes, counts, slot_cnt, slot_off, mt_start, order, act, y, total;
+    size_t ctrl, ids, w, lrank, dest, src, hist, chunk_tot, chunk_base, gate_logits, gate_ws, gate_ws_bytes, counts, slot_cnt, slot_off, mt_start, order, act, y, xpk, total;
     int64_t max_rows, NB;
 };
 
@@ -34,7 +34,7 @@ size_t gate_workspace_bytes(int32_t dtype, int64_t T, int32_t H, int32_t E) {
 }
 
 Layout make_layout(int64_t T, int32_t k, int32_t E, int32_t S, int32_t nslots, int32_t H, int32_t I,
-                   int32_t dtype, int64_t max_rows_arg, bool own_gate) {
+                   int32_t dtype, int64_t max_rows_arg, bool own_gate, bool stream) {
     Layout L;
     const int64_t A = T * k;
     const size_t es = dtype == CRAFT_BF16 ? 2 : 4;
@@ -62,8 +62,9 @@ Layout make_layout(int64_t T, int32_t k, int32_t E, int32_t S, int32_t nslots, i
     L.slot_off = take((size_t)(S + 1) * 4);
     L.mt_start = take((size_t)(nslots + 1) * 4 * 2);
     L.order = take((size_t)(nslots + 1) * 4);
-    L.act = take((size_t)L.max_rows * I * es);
-    L.y = take((size_t)L.max_rows * H * es);
+    L.act = take(stream ? stream_bytes(L.max_rows, nslots, I) : (size_t)L.max_rows * I * es);
+    // the token rows of a small batch are done with when the down GEMM writes y
+    L.y = L.xpk = take(std::max((size_t)L.max_rows * H * es, stream ? stream_bytes(L.max_rows, nslots, H) : 0));
     L.total = off;
     return L;
 }
@@ -156,7 +157,7 @@ double ffn_makespan(const std::vector<double> &slot_rows, int32_t frags, bool ev
     return end;
 }
 
-struct tile_choice { int32_t frags[2]; bool riders[2]; };
+struct tile_choice { int32_t frags[2]; bool riders[2]; bool stream = false; };
 
 tile_choice choose_tiles(const craft_plan_t *plan, int32_t layer, int32_t rank, int64_t T, int32_t k,
                          int32_t H, int32_t I, int32_t cus) {
@@ -174,6 +175,7 @@ tile_choice choose_tiles(const craft_plan_t *plan, int32_t layer, int32_t rank, 
         rows.push_back(est >= 0.2 ? std::max(1.0, est) : 0.0);
     }
     std::sort(rows.begin(), rows.end(), std::greater<double>());
+    best.stream = rows.empty() || rows[0] <= (double)kStreamRows;
     for (int kind = 0; kind < 2; ++kind) {
         const int64_t K = kind == 0 ? H : I, N = kind == 0 ? I : H;
         const int64_t nt = kind == 0 ? (N + 127) / 128 : (N + 255) / 256;
@@ -209,10 +211,9 @@ tile_choice choose_tiles(const craft_plan_t *plan, int32_t layer, int32_t rank, 
 
 // The choice for (layer, rank, T, k, H, I) is made once and kept with the plan: later forwards
 // of the same shape find it by walking a short insert-only list, without a lock.
-tile_choice tiles_for(const craft_plan_t *plan, int32_t layer, int32_t rank, const craft_fwd_args *a,
-                      bool packed) {
+tile_choice tile_choice_of(const craft_plan_t *plan, int32_t layer, int32_t rank, const craft_fwd_args *a,
+                           bool packed, bool may_stream) {
     if (a->dtype != CRAFT_BF16) return {{kFragsF32, kFragsF32}, {false, false}};
-    if (!packed) return {{kFragsBf16, kFragsBf16}, {false, false}};
     craft_rank_state &rs = plan->state(layer, rank);
     auto find = [&]() -> const craft_tile_choice * {
         for (const craft_tile_choice *t = rs.tiles.load(std::memory_order_acquire); t; t = t->next)
@@ -226,22 +227,34 @@ tile_choice tiles_for(const craft_plan_t *plan, int32_t layer, int32_t rank, con
         if (!hit) {
             const tile_choice c = choose_tiles(plan, layer, rank, a->T, a->k, a->H, a->I, cached_num_cu());
             craft_tile_choice *n = new craft_tile_choice{a->T, a->k, a->H, a->I, {c.frags[0], c.frags[1]},
-                                                         {c.riders[0], c.riders[1]},
+                                                         {c.riders[0], c.riders[1]}, c.stream,
                                                          rs.tiles.load(std::memory_order_relaxed)};
             rs.tiles.store(n, std::memory_order_release);
             hit = n;
         }
     }
-    tile_choice c{{hit->frags[0], hit->frags[1]}, {hit->riders[0], hit->riders[1]}};
-    // the caller's own heights: riders wherever such tiles can carry them, unless told
+    tile_choice c{{hit->frags[0], hit->frags[1]}, {hit->riders[0], hit->riders[1]}, false};
     const int32_t rows_arg[2] = {a->tile_rows_gateup, a->tile_rows_down};
     const int32_t riders_arg[2] = {a->riders_gateup, a->riders_down};
+    const bool told = rows_arg[0] || rows_arg[1] || riders_arg[0] || riders_arg[1];
+    // the streaming kernels address x and a weight matrix by 32-bit byte offsets (the packed
+    // kernels' sizes are checked with the other arguments)
+    const int64_t limit = (int64_t)1 << 32;
+    if (may_stream && hit->stream && !(packed && told) && a->T * (int64_t)a->H * 2 < limit && (int64_t)a->I * a->H * 2 < limit)
+        return {{kStreamRows / 32, kStreamRows / 32}, {false, false}, true};
+    if (!packed) return {{kFragsBf16, kFragsBf16}, {false, false}};
+    // the caller's own heights: riders wherever such tiles can carry them, unless told
     for (int kind = 0; kind < 2; ++kind) {
         if (rows_arg[kind]) { c.frags[kind] = rows_arg[kind] / 32; c.riders[kind] = true; }
         if (riders_arg[kind]) c.riders[kind] = riders_arg[kind] > 0;
         c.riders[kind] = c.riders[kind] && std::abs(c.frags[kind]) <= kRiderHostFrags;
     }
     return c;
+}
+
+tile_choice tiles_for(const craft_plan_t *plan, int32_t layer, int32_t rank, const craft_fwd_args *a, bool packed) {
+    const int32_t S = (int32_t)plan->layers[layer].slot_expert.size();
+    return tile_choice_of(plan, layer, rank, a, packed, small_dispatch(a->T, S));
 }
 
 craft_status check_fwd(const craft_plan_t *plan, int32_t layer, int32_t rank, const craft_fwd_args *a) {
@@ -289,7 +302,7 @@ craft_status craft_router_logits(int32_t dtype, const void *x, const void *w_rou
     if (st != CRAFT_OK) return st;
     const bool split = workspace && need > 0 && workspace_bytes >= need;
     RouterArgs ra{dtype, x, w_router, T, H, E, logits, cached_num_cu(),
-                  split ? static_cast<float *>(workspace) : nullptr, 1};
+                  split ? static_cast<float *>(workspace) : nullptr, 1, false};
     return launch_router_logits(ra, as_stream(stream)) == hipSuccess ? CRAFT_OK : CRAFT_EHIP;
 }
 
@@ -298,7 +311,7 @@ craft_status craft_route_topk(const float *logits, int64_t T, int32_t E, int32_t
     if (T < 0 || E <= 0 || E > 1024 || k <= 0 || k > E || k > 64) return CRAFT_EINVAL;
     if (T == 0) return CRAFT_OK;
     if (!logits || !ids || !w || !aligned(logits, 4) || !aligned(ids, 4) || !aligned(w, 4)) return CRAFT_EINVAL;
-    RouteArgs ra{logits, T, E, k, renormalize ? 1 : 0, ids, w, nullptr, nullptr, nullptr};
+    RouteArgs ra{logits, T, E, k, renormalize ? 1 : 0, ids, w, nullptr, nullptr, nullptr, 1};
     return launch_route(ra, as_stream(stream)) == hipSuccess ? CRAFT_OK : CRAFT_EHIP;
 }
 
@@ -435,8 +448,12 @@ craft_status craft_moe_rank_forward_workspace(const craft_plan_t *plan, int32_t 
     const craft_layer_plan &lp = plan->layers[layer];
     const int32_t nslots = lp.rank_slot_off[rank + 1] - lp.rank_slot_off[rank];
     Layout L = make_layout(a->T, a->k, plan->E, (int32_t)lp.slot_expert.size(), nslots, a->H, a->I,
-                           a->dtype, a->max_rows, a->logits == nullptr);
+                           a->dtype, a->max_rows, a->logits == nullptr, false);
     *bytes = L.total;
+    const bool packed = a->w_gateup_packed && a->w_down_packed;
+    if (tiles_for(plan, layer, rank, a, packed).stream)
+        *bytes = std::max(*bytes, make_layout(a->T, a->k, plan->E, (int32_t)lp.slot_expert.size(), nslots, a->H, a->I,
+                                              a->dtype, a->max_rows, a->logits == nullptr, true).total);
     return CRAFT_OK;
 }
 
@@ -485,7 +502,7 @@ craft_status forward_on(const craft_plan_t *plan, int32_t layer, int32_t rank, c
     const int32_t s_lo = lp.rank_slot_off[rank], s_hi = lp.rank_slot_off[rank + 1];
     const int32_t nslots = s_hi - s_lo;
     const bool own_gate = a->logits == nullptr;
-    Layout L = make_layout(a->T, a->k, E, S, nslots, a->H, a->I, a->dtype, a->max_rows, own_gate);
+    Layout L = make_layout(a->T, a->k, E, S, nslots, a->H, a->I, a->dtype, a->max_rows, own_gate, false);
     if (workspace_bytes < L.total) return CRAFT_EWORKSPACE;
     if (a->T > 0) {
         if (!a->x || !a->out || (own_gate && !a->w_router)) return CRAFT_EINVAL;
@@ -507,6 +524,15 @@ craft_status forward_on(const craft_plan_t *plan, int32_t layer, int32_t rank, c
             if (a->T * (int64_t)a->H * 2 >= limit || (int64_t)gub >= limit || (int64_t)dnb >= limit) return CRAFT_EINVAL;
         }
     }
+    const bool packed = a->w_gateup_packed && a->w_down_packed;
+    tile_choice tiles = tiles_for(plan, layer, rank, a, packed);
+    const bool small = small_dispatch(a->T, S);
+    if (tiles.stream) {
+        // a workspace of the size that does for the tiles does for them still
+        const Layout Ls = make_layout(a->T, a->k, E, S, nslots, a->H, a->I, a->dtype, a->max_rows, own_gate, true);
+        if (workspace_bytes >= Ls.total) L = Ls;
+        else tiles = tile_choice_of(plan, layer, rank, a, packed, false);
+    }
     hipStream_t s = as_stream(stream);
     unsigned char *ws = static_cast<unsigned char *>(workspace);
     int32_t *ctrl = reinterpret_cast<int32_t *>(ws + L.ctrl);
@@ -524,19 +550,20 @@ craft_status forward_on(const craft_plan_t *plan, int32_t layer, int32_t rank, c
     int32_t *slot_off = reinterpret_cast<int32_t *>(ws + L.slot_off);
     int32_t *mt_start = reinterpret_cast<int32_t *>(ws + L.mt_start);
     int32_t *order = reinterpret_cast<int32_t *>(ws + L.order);
-    const bool packed = a->w_gateup_packed && a->w_down_packed;
-    const tile_choice tiles = tiles_for(plan, layer, rank, a, packed);
     const int32_t *tables = static_cast<const int32_t *>(a->tables);
 
     // 0 gating network, unless the scores are handed in
     const float *logits = a->logits;
+    int nparts = 1;
     if (own_gate && a->T > 0) {
         ScopedEvent ev(CRAFT_K_GATE, s);
         float *own = reinterpret_cast<float *>(ws + L.gate_logits);
         RouterArgs ga{a->dtype, a->x, a->w_router, a->T, a->H, E, own, cached_num_cu(),
-                      L.gate_ws_bytes ? reinterpret_cast<float *>(ws + L.gate_ws) : nullptr, 1};
+                      L.gate_ws_bytes ? reinterpret_cast<float *>(ws + L.gate_ws) : nullptr, 1, E <= 512};
         if (launch_router_logits(ga, s) != hipSuccess) return CRAFT_EHIP;
-        logits = own;
+        // a split gate's partial scores are added by the routing kernel
+        nparts = ga.keep_parts && L.gate_ws_bytes ? (int)(L.gate_ws_bytes / ((size_t)a->T * E * sizeof(float))) : 1;
+        logits = nparts > 1 ? ga.part : own;
     }
     // 1 route (+ per-block ranks and counts); user copies of ids / weights are written by the
     // same kernel when asked for, so route straight into them and alias the workspace views
@@ -544,39 +571,44 @@ craft_status forward_on(const craft_plan_t *plan, int32_t layer, int32_t rank, c
     float *w_out = a->topk_w ? a->topk_w : w;
     {
         ScopedEvent ev(CRAFT_K_ROUTE, s);
-        RouteArgs ra{logits, a->T, E, a->k, a->renormalize ? 1 : 0, ids_out, w_out, lrank, hist, ctrl};
+        RouteArgs ra{logits, a->T, E, a->k, a->renormalize ? 1 : 0, ids_out, w_out, lrank, hist, ctrl, nparts};
         if (launch_route(ra, s) != hipSuccess) return CRAFT_EHIP;
     }
-    // 2 per-expert totals, slot offsets, tile table
-    {
-        ScopedEvent ev(CRAFT_K_SCAN, s);
-        ScanArgs sa{hist, chunk_tot, chunk_base, (int32_t)L.NB, E, tables, S, s_lo, s_hi, L.max_rows,
-                    counts, slot_cnt, slot_off, ctrl, a->counts, a->slot_cnt, a->slot_off};
-        if (launch_scan(sa, s) != hipSuccess) return CRAFT_EHIP;
-    }
-    // 3 dispatch permutation (and, beside it, the tile tables of the two GEMMs)
-    {
+    // 2 per-expert totals, slot offsets; 3 dispatch permutation (and, beside it, the tile tables of
+    // the two GEMMs): two launches, or one for a batch of few blocks
+    DispatchArgs da{ids_out, lrank, hist, chunked ? chunk_base : nullptr, a->T, a->k, E, tables, slot_off, dest, src,
+                    a->dest, a->src, slot_cnt, s_lo, s_hi, tiles.frags[0], tiles.frags[1],
+                    tiles.riders[0] ? (a->I + 127) / 128 : 0, tiles.riders[1] ? (a->H + 255) / 256 : 0,
+                    mt_start, order, ctrl};
+    if (small) {
         ScopedEvent ev(CRAFT_K_DISPATCH, s);
-        DispatchArgs da{ids_out, lrank, hist, chunked ? chunk_base : nullptr, a->T, a->k, E, tables, slot_off, dest, src,
-                        a->dest, a->src, slot_cnt, s_lo, s_hi, tiles.frags[0], tiles.frags[1],
-                        tiles.riders[0] ? (a->I + 127) / 128 : 0, tiles.riders[1] ? (a->H + 255) / 256 : 0,
-                        mt_start, order, ctrl};
+        SmallDispatchArgs sd{da, craft_tables_layout(E, S), S, L.max_rows, counts, slot_cnt, slot_off, a->counts, a->slot_cnt, a->slot_off,
+                             a->x, a->H, tiles.stream ? ws + L.xpk : nullptr, 0, 0};
+        if (launch_dispatch_small(sd, s) != hipSuccess) return CRAFT_EHIP;
+    } else {
+        {
+            ScopedEvent ev(CRAFT_K_SCAN, s);
+            ScanArgs sa{hist, chunk_tot, chunk_base, (int32_t)L.NB, E, tables, S, s_lo, s_hi, L.max_rows,
+                        counts, slot_cnt, slot_off, ctrl, a->counts, a->slot_cnt, a->slot_off};
+            if (launch_scan(sa, s) != hipSuccess) return CRAFT_EHIP;
+        }
+        ScopedEvent ev(CRAFT_K_DISPATCH, s);
         if (launch_dispatch(da, s) != hipSuccess) return CRAFT_EHIP;
     }
     // 4 grouped FFN
     FfnArgs fa{a->dtype, a->H, a->I, a->k, s_lo, nslots, a->x, src, slot_off, mt_start, order, ctrl,
                a->w_gate, a->w_up, a->w_down, a->w_gateup_packed, a->w_down_packed,
-               ws + L.act, ws + L.y, L.max_rows, cached_num_cu(), a->weight_format == CRAFT_W_E4M3 ? 1 : 0,
+               ws + L.xpk, ws + L.act, ws + L.y, L.max_rows, cached_num_cu(), a->weight_format == CRAFT_W_E4M3 ? 1 : 0,
                tiles.frags[0], tiles.frags[1]};
     if (a->T > 0) {
         {
             ScopedEvent ev(CRAFT_K_GATEUP, s);
-            if ((packed ? launch_gateup_packed(fa, s) : launch_gateup(fa, s)) != hipSuccess)
+            if ((tiles.stream ? launch_gateup_stream(fa, packed, s) : packed ? launch_gateup_packed(fa, s) : launch_gateup(fa, s)) != hipSuccess)
                 return CRAFT_EHIP;
         }
         {
             ScopedEvent ev(CRAFT_K_DOWN, s);
-            if ((packed ? launch_down_packed(fa, s) : launch_down(fa, s)) != hipSuccess)
+            if ((tiles.stream ? launch_down_stream(fa, packed, s) : packed ? launch_down_packed(fa, s) : launch_down(fa, s)) != hipSuccess)
                 return CRAFT_EHIP;
         }
     }
@@ -609,7 +641,7 @@ craft_status craft_moe_rank_forward_static(const craft_plan_t *plan, int32_t lay
     const craft_layer_plan &lp = plan->layers[layer];
     const int32_t nslots = lp.rank_slot_off[rank + 1] - lp.rank_slot_off[rank];
     const Layout L = make_layout(a->T, a->k, plan->E, (int32_t)lp.slot_expert.size(), nslots, a->H, a->I,
-                                 a->dtype, a->max_rows, a->logits == nullptr);
+                                 a->dtype, a->max_rows, a->logits == nullptr, false);
     if (L.total > kStaticScratchBytes) return CRAFT_EINFEASIBLE;
     void *ws = nullptr;
     st = static_scratch(&ws);

@@ -49,6 +49,25 @@ constexpr int kRiderHostFrags = 7;
 constexpr int kFragsBf16 = 4;      // LDS-staged bf16 kernels (row-major weights): 128 rows
 constexpr int kFragsPacked = 8;    // weight-streaming bf16 kernels (packed weights): 256 rows
 constexpr int kFragsF32 = 1;
+
+// Small batches (ffn_stream.hip): most rows of a slot against one pass over its weights, and
+// where its activations lie.  They are kept as operand fragments: 16 rows x 32 contraction
+// elements are 64 lanes x 16 bytes, lane l holding row l & 15, elements 8 (l >> 4) .. + 7; the
+// fragments of one row group follow one another, whole 64-wide slabs of them.  Read as rows, the
+// 16 pieces of a request lie a row apart and cost more than the weights do (H = 7168, two slots of
+// 57 and 52 rows: forward 78 us as rows, 61 as fragments).  A slot starts a fragment of its own;
+// rows / 16 + slots before it is always room enough for the earlier ones.
+constexpr int kStreamRows = 64;
+__host__ __device__ inline int32_t stream_fragment(int32_t first_row, int32_t slot, int32_t row) {
+    return (first_row >> 4) + slot + (row >> 4);
+}
+// byte offset of 16-byte piece c (elements 8c ..) of row r16 of a fragment row
+__host__ __device__ inline uint32_t stream_piece(uint32_t c, uint32_t r16) {
+    return (c >> 2) * 1024u + ((c & 3u) * 16u + r16) * 16u;
+}
+inline size_t stream_bytes(int64_t max_rows, int32_t nslots, int32_t K) {
+    return (size_t)(max_rows / 16 + nslots + 1) * (size_t)((K + 63) / 64) * 2048;
+}
 constexpr int kBM_packed = kFragsPacked * 32;
 
 struct RouterArgs {
@@ -61,6 +80,7 @@ struct RouterArgs {
     int32_t num_cu;
     float *part;              // [nsplit][T][E] partial scores when the contraction is split; may be null
     int32_t nsplit;           // set by the launcher
+    bool keep_parts;          // with a split contraction: leave the sums to the reader of `part`
 };
 hipError_t launch_router_logits(const RouterArgs &a, hipStream_t s);
 void router_logits_shape(int64_t T, int32_t H, int32_t E, int32_t num_cu, bool workspace, int *nxf, int *nsplit);
@@ -74,6 +94,7 @@ struct RouteArgs {
     uint8_t *lrank;     // [T][k] rank of the assignment among same-expert ones of its block; may be null
     int32_t *hist;      // [NB][E] per-block expert counts; may be null
     int32_t *ctrl;      // control words to clear; may be null
+    int32_t nparts;     // > 1: a score is the sum of this many partial scores, [nparts][T][E] at `logits` (E <= 512)
 };
 hipError_t launch_route(const RouteArgs &a, hipStream_t s);
 
@@ -116,6 +137,23 @@ struct DispatchArgs {
 };
 hipError_t launch_dispatch(const DispatchArgs &a, hipStream_t s);
 
+// Batches of at most this many 32-token blocks: scan and dispatch in one launch.
+constexpr int kSmallBlocks = 16;
+struct SmallDispatchArgs {
+    DispatchArgs d;           // base: the blocks' counts themselves; chunk_base, slot_off and slot_cnt unused
+    craft_tables_header lay;  // of d.tables, known on the host: one round trip less
+    int32_t S;
+    int64_t max_rows;
+    int32_t *counts, *slot_cnt, *slot_off_out;
+    int32_t *user_counts, *user_slot_cnt, *user_slot_off;   // optional copies
+    const void *x;            // [T][H] bf16
+    int32_t H;
+    unsigned char *xpk;       // where the small-batch FFN reads the token rows; null: not copied
+    int32_t NB, slices;       // set by the launcher
+};
+bool small_dispatch(int64_t T, int32_t S);
+hipError_t launch_dispatch_small(SmallDispatchArgs a, hipStream_t s);
+
 struct FfnArgs {
     int32_t dtype;
     int32_t H, I, k;
@@ -128,7 +166,8 @@ struct FfnArgs {
     int32_t *ctrl;
     const void *const *w_gate, *const *w_up, *const *w_down;   // row-major weights per slot
     const void *const *wp_gateup, *const *wp_down;             // fragment-packed weights per slot
-    void *act;                     // [max_rows][I] SwiGLU activations
+    const void *xpk;               // small batches: token rows as fragments
+    void *act;                     // [max_rows][I] SwiGLU activations; small batches: as fragments
     void *y;                       // [max_rows][H]
     int64_t max_rows;
     int32_t num_cu;
@@ -140,6 +179,8 @@ hipError_t launch_gateup(const FfnArgs &a, hipStream_t s);
 hipError_t launch_down(const FfnArgs &a, hipStream_t s);
 hipError_t launch_gateup_packed(const FfnArgs &a, hipStream_t s);
 hipError_t launch_down_packed(const FfnArgs &a, hipStream_t s);
+hipError_t launch_gateup_stream(const FfnArgs &a, bool packed, hipStream_t s);
+hipError_t launch_down_stream(const FfnArgs &a, bool packed, hipStream_t s);
 void packed_sizes(int32_t H, int32_t I, size_t *gateup_bytes, size_t *down_bytes);
 hipError_t launch_pack(int32_t H, int32_t I, const void *wg, const void *wu, const void *wd,
                        void *pgu, void *pdn, hipStream_t s);

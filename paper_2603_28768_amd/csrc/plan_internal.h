@@ -39,6 +39,7 @@ struct craft_tile_choice {
     int32_t k, H, I;
     int32_t frags[2];
     bool riders[2];
+    bool stream;
     craft_tile_choice *next;
 };
 
@@ -86,5 +87,19 @@ struct craft_tables_header {
     int32_t pad;
 };
 
+// where the tables of E experts and S slots lie; the rank's slots are left blank
+inline craft_tables_header craft_tables_layout(int32_t E, int32_t S) {
+    craft_tables_header h{};
+    h.E = E;
+    h.S = S;
+    int32_t w = (int32_t)(sizeof(h) / sizeof(int32_t));
+    h.off_copies = w; w += E;
+    h.off_efirst = w; w += E + 1;
+    h.off_eslots = w; w += S;
+    h.off_slot_expert = w; w += S;
+    h.off_slot_copy = w; w += S;
+    h.total_words = w;
+    return h;
+}
 size_t craft_tables_words(int32_t E, int32_t S);
 void craft_tables_build(const craft_layer_plan &lp, int32_t E, int32_t rank, int32_t *buf);

@@ -279,19 +279,9 @@ size_t craft_tables_words(int32_t E, int32_t S) {
 
 void craft_tables_build(const craft_layer_plan &lp, int32_t E, int32_t rank, int32_t *buf) {
     const int32_t S = (int32_t)lp.slot_expert.size();
-    craft_tables_header h;
-    std::memset(&h, 0, sizeof(h));
-    h.E = E;
-    h.S = S;
+    craft_tables_header h = craft_tables_layout(E, S);
     h.s_lo = lp.rank_slot_off[rank];
     h.s_hi = lp.rank_slot_off[rank + 1];
-    int32_t w = (int32_t)(sizeof(h) / sizeof(int32_t));
-    h.off_copies = w; w += E;
-    h.off_efirst = w; w += E + 1;
-    h.off_eslots = w; w += S;
-    h.off_slot_expert = w; w += S;
-    h.off_slot_copy = w; w += S;
-    h.total_words = w;
     std::memcpy(buf, &h, sizeof(h));
     int32_t *copies = buf + h.off_copies, *efirst = buf + h.off_efirst;
     int32_t *eslots = buf + h.off_eslots, *sexp = buf + h.off_slot_expert;

@@ -4,7 +4,8 @@
 // tokens at once and every cross-lane step is a row-local DPP move (quad permutes and
 // row mirrors), not an LDS permute.  A lane holds the scores of experts 4*lane..4*lane+3,
 // +64, +128, ... (16-byte loads; a token's row is read as contiguous 256-byte pieces).
-// Each of the k picks is an arg-max over (score, expert id): first inside the lane in
+// Up to 16 picks are made at once (see the kernel); otherwise, or where too many scores tie for
+// that, each of the k picks is an arg-max over (score, expert id): first inside the lane in
 // ascending expert order, then a four-step butterfly over the row.  Scores are compared
 // raw, never their exponentials, and equal scores resolve to the lower expert id.
 //
@@ -13,6 +14,9 @@
 // the number of set bits below a token's own bit is that assignment's rank among the
 // block's assignments to the expert (experts of one token are distinct), and the
 // population count is the block's contribution to the expert's load.
+#include <type_traits>
+#include <utility>
+
 #include "kernels.h"
 
 namespace craft {
@@ -52,10 +56,43 @@ __device__ __forceinline__ float row_sum(float v) {
     return v;
 }
 
-// NQ = 16-byte score chunks per lane (each chunk = 4 experts; a row covers 64 experts per chunk)
-template <int NQ>
+__device__ __forceinline__ uint64_t row_rotate(uint64_t v, std::integral_constant<int, 0>) { return v; }
+template <int N>
+__device__ __forceinline__ uint64_t row_rotate(uint64_t v, std::integral_constant<int, N>) {
+    constexpr int kRor = 0x120;
+    return (uint64_t)(uint32_t)dpp_i<kRor + N>((int)(v >> 32)) << 32 | (uint32_t)dpp_i<kRor + N>((int)v);
+}
+template <typename F, int... N>
+__device__ __forceinline__ void each_rotation(F &&f, std::integer_sequence<int, N...>) {
+    (f(std::integral_constant<int, N>{}), ...);
+}
+// Score and expert as one integer that is larger for the better pick: the float's bits made
+// monotone (-0 counts as 0), then the lower id.
+__device__ __forceinline__ uint64_t pick_key(float v, int id) {
+    const uint32_t u = __float_as_uint(v + 0.0f);
+    return (uint64_t)(u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u)) << 32 | (uint32_t)~id;
+}
+__device__ __forceinline__ float key_score(uint64_t key) {
+    const uint32_t u = (uint32_t)(key >> 32);
+    return __uint_as_float(u ^ (((int32_t)u >> 31 ? 0u : ~0u) | 0x80000000u));
+}
+// How many of the row's 16 NC candidates beat candidate `own`.
+template <int NC>
+__device__ __forceinline__ int row_rank(const uint64_t (&key)[NC], uint64_t own) {
+    int r = 0;
+    each_rotation([&](auto n) {
+#pragma unroll
+        for (int i = 0; i < NC; ++i) r += row_rotate(key[i], n) > own ? 1 : 0;
+    }, std::make_integer_sequence<int, 16>{});
+    return r;
+}
+
+// NQ = 16-byte score chunks per lane (each chunk = 4 experts; a row covers 64 experts per chunk).
+// PARTS: the scores come as partial sums of the gating network.
+template <int NQ, bool PARTS>
 __global__ __launch_bounds__(kThreads) void route_kernel(RouteArgs a) {
     __shared__ uint32_t mask[kMaxE];
+    __shared__ uint64_t cand[kTokPerBlock][32];
     const int tid = threadIdx.x;
     const int sub = tid & 15;                      // lane inside the token's row
     const bool ranks = a.hist != nullptr;
@@ -81,55 +118,151 @@ __global__ __launch_bounds__(kThreads) void route_kernel(RouteArgs a) {
         // them (k <= E, and scores are finite by contract).
         constexpr float kGone = -__builtin_huge_valf();
         float v[NQ][4];
-        auto load_scores = [&]() {
+        // no branch around a load, only one around all of them: they travel together
+        auto load_row = [&](const float *from, float (&to)[NQ][4]) {
+            if (vec_ok) {
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) {
-                const int e0 = q * 64 + sub * 4;
-                if (vec_ok && e0 + 3 < a.E) {
-                    const float4 f = *reinterpret_cast<const float4 *>(row + e0);
-                    v[q][0] = f.x; v[q][1] = f.y; v[q][2] = f.z; v[q][3] = f.w;
-                } else {
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) v[q][c] = e0 + c < a.E ? row[e0 + c] : kGone;
+                for (int q = 0; q < NQ; ++q) {
+                    const float4 f = *reinterpret_cast<const float4 *>(from + min(q * 64 + sub * 4, a.E - 4));
+                    to[q][0] = f.x; to[q][1] = f.y; to[q][2] = f.z; to[q][3] = f.w;
                 }
+            } else {
+#pragma unroll
+                for (int q = 0; q < NQ; ++q)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) to[q][c] = from[min(q * 64 + sub * 4 + c, a.E - 1)];
             }
+        };
+        auto load_scores = [&]() {
+            load_row(row, v);
+            // the gate's partial scores, added in ascending order of the split; a few parts are
+            // requested together, one by one each would cost a round trip
+            constexpr int G = NQ <= 4 ? 7 : NQ <= 6 ? 3 : 1;
+            if (PARTS)
+                for (int z0 = 1; z0 < a.nparts; z0 += G) {
+                    float f[G][NQ][4];
+#pragma unroll
+                    for (int g = 0; g < G; ++g) load_row(row + (int64_t)min(z0 + g, a.nparts - 1) * a.T * a.E, f[g]);
+#pragma unroll
+                    for (int g = 0; g < G; ++g)
+                        if (z0 + g < a.nparts)
+#pragma unroll
+                            for (int q = 0; q < NQ; ++q)
+#pragma unroll
+                                for (int c = 0; c < 4; ++c) v[q][c] += f[g][q][c];
+                }
+#pragma unroll
+            for (int q = 0; q < NQ; ++q)
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    if (q * 64 + sub * 4 + c >= a.E) v[q][c] = kGone;
         };
         load_scores();
 
         float pick_v[kMaxPickSlots];
         float first_v = 0.0f;
 #pragma unroll
-        for (int s = 0; s < kMaxPickSlots; ++s) {
-            pick_v[s] = 0.0f;
-            const int jn = min(16, a.k - s * 16);  // picks that land in slot s
-            for (int j = 0; j < jn; ++j) {
-                // the lane's best: a tournament in ascending expert order, the later entry
-                // winning only when strictly greater, so equal scores keep the lower id
-                float tv[NQ * 4];
-                int ti[NQ * 4];
+        for (int s = 0; s < kMaxPickSlots; ++s) pick_v[s] = 0.0f;
+
+        // Few of the row's scores can be among its k best: the k-th largest of the 16 lanes' maxima
+        // is a bound that k of them reach, and a dozen or so reach in all.  Those are gathered
+        // through LDS, one or two to a lane, and each finds its place by being compared with
+        // every other (E = 256, k = 8: a third of the instructions of k arg-max rounds).
+        const bool few = NQ <= 8 && a.k <= 16;     // more than 512 scores: no registers for it
+        int n_cand = 0;
+        float bound = kGone;
+        if (few) {
+            float top = v[0][0];
 #pragma unroll
-                for (int q = 0; q < NQ; ++q)
+            for (int q = 0; q < NQ; ++q)
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) { tv[q * 4 + c] = v[q][c]; ti[q * 4 + c] = q * 64 + sub * 4 + c; }
+                for (int c = 0; c < 4; ++c) top = fmaxf(top, v[q][c]);
+            int above = 0;
+            each_rotation([&](auto n) {
+                if constexpr (n.value > 0) above += dpp_f<0x120 + n.value>(top) > top ? 1 : 0;
+            }, std::make_integer_sequence<int, 16>{});
+            bound = above < a.k ? top : __builtin_huge_valf();
+            bound = fminf(bound, dpp_f<kXor1>(bound));
+            bound = fminf(bound, dpp_f<kXor2>(bound));
+            bound = fminf(bound, dpp_f<kHalfMirror>(bound));
+            bound = fminf(bound, dpp_f<kMirror>(bound));
+            first_v = fmaxf(top, dpp_f<kXor1>(top));
+            first_v = fmaxf(first_v, dpp_f<kXor2>(first_v));
+            first_v = fmaxf(first_v, dpp_f<kHalfMirror>(first_v));
+            first_v = fmaxf(first_v, dpp_f<kMirror>(first_v));
 #pragma unroll
-                for (int width = 1; width < NQ * 4; width *= 2)
+            for (int q = 0; q < NQ; ++q)
 #pragma unroll
-                    for (int i = 0; i + width < NQ * 4; i += 2 * width)
-                        if (tv[i + width] > tv[i]) { tv[i] = tv[i + width]; ti[i] = ti[i + width]; }
-                float bv = tv[0];
-                int bi = ti[0];
-                argmax_step<kXor1>(bv, bi);
-                argmax_step<kXor2>(bv, bi);
-                argmax_step<kHalfMirror>(bv, bi);
-                argmax_step<kMirror>(bv, bi);
-                // the owner retires the pick; lane j of the row keeps it for the output
+                for (int c = 0; c < 4; ++c) n_cand += v[q][c] >= bound ? 1 : 0;
+        }
+        int upto = n_cand;                         // candidates of this lane and the ones before it
+        upto += dpp_i<0x111>(upto);
+        upto += dpp_i<0x112>(upto);
+        upto += dpp_i<0x114>(upto);
+        upto += dpp_i<0x118>(upto);
+        const int row_cands = __shfl(upto, 15, 16);
+        if (few && __ballot(row_cands > 32 || row_cands < a.k) == 0) {
+            int at = upto - n_cand;
 #pragma unroll
-                for (int q = 0; q < NQ; ++q)
+            for (int q = 0; q < NQ; ++q)
 #pragma unroll
-                    for (int c = 0; c < 4; ++c)
-                        if (bi == q * 64 + sub * 4 + c) v[q][c] = kGone;
-                if (j == sub) { pick_v[s] = bv; my_id[s] = bi; }
-                if (s == 0 && j == 0) first_v = bv;       // the row maximum
+                for (int c = 0; c < 4; ++c)
+                    if (v[q][c] >= bound) cand[tl][at++] = pick_key(v[q][c], q * 64 + sub * 4 + c);
+            __builtin_amdgcn_wave_barrier();       // one wave's own rows: LDS keeps its order
+            const bool wide = __ballot(row_cands > 16) != 0;
+            uint64_t key[2] = {sub < row_cands ? cand[tl][sub] : 0, 0};
+            int rank[2] = {0, 32};
+            if (wide) {
+                key[1] = 16 + sub < row_cands ? cand[tl][16 + sub] : 0;
+                rank[0] = row_rank(key, key[0]);
+                rank[1] = row_rank(key, key[1]);
+            } else {
+                const uint64_t one[1] = {key[0]};
+                rank[0] = row_rank(one, key[0]);
+            }
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+                if (key[i] && rank[i] < a.k) cand[tl][rank[i]] = key[i];
+            __builtin_amdgcn_wave_barrier();
+            if (sub < a.k) {
+                const uint64_t mine = cand[tl][sub];
+                pick_v[0] = key_score(mine);
+                my_id[0] = (int)~(uint32_t)mine;
+            }
+        } else {
+#pragma unroll
+            for (int s = 0; s < kMaxPickSlots; ++s) {
+                const int jn = min(16, a.k - s * 16);  // picks that land in slot s
+                for (int j = 0; j < jn; ++j) {
+                    // the lane's best: a tournament in ascending expert order, the later entry
+                    // winning only when strictly greater, so equal scores keep the lower id
+                    float tv[NQ * 4];
+                    int ti[NQ * 4];
+#pragma unroll
+                    for (int q = 0; q < NQ; ++q)
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) { tv[q * 4 + c] = v[q][c]; ti[q * 4 + c] = q * 64 + sub * 4 + c; }
+#pragma unroll
+                    for (int width = 1; width < NQ * 4; width *= 2)
+#pragma unroll
+                        for (int i = 0; i + width < NQ * 4; i += 2 * width)
+                            if (tv[i + width] > tv[i]) { tv[i] = tv[i + width]; ti[i] = ti[i + width]; }
+                    float bv = tv[0];
+                    int bi = ti[0];
+                    argmax_step<kXor1>(bv, bi);
+                    argmax_step<kXor2>(bv, bi);
+                    argmax_step<kHalfMirror>(bv, bi);
+                    argmax_step<kMirror>(bv, bi);
+                    // the owner retires the pick; lane j of the row keeps it for the output
+#pragma unroll
+                    for (int q = 0; q < NQ; ++q)
+#pragma unroll
+                        for (int c = 0; c < 4; ++c)
+                            if (bi == q * 64 + sub * 4 + c) v[q][c] = kGone;
+                    if (j == sub) { pick_v[s] = bv; my_id[s] = bi; }
+                    if (s == 0 && j == 0) first_v = bv;       // the row maximum
+                }
             }
         }
         // softmax weight of the picks
@@ -192,12 +325,17 @@ hipError_t launch_route(const RouteArgs &a, hipStream_t s) {
     const int64_t nb = (a.T + kTokPerBlock - 1) / kTokPerBlock;
     dim3 grid((unsigned)nb), block(kThreads);
     const int nq = (a.E + 63) / 64;
-    if (nq <= 1) hipLaunchKernelGGL(route_kernel<1>, grid, block, 0, s, a);
-    else if (nq <= 2) hipLaunchKernelGGL(route_kernel<2>, grid, block, 0, s, a);
-    else if (nq <= 4) hipLaunchKernelGGL(route_kernel<4>, grid, block, 0, s, a);
-    else if (nq <= 6) hipLaunchKernelGGL(route_kernel<6>, grid, block, 0, s, a);
-    else if (nq <= 8) hipLaunchKernelGGL(route_kernel<8>, grid, block, 0, s, a);
-    else hipLaunchKernelGGL(route_kernel<16>, grid, block, 0, s, a);
+    if (nq > 8 && a.nparts > 1) return hipErrorInvalidValue;
+    auto go = [&](auto n) {
+        if (n.value <= 8 && a.nparts > 1) hipLaunchKernelGGL((route_kernel<(n.value <= 8 ? n.value : 8), true>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((route_kernel<n.value, false>), grid, block, 0, s, a);
+    };
+    if (nq <= 1) go(std::integral_constant<int, 1>{});
+    else if (nq <= 2) go(std::integral_constant<int, 2>{});
+    else if (nq <= 4) go(std::integral_constant<int, 4>{});
+    else if (nq <= 6) go(std::integral_constant<int, 6>{});
+    else if (nq <= 8) go(std::integral_constant<int, 8>{});
+    else go(std::integral_constant<int, 16>{});
     return hipGetLastError();
 }
 

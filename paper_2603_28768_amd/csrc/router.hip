@@ -26,6 +26,7 @@
 namespace craft {
 namespace {
 
+constexpr int kThinBatch = 128;         // tokens up to which the gate is read by thin tiles
 constexpr int GK = 64;                  // contraction slab
 constexpr int GROWB = GK * 2 + 16;      // padded LDS row, bytes
 typedef unsigned int gu32x4_t __attribute__((ext_vector_type(4)));
@@ -134,6 +135,79 @@ __global__ __launch_bounds__(256) void router_logits_bf16_kernel(RouterArgs a) {
     }
 }
 
+// A small batch: nothing but the gate's weights to read, E H 2 bytes that a few tall tiles would
+// pull through a few CUs (8 tokens, E = 256, H = 7168: 23 us).  A workgroup takes 16 experts against
+// up to 64 tokens and one split of the contraction, its four waves every fourth 64-wide slab of
+// that, both operands straight from global memory in the operand layout of
+// v_mfma_f32_16x16x32_bf16; the waves' sums meet in LDS and are added in wave order.
+constexpr int kThinWaves = 4;
+constexpr int kThinTokens = 64;
+template <int NXF>
+__device__ __forceinline__ void thin_tile(const RouterArgs &a, int64_t t0, int e0, int kbeg, int kend, float *dst, f32x4_t *sums) {
+    constexpr int PW = 4;                                  // slabs in flight per wave
+    const int lane = threadIdx.x & 63, q = lane >> 4, r16 = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int hchunks = a.H >> 3;
+    gchunk_t wrow = (gchunk_t)a.w + (int64_t)min(e0 + r16, a.E - 1) * hchunks, xrow[NXF];
+#pragma unroll
+    for (int g = 0; g < NXF; ++g) xrow[g] = (gchunk_t)a.x + min(t0 + 16 * g + r16, a.T - 1) * hchunks;
+    f32x4_t acc[NXF];
+#pragma unroll
+    for (int g = 0; g < NXF; ++g) acc[g] = (f32x4_t)(0.0f);
+    const gu32x4_t zero = {0u, 0u, 0u, 0u};
+    for (int s0 = kbeg + wave; s0 < kend; s0 += PW * kThinWaves) {
+        gu32x4_t w[PW][2], x[PW][2][NXF];
+#pragma unroll
+        for (int u = 0; u < PW; ++u)
+#pragma unroll
+            for (int st = 0; st < 2; ++st) {
+                // past the split or the rows: read from inside them, replaced by zeros below
+                const int c = min((s0 + u * kThinWaves) * 8 + st * 4 + q, hchunks - 1);
+                w[u][st] = wrow[c];
+#pragma unroll
+                for (int g = 0; g < NXF; ++g) x[u][st][g] = xrow[g][c];
+            }
+#pragma unroll
+        for (int u = 0; u < PW; ++u) {
+            const int s = s0 + u * kThinWaves;
+#pragma unroll
+            for (int st = 0; st < 2; ++st) {
+                const bool in = s < kend && s * 8 + st * 4 + q < hchunks;
+                const bf16x8_t wf = __builtin_bit_cast(bf16x8_t, in ? w[u][st] : zero);
+#pragma unroll
+                for (int g = 0; g < NXF; ++g)
+                    acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, __builtin_bit_cast(bf16x8_t, in ? x[u][st][g] : zero),
+                                                                     acc[g], 0, 0, 0);
+            }
+        }
+    }
+#pragma unroll
+    for (int g = 0; g < NXF; ++g) sums[(wave * NXF + g) * 64 + lane] = acc[g];
+    __syncthreads();
+    // element v of lane l: expert e0 + 4 (l >> 4) + v, token l & 15 of the fragment
+    for (int g = wave; g < NXF; g += kThinWaves) {
+        f32x4_t v = sums[g * 64 + lane];
+#pragma unroll
+        for (int z = 1; z < kThinWaves; ++z) v += sums[(z * NXF + g) * 64 + lane];
+        const int64_t t = t0 + 16 * g + r16;
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            if (t < a.T && e0 + 4 * q + c < a.E) dst[t * a.E + e0 + 4 * q + c] = v[c];
+    }
+}
+__global__ __launch_bounds__(64 * kThinWaves) void router_thin_kernel(RouterArgs a) {
+    __shared__ f32x4_t sums[kThinWaves * (kThinTokens / 16) * 64];
+    const int64_t t0 = (int64_t)blockIdx.y * kThinTokens;
+    const int e0 = blockIdx.x * 16;
+    const int nk = (a.H + GK - 1) / GK, per = (nk + a.nsplit - 1) / a.nsplit;
+    const int kbeg = min(nk, (int)blockIdx.z * per), kend = min(nk, kbeg + per);
+    float *dst = a.nsplit > 1 ? a.part + (int64_t)blockIdx.z * a.T * a.E : a.logits;
+    const int64_t tokens = a.T - t0;
+    if (tokens <= 16) thin_tile<1>(a, t0, e0, kbeg, kend, dst, sums);
+    else if (tokens <= 32) thin_tile<2>(a, t0, e0, kbeg, kend, dst, sums);
+    else thin_tile<4>(a, t0, e0, kbeg, kend, dst, sums);
+}
+
 // logits = sum of the partial scores, in ascending order of the split
 __global__ __launch_bounds__(256) void router_reduce_kernel(const float *part, int nsplit, int64_t n, float *logits) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -167,11 +241,6 @@ hipError_t launch_bf16(const RouterArgs &a, hipStream_t s) {
     const dim3 grid((unsigned)((a.T + NXF * 32 - 1) / (NXF * 32)), (unsigned)((a.E + NB * 128 - 1) / (NB * 128)),
                     (unsigned)a.nsplit);
     hipLaunchKernelGGL((router_logits_bf16_kernel<NB, NXF, D>), grid, dim3(256), lds, s, a);
-    if (a.nsplit > 1) {
-        const int64_t n = a.T * a.E;
-        hipLaunchKernelGGL(router_reduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
-                           a.part, a.nsplit, n, a.logits);
-    }
     return hipGetLastError();
 }
 
@@ -208,18 +277,29 @@ hipError_t launch_router_logits(const RouterArgs &a, hipStream_t s) {
     router_logits_shape(a.T, a.H, a.E, a.num_cu, a.part != nullptr, &nxf, &nsplit);
     RouterArgs b = a;
     b.nsplit = nsplit;
-    switch (nb * 16 + nxf) {
-        case 1 * 16 + 1: return launch_bf16<1, 1, 4>(b, s);
-        case 1 * 16 + 2: return launch_bf16<1, 2, 4>(b, s);
-        case 1 * 16 + 4: return launch_bf16<1, 4, 4>(b, s);
-        case 2 * 16 + 1: return launch_bf16<2, 1, 4>(b, s);
-        case 2 * 16 + 2: return launch_bf16<2, 2, 4>(b, s);
-        case 2 * 16 + 4: return launch_bf16<2, 4, 3>(b, s);
-        case 3 * 16 + 1: return launch_bf16<3, 1, 3>(b, s);
-        case 3 * 16 + 2: return launch_bf16<3, 2, 3>(b, s);
-        case 3 * 16 + 4: return launch_bf16<3, 4, 1>(b, s);
-        default: return launch_bf16<4, 1, 3>(b, s);
+    hipError_t err;
+    if (a.T <= kThinBatch) {
+        const dim3 grid((unsigned)((a.E + 15) / 16), (unsigned)((a.T + kThinTokens - 1) / kThinTokens), (unsigned)nsplit);
+        hipLaunchKernelGGL(router_thin_kernel, grid, dim3(64 * kThinWaves), 0, s, b);
+        err = hipGetLastError();
+    } else {
+        switch (nb * 16 + nxf) {
+            case 1 * 16 + 1: err = launch_bf16<1, 1, 4>(b, s); break;
+            case 1 * 16 + 2: err = launch_bf16<1, 2, 4>(b, s); break;
+            case 1 * 16 + 4: err = launch_bf16<1, 4, 4>(b, s); break;
+            case 2 * 16 + 1: err = launch_bf16<2, 1, 4>(b, s); break;
+            case 2 * 16 + 2: err = launch_bf16<2, 2, 4>(b, s); break;
+            case 2 * 16 + 4: err = launch_bf16<2, 4, 3>(b, s); break;
+            case 3 * 16 + 1: err = launch_bf16<3, 1, 3>(b, s); break;
+            case 3 * 16 + 2: err = launch_bf16<3, 2, 3>(b, s); break;
+            case 3 * 16 + 4: err = launch_bf16<3, 4, 1>(b, s); break;
+            default: err = launch_bf16<4, 1, 3>(b, s); break;
+        }
     }
+    if (err != hipSuccess || nsplit == 1 || a.keep_parts) return err;
+    const int64_t n = a.T * a.E;
+    hipLaunchKernelGGL(router_reduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a.part, nsplit, n, a.logits);
+    return hipGetLastError();
 }
 
 }  // namespace craft

@@ -646,6 +646,29 @@ def test_block_ordered_tile_list_with_ragged_bands(torch_cuda):
     _check_rank(torch_cuda, case, 0, packed=True, cover=True)
 
 
+@pytest.mark.parametrize("weights", ["packed", "e4m3", "rowmajor"])
+@pytest.mark.parametrize("T,H,I,E,k,D,zipf,eval_zipf", [
+    (1, 64, 32, 8, 1, 1, 1.0, 1.0),            # a single row; fewer slabs than waves
+    (16, 72, 40, 8, 8, 2, 1.0, 1.0),           # exactly one fragment per slot; ragged K and N
+    (17, 520, 200, 6, 6, 1, 1.0, 1.0),         # one row into the second fragment
+    (33, 1544, 456, 6, 6, 1, 1.0, 1.0),        # one row into the third; a full ring with a remainder
+    (64, 2112, 1288, 4, 4, 1, 1.0, 1.0),       # the most rows of one pass over the weights
+    (200, 264, 136, 32, 4, 1, 0.0, 2.0),       # more rows than the plan expects: several passes
+    (40, 128, 64, 300, 4, 1, 1.0, 1.0)])       # more slots than the tile tables in LDS hold
+def test_small_batches_stream_the_weights(torch_cuda, T, H, I, E, k, D, zipf, eval_zipf, weights):
+    cfg = synth.scaled(synth.CONFIGS["qwen3"], T=T, H=H, I=I, E=E, k=k, D=D, replica_slots=0, zipf_s=zipf,
+                       profile_batches=4)
+    print("small batch", cfg, weights, flush=True)
+    case = Case(cfg, w8=weights == "e4m3")
+    if eval_zipf != zipf:
+        case = Case(cfg, plan=case.plan, pop=synth.popularity(E, eval_zipf, 1, 0), w8=case.w8)
+        assert case.slot_cnt.max() > 64
+    for g in range(D):
+        fwd, _, _ = case.gpu_rank(g, packed=weights != "rowmajor")
+        assert fwd.tile_choice() == (64, 64, 0, 0)
+        _check_rank(torch_cuda, case, g, packed=weights != "rowmajor")
+
+
 # -------------------------------------------------- full-size configurations
 
 @pytest.mark.parametrize("name", ["qwen3", "dsv3", "kimi"])
