@@ -291,48 +291,95 @@ __global__ __launch_bounds__(256) void dispatch_kernel(DispatchArgs a) {
     }
 }
 
-// Scan and dispatch of a small batch in one launch.  With few blocks of tokens every workgroup can
-// afford to derive all of it for itself -- the experts' counts, the rows and offsets of the slots --
-// and needs no other workgroup's results: one launch, and one round trip through memory, less
-// (T = 256, E = 384: 14.3 -> 8 us for the two).  A workgroup handles one block of 32 tokens; the
-// first one of a block writes its dest / src.  For the small-batch FFN the token rows bound for
-// this rank are copied into fragment order on the way, by a.slices workgroups per block that
-// take a share of the columns each.  The last workgroup builds the tile tables.
-constexpr int kSmallThreads = 512;
-constexpr int kSmallSlots = 2048;
-__global__ __launch_bounds__(kSmallThreads) void dispatch_small_kernel(SmallDispatchArgs sa) {
+// Per-expert prefixes over the blocks of a chunk and the chunk's totals, nothing that needs another
+// workgroup's results: a workgroup takes kDirectChunk blocks for 64 experts, a wave an eighth of
+// them, a lane one expert.
+constexpr int kDirectWaves = 8;
+__global__ __launch_bounds__(64 * kDirectWaves) void prefix_kernel(int32_t *hist, int32_t *tot, int32_t NB, int32_t E) {
+    __shared__ int32_t part[kDirectWaves][64];
+    constexpr int kKeep = kDirectChunk / kDirectWaves;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int groups = (E + 63) / 64, chunk = blockIdx.x / groups, e = blockIdx.x % groups * 64 + lane;
+    const int b0 = chunk * kDirectChunk + wave * kKeep;
+    int32_t keep[kKeep], sum = 0;
+#pragma unroll
+    for (int i = 0; i < kKeep; ++i) keep[i] = hist[(int64_t)min(b0 + i, NB - 1) * E + min(e, E - 1)];
+#pragma unroll
+    for (int i = 0; i < kKeep; ++i) sum += b0 + i < NB ? keep[i] : 0;
+    part[wave][lane] = sum;
+    __syncthreads();
+    int32_t run = 0, total = 0;
+#pragma unroll
+    for (int w = 0; w < kDirectWaves; ++w) {
+        const int32_t v = part[w][lane];
+        if (w < wave) run += v;
+        total += v;
+    }
+    if (e >= E) return;
+#pragma unroll
+    for (int i = 0; i < kKeep; ++i)
+        if (b0 + i < NB) { hist[(int64_t)(b0 + i) * E + e] = run; run += keep[i]; }
+    if (wave == 0) tot[(int64_t)chunk * E + e] = total;
+}
+
+// Dispatch without a serial step in front of it.  Every workgroup derives what it needs for itself
+// -- the experts' counts from the totals of the chunks of blocks, the rows and offsets of the slots --
+// and needs no other workgroup's results.  In a batch of up to kSmallBlocks blocks a chunk is a
+// single block, whose counts the routing kernel has left: no other launch at all (T = 256, E = 384:
+// 14.3 -> 8.7 us for the two).  In a larger one prefix_kernel runs in front (T = 16384, E = 384:
+// scan 14.9 and dispatch 5.4 us -> 4.8 and 8.3; T = 32768, E = 256: 17.9 and 8.5 -> 5.2 and 12.9).  A workgroup handles one block of 32 tokens, a few
+// neighbouring ones in a large batch.  COPY, for the small-batch FFN: the token rows bound
+// for this rank are copied into fragment order on the way, by sa.slices workgroups per block that
+// take a share of the columns each (the first one writes dest / src).  The last workgroup builds the tile tables.
+constexpr int kDirectThreads = 512;
+constexpr int kDirectSlots = 2048;
+template <bool COPY>
+__global__ __launch_bounds__(kDirectThreads) void dispatch_direct_kernel(DirectDispatchArgs sa) {
     const DispatchArgs &a = sa.d;
-    __shared__ int32_t cnt[1024], before[1024], ncopies[1024], first[1024];
-    __shared__ int32_t soff[kSmallSlots + 1], slots_of[kSmallSlots];
-    __shared__ int32_t wsum[kSmallThreads / 64];
+    __shared__ int32_t cnt[1024], before[1024], ncopies[1024];
+    __shared__ uint16_t first[1024], slots_of[kDirectSlots];
+    __shared__ int32_t soff[kDirectSlots + 1];
+    __shared__ int32_t wsum[kDirectThreads / 64];
     __shared__ int32_t list_len;
-    __shared__ int32_t list[2 * kTokPerBlock * 64];        // token and packed row of the assignments to copy
+    __shared__ int32_t list[COPY ? 2 * kTokPerBlock * 64 : 1];     // token and packed row of the assignments to copy
     const int32_t *copies = a.tables + sa.lay.off_copies;
     const int32_t *efirst = a.tables + sa.lay.off_efirst;
     const int32_t *eslots = a.tables + sa.lay.off_eslots;
     const int32_t *slot_expert = a.tables + sa.lay.off_slot_expert;
     const int32_t *slot_copy = a.tables + sa.lay.off_slot_copy;
     const bool tables = blockIdx.x == gridDim.x - 1;
-    const int32_t b = blockIdx.x / sa.slices, slice = blockIdx.x % sa.slices;
+    // Workgroups go round the XCDs; neighbouring blocks stay on one: their entries of src lie side by
+    // side, and a line that several XCDs write pieces of is written back by each of them.
+    const int32_t spans = (int32_t)gridDim.x - 1;          // (with one slice: a multiple of 8)
+    const int32_t turn = blockIdx.x / sa.slices, slice = blockIdx.x % sa.slices;
+    const int32_t b = (sa.slices > 1 ? turn : turn % 8 * (spans / 8) + turn / 8) * sa.span;
     const bool writer = tables;                            // of what there is one of per batch
+    const int32_t own = b / sa.chunk_blocks;               // (a span lies inside one chunk)
 
     // Everything that is looked up through something else later on is requested here, at once:
     // the launch is a chain of round trips to memory, and this is the only long link.
-    const int32_t per_block = kTokPerBlock * a.k;
-    const int64_t A = a.T * a.k, as0 = (int64_t)b * per_block + threadIdx.x;
-    const bool have0 = !tables && threadIdx.x < per_block && as0 < A;
-    const int32_t e0 = have0 ? a.ids[as0] : 0, lrank0 = have0 ? (int32_t)a.lrank[as0] : 0;
+    const int32_t per_block = kTokPerBlock * a.k, mine_n = per_block * sa.span;
+    const int64_t A = a.T * a.k, as0 = (int64_t)b * per_block;
+    constexpr int kFirst = 2;                              // assignments of a thread that are looked up ahead
+    int32_t e0[kFirst], rank0[kFirst];                     // expert, place among its assignments of the chunk
+#pragma unroll
+    for (int u = 0; u < kFirst; ++u) {
+        const int32_t i = threadIdx.x + u * kDirectThreads;
+        const bool have = !tables && i < mine_n && as0 + i < A;
+        e0[u] = have ? a.ids[as0 + i] : 0;
+        rank0[u] = have ? (int32_t)a.lrank[as0 + i] : 0;
+    }
     const int32_t ex0 = threadIdx.x < sa.S ? slot_expert[threadIdx.x] : 0, q0 = threadIdx.x < sa.S ? slot_copy[threadIdx.x] : 0;
-    for (int32_t p = threadIdx.x; p < sa.S; p += kSmallThreads) slots_of[p] = eslots[p];
+    for (int32_t p = threadIdx.x; p < sa.S; p += kDirectThreads) slots_of[p] = (uint16_t)eslots[p];
     if (threadIdx.x == 0) list_len = 0;
-    for (int32_t e = threadIdx.x; e < a.E; e += kSmallThreads) {
+    for (int32_t e = threadIdx.x; e < a.E; e += kDirectThreads) {
         int32_t total = 0, mine = 0;
         ncopies[e] = copies[e];
-        first[e] = efirst[e];
+        first[e] = (uint16_t)efirst[e];
 #pragma unroll 16
-        for (int32_t i = 0; i < sa.NB; ++i) {
-            const int32_t v = a.base[(int64_t)i * a.E + e];
-            mine = i == b ? total : mine;
+        for (int32_t i = 0; i < sa.ntot; ++i) {
+            const int32_t v = sa.tot[(int64_t)i * a.E + e];
+            mine = i == own ? total : mine;
             total += v;
         }
         cnt[e] = total;
@@ -342,9 +389,15 @@ __global__ __launch_bounds__(kSmallThreads) void dispatch_small_kernel(SmallDisp
             if (sa.user_counts) sa.user_counts[e] = total;
         }
     }
+    if (sa.local && !tables)
+#pragma unroll
+        for (int u = 0; u < kFirst; ++u) {
+            const int32_t i = threadIdx.x + u * kDirectThreads;
+            if (i < mine_n && as0 + i < A) rank0[u] += a.base[(int64_t)(b + i / per_block) * a.E + e0[u]];
+        }
     __syncthreads();
     int32_t carry = 0;
-    for (int32_t base = 0; base < sa.S; base += kSmallThreads) {
+    for (int32_t base = 0; base < sa.S; base += kDirectThreads) {
         const int32_t p = base + threadIdx.x;
         int32_t r = 0;
         if (p < sa.S) {
@@ -353,7 +406,7 @@ __global__ __launch_bounds__(kSmallThreads) void dispatch_small_kernel(SmallDisp
             r = n > q ? (n - q + c - 1) / c : 0;
         }
         int32_t chunk_total;
-        const int32_t off = carry + block_exclusive_scan<kSmallThreads / 64>(r, wsum, &chunk_total);
+        const int32_t off = carry + block_exclusive_scan<kDirectThreads / 64>(r, wsum, &chunk_total);
         if (p < sa.S) {
             soff[p] = off;
             if (writer) {
@@ -376,16 +429,13 @@ __global__ __launch_bounds__(kSmallThreads) void dispatch_small_kernel(SmallDisp
             a.ctrl[CTRL_ROWS] = hi - lo;
             a.ctrl[CTRL_OVERFLOW] = ovf ? 1 : 0;
         }
-        build_tile_tables<kSmallThreads>(a, ovf, [&](int32_t sl) { return soff[a.s_lo + sl + 1] - soff[a.s_lo + sl]; });
+        build_tile_tables<kDirectThreads>(a, ovf, [&](int32_t sl) { return soff[a.s_lo + sl + 1] - soff[a.s_lo + sl]; });
         return;
     }
 
-    for (int32_t i = threadIdx.x; i < per_block; i += kSmallThreads) {
-        const int64_t as = (int64_t)b * per_block + i;
-        if (as >= A) break;
-        const bool ahead = i == (int32_t)threadIdx.x;
-        const int32_t e = ahead ? e0 : a.ids[as];
-        const int32_t idx = before[e] + (ahead ? lrank0 : (int32_t)a.lrank[as]);
+    auto place = [&](int32_t i, int32_t e, int32_t rank) {
+        const int64_t as = as0 + i;
+        const int32_t idx = before[e] + rank;
         const int32_t c = ncopies[e];
         const int32_t p = slots_of[first[e] + idx % c];
         const int32_t row = idx / c, d = soff[p] + row;
@@ -395,19 +445,28 @@ __global__ __launch_bounds__(kSmallThreads) void dispatch_small_kernel(SmallDisp
             if (a.user_dest) a.user_dest[as] = d;
             if (a.user_src) a.user_src[d] = (int32_t)as;
         }
-        if (sa.xpk && !ovf && p >= a.s_lo && p < a.s_hi) {
+        if (COPY && !ovf && p >= a.s_lo && p < a.s_hi) {
             const int32_t at = atomicAdd(&list_len, 1);    // the order of the copies does not matter
             list[2 * at] = (int32_t)(as / a.k);
             list[2 * at + 1] = stream_fragment(soff[p] - lo, p - a.s_lo, row) * 16 + (row & 15);
         }
+    };
+#pragma unroll
+    for (int u = 0; u < kFirst; ++u) {
+        const int32_t i = threadIdx.x + u * kDirectThreads;
+        if (i < mine_n && as0 + i < A) place(i, e0[u], rank0[u]);
     }
-    if (!sa.xpk) return;
+    for (int32_t i = threadIdx.x + kFirst * kDirectThreads; i < mine_n && as0 + i < A; i += kDirectThreads) {
+        const int32_t e = a.ids[as0 + i];
+        place(i, e, (int32_t)a.lrank[as0 + i] + (sa.local ? a.base[(int64_t)(b + i / per_block) * a.E + e] : 0));
+    }
+    if (!COPY) return;
     __syncthreads();
     const int32_t pieces = sa.H >> 3;                      // 16-byte pieces of a row, this slice's share of them
     const int32_t c0 = (int32_t)((int64_t)pieces * slice / sa.slices), nc = (int32_t)((int64_t)pieces * (slice + 1) / sa.slices) - c0;
     const int64_t frag_bytes = (int64_t)((sa.H + 63) / 64) * 2048;
     const int32_t n = list_len * nc;
-    for (int32_t i = threadIdx.x; i < n; i += kSmallThreads) {
+    for (int32_t i = threadIdx.x; i < n; i += kDirectThreads) {
         const int32_t at = i / nc, c = c0 + i % nc;
         const int32_t row = list[2 * at + 1];
         const uint4 v = reinterpret_cast<const uint4 *>(static_cast<const unsigned char *>(sa.x) + (int64_t)list[2 * at] * sa.H * 2)[c];
@@ -417,13 +476,32 @@ __global__ __launch_bounds__(kSmallThreads) void dispatch_small_kernel(SmallDisp
 
 }  // namespace
 
-bool small_dispatch(int64_t T, int32_t S) { return T > 0 && T <= (int64_t)kSmallBlocks * kTokPerBlock && S <= kSmallSlots; }
+// (up to 16 chunks: every workgroup reads all of their totals)
+bool direct_dispatch(int64_t T, int32_t S) { return T > 0 && T <= 16ll * kDirectChunk * kTokPerBlock && S <= kDirectSlots; }
+bool small_dispatch(int64_t T, int32_t S) { return direct_dispatch(T, S) && T <= (int64_t)kSmallBlocks * kTokPerBlock; }
 
-hipError_t launch_dispatch_small(SmallDispatchArgs a, hipStream_t s) {
-    a.NB = (int32_t)((a.d.T + kTokPerBlock - 1) / kTokPerBlock);
+hipError_t launch_prefix(int32_t *hist, int32_t *chunk_tot, int32_t NB, int32_t E, hipStream_t s) {
+    if (NB <= kSmallBlocks) return hipSuccess;
+    const unsigned grid = (unsigned)((NB + kDirectChunk - 1) / kDirectChunk) * (unsigned)((E + 63) / 64);
+    hipLaunchKernelGGL(prefix_kernel, dim3(grid), dim3(64 * kDirectWaves), 0, s, hist, chunk_tot, NB, E);
+    return hipGetLastError();
+}
+
+hipError_t launch_dispatch_direct(DirectDispatchArgs a, const int32_t *chunk_tot, hipStream_t s) {
+    const int32_t NB = (int32_t)((a.d.T + kTokPerBlock - 1) / kTokPerBlock);
+    a.local = NB > kSmallBlocks;
+    a.chunk_blocks = a.local ? kDirectChunk : 1;
+    a.ntot = (NB + a.chunk_blocks - 1) / a.chunk_blocks;
+    a.tot = a.local ? chunk_tot : a.d.base;
     // enough workgroups to copy at memory speed, at least a few hundred columns each
-    a.slices = a.xpk ? std::max(1, std::min({256 / a.NB, a.H / 256, 16})) : 1;
-    hipLaunchKernelGGL(dispatch_small_kernel, dim3((unsigned)(a.NB * a.slices + 1)), dim3(kSmallThreads), 0, s, a);
+    a.slices = a.xpk ? std::max(1, std::min({256 / NB, a.H / 256, 16})) : 1;
+    // what a workgroup derives for itself is worth a few blocks where there are enough of them
+    a.span = 1;
+    while (a.local && a.span < 8 && NB / (a.span * 2) >= 256) a.span *= 2;
+    const int32_t spans = (NB + a.span - 1) / a.span;
+    const dim3 grid((unsigned)((a.slices > 1 ? spans * a.slices : (spans + 7) / 8 * 8) + 1)), block(kDirectThreads);
+    if (a.xpk) hipLaunchKernelGGL(dispatch_direct_kernel<true>, grid, block, 0, s, a);
+    else hipLaunchKernelGGL(dispatch_direct_kernel<false>, grid, block, 0, s, a);
     return hipGetLastError();
 }
 

@@ -1,6 +1,7 @@
 // Device-side entry points of the C ABI: argument checks, workspace layout, launches.
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -52,7 +53,7 @@ Layout make_layout(int64_t T, int32_t k, int32_t E, int32_t S, int32_t nslots, i
     L.hist = take((size_t)L.NB * E * 4);
     const size_t chunks = (size_t)(L.NB + kScanChunk - 1) / kScanChunk;
     L.chunk_tot = take(chunks * E * 4);
-    L.chunk_base = take(chunks * E * 4);
+    L.chunk_base = take(chunks * E * 4);             // right behind chunk_tot
     // scores and the split gate's partial scores, when the forward runs the gating network
     L.gate_ws_bytes = own_gate ? gate_workspace_bytes(dtype, T, H, E) : 0;
     L.gate_logits = take(own_gate ? (size_t)T * E * 4 : 0);
@@ -157,7 +158,7 @@ double ffn_makespan(const std::vector<double> &slot_rows, int32_t frags, bool ev
     return end;
 }
 
-struct tile_choice { int32_t frags[2]; bool riders[2]; bool stream = false; };
+struct tile_choice { int32_t frags[2]; bool riders[2]; bool stream = false, stream_rowmajor = false; };
 
 tile_choice choose_tiles(const craft_plan_t *plan, int32_t layer, int32_t rank, int64_t T, int32_t k,
                          int32_t H, int32_t I, int32_t cus) {
@@ -175,7 +176,17 @@ tile_choice choose_tiles(const craft_plan_t *plan, int32_t layer, int32_t rank, 
         rows.push_back(est >= 0.2 ? std::max(1.0, est) : 0.0);
     }
     std::sort(rows.begin(), rows.end(), std::greater<double>());
-    best.stream = rows.empty() || rows[0] <= (double)kStreamRows;
+    // Small batches are streamed (ffn_stream.hip) where that is faster, on MI355X:
+    //   - few slots, less than a half-width tile per CU between them, up to two passes of 64 rows:
+    //     the tiles leave CUs without work (H = 7168, I = 2048, us a forward, streamed / tiles: two
+    //     slots of 10 rows 51 / 76, of 57 59 / 90, of 76 87 / 134; of 153 rows 120 / 105)
+    //   - more slots, row-major weights, a single pass: 94 / 113 with eight live slots of up to 48
+    //     rows at H = 4096, I = 1536, 134 / 129 with up to 72.  Packed tiles are as fast: 80 / 72.
+    int64_t passes = 0;
+    for (double r : rows) passes += (int64_t)std::ceil(r / kStreamRows);
+    const double most = rows.empty() ? 0.0 : rows[0];
+    best.stream = most <= 2.0 * kStreamRows && passes * 2 * ((I + 127) / 128) <= cus;
+    best.stream_rowmajor = best.stream || most <= (double)kStreamRows;
     for (int kind = 0; kind < 2; ++kind) {
         const int64_t K = kind == 0 ? H : I, N = kind == 0 ? I : H;
         const int64_t nt = kind == 0 ? (N + 127) / 128 : (N + 255) / 256;
@@ -227,7 +238,7 @@ tile_choice tile_choice_of(const craft_plan_t *plan, int32_t layer, int32_t rank
         if (!hit) {
             const tile_choice c = choose_tiles(plan, layer, rank, a->T, a->k, a->H, a->I, cached_num_cu());
             craft_tile_choice *n = new craft_tile_choice{a->T, a->k, a->H, a->I, {c.frags[0], c.frags[1]},
-                                                         {c.riders[0], c.riders[1]}, c.stream,
+                                                         {c.riders[0], c.riders[1]}, c.stream, c.stream_rowmajor,
                                                          rs.tiles.load(std::memory_order_relaxed)};
             rs.tiles.store(n, std::memory_order_release);
             hit = n;
@@ -240,7 +251,7 @@ tile_choice tile_choice_of(const craft_plan_t *plan, int32_t layer, int32_t rank
     // the streaming kernels address x and a weight matrix by 32-bit byte offsets (the packed
     // kernels' sizes are checked with the other arguments)
     const int64_t limit = (int64_t)1 << 32;
-    if (may_stream && hit->stream && !(packed && told) && a->T * (int64_t)a->H * 2 < limit && (int64_t)a->I * a->H * 2 < limit)
+    if (may_stream && (packed ? hit->stream && !told : hit->stream_rowmajor) && a->T * (int64_t)a->H * 2 < limit && (int64_t)a->I * a->H * 2 < limit)
         return {{kStreamRows / 32, kStreamRows / 32}, {false, false}, true};
     if (!packed) return {{kFragsBf16, kFragsBf16}, {false, false}};
     // the caller's own heights: riders wherever such tiles can carry them, unless told
@@ -526,7 +537,6 @@ craft_status forward_on(const craft_plan_t *plan, int32_t layer, int32_t rank, c
     }
     const bool packed = a->w_gateup_packed && a->w_down_packed;
     tile_choice tiles = tiles_for(plan, layer, rank, a, packed);
-    const bool small = small_dispatch(a->T, S);
     if (tiles.stream) {
         // a workspace of the size that does for the tiles does for them still
         const Layout Ls = make_layout(a->T, a->k, E, S, nslots, a->H, a->I, a->dtype, a->max_rows, own_gate, true);
@@ -580,11 +590,15 @@ craft_status forward_on(const craft_plan_t *plan, int32_t layer, int32_t rank, c
                     a->dest, a->src, slot_cnt, s_lo, s_hi, tiles.frags[0], tiles.frags[1],
                     tiles.riders[0] ? (a->I + 127) / 128 : 0, tiles.riders[1] ? (a->H + 255) / 256 : 0,
                     mt_start, order, ctrl};
-    if (small) {
+    if (direct_dispatch(a->T, S)) {
+        if (L.NB > kSmallBlocks) {
+            ScopedEvent ev(CRAFT_K_SCAN, s);
+            if (launch_prefix(hist, chunk_tot, (int32_t)L.NB, E, s) != hipSuccess) return CRAFT_EHIP;
+        }
         ScopedEvent ev(CRAFT_K_DISPATCH, s);
-        SmallDispatchArgs sd{da, craft_tables_layout(E, S), S, L.max_rows, counts, slot_cnt, slot_off, a->counts, a->slot_cnt, a->slot_off,
-                             a->x, a->H, tiles.stream ? ws + L.xpk : nullptr, 0, 0};
-        if (launch_dispatch_small(sd, s) != hipSuccess) return CRAFT_EHIP;
+        DirectDispatchArgs dd{da, craft_tables_layout(E, S), S, L.max_rows, counts, slot_cnt, slot_off, a->counts, a->slot_cnt,
+                              a->slot_off, a->x, a->H, tiles.stream ? ws + L.xpk : nullptr, nullptr, 0, 0, 0, 0, false};
+        if (launch_dispatch_direct(dd, chunk_tot, s) != hipSuccess) return CRAFT_EHIP;
     } else {
         {
             ScopedEvent ev(CRAFT_K_SCAN, s);
@@ -599,7 +613,7 @@ craft_status forward_on(const craft_plan_t *plan, int32_t layer, int32_t rank, c
     FfnArgs fa{a->dtype, a->H, a->I, a->k, s_lo, nslots, a->x, src, slot_off, mt_start, order, ctrl,
                a->w_gate, a->w_up, a->w_down, a->w_gateup_packed, a->w_down_packed,
                ws + L.xpk, ws + L.act, ws + L.y, L.max_rows, cached_num_cu(), a->weight_format == CRAFT_W_E4M3 ? 1 : 0,
-               tiles.frags[0], tiles.frags[1]};
+               tiles.frags[0], tiles.frags[1], a->T * (int64_t)a->H * 2 >= (int64_t)1 << 32};
     if (a->T > 0) {
         {
             ScopedEvent ev(CRAFT_K_GATEUP, s);

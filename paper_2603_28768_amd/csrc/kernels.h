@@ -137,10 +137,12 @@ struct DispatchArgs {
 };
 hipError_t launch_dispatch(const DispatchArgs &a, hipStream_t s);
 
-// Batches of at most this many 32-token blocks: scan and dispatch in one launch.
-constexpr int kSmallBlocks = 16;
-struct SmallDispatchArgs {
-    DispatchArgs d;           // base: the blocks' counts themselves; chunk_base, slot_off and slot_cnt unused
+// Without the scan: see dispatch_direct_kernel.  Batches of at most kSmallBlocks 32-token blocks
+// need no other launch, larger ones launch_prefix over chunks of kDirectChunk blocks.
+constexpr int kSmallBlocks = 32;
+constexpr int kDirectChunk = kScanChunk / 2;   // the totals take the room of the scan's chunk_tot and chunk_base
+struct DirectDispatchArgs {
+    DispatchArgs d;           // base: the blocks' counts, or their prefixes inside a chunk; chunk_base, slot_off and slot_cnt unused
     craft_tables_header lay;  // of d.tables, known on the host: one round trip less
     int32_t S;
     int64_t max_rows;
@@ -149,10 +151,15 @@ struct SmallDispatchArgs {
     const void *x;            // [T][H] bf16
     int32_t H;
     unsigned char *xpk;       // where the small-batch FFN reads the token rows; null: not copied
-    int32_t NB, slices;       // set by the launcher
+    // set by the launcher
+    const int32_t *tot;       // [ntot][E] counts of the chunks of blocks
+    int32_t ntot, chunk_blocks, slices, span;
+    bool local;               // the blocks' prefixes inside their chunk come on top
 };
+bool direct_dispatch(int64_t T, int32_t S);
 bool small_dispatch(int64_t T, int32_t S);
-hipError_t launch_dispatch_small(SmallDispatchArgs a, hipStream_t s);
+hipError_t launch_prefix(int32_t *hist, int32_t *chunk_tot, int32_t NB, int32_t E, hipStream_t s);
+hipError_t launch_dispatch_direct(DirectDispatchArgs a, const int32_t *chunk_tot, hipStream_t s);
 
 struct FfnArgs {
     int32_t dtype;
@@ -174,6 +181,7 @@ struct FfnArgs {
     int32_t w8;                    // packed weights are E4M3 codes with row scales behind the stream
     int32_t frags_gu, frags_dn;    // most 32-row fragments per row-tile the tile tables were built for;
                                    // negative: fragments shared evenly among a slot's row-tiles
+    bool far_x;                    // x has rows more than 4 GiB from its start (row-major weights only)
 };
 hipError_t launch_gateup(const FfnArgs &a, hipStream_t s);
 hipError_t launch_down(const FfnArgs &a, hipStream_t s);

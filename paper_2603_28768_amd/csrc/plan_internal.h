@@ -39,7 +39,7 @@ struct craft_tile_choice {
     int32_t k, H, I;
     int32_t frags[2];
     bool riders[2];
-    bool stream;
+    bool stream, stream_rowmajor;
     craft_tile_choice *next;
 };
 

@@ -26,6 +26,8 @@ constexpr int kThreads = 16 * kTokPerBlock;   // a 16-lane row per token of the 
 constexpr int kMaxE = 1024;
 constexpr int kMaxPickSlots = 4;     // k <= 64 picks, 16 lanes per token
 
+typedef float score4_t __attribute__((ext_vector_type(4)));
+
 template <int CTRL>
 __device__ __forceinline__ float dpp_f(float v) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
@@ -56,11 +58,9 @@ __device__ __forceinline__ float row_sum(float v) {
     return v;
 }
 
-__device__ __forceinline__ uint64_t row_rotate(uint64_t v, std::integral_constant<int, 0>) { return v; }
-template <int N>
-__device__ __forceinline__ uint64_t row_rotate(uint64_t v, std::integral_constant<int, N>) {
-    constexpr int kRor = 0x120;
-    return (uint64_t)(uint32_t)dpp_i<kRor + N>((int)(v >> 32)) << 32 | (uint32_t)dpp_i<kRor + N>((int)v);
+__device__ __forceinline__ uint64_t row_rotate(uint64_t v) {
+    constexpr int kRor1 = 0x121;
+    return (uint64_t)(uint32_t)dpp_i<kRor1>((int)(v >> 32)) << 32 | (uint32_t)dpp_i<kRor1>((int)v);
 }
 template <typename F, int... N>
 __device__ __forceinline__ void each_rotation(F &&f, std::integer_sequence<int, N...>) {
@@ -76,15 +76,25 @@ __device__ __forceinline__ float key_score(uint64_t key) {
     const uint32_t u = (uint32_t)(key >> 32);
     return __uint_as_float(u ^ (((int32_t)u >> 31 ? 0u : ~0u) | 0x80000000u));
 }
-// How many of the row's 16 NC candidates beat candidate `own`.
+// How many of the row's 16 NC candidates beat the lane's own ones.  The row goes round one lane at a
+// time: rotations by every distance at once take registers that cost waves.
 template <int NC>
-__device__ __forceinline__ int row_rank(const uint64_t (&key)[NC], uint64_t own) {
-    int r = 0;
-    each_rotation([&](auto n) {
+__device__ __forceinline__ void row_rank(const uint64_t (&key)[NC], int (&rank)[NC]) {
+    uint64_t at[NC];
 #pragma unroll
-        for (int i = 0; i < NC; ++i) r += row_rotate(key[i], n) > own ? 1 : 0;
-    }, std::make_integer_sequence<int, 16>{});
-    return r;
+    for (int i = 0; i < NC; ++i) { at[i] = key[i]; rank[i] = 0; }
+#pragma unroll 1
+    for (int n = 0; n < 16; n += 4) {
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+#pragma unroll
+            for (int i = 0; i < NC; ++i)
+#pragma unroll
+                for (int j = 0; j < NC; ++j) rank[j] += at[i] > key[j] ? 1 : 0;
+#pragma unroll
+            for (int i = 0; i < NC; ++i) at[i] = row_rotate(at[i]);
+        }
+    }
 }
 
 // NQ = 16-byte score chunks per lane (each chunk = 4 experts; a row covers 64 experts per chunk).
@@ -123,8 +133,9 @@ __global__ __launch_bounds__(kThreads) void route_kernel(RouteArgs a) {
             if (vec_ok) {
 #pragma unroll
                 for (int q = 0; q < NQ; ++q) {
-                    const float4 f = *reinterpret_cast<const float4 *>(from + min(q * 64 + sub * 4, a.E - 4));
-                    to[q][0] = f.x; to[q][1] = f.y; to[q][2] = f.z; to[q][3] = f.w;
+                    // (a vector type, not float4: four loads of a struct are merged with the other branch's)
+                    const score4_t f = *reinterpret_cast<const score4_t *>(from + min(q * 64 + sub * 4, a.E - 4));
+                    to[q][0] = f[0]; to[q][1] = f[1]; to[q][2] = f[2]; to[q][3] = f[3];
                 }
             } else {
 #pragma unroll
@@ -167,7 +178,8 @@ __global__ __launch_bounds__(kThreads) void route_kernel(RouteArgs a) {
         // Few of the row's scores can be among its k best: the k-th largest of the 16 lanes' maxima
         // is a bound that k of them reach, and a dozen or so reach in all.  Those are gathered
         // through LDS, one or two to a lane, and each finds its place by being compared with
-        // every other (E = 256, k = 8: a third of the instructions of k arg-max rounds).
+        // every other (k = 8: T = 32768, E = 256 20.6 -> 14.2 us, T = 16384, E = 384 15.9 -> 9.0, against k arg-max
+        // rounds).
         const bool few = NQ <= 8 && a.k <= 16;     // more than 512 scores: no registers for it
         int n_cand = 0;
         float bound = kGone;
@@ -214,11 +226,12 @@ __global__ __launch_bounds__(kThreads) void route_kernel(RouteArgs a) {
             int rank[2] = {0, 32};
             if (wide) {
                 key[1] = 16 + sub < row_cands ? cand[tl][16 + sub] : 0;
-                rank[0] = row_rank(key, key[0]);
-                rank[1] = row_rank(key, key[1]);
+                row_rank(key, rank);
             } else {
                 const uint64_t one[1] = {key[0]};
-                rank[0] = row_rank(one, key[0]);
+                int r[1];
+                row_rank(one, r);
+                rank[0] = r[0];
             }
             __builtin_amdgcn_wave_barrier();
 #pragma unroll
@@ -235,21 +248,15 @@ __global__ __launch_bounds__(kThreads) void route_kernel(RouteArgs a) {
             for (int s = 0; s < kMaxPickSlots; ++s) {
                 const int jn = min(16, a.k - s * 16);  // picks that land in slot s
                 for (int j = 0; j < jn; ++j) {
-                    // the lane's best: a tournament in ascending expert order, the later entry
-                    // winning only when strictly greater, so equal scores keep the lower id
-                    float tv[NQ * 4];
-                    int ti[NQ * 4];
+                    // the lane's best, in ascending expert order: a later one wins only when
+                    // strictly greater, so equal scores keep the lower id
+                    float bv = v[0][0];
+                    int bi = sub * 4;
 #pragma unroll
                     for (int q = 0; q < NQ; ++q)
 #pragma unroll
-                        for (int c = 0; c < 4; ++c) { tv[q * 4 + c] = v[q][c]; ti[q * 4 + c] = q * 64 + sub * 4 + c; }
-#pragma unroll
-                    for (int width = 1; width < NQ * 4; width *= 2)
-#pragma unroll
-                        for (int i = 0; i + width < NQ * 4; i += 2 * width)
-                            if (tv[i + width] > tv[i]) { tv[i] = tv[i + width]; ti[i] = ti[i + width]; }
-                    float bv = tv[0];
-                    int bi = ti[0];
+                        for (int c = 0; c < 4; ++c)
+                            if (v[q][c] > bv) { bv = v[q][c]; bi = q * 64 + sub * 4 + c; }
                     argmax_step<kXor1>(bv, bi);
                     argmax_step<kXor2>(bv, bi);
                     argmax_step<kHalfMirror>(bv, bi);
