@@ -171,4 +171,44 @@ static __device__ __forceinline__ F wload(ubase_t base, uint32_t &off) {
     return *p;
 }
 
+// 16 bytes per lane from base + off straight into LDS at lds + 16 * lane (lds: the byte address
+// of the wave's 1 KiB destination, wave-uniform; it goes through M0, which the compiler keeps
+// nothing in across statements).  The compiler does not know that this is a load: it neither
+// counts it among the outstanding requests (its own waits for other loads then only wait longer
+// than needed, requests complete in order) nor waits for it before LDS reads (dma_wait does).
+static __device__ __forceinline__ void dma_chunk(ubase_t base, uint32_t off, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                 :: "s"(lds), "v"(off), "s"(base) : "memory");
+}
+// dma_chunk in two statements, with at least one instruction between them
+static __device__ __forceinline__ void dma_to(uint32_t lds) { asm volatile("s_mov_b32 m0, %0" :: "s"(lds) : "memory"); }
+static __device__ __forceinline__ void dma_request(ubase_t base, uint32_t off) {
+    asm volatile("global_load_lds_dwordx4 %0, %1" :: "v"(off), "s"(base) : "memory");
+}
+// the same from an address of the lane's own
+static __device__ __forceinline__ void dma_request_at(ubase_t p) {
+    asm volatile("global_load_lds_dwordx4 %0, off" :: "v"(p) : "memory");
+}
+// wait until at most N of this wave's requests are outstanding
+template <int N> static __device__ __forceinline__ void dma_wait() {
+    asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory");
+}
+
+// acc += w x^T for a 16-row weight fragment and a 16-row activation fragment over 32
+// contraction elements.  Written out as an instruction whose accumulator operand is both read
+// and written (an accumulation register tuple, "+a"): a tall tile's 64 accumulators fill the
+// accumulation half of the register file exactly, and every copy the register allocator makes
+// when result and addend are two values costs moves through the other half.  The compiler does
+// not know that this is a matrix instruction: the waits it would insert between a matrix
+// instruction and a read of its result are the caller's — inside the
+// contraction loop an accumulator is touched again only a whole half-step later.
+// FRESH: an operand has just been written by ordinary vector instructions (8-bit weights
+// widened to bf16); a matrix instruction may read such a register two issue cycles later at
+// the earliest, which the compiler would see to for an instruction it knows.
+template <bool FRESH>
+static __device__ __forceinline__ void mfma16(bf16x8_t w, bf16x8_t x, f32x4_t &c) {
+    if (FRESH) asm("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(w), "v"(x));
+    else asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(w), "v"(x));
+}
+
 }  // namespace craft

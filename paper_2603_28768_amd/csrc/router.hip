@@ -6,132 +6,62 @@
 //
 // A skinny GEMM: few output columns (E = 128 .. 384), so the tokens' activations are what
 // has to cross HBM (once) and the gate's weights are re-read from L2 by every workgroup.
-// bf16: a workgroup of four waves takes NXF fragments of 32 tokens against up to 512 experts
-// (more experts: further workgroups along y); wave w owns the blocks of 32 experts w, w + 4, ..
-// Both operands are staged through LDS in slabs of 64 (rows padded to 144 bytes, two stages,
-// one barrier per slab) and D slabs travel in registers ahead of the one being multiplied
-// (v_mfma_f32_32x32x16_bf16).  The activations feed the MFMA's row operand and the gate rows
-// its column operand, so that for each accumulator element lanes 0-31 hold 32 consecutive
-// experts of one token: stores are 128 contiguous bytes.
-// What bounds it: every workgroup pulls the whole gate out of L2, so T H 2 (1 + E / tokens
-// per workgroup) bytes move from L2 into the CUs, at the 11-12 TB/s the chip sustains there
-// with every CU pulling.  Taller workgroups move less but there are only T / 128 of them, so
-// with a workspace the contraction is split over up to 8 workgroups per tile: each writes
-// its partial scores and a second kernel adds them in ascending order of the split (a fixed
-// order: the result does not depend on scheduling).  Gate rows loaded straight into
-// registers in operand layout (32-byte pieces of 32 rows per request) measured slower.
+// bf16: 32, 64 or 128 tokens against up to 256 experts per workgroup (nt_tile.h), the experts as the
+// matrix instruction's row operand, so that a lane holds four neighbouring experts of a token:
+// 16-byte stores.  Every workgroup pulls the whole gate out of L2, so T H 2 (1 + E / tokens per
+// workgroup) bytes move from L2 into the CUs; taller workgroups move less but there are only
+// T / 128 of them, so with a workspace the contraction is split over up to 8 workgroups per tile:
+// each writes its partial scores and a second kernel (or the routing kernel) adds them in ascending
+// order of the split (a fixed order: the result does not depend on scheduling).
 // fp32: one thread per score, a plain chain of fused multiply-adds (small configurations).
-#include "ffn_common.h"
+#include "nt_tile.h"
 
 namespace craft {
 namespace {
 
 constexpr int kThinBatch = 128;         // tokens up to which the gate is read by thin tiles
 constexpr int GK = 64;                  // contraction slab
-constexpr int GROWB = GK * 2 + 16;      // padded LDS row, bytes
 typedef unsigned int gu32x4_t __attribute__((ext_vector_type(4)));
 typedef const gu32x4_t __attribute__((address_space(1))) *gchunk_t;
 
-template <int NB, int NXF, int D>
-__global__ __launch_bounds__(256) void router_logits_bf16_kernel(RouterArgs a) {
-    extern __shared__ __attribute__((aligned(16))) unsigned char gate_smem[];
-    constexpr int STAGEB = (NXF * 32 + NB * 128) * GROWB;  // activations [NXF * 32] rows, gate [NB * 128]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int lr = tid >> 3, kc = tid & 7;                 // row (plus 32 i) and 16-byte chunk staged
-    const int frag_off = (lane & 31) * GROWB + (lane >> 5) * 16;
-    const int64_t t0 = (int64_t)blockIdx.x * (NXF * 32);
-    const int e0 = blockIdx.y * (NB * 128);
-    const int hchunks = a.H >> 3;                          // 16-byte chunks per row
-    // this workgroup's share of the contraction: slabs kbeg .. kbeg + nk - 1 (nk may be 0)
-    const int nk_all = (a.H + GK - 1) / GK;
-    const int per = (nk_all + a.nsplit - 1) / a.nsplit;
-    const int kbeg = min(nk_all, (int)blockIdx.z * per);
-    const int nk = min(nk_all, kbeg + per) - kbeg;
+template <int FA, int FB>
+__global__ __launch_bounds__(kNtThreads) void router_logits_bf16_kernel(RouterArgs a) {
+    __shared__ __attribute__((aligned(16))) unsigned char gate_smem[nt_lds_bytes<FA, FB>()];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int64_t t0 = (int64_t)blockIdx.x * (FB * 32);
+    const int e0 = blockIdx.y * (FA * 32);
+    // this workgroup's share of the contraction (may be empty)
+    const int nk = (a.H + GK - 1) / GK, per = (nk + a.nsplit - 1) / a.nsplit;
+    const int kbeg = min(nk, (int)blockIdx.z * per), kend = min(nk, kbeg + per);
     float *dst = a.nsplit > 1 ? a.part + (int64_t)blockIdx.z * a.T * a.E : a.logits;
-
     // rows past the end are clamped into the matrix (their results are not stored)
-    gchunk_t xrow[NXF], wrow[NB * 4];
+    auto eoff = [&](int i) { return (uint32_t)min(i, a.E - 1 - e0) * (uint32_t)a.H * 2u; };
+    auto toff = [&](int i) { return (uint32_t)min((int64_t)i, a.T - 1 - t0) * (uint32_t)a.H * 2u; };
+    f32x4_t acc[FA][FB];
 #pragma unroll
-    for (int i = 0; i < NXF; ++i)
-        xrow[i] = (gchunk_t)a.x + min(t0 + lr + 32 * i, a.T - 1) * hchunks;
+    for (int f = 0; f < FA; ++f)
 #pragma unroll
-    for (int j = 0; j < NB * 4; ++j)
-        wrow[j] = (gchunk_t)a.w + (int64_t)min(e0 + lr + 32 * j, a.E - 1) * hchunks;
-
-    f32x16_t acc[NB][NXF];
+        for (int g = 0; g < FB; ++g) acc[f][g] = (f32x4_t)(0.0f);
+    nt_tile<FA, FB>(gate_smem, uniform_base(static_cast<ubase_t>(a.w) + (int64_t)e0 * a.H * 2), eoff,
+                    uniform_base(static_cast<ubase_t>(a.x) + t0 * a.H * 2), toff, a.H, kbeg, kend, acc);
+    const bool whole = (a.E & 3) == 0 && (reinterpret_cast<uintptr_t>(dst) & 15) == 0;
 #pragma unroll
-    for (int b = 0; b < NB; ++b)
+    for (int g = 0; g < FB; ++g) {
+        const int64_t t = t0 + ((wave & 1) * FB + g) * 16 + (lane & 15);
 #pragma unroll
-        for (int g = 0; g < NXF; ++g)
+        for (int f = 0; f < FA; ++f) {
+            const int e = e0 + ((wave >> 1) * FA + f) * 16 + (lane >> 4) * 4;
+            if (t >= a.T || e >= a.E) continue;
+            float *to = dst + t * a.E + e;
+            if (whole) {
+                *reinterpret_cast<f32x4_t *>(to) = acc[f][g];
+            } else {
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[b][g][v] = 0.0f;
-
-    gu32x4_t xr[D][NXF], wr[D][NB * 4];
-    const gu32x4_t zero = {0u, 0u, 0u, 0u};
-    // Slab ks -> register set d.  A chunk past the end of the rows is read from inside the
-    // rows instead and replaced by zeros when it goes to LDS: touching the value here would
-    // make the wave wait for the load on the spot.
-#define GATE_REQUEST(d, ks)                                                              \
-    {                                                                                    \
-        const int c = min((ks) * (GK / 8) + kc, hchunks - 1);                            \
-        _Pragma("unroll") for (int i = 0; i < NXF; ++i) xr[d][i] = xrow[i][c];           \
-        _Pragma("unroll") for (int j = 0; j < NB * 4; ++j) wr[d][j] = wrow[j][c];        \
-    }
-    // no branch around a request, here or in the loop: the count of loads in flight has to be
-    // the same on every path for the waits to let D slabs stay outstanding (past the last
-    // slab the last one is requested again and never used)
-#pragma unroll
-    for (int d = 0; d < D; ++d) GATE_REQUEST(d, min(kbeg + d, nk_all - 1))
-    for (int ks0 = 0; ks0 < nk; ks0 += 2 * D) {
-#pragma unroll
-        for (int dd = 0; dd < 2 * D; ++dd) {               // 2 D slabs per trip: set and stage are static
-            const int ks = ks0 + dd;
-            if (ks >= nk) break;
-            const int d = dd % D;
-            unsigned char *xs = gate_smem + (dd & 1) * STAGEB;
-            unsigned char *ws = xs + NXF * 32 * GROWB;
-            const bool in = (kbeg + ks) * (GK / 8) + kc < hchunks;
-#pragma unroll
-            for (int i = 0; i < NXF; ++i)
-                *reinterpret_cast<gu32x4_t *>(xs + (lr + 32 * i) * GROWB + kc * 16) = in ? xr[d][i] : zero;
-#pragma unroll
-            for (int j = 0; j < NB * 4; ++j)
-                *reinterpret_cast<gu32x4_t *>(ws + (lr + 32 * j) * GROWB + kc * 16) = in ? wr[d][j] : zero;
-            // one barrier per slab: the other stage is rewritten only after every wave has
-            // passed this one, that is, has finished reading it
-            __syncthreads();
-            GATE_REQUEST(d, min(kbeg + ks + D, nk_all - 1))
-#pragma unroll
-            for (int step = 0; step < GK / 16; ++step) {
-                bf16x8_t xa[NXF];
-#pragma unroll
-                for (int g = 0; g < NXF; ++g)
-                    xa[g] = *reinterpret_cast<const bf16x8_t *>(xs + g * 32 * GROWB + frag_off + step * 32);
-#pragma unroll
-                for (int b = 0; b < NB; ++b) {
-                    const bf16x8_t wb = *reinterpret_cast<const bf16x8_t *>(
-                        ws + (b * 4 + wave) * 32 * GROWB + frag_off + step * 32);
-#pragma unroll
-                    for (int g = 0; g < NXF; ++g)
-                        acc[b][g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa[g], wb, acc[b][g], 0, 0, 0);
-                }
+                for (int c = 0; c < 4; ++c)
+                    if (e + c < a.E) to[c] = acc[f][g][c];
             }
         }
-    }
-#undef GATE_REQUEST
-
-    // accumulator element v of lane l: token row (v/4)*8 + (l>>5)*4 + v%4 of the fragment,
-    // expert (l & 31) of the block
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-        const int e = e0 + (b * 4 + wave) * 32 + (lane & 31);
-#pragma unroll
-        for (int g = 0; g < NXF; ++g)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int64_t t = t0 + g * 32 + (v / 4) * 8 + (lane >> 5) * 4 + v % 4;
-                if (t < a.T && e < a.E) dst[t * a.E + e] = acc[b][g][v];
-            }
     }
 }
 
@@ -209,11 +139,16 @@ __global__ __launch_bounds__(64 * kThinWaves) void router_thin_kernel(RouterArgs
 }
 
 // logits = sum of the partial scores, in ascending order of the split
-__global__ __launch_bounds__(256) void router_reduce_kernel(const float *part, int nsplit, int64_t n, float *logits) {
+template <typename V, int NSPLIT>
+__global__ __launch_bounds__(256) void router_reduce_kernel(const V *part, int64_t n, V *logits) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    float s = part[i];
-    for (int z = 1; z < nsplit; ++z) s += part[(int64_t)z * n + i];
+    V v[NSPLIT];                                           // all parts are requested before the first is added
+#pragma unroll
+    for (int z = 0; z < NSPLIT; ++z) v[z] = part[(int64_t)z * n + i];
+    V s = v[0];
+#pragma unroll
+    for (int z = 1; z < NSPLIT; ++z) s += v[z];
     logits[i] = s;
 }
 
@@ -227,21 +162,24 @@ __global__ __launch_bounds__(256) void router_logits_f32_kernel(RouterArgs a) {
     a.logits[o] = s;
 }
 
-template <int NB, int NXF, int D>
+template <typename V>
+void launch_reduce(const RouterArgs &a, int nsplit, int64_t n, hipStream_t s) {
+    const dim3 grid((unsigned)((n + 255) / 256)), block(256);
+    const V *part = reinterpret_cast<const V *>(a.part);
+    V *out = reinterpret_cast<V *>(a.logits);
+    if (nsplit == 2) hipLaunchKernelGGL((router_reduce_kernel<V, 2>), grid, block, 0, s, part, n, out);
+    else if (nsplit == 4) hipLaunchKernelGGL((router_reduce_kernel<V, 4>), grid, block, 0, s, part, n, out);
+    else hipLaunchKernelGGL((router_reduce_kernel<V, 8>), grid, block, 0, s, part, n, out);
+}
+template <int FA, int FB>
 hipError_t launch_bf16(const RouterArgs &a, hipStream_t s) {
-    constexpr size_t lds = (size_t)2 * (NXF * 32 + NB * 128) * GROWB;
-    static_assert(lds <= 160 * 1024, "two stages have to fit the CU's LDS");
-    static bool raised = false;                            // more than the default 64 KB of LDS
-    if (!raised && lds > 64 * 1024) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(router_logits_bf16_kernel<NB, NXF, D>),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-        raised = true;
-    }
-    const dim3 grid((unsigned)((a.T + NXF * 32 - 1) / (NXF * 32)), (unsigned)((a.E + NB * 128 - 1) / (NB * 128)),
-                    (unsigned)a.nsplit);
-    hipLaunchKernelGGL((router_logits_bf16_kernel<NB, NXF, D>), grid, dim3(256), lds, s, a);
+    const dim3 grid((unsigned)((a.T + FB * 32 - 1) / (FB * 32)), (unsigned)((a.E + FA * 32 - 1) / (FA * 32)), (unsigned)a.nsplit);
+    hipLaunchKernelGGL((router_logits_bf16_kernel<FA, FB>), grid, dim3(kNtThreads), 0, s, a);
     return hipGetLastError();
+}
+template <int FA>
+hipError_t launch_bf16(const RouterArgs &a, int nxf, hipStream_t s) {
+    return nxf == 1 ? launch_bf16<FA, 1>(a, s) : nxf == 2 ? launch_bf16<FA, 2>(a, s) : launch_bf16<FA, 4>(a, s);
 }
 
 }  // namespace
@@ -272,7 +210,6 @@ hipError_t launch_router_logits(const RouterArgs &a, hipStream_t s) {
         hipLaunchKernelGGL(router_logits_f32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a);
         return hipGetLastError();
     }
-    const int nb = a.E > 512 ? 4 : (a.E + 127) / 128;      // blocks of 32 experts per wave
     int nxf, nsplit;
     router_logits_shape(a.T, a.H, a.E, a.num_cu, a.part != nullptr, &nxf, &nsplit);
     RouterArgs b = a;
@@ -283,22 +220,15 @@ hipError_t launch_router_logits(const RouterArgs &a, hipStream_t s) {
         hipLaunchKernelGGL(router_thin_kernel, grid, dim3(64 * kThinWaves), 0, s, b);
         err = hipGetLastError();
     } else {
-        switch (nb * 16 + nxf) {
-            case 1 * 16 + 1: err = launch_bf16<1, 1, 4>(b, s); break;
-            case 1 * 16 + 2: err = launch_bf16<1, 2, 4>(b, s); break;
-            case 1 * 16 + 4: err = launch_bf16<1, 4, 4>(b, s); break;
-            case 2 * 16 + 1: err = launch_bf16<2, 1, 4>(b, s); break;
-            case 2 * 16 + 2: err = launch_bf16<2, 2, 4>(b, s); break;
-            case 2 * 16 + 4: err = launch_bf16<2, 4, 3>(b, s); break;
-            case 3 * 16 + 1: err = launch_bf16<3, 1, 3>(b, s); break;
-            case 3 * 16 + 2: err = launch_bf16<3, 2, 3>(b, s); break;
-            case 3 * 16 + 4: err = launch_bf16<3, 4, 1>(b, s); break;
-            default: err = launch_bf16<4, 1, 3>(b, s); break;
-        }
+        // blocks of up to 256 experts, as even as they come
+        const int blocks = (a.E + 255) / 256, rows = (a.E + blocks - 1) / blocks;
+        err = rows <= 64 ? launch_bf16<2>(b, nxf, s) : rows <= 128 ? launch_bf16<4>(b, nxf, s)
+              : rows <= 192 ? launch_bf16<6>(b, nxf, s) : launch_bf16<8>(b, nxf, s);
     }
     if (err != hipSuccess || nsplit == 1 || a.keep_parts) return err;
     const int64_t n = a.T * a.E;
-    hipLaunchKernelGGL(router_reduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a.part, nsplit, n, a.logits);
+    if (n % 4 == 0 && (reinterpret_cast<uintptr_t>(a.logits) & 15) == 0) launch_reduce<f32x4_t>(a, nsplit, n / 4, s);
+    else launch_reduce<float>(a, nsplit, n, s);
     return hipGetLastError();
 }
 
