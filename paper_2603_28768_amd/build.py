@@ -28,9 +28,10 @@ def _hipcc() -> str:
     return "hipcc"
 
 
-# Sources whose matrix instructions are written as asm statements, which the compiler's hazard
-# pass does not recognise: their emitted code is checked here instead (check_matrix_operands).
-ASM_MFMA_SOURCES = {"ffn_packed.hip"}
+# Sources whose matrix instructions (ffn_packed.hip) or loads into LDS are written as asm
+# statements, which the compiler's hazard pass does not recognise: their emitted code is checked
+# here instead (check_matrix_operands).
+ASM_MFMA_SOURCES = {"ffn_packed.hip", "ffn.hip", "router.hip"}
 
 
 def _registers(token: str) -> set:

@@ -7,258 +7,258 @@
 //   down    : y[r][h]   = sum_i act[r][i] Wd[h][i]
 //
 // Work is cut into tiles of (slot, column tile, row tile).  Slots differ wildly in rows
-// under skewed routing, so the tile list is data dependent: the scan kernel leaves a
-// prefix table of row tiles per slot in device memory and a persistent grid walks the
-// flattened list; a slot with no rows contributes no tile, a slot with few rows one
-// (ragged) row tile per column tile.  Row tiles of the same (slot, column tile) are
-// adjacent in the list and the workgroup-to-tile mapping keeps neighbours on one XCD, so
+// under skewed routing, so the tile list is data dependent: a prefix table of row tiles per
+// slot is left in device memory, a persistent grid takes its first tiles by position and the
+// rest from a counter, busiest slots first; a slot with no rows contributes no tile, a slot with
+// few rows one (ragged) row tile per column tile.  Row tiles of the same (slot, column tile)
+// are adjacent in the list and the workgroup-to-tile mapping keeps neighbours on one XCD, so
 // a weight tile is fetched from HBM once and re-read from that XCD's L2.
 //
-// bf16 path: 128 x 128 x 64 tiles on v_mfma_f32_32x32x16_bf16, fp32 accumulation, both
-// operands staged through LDS (double buffered, rows padded to 144 bytes so 16-byte
-// fragment reads spread over all banks).  The weight rows feed the MFMA's row operand and
-// the activation rows its column operand, so that a lane ends up with four consecutive
-// output columns of one activation row (an 8-byte store).  For gate/up the 128 weight rows
-// of a tile are 64 gate rows and the matching 64 up rows; each wave holds gate and up
-// accumulators for the same outputs and applies SwiGLU in registers.  The gate/up GEMM
-// reads its rows straight from x through the dispatch permutation (no staged copy).
+// bf16 path: 256 weight rows against 32, 64 or 128 activation rows (nt_tile.h).  For gate/up
+// the weight rows of a tile are 128 gate and the 128 matching up rows, 16 of one followed by 16 of
+// the other, so that gate and up of one output meet in the same lane and element of two
+// accumulators: SwiGLU is applied in registers.  The gate/up GEMM reads its rows straight from x
+// through the dispatch permutation (no staged copy).  What bounds it is what a CU pulls out of its
+// L2, 48 KiB per slab of a tall tile in 1.4 us: taller tiles move less but come out in fewer
+// rounds.  1777 tokens on 17 slots, H = 4096, I = 1536: gate/up 190 -> 117 us, down 84 -> 63 (before: 128 x
+// 128 tiles through registers, one slab ahead).
 //
-// fp32 path: a plain LDS-tiled FMA kernel with the same tile list (small configurations).
-#include "ffn_common.h"
+// fp32 path: units of 16 columns and 32 rows from the same tile list (small configurations).
+#include <type_traits>
+
+#include "nt_tile.h"
 
 namespace craft {
 namespace {
 
 // ------------------------------------------------------------------ bf16 / MFMA
-constexpr int BM = kFragsBf16 * 32; // most activation rows per tile
-constexpr int BK = 64;            // contraction slab
-constexpr int ROWB = BK * 2 + 16; // padded LDS row, bytes
-constexpr int TILEB = 128 * ROWB; // one operand tile
-constexpr int STAGEB = 2 * TILEB;
+// Row of the A operand of a tile -> weight row, relative to the tile's first output column.  For
+// gate/up, 16 gate rows are followed by the 16 up rows of the same columns.
+template <bool GATEUP> static __device__ __forceinline__ int weight_row(int r) {
+    return GATEUP ? (r >> 5) * 16 + (r & 15) : r;
+}
 
-template <bool GATEUP>
-__global__ __launch_bounds__(256, 2) void ffn_bf16_kernel(FfnArgs a) {
-    __shared__ __attribute__((aligned(16))) unsigned char smem[2 * STAGEB];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wn = wave & 1, wm = wave >> 1;
+template <bool GATEUP, int FB, bool FAR>
+__device__ __forceinline__ int32_t bf16_tile(const FfnArgs &a, const Tile &t, unsigned char *smem, int K, int N, int32_t lo_pos,
+                                             int32_t *counter) {
+    constexpr int FA = 8;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    // chunks of 32 rows of A: the first two waves fetch gate rows, the others up rows
+    const void *w = GATEUP ? (wave < 2 ? a.w_gate[t.slot] : a.w_up[t.slot]) : a.w_down[t.slot];
+    const ubase_t wbase = uniform_base(static_cast<ubase_t>(w) + (int64_t)t.n0 * K * 2);
+    auto woff = [&](int r) { return (uint32_t)min(weight_row<GATEUP>(r), N - 1 - t.n0) * (uint32_t)K * 2u; };
+    const ubase_t xbase = uniform_base(GATEUP ? static_cast<ubase_t>(a.x)
+                                              : static_cast<ubase_t>(a.act) + (int64_t)(t.pos0 + t.m0 - lo_pos) * K * 2);
+    typedef typename std::conditional<FAR, uint64_t, uint32_t>::type off_t;
+    auto xoff = [&](int r) {
+        const int rr = min(r, t.rows - 1);
+        return (off_t)(GATEUP ? a.src[t.pos0 + t.m0 + rr] / a.k : rr) * (off_t)K * (off_t)2;
+    };
+    f32x4_t acc[FA][FB];
+#pragma unroll
+    for (int f = 0; f < FA; ++f)
+#pragma unroll
+        for (int g = 0; g < FB; ++g) acc[f][g] = (f32x4_t)(0.0f);
+    // (the other wave's matrix counts too: all waves have to take the same path)
+    const uintptr_t bits = reinterpret_cast<uintptr_t>(GATEUP ? a.w_gate[t.slot] : a.w_down[t.slot]) |
+                           reinterpret_cast<uintptr_t>(GATEUP ? a.w_up[t.slot] : a.w_down[t.slot]);
+    if ((__builtin_amdgcn_readfirstlane((int)bits) & 15) == 0) nt_tile<FA, FB>(smem, wbase, woff, xbase, xoff, K, 0, (K + 63) / 64, acc);
+    else nt_tile_unaligned<FA, FB>(smem, wbase, woff, xbase, xoff, K, 0, (K + 63) / 64, acc);
+    // the next tile is claimed here, its number arrives while the results are stored
+    // (an increment: an add of a uniform value becomes a wave-wide reduction)
+    int32_t claimed = 0;
+    if (threadIdx.x == 0) claimed = (int32_t)atomicInc(reinterpret_cast<unsigned int *>(counter), 0xffffffffu);
+    unsigned short *outp = static_cast<unsigned short *>(GATEUP ? a.act : a.y);
+#pragma unroll
+    for (int g = 0; g < FB; ++g) {
+        const int m = ((wave & 1) * FB + g) * 16 + (lane & 15);
+        unsigned short *orow = outp + (int64_t)(t.pos0 + t.m0 + m - lo_pos) * N;
+#pragma unroll
+        for (int f = 0; f < FA; f += GATEUP ? 2 : 1) {
+            const int col = t.n0 + weight_row<GATEUP>(((wave >> 1) * FA + f) * 16) + (lane >> 4) * 4;
+            if (m >= t.rows || col >= N) continue;
+            float v[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) v[c] = GATEUP ? silu(acc[f][g][c]) * acc[f + (GATEUP ? 1 : 0)][g][c] : acc[f][g][c];
+            *reinterpret_cast<uint2 *>(orow + col) = make_uint2(bf16_pair(v[0], v[1]), bf16_pair(v[2], v[3]));
+        }
+    }
+    return claimed;
+}
+
+template <bool GATEUP, bool FAR>
+__global__ __launch_bounds__(kNtThreads, 1) void ffn_bf16_kernel(FfnArgs a) {
+    __shared__ __attribute__((aligned(16))) unsigned char ffn_smem[kNtLds];
+    __shared__ TileTables tt;
+    __shared__ int64_t next_item;
+    const int32_t *mt_start = a.mt_start + (GATEUP ? 0 : a.nslots + 1);
+    const bool small = a.nslots <= TileTables::kMaxSlots;
+    if (small) load_tile_tables(a, mt_start, tt);
     const int K = GATEUP ? a.H : a.I;              // contraction length
     const int N = GATEUP ? a.I : a.H;              // output columns
-    constexpr int BN = GATEUP ? 64 : 128;          // output columns per tile
+    constexpr int BN = GATEUP ? 128 : 256;         // output columns per tile
     const int nt = (N + BN - 1) / BN;
-    const int nk = (K + BK - 1) / BK;
-    const int32_t *mt_start = a.mt_start + (GATEUP ? 0 : a.nslots + 1);
     const int64_t total = (int64_t)mt_start[a.nslots] * nt;
     const int32_t lo_pos = a.slot_off[a.s_lo];
-    const unsigned short *xin = static_cast<const unsigned short *>(GATEUP ? a.x : a.act);
-
-    const int lr = tid >> 3;                       // row handled when loading (plus 32*i)
-    const int kc = tid & 7;                        // 16-byte chunk inside the slab
-    const int nf0 = GATEUP ? wn * 32 : wn * 64;    // weight-row fragments of this wave
-    const int nf1 = GATEUP ? 64 + wn * 32 : wn * 64 + 32;
-    const int mf0 = wm * 64, mf1 = wm * 64 + 32;   // activation-row fragments
-    const int frag_off = (lane & 31) * ROWB + (lane >> 5) * 16;
-
-    for (int64_t w = first_tile(total); w < total; w += gridDim.x) {
-        const Tile t = decode_tile(a, mt_start, w, nt, BN, GATEUP ? a.frags_gu : a.frags_dn);
-        const unsigned short *wa = static_cast<const unsigned short *>(
-            GATEUP ? a.w_gate[t.slot] : a.w_down[t.slot]);
-        const unsigned short *wb = GATEUP ? static_cast<const unsigned short *>(a.w_up[t.slot]) : wa;
-
-        const unsigned short *xp[4], *wp[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int r = lr + 32 * i;
-            const int rr = min(r, t.rows - 1);
-            const int32_t pos = t.pos0 + t.m0 + rr;
-            if (GATEUP) xp[i] = xin + (int64_t)(a.src[pos] / a.k) * K + kc * 8;
-            else xp[i] = xin + (int64_t)(pos - lo_pos) * K + kc * 8;
-            int wr;
-            const unsigned short *wbase;
-            if (GATEUP) { wr = t.n0 + (r & 63); wbase = r < 64 ? wa : wb; }
-            else { wr = t.n0 + r; wbase = wa; }
-            wr = min(wr, N - 1);
-            wp[i] = wbase + (int64_t)wr * K + kc * 8;
-        }
-
-        f32x16_t acc[2][2];
-#pragma unroll
-        for (int f = 0; f < 2; ++f)
-#pragma unroll
-            for (int g = 0; g < 2; ++g)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) acc[f][g][v] = 0.0f;
-
-        uint4 xr[4], wr4[4];
-        auto load_slab = [&](int ks) {
-            const int koff = ks * BK;
-            const bool ok = koff + kc * 8 < K;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                xr[i] = ok ? *reinterpret_cast<const uint4 *>(xp[i] + koff) : make_uint4(0, 0, 0, 0);
-                wr4[i] = ok ? *reinterpret_cast<const uint4 *>(wp[i] + koff) : make_uint4(0, 0, 0, 0);
-            }
-        };
-        auto store_slab = [&](int stage) {
-            unsigned char *ws = smem + stage * STAGEB, *xs = ws + TILEB;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int off = (lr + 32 * i) * ROWB + kc * 16;
-                *reinterpret_cast<uint4 *>(ws + off) = wr4[i];
-                *reinterpret_cast<uint4 *>(xs + off) = xr[i];
-            }
-        };
-
-        load_slab(0);
-        store_slab(0);
+    const int32_t fmax = GATEUP ? a.frags_gu : a.frags_dn;
+    int32_t *const counter = a.ctrl + (GATEUP ? CTRL_WORK_GATEUP : CTRL_WORK_DOWN);
+    int64_t w = first_tile(total);                 // first tile by position, the rest on demand
+    while (w < total) {
+        Tile t = small ? decode_tile(a, tt, w, nt, BN, fmax) : decode_tile(a, mt_start, w, nt, BN, fmax);
+        t.slot = __builtin_amdgcn_readfirstlane(t.slot);
+        t.n0 = __builtin_amdgcn_readfirstlane(t.n0);
+        t.rows = __builtin_amdgcn_readfirstlane(t.rows);
+        int32_t claimed;
+        if (t.rows <= 32) claimed = bf16_tile<GATEUP, 1, FAR>(a, t, ffn_smem, K, N, lo_pos, counter);
+        else if (t.rows <= 64) claimed = bf16_tile<GATEUP, 2, FAR>(a, t, ffn_smem, K, N, lo_pos, counter);
+        else claimed = bf16_tile<GATEUP, 4, FAR>(a, t, ffn_smem, K, N, lo_pos, counter);
+        if (threadIdx.x == 0) next_item = (int64_t)gridDim.x + claimed;
         __syncthreads();
-        for (int ks = 0; ks < nk; ++ks) {
-            const int cur = ks & 1;
-            if (ks + 1 < nk) load_slab(ks + 1);
-            const unsigned char *ws = smem + cur * STAGEB, *xs = ws + TILEB;
-#pragma unroll
-            for (int kk = 0; kk < BK / 16; ++kk) {
-                const int ko = frag_off + kk * 32;
-                const bf16x8_t w0 = *reinterpret_cast<const bf16x8_t *>(ws + nf0 * ROWB + ko);
-                const bf16x8_t w1 = *reinterpret_cast<const bf16x8_t *>(ws + nf1 * ROWB + ko);
-                const bf16x8_t x0 = *reinterpret_cast<const bf16x8_t *>(xs + mf0 * ROWB + ko);
-                const bf16x8_t x1 = *reinterpret_cast<const bf16x8_t *>(xs + mf1 * ROWB + ko);
-                acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w0, x0, acc[0][0], 0, 0, 0);
-                acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w0, x1, acc[0][1], 0, 0, 0);
-                acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w1, x0, acc[1][0], 0, 0, 0);
-                acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w1, x1, acc[1][1], 0, 0, 0);
-            }
-            if (ks + 1 < nk) store_slab(cur ^ 1);
-            __syncthreads();
-        }
-
-        // epilogue: lane holds, for activation row (lane & 31) of each row fragment, output
-        // columns vg*8 + (lane>>5)*4 + 0..3 of each weight fragment
-        unsigned short *outp = static_cast<unsigned short *>(GATEUP ? a.act : a.y);
-#pragma unroll
-        for (int g = 0; g < 2; ++g) {
-            const int m = (g ? mf1 : mf0) + (lane & 31);
-            if (m >= t.rows) continue;
-            unsigned short *orow = outp + (int64_t)(t.pos0 + t.m0 + m - lo_pos) * N;
-#pragma unroll
-            for (int vg = 0; vg < 4; ++vg) {
-                const int nloc = vg * 8 + (lane >> 5) * 4;
-                if (GATEUP) {
-                    const int col = t.n0 + wn * 32 + nloc;
-                    if (col < N) {
-                        uint32_t h[4];
-#pragma unroll
-                        for (int c = 0; c < 4; ++c)
-                            h[c] = bf16_rne(silu(acc[0][g][vg * 4 + c]) * acc[1][g][vg * 4 + c]);
-                        *reinterpret_cast<uint2 *>(orow + col) =
-                            make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
-                    }
-                } else {
-#pragma unroll
-                    for (int f = 0; f < 2; ++f) {
-                        const int col = t.n0 + (f ? nf1 : nf0) + nloc;
-                        if (col < N) {
-                            uint32_t h[4];
-#pragma unroll
-                            for (int c = 0; c < 4; ++c) h[c] = bf16_rne(acc[f][g][vg * 4 + c]);
-                            *reinterpret_cast<uint2 *>(orow + col) =
-                                make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
-                        }
-                    }
-                }
-            }
-        }
+        w = next_item;                             // (written again only after the next tile's barriers)
     }
 }
 
 // ------------------------------------------------------------------------ fp32
-constexpr int FM = kFragsF32 * 32;  // rows per tile
-constexpr int FN = 32;            // output columns per tile
-constexpr int FK = 32;            // contraction slab
+// A unit is 16 output columns (16 weight rows, for gate/up 16 of each) against up to 32 activation
+// rows; the four waves take every fourth 16-wide piece of the contraction and add their sums up
+// in LDS, in wave order.  Both operands go straight from memory into the operand registers of
+// v_mfma_f32_16x16x4_f32, 16 bytes per lane: lane l holds row l & 15, elements 4 (l >> 4) .. + 3 of a
+// piece, and the four matrix instructions of a piece take one of them each.  These layers are small
+// and a launch is a chain of round trips: looking up the unit, its rows, one or two rounds of
+// operands.  256 tokens, H = 128, I = 256: gate/up 13.9 -> 7.3 us, down 17.0 -> 6.0 (before: 32 x 32
+// tiles of plain multiply-adds, staged through LDS by one wave's worth of requests at a time).
+constexpr int FN = 16;            // output columns per unit
+constexpr int FK = 16;            // contraction elements per piece
+constexpr int kF32Waves = 4;
+typedef float f32x4_a4_t __attribute__((ext_vector_type(4), aligned(4)));
+
+// rows: 16-row fragments of activations, 1 or 2
+template <bool GATEUP, int NXF>
+__device__ __forceinline__ void f32_unit(const FfnArgs &a, const Tile &t, int K, int N, int32_t lo_pos, f32x4_t *part) {
+    constexpr int NW = GATEUP ? 2 : 1, PW = 4;     // weight fragments; pieces in flight per wave
+    const int lane = threadIdx.x & 63, q = lane >> 4, r16 = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const float *w[NW], *x[NXF];
+    const float *wbase[2] = {static_cast<const float *>(GATEUP ? a.w_gate[t.slot] : a.w_down[t.slot]),
+                             GATEUP ? static_cast<const float *>(a.w_up[t.slot]) : nullptr};
+    // 16 bytes at a time from weights that are aligned to that (rows are whole multiples of it)
+    const bool whole = ((reinterpret_cast<uintptr_t>(wbase[0]) | reinterpret_cast<uintptr_t>(wbase[1])) & 15) == 0;
+#pragma unroll
+    for (int h = 0; h < NW; ++h) w[h] = wbase[h] + (int64_t)min(t.n0 + r16, N - 1) * K;
+#pragma unroll
+    for (int g = 0; g < NXF; ++g) {
+        const int32_t pos = t.pos0 + t.m0 + min(16 * g + r16, t.rows - 1);
+        x[g] = GATEUP ? static_cast<const float *>(a.x) + (int64_t)(a.src[pos] / a.k) * K
+                      : static_cast<const float *>(a.act) + (int64_t)(pos - lo_pos) * K;
+    }
+    f32x4_t acc[NW][NXF];
+#pragma unroll
+    for (int h = 0; h < NW; ++h)
+#pragma unroll
+        for (int g = 0; g < NXF; ++g) acc[h][g] = (f32x4_t)(0.0f);
+    const int pieces = (K + FK - 1) / FK;
+    for (int c0 = wave; c0 < pieces; c0 += PW * kF32Waves) {
+        f32x4_t wv[PW][NW], xv[PW][NXF];
+        // past the end: read from inside the row, replaced by zeros below
+        if (whole) {
+#pragma unroll
+            for (int u = 0; u < PW; ++u)
+#pragma unroll
+                for (int h = 0; h < NW; ++h)
+                    wv[u][h] = *reinterpret_cast<const f32x4_t *>(w[h] + min((c0 + u * kF32Waves) * FK + 4 * q, K - 4));
+        } else {
+#pragma unroll
+            for (int u = 0; u < PW; ++u)
+#pragma unroll
+                for (int h = 0; h < NW; ++h)
+                    wv[u][h] = *reinterpret_cast<const f32x4_a4_t *>(w[h] + min((c0 + u * kF32Waves) * FK + 4 * q, K - 4));
+        }
+#pragma unroll
+        for (int u = 0; u < PW; ++u)
+#pragma unroll
+            for (int g = 0; g < NXF; ++g)
+                xv[u][g] = *reinterpret_cast<const f32x4_t *>(x[g] + min((c0 + u * kF32Waves) * FK + 4 * q, K - 4));
+#pragma unroll
+        for (int u = 0; u < PW; ++u) {
+            const bool in = (c0 + u * kF32Waves) * FK + 4 * q < K;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int h = 0; h < NW; ++h)
+#pragma unroll
+                    for (int g = 0; g < NXF; ++g)
+                        acc[h][g] = __builtin_amdgcn_mfma_f32_16x16x4f32(in ? wv[u][h][e] : 0.0f, in ? xv[u][g][e] : 0.0f,
+                                                                         acc[h][g], 0, 0, 0);
+        }
+    }
+    __syncthreads();                               // the last unit's sums have been read
+#pragma unroll
+    for (int h = 0; h < NW; ++h)
+#pragma unroll
+        for (int g = 0; g < NXF; ++g) part[((wave * NW + h) * NXF + g) * 64 + lane] = acc[h][g];
+    __syncthreads();
+    // element v of lane l is weight row 4 (l >> 4) + v and row l & 15 of its fragment
+    if (wave < NXF) {
+        f32x4_t s[NW];
+#pragma unroll
+        for (int h = 0; h < NW; ++h) {
+            s[h] = part[(h * NXF + wave) * 64 + lane];
+#pragma unroll
+            for (int v = 1; v < kF32Waves; ++v) s[h] += part[((v * NW + h) * NXF + wave) * 64 + lane];
+        }
+        if (GATEUP)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) s[0][c] = (s[0][c] / (1.0f + expf(-s[0][c]))) * s[NW - 1][c];
+        const int m = 16 * wave + r16, col = t.n0 + 4 * q;
+        if (m < t.rows && col < N)                 // N is a multiple of 4
+            *reinterpret_cast<f32x4_t *>(static_cast<float *>(GATEUP ? a.act : a.y) +
+                                         (int64_t)(t.pos0 + t.m0 + m - lo_pos) * N + col) = s[0];
+    }
+}
 
 template <bool GATEUP>
-__global__ __launch_bounds__(256) void ffn_f32_kernel(FfnArgs a) {
-    __shared__ float xs[FM][FK + 1];
-    __shared__ float was[FN][FK + 1];
-    __shared__ float wbs[FN][FK + 1];
-    const int tid = threadIdx.x, tx = tid & 31, ty = tid >> 5;
+__global__ __launch_bounds__(64 * kF32Waves) void ffn_f32_kernel(FfnArgs a) {
+    __shared__ f32x4_t part[kF32Waves * 2 * 2 * 64];
+    __shared__ TileTables tt;
     const int K = GATEUP ? a.H : a.I;
     const int N = GATEUP ? a.I : a.H;
     const int nt = (N + FN - 1) / FN;
     const int32_t *mt_start = a.mt_start + (GATEUP ? 0 : a.nslots + 1);
-    const int64_t total = (int64_t)mt_start[a.nslots] * nt;
-    const int32_t lo_pos = a.slot_off[a.s_lo];
-    const float *xin = static_cast<const float *>(GATEUP ? a.x : a.act);
-
-    for (int64_t w = ((int64_t)blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8; w < total; w += gridDim.x) {
-        const Tile t = decode_tile(a, mt_start, w, nt, FN, GATEUP ? a.frags_gu : a.frags_dn);
-        const float *wa = static_cast<const float *>(GATEUP ? a.w_gate[t.slot] : a.w_down[t.slot]);
-        const float *wb = GATEUP ? static_cast<const float *>(a.w_up[t.slot]) : wa;
-        const float *xrow[4], *warow[4], *wbrow[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int r = ty + 8 * i;
-            const int32_t pos = t.pos0 + t.m0 + min(r, t.rows - 1);
-            xrow[i] = GATEUP ? xin + (int64_t)(a.src[pos] / a.k) * K : xin + (int64_t)(pos - lo_pos) * K;
-            const int wr = min(t.n0 + r, N - 1);
-            warow[i] = wa + (int64_t)wr * K;
-            wbrow[i] = wb + (int64_t)wr * K;
-        }
-        float ga[4] = {0, 0, 0, 0}, ub[4] = {0, 0, 0, 0};
-        for (int k0 = 0; k0 < K; k0 += FK) {
-            const bool ok = k0 + tx < K;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int r = ty + 8 * i;
-                xs[r][tx] = ok ? xrow[i][k0 + tx] : 0.0f;
-                was[r][tx] = ok ? warow[i][k0 + tx] : 0.0f;
-                if (GATEUP) wbs[r][tx] = ok ? wbrow[i][k0 + tx] : 0.0f;
-            }
-            __syncthreads();
-#pragma unroll 8
-            for (int kk = 0; kk < FK; ++kk) {
-                const float wv = was[tx][kk];
-                const float uv = GATEUP ? wbs[tx][kk] : 0.0f;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const float xv = xs[ty * 4 + j][kk];
-                    ga[j] += xv * wv;
-                    if (GATEUP) ub[j] += xv * uv;
-                }
-            }
-            __syncthreads();
-        }
-        float *outp = static_cast<float *>(GATEUP ? a.act : a.y);
-        const int col = t.n0 + tx;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int m = ty * 4 + j;
-            if (m < t.rows && col < N) {
-                const float g = ga[j];
-                const float val = GATEUP ? (g / (1.0f + expf(-g))) * ub[j] : g;
-                outp[(int64_t)(t.pos0 + t.m0 + m - lo_pos) * N + col] = val;
-            }
-        }
+    const int32_t fmax = GATEUP ? a.frags_gu : a.frags_dn;
+    const bool small = a.nslots <= TileTables::kMaxSlots;
+    if (small) load_tile_tables(a, mt_start, tt);
+    const int64_t total = (int64_t)(small ? tt.mt_start[a.nslots] : mt_start[a.nslots]) * nt;
+    const int32_t lo_pos = small ? tt.slot_off[0] : a.slot_off[a.s_lo];
+    for (int64_t w = blockIdx.x; w < total; w += gridDim.x) {
+        const Tile t = small ? decode_tile(a, tt, w, nt, FN, fmax) : decode_tile(a, mt_start, w, nt, FN, fmax);
+        if (t.rows <= 16) f32_unit<GATEUP, 1>(a, t, K, N, lo_pos, part);
+        else f32_unit<GATEUP, 2>(a, t, K, N, lo_pos, part);
     }
 }
 
 template <bool GATEUP>
 hipError_t launch_ffn(const FfnArgs &a, hipStream_t s) {
     if (a.nslots <= 0 || a.max_rows <= 0) return hipSuccess;
-    const int K = GATEUP ? a.H : a.I, N = GATEUP ? a.I : a.H;
-    (void)K;
+    const int N = GATEUP ? a.I : a.H;
     if (a.dtype == CRAFT_BF16) {
-        const int bn = GATEUP ? 64 : 128;
+        const int bn = GATEUP ? 128 : 256;
         const int64_t nt = (N + bn - 1) / bn;
-        const int64_t bound = (a.max_rows / BM + a.nslots) * nt;    // most tiles any batch can have
-        int64_t grid = std::min<int64_t>(bound, (int64_t)a.num_cu * 2);
+        const int64_t bound = (a.max_rows / (kFragsBf16 * 32) + a.nslots) * nt;     // most tiles any batch can have
+        int64_t grid = std::min<int64_t>(bound, (int64_t)a.num_cu);
         grid = std::max<int64_t>(8, (grid + 7) / 8 * 8);
-        hipLaunchKernelGGL(ffn_bf16_kernel<GATEUP>, dim3((unsigned)grid), dim3(256), 0, s, a);
+        // token rows are fetched at 32-bit offsets where x allows it
+        if constexpr (GATEUP)
+            if (a.far_x) {
+                hipLaunchKernelGGL((ffn_bf16_kernel<GATEUP, true>), dim3((unsigned)grid), dim3(kNtThreads), 0, s, a);
+                return hipGetLastError();
+            }
+        hipLaunchKernelGGL((ffn_bf16_kernel<GATEUP, false>), dim3((unsigned)grid), dim3(kNtThreads), 0, s, a);
     } else {
         const int64_t nt = (N + FN - 1) / FN;
-        const int64_t bound = (a.max_rows / FM + a.nslots) * nt;
-        int64_t grid = std::min<int64_t>(bound, (int64_t)a.num_cu * 8);
-        grid = std::max<int64_t>(8, (grid + 7) / 8 * 8);
-        hipLaunchKernelGGL(ffn_f32_kernel<GATEUP>, dim3((unsigned)grid), dim3(256), 0, s, a);
+        const int64_t bound = (a.max_rows / (kFragsF32 * 32) + a.nslots) * nt;
+        const int64_t grid = std::min<int64_t>(bound, (int64_t)a.num_cu * 4);
+        hipLaunchKernelGGL(ffn_f32_kernel<GATEUP>, dim3((unsigned)grid), dim3(64 * kF32Waves), 0, s, a);
     }
     return hipGetLastError();
 }

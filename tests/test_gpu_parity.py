@@ -134,6 +134,9 @@ GATE_TOL = 1e-4
     ("bf16", 300, 2048, 200),        # with a workspace: the contraction split eight ways
     ("bf16", 200, 1000, 100),        # split, ragged last slab and a last split shorter than the rest
     ("bf16", 200, 1024, 384),        # split with three blocks of experts per wave
+    ("bf16", 129, 192, 60),          # the smallest batch past the thin tiles; as many slabs as stages
+    ("bf16", 260, 456, 1000),        # four blocks of experts, the last one ragged
+    ("bf16", 16500, 136, 150),       # two fragments of tokens without a workspace, ragged slab
     ("f32", 50, 100, 12)])
 def test_router_logits_parity(torch_cuda, dtype, T, H, E):
     cfg = synth.scaled(synth.CONFIGS["qwen3"], dtype=dtype, T=T, H=H, E=E)
@@ -667,6 +670,61 @@ def test_small_batches_stream_the_weights(torch_cuda, T, H, I, E, k, D, zipf, ev
         fwd, _, _ = case.gpu_rank(g, packed=weights != "rowmajor")
         assert fwd.tile_choice() == (64, 64, 0, 0)
         _check_rank(torch_cuda, case, g, packed=weights != "rowmajor")
+
+
+@pytest.mark.parametrize("H,I", [(8, 16), (64, 128), (128, 264), (200, 72), (256, 400), (520, 192)])
+def test_rowmajor_tiles_of_every_height(torch_cuda, H, I):
+    # one to nine slabs, ragged and whole, and slots on both sides of 32, 64 and 128 rows
+    cfg = synth.scaled(synth.CONFIGS["qwen3"], T=1100, H=H, I=I, E=24, k=2, D=1, replica_slots=0, zipf_s=1.2, profile_batches=2)
+    case = Case(cfg)
+    rows = case.slot_cnt
+    assert (rows > 128).any() and ((rows > 64) & (rows <= 128)).any() and ((rows > 32) & (rows <= 64)).any() and (rows <= 32).any()
+    _check_rank(torch_cuda, case, 0, packed=False)
+
+
+@pytest.mark.parametrize("dtype,T,H,I,E", [("bf16", 1100, 200, 72, 24), ("bf16", 40, 200, 72, 6), ("f32", 300, 52, 36, 8)])
+def test_rowmajor_weights_at_any_element(torch_cuda, dtype, T, H, I, E):
+    # contiguous views that start one element into an allocation: the same bits as aligned weights
+    torch = torch_cuda
+    cfg = synth.scaled(synth.CONFIGS["qwen3"], dtype=dtype, T=T, H=H, I=I, E=E, k=2, D=1, replica_slots=0, zipf_s=1.2, profile_batches=2)
+    case = Case(cfg)
+    fwd, x, logits = case.gpu_rank(0)
+    want = _np(fwd(x, logits).clone())
+
+    def shifted(m):
+        flat = torch.empty(m.numel() + 1, dtype=m.dtype, device=m.device)
+        v = flat[1:].view(m.shape)
+        v.copy_(m)
+        assert v.data_ptr() % 16 == m.element_size()
+        return v
+    ws = [[shifted(m) for m in ms] for ms in fwd._weights]
+    odd = binding.RankForward(case.plan, 0, 0, dtype, T, H, I, cfg.k, *ws)
+    got = _np(odd(x, logits))
+    assert np.array_equal(got, want)
+
+
+def test_rowmajor_weights_with_tokens_past_4_gib(torch_cuda):
+    # the gate/up GEMM leaves its 32-bit row offsets; the last tokens against a plain fp32 product
+    torch = torch_cuda
+    T, H, I, E, D = 310_000, 7168, 16, 64, 64
+    plan = binding.Plan(np.full((1, 1, E), 8, dtype=np.int64), D, 0)
+    e = int(plan.layer(0)["slot_expert"][plan.layer(0)["rank_slot_off"][5]])
+    g = torch.Generator(device="cuda:0").manual_seed(5)
+    x = torch.randn((T, H), generator=g, device="cuda:0", dtype=torch.bfloat16)
+    w = [torch.randn(s, generator=g, device="cuda:0").bfloat16() * c for s, c in (((I, H), 0.01), ((I, H), 0.01), ((H, I), 0.25))]
+    logits = torch.zeros((T, E), device="cuda:0")
+    picked = torch.arange(T, device="cuda:0") % E
+    logits[torch.arange(T, device="cuda:0"), picked] = 4.0
+    fwd = binding.RankForward(plan, 0, 5, "bf16", T, H, I, 1, [w[0]], [w[1]], [w[2]])
+    out = fwd(x, logits)
+    assert fwd.result() == (int((picked == e).sum()), 0)
+    toks = torch.nonzero(picked == e).flatten()[-100:]
+    assert int(toks[0]) * H * 2 >= 1 << 32
+    xs = x[toks].float()
+    act = (torch.nn.functional.silu(xs @ w[0].float().t()) * (xs @ w[1].float().t())).bfloat16().float()
+    ref = act @ w[2].float().t()
+    assert (out[toks].float() - ref).abs().max() <= TOL["bf16"] * ref.abs().max()
+    assert int(torch.count_nonzero(out[torch.nonzero(picked != e).flatten()[-100:]])) == 0
 
 
 # -------------------------------------------------- full-size configurations
