@@ -222,7 +222,7 @@ __device__ void build_tile_tables(const DispatchArgs &a, bool ovf, const ROWS &r
     // row-tiles per slot: its 32-row fragments over the launch's tile height, rounded up
     int32_t mtotal[2], riders[2];
     for (int kind = 0; kind < 2; ++kind) {
-        const int32_t fmax = abs(kind == 0 ? a.frags_gu : a.frags_dn);
+        const int32_t cut = kind == 0 ? a.frags_gu : a.frags_dn;
         int32_t *mt_out = a.mt_start + kind * (nslots + 1);
         int32_t carry = 0;
         if (threadIdx.x == 0) hot_mtiles = 0;
@@ -230,7 +230,7 @@ __device__ void build_tile_tables(const DispatchArgs &a, bool ovf, const ROWS &r
         for (int32_t base = 0; base < nslots; base += kTableThreads) {
             const int32_t pos = base + threadIdx.x;
             const int32_t F = pos < nslots && !ovf ? (sorted_rows[pos] + 31) >> 5 : 0;
-            const int32_t mt = (F + fmax - 1) / fmax;
+            const int32_t mt = row_tiles(F, cut);
             int32_t chunk_total;
             const int32_t off = carry + block_exclusive_scan<kTableThreads / 64>(mt, wsum, &chunk_total);
             if (pos < nslots) mt_out[pos] = off;
@@ -246,7 +246,7 @@ __device__ void build_tile_tables(const DispatchArgs &a, bool ovf, const ROWS &r
         // (4 nt units) is carried whole or not at all
         const int64_t nt = kind == 0 ? a.nt_gu : a.nt_dn;
         const int64_t units2 = (int64_t)ncold2 * 4 * nt, units = units2 + (int64_t)(ncold - ncold2) * 2 * nt;
-        int64_t carried = fmax <= kRiderHostFrags ? min((int64_t)hot_mtiles * nt, units) : 0;
+        int64_t carried = tile_height(cut) <= kRiderHostFrags ? min((int64_t)hot_mtiles * nt, units) : 0;
         if (nt > 0 && carried < units2) carried = carried / (4 * nt) * (4 * nt);
         riders[kind] = (int32_t)carried;
         __syncthreads();                           // hot_mtiles is rewritten by the next kind

@@ -23,7 +23,7 @@ struct Tile {
 
 // Flattened work item w -> tile.  nt = column tiles per slot, bn = columns per tile.
 // mt_start[p] = row-tiles before position p of the busiest-first slot order.  A slot's rows
-// are cut into F 32-row fragments and m = ceil(F / f) row-tiles, either f fragments each with
+// are cut into F 32-row fragments and m row-tiles (row_tiles), either f fragments each with
 // a remainder at the end, or shared as evenly as whole fragments allow (row-tile i takes
 // fragments floor(i F / m) .. floor((i+1) F / m)); the launch says which.
 //
@@ -54,7 +54,7 @@ static __device__ __forceinline__ void load_tile_tables(const FfnArgs &a, const 
     __syncthreads();
 }
 // MT, ORD, OFF: the three tables, in global memory or in a workgroup's LDS copy
-// fmax > 0: row-tiles of fmax fragments and a remainder; fmax < 0: |fmax| at most, shared evenly
+// fmax > 0: row-tiles of fmax fragments and a remainder; fmax < 0: shared evenly
 template <typename MT, typename ORD, typename OFF>
 static __device__ __forceinline__ Tile decode_tile_in(int32_t nslots, const MT &mt_start, const ORD &order,
                                                       const OFF &slot_off, int64_t w, int32_t nt, int32_t bn,

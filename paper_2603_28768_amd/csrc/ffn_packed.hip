@@ -610,7 +610,7 @@ hipError_t launch_packed(const FfnArgs &a, hipStream_t s) {
     const int N = GATEUP ? a.I : a.H;
     const int bn = GATEUP ? 128 : 256;
     const int64_t nt = (N + bn - 1) / bn;
-    const int64_t bound = (a.max_rows / (32 * std::abs(GATEUP ? a.frags_gu : a.frags_dn)) + 2 * a.nslots) * nt;
+    const int64_t bound = (row_tiles((int32_t)std::min<int64_t>(a.max_rows / 32, 1 << 24), GATEUP ? a.frags_gu : a.frags_dn) + 2 * a.nslots) * nt;
     int64_t grid = std::min<int64_t>(bound, (int64_t)a.num_cu);
     grid = std::max<int64_t>(8, (grid + 7) / 8 * 8);
     if (a.w8) hipLaunchKernelGGL((ffn_packed_kernel<GATEUP, true>), dim3((unsigned)grid), dim3(256), 0, s, a);

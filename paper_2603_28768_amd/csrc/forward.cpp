@@ -120,7 +120,7 @@ int cached_num_cu() {
 // CU) plus a part per fragment.  The constants are fitted to tile timings on MI355X under
 // full load; replayed against measured sweeps of the height on three workloads the model
 // picks the fastest or second-fastest height each time.
-double ffn_makespan(const std::vector<double> &slot_rows, int32_t frags, bool even, int64_t nt,
+double ffn_makespan(const std::vector<double> &slot_rows, int32_t frags, int64_t nt,
                     double fixed_us, double frag_us, bool riders, double rider_us, int32_t cus) {
     // the tile list as the kernel walks it: busy slots first (rows sorted, busiest first)
     std::vector<double> cost;
@@ -129,16 +129,16 @@ double ffn_makespan(const std::vector<double> &slot_rows, int32_t frags, bool ev
         const int64_t F = (int64_t)((r + 31.0) / 32.0);
         if (F <= 0) continue;
         if (r <= (double)kColdRows) { ncold += 1; ncold2 += F > 1 ? 1 : 0; continue; }
-        const int64_t m = (F + frags - 1) / frags;
+        const int64_t m = row_tiles((int32_t)F, frags);
         for (int64_t n = 0; n < nt; ++n)
             for (int64_t i = 0; i < m; ++i) {
-                const int64_t f = even ? (i + 1) * F / m - i * F / m : std::min<int64_t>(frags, F - i * frags);
+                const int64_t f = frags < 0 ? (i + 1) * F / m - i * F / m : std::min<int64_t>(frags, F - i * frags);
                 cost.push_back(fixed_us + frag_us * (double)f);
             }
     }
     // rider units go to the first tiles, one each (see kRiderHostFrags)
     const int64_t units2 = ncold2 * 4 * nt, units = units2 + (ncold - ncold2) * 2 * nt;
-    int64_t carried = riders && frags <= kRiderHostFrags ? std::min<int64_t>((int64_t)cost.size(), units) : 0;
+    int64_t carried = riders && tile_height(frags) <= kRiderHostFrags ? std::min<int64_t>((int64_t)cost.size(), units) : 0;
     if (carried < units2) carried = carried / (4 * nt) * (4 * nt);
     for (int64_t u = 0; u < carried; ++u) cost[(size_t)u] += rider_us;
     // what is left of the cold slots: half-width tiles, about half the cost
@@ -206,16 +206,20 @@ tile_choice choose_tiles(const craft_plan_t *plan, int32_t layer, int32_t rank, 
             if (r > (double)kColdRows) tall_tiles += (((int64_t)((r + 31.0) / 32.0) + kFragsPacked - 1) / kFragsPacked) * nt;
         if (tall_tiles > 2 * (int64_t)cus) continue;
         double best_t = 0.0;
-        for (int32_t f = kFragsPacked; f >= 4; --f)
-            for (int even = 0; even < 2; ++even)
-                for (int riders = 0; riders < (f <= kRiderHostFrags ? 2 : 1); ++riders) {
-                    const double t = ffn_makespan(rows, f, even != 0, nt, fixed_us, frag_us, riders != 0, rider_us, cus);
-                    if ((f == kFragsPacked && !even) || t < best_t * 0.98) {    // a change has to earn it
-                        best_t = t;
-                        best.frags[kind] = even ? -f : f;
-                        best.riders[kind] = riders != 0;
-                    }
+        auto consider = [&](int32_t frags) {
+            for (int riders = 0; riders < (tile_height(frags) <= kRiderHostFrags ? 2 : 1); ++riders) {
+                const double t = ffn_makespan(rows, frags, nt, fixed_us, frag_us, riders != 0, rider_us, cus);
+                if (frags == kFragsPacked || t < best_t * 0.97) {       // a change has to earn it
+                    best_t = t;
+                    best.frags[kind] = frags;
+                    best.riders[kind] = riders != 0;
                 }
+            }
+        };
+        // whole fragments with a remainder, or shared evenly, in steps that also reach the counts of
+        // row-tiles between those of two whole heights
+        for (int32_t f = kFragsPacked; f >= 4; --f) consider(f);
+        for (int32_t f10 = 10 * kFragsPacked; f10 >= 40; f10 -= 2) consider(-f10);
     }
     return best;
 }
@@ -258,7 +262,7 @@ tile_choice tile_choice_of(const craft_plan_t *plan, int32_t layer, int32_t rank
     for (int kind = 0; kind < 2; ++kind) {
         if (rows_arg[kind]) { c.frags[kind] = rows_arg[kind] / 32; c.riders[kind] = true; }
         if (riders_arg[kind]) c.riders[kind] = riders_arg[kind] > 0;
-        c.riders[kind] = c.riders[kind] && std::abs(c.frags[kind]) <= kRiderHostFrags;
+        c.riders[kind] = c.riders[kind] && tile_height(c.frags[kind]) <= kRiderHostFrags;
     }
     return c;
 }
@@ -671,8 +675,8 @@ craft_status craft_moe_rank_forward_tiles(const craft_plan_t *plan, int32_t laye
     if (st != CRAFT_OK) return st;
     const bool packed = a->w_gateup_packed && a->w_down_packed;
     const tile_choice c = tiles_for(plan, layer, rank, a, packed);
-    if (rows_gateup) *rows_gateup = 32 * std::abs(c.frags[0]);
-    if (rows_down) *rows_down = 32 * std::abs(c.frags[1]);
+    if (rows_gateup) *rows_gateup = 32 * tile_height(c.frags[0]);
+    if (rows_down) *rows_down = 32 * tile_height(c.frags[1]);
     if (riders_gateup) *riders_gateup = c.riders[0] ? 1 : 0;
     if (riders_down) *riders_down = c.riders[1] ? 1 : 0;
     return CRAFT_OK;

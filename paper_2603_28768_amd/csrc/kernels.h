@@ -70,6 +70,15 @@ inline size_t stream_bytes(int64_t max_rows, int32_t nslots, int32_t K) {
 }
 constexpr int kBM_packed = kFragsPacked * 32;
 
+// How a launch cuts the F 32-row fragments of a slot into row-tiles: frags > 0, tiles of that many
+// and a remainder; frags < 0, ceil(10 F / -frags) tiles that share them as evenly as whole
+// fragments allow (tenths, so that there are more than four ways to cut a few slots).
+__host__ __device__ inline int32_t row_tiles(int32_t F, int32_t frags) {
+    return frags > 0 ? (F + frags - 1) / frags : (10 * F - frags - 1) / -frags;
+}
+// most fragments of a row-tile
+__host__ __device__ inline int32_t tile_height(int32_t frags) { return frags > 0 ? frags : (9 - frags) / 10; }
+
 struct RouterArgs {
     int32_t dtype;
     const void *x;            // [T][H]
@@ -128,7 +137,7 @@ struct DispatchArgs {
     // for the extra workgroup that builds the tile tables of the grouped GEMMs
     const int32_t *slot_cnt;  // [S] rows per slot
     int32_t s_lo, s_hi;       // the rank's slots
-    int32_t frags_gu, frags_dn;   // most 32-row fragments per row-tile, gate/up and down GEMM (sign: see FfnArgs)
+    int32_t frags_gu, frags_dn;   // how a slot's rows are cut (row_tiles), gate/up and down GEMM
     int32_t nt_gu, nt_dn;     // column tiles per slot of the two packed GEMMs; 0: no riders
     int32_t *mt_start;        // [2][s_hi - s_lo + 1] row-tile prefix over the rank's slots, busiest slot
                               // first: for the gate/up GEMM, then for the down GEMM
@@ -179,8 +188,7 @@ struct FfnArgs {
     int64_t max_rows;
     int32_t num_cu;
     int32_t w8;                    // packed weights are E4M3 codes with row scales behind the stream
-    int32_t frags_gu, frags_dn;    // most 32-row fragments per row-tile the tile tables were built for;
-                                   // negative: fragments shared evenly among a slot's row-tiles
+    int32_t frags_gu, frags_dn;    // how the tile tables cut a slot's rows (row_tiles)
     bool far_x;                    // x has rows more than 4 GiB from its start (row-major weights only)
 };
 hipError_t launch_gateup(const FfnArgs &a, hipStream_t s);
