@@ -377,7 +377,10 @@ craft_status craft_moe_rank_forward_static(const craft_plan_t *plan, int32_t lay
  * the tiles of the busy slots (1) or get tiles of their own (0).  With packed weights both
  * are chosen per (plan, layer, rank, T, k, H, I) from the loads the plan was made from, by
  * playing the launch through against a cost model, so that the tiles of the busy slots fill
- * the CUs in whole rounds; the choice is kept in the plan.  Any output pointer may be NULL.
+ * the CUs in whole rounds; the choice is kept in the plan.  64 rows in both: a small batch whose
+ * weights are streamed, with at most 64 rows of a slot against one pass over them (not with
+ * tuning knobs set, and only where the workspace is of the size
+ * craft_moe_rank_forward_workspace names for it).  Any output pointer may be NULL.
  * Host-side, no device work. */
 craft_status craft_moe_rank_forward_tiles(const craft_plan_t *plan, int32_t layer, int32_t rank,
                                           const craft_fwd_args *args, int32_t *rows_gateup,

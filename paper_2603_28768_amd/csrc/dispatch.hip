@@ -327,10 +327,12 @@ __global__ __launch_bounds__(64 * kDirectWaves) void prefix_kernel(int32_t *hist
 // and needs no other workgroup's results.  In a batch of up to kSmallBlocks blocks a chunk is a
 // single block, whose counts the routing kernel has left: no other launch at all (T = 256, E = 384:
 // 14.3 -> 8.7 us for the two).  In a larger one prefix_kernel runs in front (T = 16384, E = 384:
-// scan 14.9 and dispatch 5.4 us -> 4.8 and 8.3; T = 32768, E = 256: 17.9 and 8.5 -> 5.2 and 12.9).  A workgroup handles one block of 32 tokens, a few
-// neighbouring ones in a large batch.  COPY, for the small-batch FFN: the token rows bound
-// for this rank are copied into fragment order on the way, by sa.slices workgroups per block that
-// take a share of the columns each (the first one writes dest / src).  The last workgroup builds the tile tables.
+// scan 14.9 and dispatch 5.4 us -> 4.8 and 8.3; T = 32768, E = 256: 17.9 and 8.5 -> 5.2 and 12.9; T =
+// 4096, E = 128: 6.7 and 5.6 -> 4.9 and 7.9).  A workgroup handles one block of 32 tokens, a few
+// neighbouring ones in a large batch.  COPY, for the small-batch FFN: the token rows bound for this
+// rank are copied into fragment order on the way, by sa.slices workgroups per block that take a
+// share of the columns each (the first one writes dest / src).  The last workgroup builds the
+// tile tables.
 constexpr int kDirectThreads = 512;
 constexpr int kDirectSlots = 2048;
 template <bool COPY>

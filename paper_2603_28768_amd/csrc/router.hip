@@ -19,7 +19,11 @@
 namespace craft {
 namespace {
 
-constexpr int kThinBatch = 128;         // tokens up to which the gate is read by thin tiles
+// Tokens up to which the gate is read by thin tiles: few tall ones leave CUs without work (8 tokens:
+// 23 us for scores of E = 256, H = 7168, thin 4.4).  From there on it depends on E, thin / tall with the
+// sum of the parts at 192 tokens: E = 256 16.5 / 19.4, E = 128 14.4 / 13.5, E = 384 21.4 / 16.6; at 1024
+// tokens 45 / 22.
+constexpr int kThinBatch = 128;
 constexpr int GK = 64;                  // contraction slab
 typedef unsigned int gu32x4_t __attribute__((ext_vector_type(4)));
 typedef const gu32x4_t __attribute__((address_space(1))) *gchunk_t;

@@ -591,7 +591,11 @@ def test_rank_with_more_slots_than_the_tile_tables_in_lds(torch_cuda):
     (8192, 384, 8, 8, 24),       # six groups, 128 blocks per wave, four waves idle
     (2000, 1024, 2, 16, 32),     # a wave per group, every block of the batch
     (8200, 72, 4, 2, 5),         # one block more than a chunk: two workgroups per group, ragged group
-    (20000, 200, 3, 4, 9)])      # three chunks of four groups
+    (20000, 200, 3, 4, 9),       # three chunks of four groups
+    (1024, 40, 2, 2, 3),         # the largest batch dispatched from the blocks' counts alone
+    (1025, 40, 2, 2, 3),         # the smallest with prefixes over chunks of blocks
+    (16385, 48, 2, 2, 3),        # two blocks to a workgroup, the last one alone
+    (65600, 16, 1, 2, 2)])       # more chunks than every workgroup reads: the scan in front
 def test_dispatch_over_block_and_expert_shapes(torch_cuda, T, E, k, D, slots):
     # how the per-block counts are dealt to the waves depends on the number of 32-token blocks
     # and of 64-expert groups: integer results against the checker on every rank, narrow FFN
