@@ -73,6 +73,10 @@ def check_matrix_operands(asm_path: str) -> int:
     other_m0 = [t for t in ins if re.search(r"\bm0\b", t) and not re.match(r"^s_mov_b32 m0, (s\d+|vcc_lo|vcc_hi|ttmp\d+)$", t.split(";")[0].strip())]
     if other_m0:
         raise RuntimeError(f"{asm_path}: M0 is used outside the row requests, e.g. {other_m0[0]}")
+    # and such a load may not be the next instruction after the one that wrote M0
+    close = [t for p, t in zip(ins, ins[1:]) if t.startswith("global_load_lds") and p.startswith("s_mov_b32 m0,")]
+    if close:
+        raise RuntimeError(f"{asm_path}: {len(close)} loads into LDS directly behind the write of their M0, e.g. {close[0]}")
     if bad:
         raise RuntimeError(f"{asm_path}: {len(bad)} matrix instructions read a register written by one of the two "
                            "vector instructions in front of them, e.g.\n  " + "\n  ".join(bad[:5]))

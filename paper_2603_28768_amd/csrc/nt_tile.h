@@ -85,7 +85,11 @@ static __device__ __forceinline__ void nt_tile(unsigned char *smem, ubase_t abas
             for (int o = m * OPS / M; o < (m + 1) * OPS / M; ++o) {
                 if (o < NR) fetch(set ^ 1, o, next, next_step);
                 else if ((o - NR) % 2 == 0) dma_to(dest(D0 + (o - NR) / 2, s2));
-                else request(D0 + (o - NR) / 2, koff);
+                else {
+                    // behind the same matrix instruction as its destination: a load may not follow M0 at once
+                    if (o > m * OPS / M) asm volatile("s_nop 0");
+                    request(D0 + (o - NR) / 2, koff);
+                }
             }
             __builtin_amdgcn_sched_barrier(0);
         }

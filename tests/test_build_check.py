@@ -33,7 +33,19 @@ def test_fresh_vector_results_are_caught(tmp_path, front):
 
 
 def test_m0_belongs_to_the_row_requests(tmp_path):
-    ok = "\ts_mov_b32 m0, s12\n\tglobal_load_lds_dwordx4 v3, s[4:5]\n" + MFMA
+    ok = "\ts_mov_b32 m0, s12\n\ts_nop 0\n\tglobal_load_lds_dwordx4 v3, s[4:5]\n" + MFMA
     assert _check(tmp_path, ok) == 1
     with pytest.raises(RuntimeError):
         _check(tmp_path, "\ts_mov_b32 m0, s12\n\tv_readlane_b32 s3, v9, m0\n" + MFMA)
+
+
+@pytest.mark.parametrize("between,settled", [
+    ("", False), (".LBB0_3:\n", False),                      # a label is no instruction
+    ("\ts_nop 0\n", True), (MFMA, True), ("\tds_read_b128 v[8:11], v20\n", True)])
+def test_a_row_request_does_not_directly_follow_its_m0(tmp_path, between, settled):
+    text = "\ts_mov_b32 m0, s12\n" + between + "\tglobal_load_lds_dwordx4 v3, s[4:5]\n" + MFMA
+    if settled:
+        assert _check(tmp_path, text) >= 1
+    else:
+        with pytest.raises(RuntimeError):
+            _check(tmp_path, text)
