@@ -44,7 +44,7 @@ __global__ __launch_bounds__(kPackThreads) void pack_kernel(PackArgs a) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int r = row0 + (lane & 15), k_lane = 8 * (lane >> 4);
     const unsigned short *row = (gateup ? a.w[h] : a.w[2]) + (int64_t)min(r, N - 1) * K;
-    unsigned char *out = (gateup ? a.gateup : a.down) + g * 2048 + h * 1024 + lane * 16;
+    unsigned char *out = (gateup ? a.gateup : a.down) + (int64_t)g * 2048 + h * 1024 + lane * 16;
     const int s0 = part * kPartSteps + 2 * wave;
     const u32x4_t zero = {0u, 0u, 0u, 0u};
     u32x4_t v[kPairs][2];
@@ -82,7 +82,7 @@ hipError_t launch_pack(int32_t H, int32_t I, const void *wg, const void *wu, con
     a.gateup_parts = ((H + 255) / 256 * 8 + kPartSteps - 1) / kPartSteps;
     a.down_parts = ((I + 255) / 256 * 8 + kPartSteps - 1) / kPartSteps;
     const int64_t blocks = 2 * ((int64_t)a.gateup_groups * a.gateup_parts + (int64_t)a.down_groups * a.down_parts);
-    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    if (blocks >= (1ll << 32) / kPackThreads) return hipErrorInvalidValue;        // a launch has fewer than 2^32 threads
     hipLaunchKernelGGL(pack_kernel, dim3((unsigned)blocks), dim3(kPackThreads), 0, s, a);
     return hipGetLastError();
 }

@@ -4,6 +4,8 @@
 //
 // E4M3: 1 sign bit, 4 exponent bits (bias 7), 3 mantissa bits; exponent field 0 is subnormal
 // (mantissa / 8 * 2^-6); no infinities; S.1111.111 is NaN; the largest finite value is 448.
+#include <algorithm>
+
 #include "kernels.h"
 
 namespace craft {
@@ -145,6 +147,7 @@ struct QuantPackArgs {
     int64_t gateup_stream, down_stream;   // bytes of the streams
     int32_t H, I;
     int32_t gateup_groups, down_groups;   // padded to whole tiles
+    int32_t first;                        // row block of the launch's first workgroup
 };
 template <int PAIRS>
 __device__ __forceinline__ void quantize_pack_rows(const unsigned short *rows, int live, int K, int ksteps,
@@ -205,7 +208,7 @@ __device__ __forceinline__ void quantize_pack_rows(const unsigned short *rows, i
 }
 __global__ __launch_bounds__(kPackThreads) void quantize_pack_e4m3_kernel(QuantPackArgs a) {
     __shared__ float part[kPackWaves][16];
-    int b = blockIdx.x;
+    int b = a.first + blockIdx.x;
     const bool gateup = b < 2 * a.gateup_groups;
     if (!gateup) b -= 2 * a.gateup_groups;
     const int g = b >> 1, h = b & 1;
@@ -213,7 +216,7 @@ __global__ __launch_bounds__(kPackThreads) void quantize_pack_e4m3_kernel(QuantP
     const int ksteps = (K + 255) / 256 * 8;
     const int64_t step_bytes = (int64_t)(gateup ? a.gateup_groups : a.down_groups) * 1024;
     const int row0 = gateup ? 16 * g : 32 * g + 16 * h;
-    unsigned char *out = (gateup ? a.gateup : a.down) + g * 1024 + h * 512;
+    unsigned char *out = (gateup ? a.gateup : a.down) + (int64_t)g * 1024 + h * 512;
     if (row0 >= N) {                               // padding groups: zero codes
         const u32x2_t zero = {0u, 0u};
         for (int s = threadIdx.x >> 6; s < ksteps; s += kPackWaves)
@@ -276,8 +279,12 @@ void packed_sizes_e4m3(int32_t H, int32_t I, size_t *gateup_bytes, size_t *down_
 
 hipError_t launch_quantize_e4m3(const void *w, int64_t rows, int32_t K, uint8_t *codes, float *scale,
                                 hipStream_t s) {
-    hipLaunchKernelGGL(quantize_e4m3_kernel, dim3((unsigned)rows), dim3(kQuantThreads), 0, s,
-                       static_cast<const u32x4_t *>(w), K / 8, reinterpret_cast<u32x2_t *>(codes), scale);
+    // a launch has fewer than 2^32 threads
+    constexpr int64_t kMost = (1ll << 31) / kQuantThreads;
+    for (int64_t r = 0; r < rows; r += kMost) {
+        hipLaunchKernelGGL(quantize_e4m3_kernel, dim3((unsigned)std::min(kMost, rows - r)), dim3(kQuantThreads), 0, s,
+                           static_cast<const u32x4_t *>(w) + r * (K / 8), K / 8, reinterpret_cast<u32x2_t *>(codes) + r * (K / 8), scale + r);
+    }
     return hipGetLastError();
 }
 
@@ -289,9 +296,11 @@ hipError_t launch_quantize_pack_e4m3(int32_t H, int32_t I, const void *wg, const
                      static_cast<const unsigned short *>(wd)},
                     static_cast<unsigned char *>(pgu), static_cast<unsigned char *>(pdn),
                     (int64_t)(gub - (size_t)2 * I * sizeof(float)), (int64_t)(dnb - (size_t)H * sizeof(float)),
-                    H, I, ((I + 15) / 16 + 7) / 8 * 8, ((H + 31) / 32 + 7) / 8 * 8};
-    hipLaunchKernelGGL(quantize_pack_e4m3_kernel, dim3((unsigned)(2 * (a.gateup_groups + a.down_groups))),
-                       dim3(kPackThreads), 0, s, a);
+                    H, I, ((I + 15) / 16 + 7) / 8 * 8, ((H + 31) / 32 + 7) / 8 * 8, 0};
+    constexpr int32_t kMost = (1ll << 31) / kPackThreads;
+    const int32_t blocks = 2 * (a.gateup_groups + a.down_groups);
+    for (; a.first < blocks; a.first += kMost)
+        hipLaunchKernelGGL(quantize_pack_e4m3_kernel, dim3((unsigned)std::min(kMost, blocks - a.first)), dim3(kPackThreads), 0, s, a);
     return hipGetLastError();
 }
 

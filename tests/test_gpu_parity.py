@@ -817,3 +817,25 @@ def test_quantize_and_pack_in_one_pass_is_the_two_steps(torch_cuda, H, I, scale)
         assert np.array_equal(codes.cpu().numpy()[finite], want_c[finite])
     assert torch.equal(pgu, want_gu)
     assert torch.equal(pdn, want_dn)
+
+
+@pytest.mark.parametrize("e4m3,I", [(False, (1 << 24) + 16), (True, (1 << 25) + 16)])
+def test_packing_an_expert_of_very_many_columns(torch_cuda, e4m3, I):
+    # a column group's place in the packed stream passes 2 GiB, the rows take more than one launch: the
+    # first step of every group
+    torch = torch_cuda
+    H = 8
+    print(f"packing H={H} I={I} e4m3={e4m3}", flush=True)
+    g = torch.Generator(device="cuda:0").manual_seed(I)
+    up = torch.randn((I, H), generator=g, device="cuda:0").bfloat16()
+    gate, down = -up, up.view(H, I)
+    packed, _ = (binding.pack_weights_e4m3 if e4m3 else binding.pack_weights)(gate, up, down)
+    groups, rows = (I // 16 + 7) // 8 * 8, I // 16
+    per = groups * 2 * 64 * 8                             # elements of one step
+    step = packed.view(torch.uint8 if e4m3 else torch.int16).reshape(-1)[:per].view(groups, 2, 64, 8)
+    for half, m in enumerate((gate, up)):
+        want = binding.quantize_e4m3(m)[0] if e4m3 else m.view(torch.int16)
+        if e4m3:                                          # rows past the first launch, each with its own scale
+            assert np.array_equal(_np(want[-4096:]), oracle.quantize_e4m3(_np(m[-4096:]))[0])
+        assert torch.equal(step[:rows, half, :16], want.view(rows, 16, H))
+        assert not step[:rows, half, 16:].any() and not step[rows:, half].any()
