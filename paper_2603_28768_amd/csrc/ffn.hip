@@ -47,14 +47,15 @@ __device__ __forceinline__ int32_t bf16_tile(const FfnArgs &a, const Tile &t, un
     // chunks of 32 rows of A: the first two waves fetch gate rows, the others up rows
     const void *w = GATEUP ? (wave < 2 ? a.w_gate[t.slot] : a.w_up[t.slot]) : a.w_down[t.slot];
     const ubase_t wbase = uniform_base(static_cast<ubase_t>(w) + (int64_t)t.n0 * K * 2);
-    auto woff = [&](int r) { return (uint32_t)min(weight_row<GATEUP>(r), N - 1 - t.n0) * (uint32_t)K * 2u; };
+    auto woff = [&](int r) { return (uint64_t)min(weight_row<GATEUP>(r), N - 1 - t.n0) * (uint64_t)K * 2u; };
     const ubase_t xbase = uniform_base(GATEUP ? static_cast<ubase_t>(a.x)
                                               : static_cast<ubase_t>(a.act) + (int64_t)(t.pos0 + t.m0 - lo_pos) * K * 2);
     typedef typename std::conditional<FAR, uint64_t, uint32_t>::type off_t;
-    auto xoff = [&](int r) {
+    auto xoff_far = [&](int r) {
         const int rr = min(r, t.rows - 1);
-        return (off_t)(GATEUP ? a.src[t.pos0 + t.m0 + rr] / a.k : rr) * (off_t)K * (off_t)2;
+        return (uint64_t)(GATEUP ? a.src[t.pos0 + t.m0 + rr] / a.k : rr) * (uint64_t)K * 2u;
     };
+    auto xoff = [&](int r) { return (off_t)xoff_far(r); };
     f32x4_t acc[FA][FB];
 #pragma unroll
     for (int f = 0; f < FA; ++f)
@@ -63,8 +64,9 @@ __device__ __forceinline__ int32_t bf16_tile(const FfnArgs &a, const Tile &t, un
     // (the other wave's matrix counts too: all waves have to take the same path)
     const uintptr_t bits = reinterpret_cast<uintptr_t>(GATEUP ? a.w_gate[t.slot] : a.w_down[t.slot]) |
                            reinterpret_cast<uintptr_t>(GATEUP ? a.w_up[t.slot] : a.w_down[t.slot]);
-    if ((__builtin_amdgcn_readfirstlane((int)bits) & 15) == 0) nt_tile<FA, FB>(smem, wbase, woff, xbase, xoff, K, 0, (K + 63) / 64, acc);
-    else nt_tile_unaligned<FA, FB>(smem, wbase, woff, xbase, xoff, K, 0, (K + 63) / 64, acc);
+    if ((__builtin_amdgcn_readfirstlane((int)bits) & 15) == 0 && K < kNtRowLimit)
+        nt_tile<FA, FB>(smem, wbase, woff, xbase, xoff, K, 0, (K + 63) / 64, acc);
+    else nt_tile_unaligned<FA, FB>(smem, wbase, woff, xbase, xoff_far, K, 0, (K + 63) / 64, acc);
     // the next tile is claimed here, its number arrives while the results are stored
     // (an increment: an add of a uniform value becomes a wave-wide reduction)
     int32_t claimed = 0;

@@ -25,8 +25,10 @@ constexpr int kNtLds = 3 * 12 * 32 * 128;          // three stages of 256 + 128 
 template <int FA, int FB> constexpr int nt_stages() { return nt_stage_bytes<FA, FB>() * 4 <= kNtLds ? 4 : 3; }
 template <int FA, int FB> constexpr int nt_lds_bytes() { return nt_stages<FA, FB>() * nt_stage_bytes<FA, FB>(); }
 
+// Rows of this many elements: 256 of them stay inside a 32-bit byte offset.
+constexpr int kNtRowLimit = 1 << 23;
 // abase, bbase: wave-uniform; aoff, boff: the byte offset of a row (0 .. 32 FA - 1, 32 FB - 1) from them.  K: elements
-// per row, a multiple of 8.  acc[f][g] += A fragment wa FA + f x B fragment wb FB + g, where wave w of
+// per row, a multiple of 8, less than kNtRowLimit.  acc[f][g] += A fragment wa FA + f x B fragment wb FB + g, where wave w of
 // the workgroup is (wa, wb) = (w >> 1, w & 1); element v of lane l is row 4 (l >> 4) + v of A's fragment
 // and row l & 15 of B's.  kbeg, kend: the slabs to take.  Ends with a barrier and nothing in flight.
 template <int FA, int FB, typename AOFF, typename BOFF>
@@ -45,7 +47,7 @@ static __device__ __forceinline__ void nt_tile(unsigned char *smem, ubase_t abas
     decltype(boff_of(0)) boff[FB];                 // 32 or 64 bits
     const int lr = (int)threadIdx.x >> 3;          // this lane's row of a 32-row chunk
 #pragma unroll
-    for (int i = 0; i < FA; ++i) aoff[i] = aoff_of(32 * i + lr);
+    for (int i = 0; i < FA; ++i) aoff[i] = (uint32_t)aoff_of(32 * i + lr);
 #pragma unroll
     for (int i = 0; i < FB; ++i) boff[i] = boff_of(32 * i + lr);
     typedef const bf16x8_t __attribute__((address_space(3))) *lds_frag_t;
@@ -162,8 +164,8 @@ static __device__ __forceinline__ void nt_tile(unsigned char *smem, ubase_t abas
         for (int g = 0; g < FB; ++g) asm volatile("" : "+a"(acc[f][g]));
 }
 
-// The same product for rows of A that are not 16-byte aligned, which loads into LDS ask for: one
-// slab at a time through registers.
+// The same product for rows of A that are not 16-byte aligned, which loads into LDS ask for, and for
+// rows of any length (64-bit offsets): one slab at a time through registers.
 template <int FA, int FB, typename AOFF, typename BOFF>
 static __device__ __forceinline__ void nt_tile_unaligned(unsigned char *smem, ubase_t abase, const AOFF &aoff_of, ubase_t bbase,
                                                          const BOFF &boff_of, int K, int kbeg, int kend, f32x4_t (&acc)[FA][FB]) {
@@ -172,8 +174,8 @@ static __device__ __forceinline__ void nt_tile_unaligned(unsigned char *smem, ub
     typedef unsigned short u16x8_t __attribute__((ext_vector_type(8)));
     const int c = lane & 7, place = (c ^ (lr & 7)) * 16;
     for (int ks = kbeg; ks < kend; ++ks) {
-        const int k = ks * 128 + c * 16;
-        const bool in = k < K * 2;
+        const int64_t k = ks * 128ll + c * 16;
+        const bool in = k < K * 2ll;
 #pragma unroll
         for (int i = 0; i < FA + FB; ++i) {
             const int r = 32 * i + lr;

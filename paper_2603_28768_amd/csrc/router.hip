@@ -219,7 +219,7 @@ hipError_t launch_router_logits(const RouterArgs &a, hipStream_t s) {
     RouterArgs b = a;
     b.nsplit = nsplit;
     hipError_t err;
-    if (a.T <= kThinBatch) {
+    if (a.T <= kThinBatch || a.H >= kNtRowLimit) {         // (thin tiles take rows of any length)
         const dim3 grid((unsigned)((a.E + 15) / 16), (unsigned)((a.T + kThinTokens - 1) / kThinTokens), (unsigned)nsplit);
         hipLaunchKernelGGL(router_thin_kernel, grid, dim3(64 * kThinWaves), 0, s, b);
         err = hipGetLastError();

@@ -839,3 +839,36 @@ def test_packing_an_expert_of_very_many_columns(torch_cuda, e4m3, I):
             assert np.array_equal(_np(want[-4096:]), oracle.quantize_e4m3(_np(m[-4096:]))[0])
         assert torch.equal(step[:rows, half, :16], want.view(rows, 16, H))
         assert not step[:rows, half, 16:].any() and not step[rows:, half].any()
+
+
+def test_router_logits_of_rows_past_32_bit_offsets(torch_cuda):
+    # 256 rows of the gate take more than 4 GiB: a gate of unit rows copies columns of x
+    torch = torch_cuda
+    T, H, E = 140, (1 << 23) + 64, 256
+    g = torch.Generator(device="cuda:0").manual_seed(3)
+    x = torch.randn((T, H), generator=g, device="cuda:0").bfloat16()
+    cols = H - 1 - 3 * torch.arange(E, device="cuda:0")
+    W = torch.zeros((E, H), dtype=torch.bfloat16, device="cuda:0")
+    W[torch.arange(E, device="cuda:0"), cols] = 1.0
+    for workspace in (None, binding.router_logits_workspace(x, W)):
+        assert torch.equal(binding.router_logits(x, W, workspace), x[:, cols].float())
+
+
+@pytest.mark.parametrize("T,H,I", [(5, 256, (1 << 24) + 64), (3, (1 << 25) + 64, 136)])
+def test_rowmajor_weights_of_rows_past_32_bit_offsets(torch_cuda, T, H, I):
+    # the rows of one weight tile lie more than 4 GiB apart
+    torch = torch_cuda
+    print(f"long rows T={T} H={H} I={I}", flush=True)
+    g = torch.Generator(device="cuda:0").manual_seed(I)
+    rand = lambda *s: torch.randn(s, generator=g, device="cuda:0", dtype=torch.bfloat16)
+    x, wg, wu, wd = rand(T, H) * H ** -0.5, rand(I, H), rand(I, H), rand(H, I) * I ** -0.5
+    plan = binding.Plan(np.full((1, 1, 1), T, dtype=np.int64), 1, 0)
+    fwd = binding.RankForward(plan, 0, 0, "bf16", T, H, I, 1, [wg], [wu], [wd])
+    out = fwd(x, torch.zeros((T, 1), device="cuda:0")).float()
+    # rows of the weights a part at a time: fp32 copies of the matrices would take most of the card
+    part = max(1, (1 << 28) // H)
+    act = torch.cat([torch.nn.functional.silu(x.float() @ a.float().t()) * (x.float() @ b.float().t())
+                     for a, b in zip(wg.split(part), wu.split(part))], dim=1).bfloat16().float()
+    part = max(1, (1 << 28) // I)
+    ref = torch.cat([act @ a.float().t() for a in wd.split(part)], dim=1)
+    assert (out - ref).abs().max() <= TOL["bf16"] * ref.abs().max()
