@@ -184,7 +184,7 @@ __device__ __forceinline__ void stream_unit(const FfnArgs &a, const Unit &t, int
                 up *= *reinterpret_cast<const f32x4_t *>(scale + N + col);
             }
 #pragma unroll
-            for (int c = 0; c < 4; ++c) v[c] = silu_fast(v[c]) * up[c];
+            for (int c = 0; c < 4; ++c) v[c] = (SRC == kRowMajor ? silu(v[c]) : silu_fast(v[c])) * up[c];   // as the tiles of each
         } else if (W8 && col < N) {
             v *= *reinterpret_cast<const f32x4_t *>(scale + col);
         }

@@ -872,3 +872,25 @@ def test_rowmajor_weights_of_rows_past_32_bit_offsets(torch_cuda, T, H, I):
     part = max(1, (1 << 28) // I)
     ref = torch.cat([act @ a.float().t() for a in wd.split(part)], dim=1)
     assert (out - ref).abs().max() <= TOL["bf16"] * ref.abs().max()
+
+
+def test_rowmajor_activation_is_the_same_in_small_and_large_batches(torch_cuda):
+    # sums of one term, a unit down-projection: what comes out is silu(g) u rounded once, so the
+    # streaming kernels and the tiles have to agree in every bit
+    torch = torch_cuda
+    E, rows, N = 8, 64, 2048
+    g = torch.Generator(device="cuda:0").manual_seed(9)
+    rand = lambda *s: torch.randn(s, generator=g, device="cuda:0").bfloat16()
+    T = E * rows
+    x, wg, wu = (torch.zeros(s, dtype=torch.bfloat16, device="cuda:0") for s in ((T, N), (N, N), (N, N)))
+    x[:, :2], wg[:, 0], wu[:, 1] = rand(T, 2), rand(N), rand(N)
+    plan = binding.Plan(np.full((1, 1, E), rows, dtype=np.int64), 1, 0)
+    fwd = binding.RankForward(plan, 0, 0, "bf16", T, N, N, 1, [wg] * E, [wu] * E, [torch.eye(N, device="cuda:0").bfloat16()] * E)
+    logits = torch.zeros((T, E), device="cuda:0")
+    logits[torch.arange(T), torch.arange(T) % E] = 4.0
+    assert fwd.tile_choice() == (64, 64, 0, 0)
+    streamed = fwd(x, logits).clone()
+    fwd.args.workspace_bytes -= 1                          # the tiles, for which there is still room
+    tiled = fwd(x, logits)
+    assert int(torch.count_nonzero(tiled)) > T * N // 2
+    assert torch.equal(streamed, tiled)
