@@ -64,9 +64,10 @@ __device__ __forceinline__ int32_t bf16_tile(const FfnArgs &a, const Tile &t, un
     // (the other wave's matrix counts too: all waves have to take the same path)
     const uintptr_t bits = reinterpret_cast<uintptr_t>(GATEUP ? a.w_gate[t.slot] : a.w_down[t.slot]) |
                            reinterpret_cast<uintptr_t>(GATEUP ? a.w_up[t.slot] : a.w_down[t.slot]);
-    if ((__builtin_amdgcn_readfirstlane((int)bits) & 15) == 0 && K < kNtRowLimit)
-        nt_tile<FA, FB>(smem, wbase, woff, xbase, xoff, K, 0, (K + 63) / 64, acc);
-    else nt_tile_unaligned<FA, FB>(smem, wbase, woff, xbase, xoff_far, K, 0, (K + 63) / 64, acc);
+    const int nk = (K + 63) / 64;
+    if (K >= kNtRowLimit) nt_tile_unaligned<FA, FB, true>(smem, wbase, woff, xbase, xoff_far, K, 0, nk, acc);
+    else if ((__builtin_amdgcn_readfirstlane((int)bits) & 15) == 0) nt_tile<FA, FB>(smem, wbase, woff, xbase, xoff, K, 0, nk, acc);
+    else nt_tile_unaligned<FA, FB, false>(smem, wbase, woff, xbase, xoff, K, 0, nk, acc);
     // the next tile is claimed here, its number arrives while the results are stored
     // (an increment: an add of a uniform value becomes a wave-wide reduction)
     int32_t claimed = 0;

@@ -164,41 +164,83 @@ static __device__ __forceinline__ void nt_tile(unsigned char *smem, ubase_t abas
         for (int g = 0; g < FB; ++g) asm volatile("" : "+a"(acc[f][g]));
 }
 
-// The same product for rows of A that are not 16-byte aligned, which loads into LDS ask for, and for
-// rows of any length (64-bit offsets): one slab at a time through registers.
-template <int FA, int FB, typename AOFF, typename BOFF>
+// The same product for rows of A that are not 16-byte aligned, which loads into LDS ask for, and, with
+// FAR, for rows of any length (64-bit offsets).  Through registers and two stages: a slab is multiplied
+// while the next one goes into the other stage and the one after that travels, one barrier per slab.
+// 1777 tokens on 17 slots, H = 4096, I = 1536, weights two bytes past alignment: 334 us a forward (one
+// slab at a time: 930; aligned: 206).  Not what holds it back: reading the two aligned blocks of a
+// piece instead of one that straddles them (352), two slabs on their way (349).
+template <int FA, int FB, bool FAR, typename AOFF, typename BOFF>
 static __device__ __forceinline__ void nt_tile_unaligned(unsigned char *smem, ubase_t abase, const AOFF &aoff_of, ubase_t bbase,
                                                          const BOFF &boff_of, int K, int kbeg, int kend, f32x4_t (&acc)[FA][FB]) {
     const int lane = threadIdx.x & 63, q = lane >> 4, wave = (int)threadIdx.x >> 6, lr = (int)threadIdx.x >> 3;
-    typedef unsigned short u16x8_a2_t __attribute__((ext_vector_type(8), aligned(2)));
     typedef unsigned short u16x8_t __attribute__((ext_vector_type(8)));
-    const int c = lane & 7, place = (c ^ (lr & 7)) * 16;
-    for (int ks = kbeg; ks < kend; ++ks) {
-        const int64_t k = ks * 128ll + c * 16;
-        const bool in = k < K * 2ll;
+    typedef unsigned short u16x8_a2_t __attribute__((ext_vector_type(8), aligned(2)));
+    // global, not flat: a wait for LDS would wait for flat loads too
+    typedef const u16x8_a2_t __attribute__((address_space(1))) *chunk_t;
+    typedef typename std::conditional<FAR, uint64_t, uint32_t>::type off_t;
+    constexpr int STAGEB = nt_stage_bytes<FA, FB>();
+    const int c = lane & 7, place = lr * 128 + (c ^ (lr & 7)) * 16;
+    off_t aoff[FA];
+    decltype(boff_of(0)) boff[FB];
 #pragma unroll
-        for (int i = 0; i < FA + FB; ++i) {
-            const int r = 32 * i + lr;
-            u16x8_t v = {};
-            if (in) v = i < FA ? (u16x8_t)*reinterpret_cast<const u16x8_a2_t *>(abase + aoff_of(r) + k)
-                               : *reinterpret_cast<const u16x8_t *>(bbase + boff_of(r - 32 * FA) + k);
-            *reinterpret_cast<u16x8_t *>(smem + r * 128 + place) = v;
-        }
-        __syncthreads();
+    for (int i = 0; i < FA; ++i) aoff[i] = (off_t)aoff_of(32 * i + lr);
+#pragma unroll
+    for (int i = 0; i < FB; ++i) boff[i] = boff_of(32 * i + lr);
+    u16x8_t av[FA], bv[FB];
+    // (past the rows or the last slab: read from inside the rows, replaced by zeros on the way into
+    // LDS or not used; no branch around a request, the waits count them)
+    auto load = [&](int ks) __attribute__((always_inline)) {
+        const off_t k = min((off_t)ks * 128u + (off_t)c * 16u, (off_t)K * 2u - 16u);
+#pragma unroll
+        for (int i = 0; i < FA; ++i) av[i] = *(chunk_t)(abase + (aoff[i] + k));
+#pragma unroll
+        for (int i = 0; i < FB; ++i) bv[i] = *(chunk_t)(bbase + (boff[i] + k));
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto store = [&](int u, int ks) __attribute__((always_inline)) {
+        unsigned char *stage = smem + u * STAGEB;
+        const bool in = (off_t)ks * 128u + (off_t)c * 16u < (off_t)K * 2u;
+#pragma unroll
+        for (int i = 0; i < FA; ++i) *reinterpret_cast<u16x8_t *>(stage + 32 * i * 128 + place) = in ? av[i] : u16x8_t{};
+#pragma unroll
+        for (int i = 0; i < FB; ++i) *reinterpret_cast<u16x8_t *>(stage + 32 * (FA + i) * 128 + place) = in ? bv[i] : u16x8_t{};
+    };
+    // slab ks is in stage u: multiplied, while the one after it goes into the other stage and the one
+    // after that is requested
+    auto slab = [&](int u, int ks) __attribute__((always_inline)) {
+        const unsigned char *stage = smem + u * STAGEB;
+        bf16x8_t a[2][FA], b[2][FB];
 #pragma unroll
         for (int step = 0; step < 2; ++step) {
             const int at = (lane & 15) * 128 + (((step * 4 + q) ^ (lane & 7)) & 7) * 16;
-            bf16x8_t b[FB];
 #pragma unroll
-            for (int g = 0; g < FB; ++g) b[g] = *reinterpret_cast<const bf16x8_t *>(smem + (FA * 32 + ((wave & 1) * FB + g) * 16) * 128 + at);
+            for (int g = 0; g < FB; ++g) b[step][g] = *reinterpret_cast<const bf16x8_t *>(stage + (FA * 32 + ((wave & 1) * FB + g) * 16) * 128 + at);
 #pragma unroll
-            for (int f = 0; f < FA; ++f) {
-                const bf16x8_t av = *reinterpret_cast<const bf16x8_t *>(smem + ((wave >> 1) * FA + f) * 16 * 128 + at);
-#pragma unroll
-                for (int g = 0; g < FB; ++g) acc[f][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, b[g], acc[f][g], 0, 0, 0);
-            }
+            for (int f = 0; f < FA; ++f) a[step][f] = *reinterpret_cast<const bf16x8_t *>(stage + ((wave >> 1) * FA + f) * 16 * 128 + at);
         }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int f = 0; f < FA; ++f)
+#pragma unroll
+            for (int g = 0; g < FB; ++g) acc[f][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0][f], b[0][g], acc[f][g], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        store(u ^ 1, ks + 1);
+        load(ks + 2);
+#pragma unroll
+        for (int f = 0; f < FA; ++f)
+#pragma unroll
+            for (int g = 0; g < FB; ++g) acc[f][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1][f], b[1][g], acc[f][g], 0, 0, 0);
         __syncthreads();
+    };
+    if (kbeg >= kend) return;
+    load(kbeg);
+    store(0, kbeg);
+    load(kbeg + 1);
+    __syncthreads();
+    for (int ks = kbeg; ks < kend; ks += 2) {
+        slab(0, ks);
+        if (ks + 1 < kend) slab(1, ks + 1);
     }
 }
 

@@ -894,3 +894,36 @@ def test_rowmajor_activation_is_the_same_in_small_and_large_batches(torch_cuda):
     tiled = fwd(x, logits)
     assert int(torch.count_nonzero(tiled)) > T * N // 2
     assert torch.equal(streamed, tiled)
+
+
+def test_rowmajor_weights_at_any_element_are_not_left_behind(torch_cuda):
+    # loads of the next slab have to travel while one is multiplied: 1.6 to 1.9 times the time of aligned
+    # weights, one slab at a time it was more than 4 times
+    torch = torch_cuda
+    E, rows, H, I = 17, 100, 4096, 1536
+    g = torch.Generator(device="cuda:0").manual_seed(2)
+    rand = lambda *s: torch.randn(s, generator=g, device="cuda:0").bfloat16()
+    plan = binding.Plan(np.full((1, 1, E), rows, dtype=np.int64), 1, 0)
+    T = E * rows
+    x, logits = rand(T, H), torch.zeros((T, E), device="cuda:0")
+    logits[torch.arange(T), torch.arange(T) % E] = 4.0
+    times = []
+    for start in (0, 1):
+        ws = [[], [], []]
+        for _ in range(E):
+            for out, s in zip(ws, ((I, H), (I, H), (H, I))):
+                out.append(rand(s[0] * s[1] + 8)[start:start + s[0] * s[1]].view(s))
+        fwd = binding.RankForward(plan, 0, 0, "bf16", T, H, I, 1, *ws)
+        assert fwd.tile_choice() == (128, 128, 0, 0)
+        best = []
+        for _ in range(6):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            for _ in range(5):
+                fwd(x, logits)
+            b.record()
+            torch.cuda.synchronize()
+            best.append(a.elapsed_time(b))
+        times.append(min(best))
+    print(f"  aligned {times[0] * 200:.0f} us, one element past it {times[1] * 200:.0f} us", flush=True)
+    assert times[1] <= 3.0 * times[0]
