@@ -158,35 +158,91 @@ double ffn_makespan(const std::vector<double> &slot_rows, int32_t frags, int64_t
     return end;
 }
 
-struct tile_choice { int32_t frags[2]; bool riders[2]; bool stream = false, stream_rowmajor = false; };
+struct tile_choice { int32_t frags[2]; bool riders[2]; bool stream = false; };
 
-tile_choice choose_tiles(const craft_plan_t *plan, int32_t layer, int32_t rank, int64_t T, int32_t k,
-                         int32_t H, int32_t I, int32_t cus) {
-    const craft_layer_plan &lp = plan->layers[layer];
-    tile_choice best{{kFragsPacked, kFragsPacked}, {false, false}};
-    double total = 0.0;
-    for (int64_t v : lp.expert_load) total += (double)v;
-    if (total <= 0.0 || T <= 0) return best;
-    std::vector<double> rows;
+// ---- small batches: streamed or tiled -------------------------------------------------------
+// Rows a slot is expected to see, from the profiled loads the plan was made from.  A slot expected to
+// see a fraction of a row is counted with one: it costs a tile per column block as soon as a single
+// token reaches it.
+double expected_rows(const craft_layer_plan &lp, int32_t slot, double tokens_per_load) {
+    const double est = lp.slot_load[slot] * tokens_per_load;
+    return est >= 0.2 ? std::max(1.0, est) : 0.0;
+}
+double tokens_per_load(const craft_layer_plan &lp, int64_t T, int32_t k) {
+    return lp.total_load > 0.0 ? (double)T * k / lp.total_load : 0.0;
+}
+
+enum { kSrcPacked = 0, kSrcE4M3 = 1, kSrcRowMajor = 2 };
+// What a unit of ffn_stream.hip and a tile of the other kernels take, in us: a + b K / 1000 for a
+// contraction of K; units by the rows of the pass (16, 32, 64), tiles by the rows of the slot (32, 64,
+// more).  Fitted on MI355X to 360 forwards of 1 to 32 live slots with 3 to 126 rows each at (H, I) =
+// (7168, 2048), (4096, 1536), (2048, 1408) and (2048, 768), streamed and tiled: the faster way is picked
+// but for 0.2 % of the time on average.  H = 7168, I = 2048, us streamed / tiled: bf16, 2 slots of 14 rows
+// 53 / 74, 3 of 44 98 / 85, 8 of 62 193 / 137; E4M3, 3 of 14 56 / 72, 6 of 14 81 / 87, 8 of 62 152 / 97;
+// row-major, 4 of 62 137 / 163, 8 of 62 235 / 188, 16 of 44 454 / 273.
+struct ffn_unit_cost {
+    double unit[3][2], tile[3][2];
+    double rest;                   // the other launches of a forward
+    double gain;                   // streamed from this ratio of the two times down
+};
+constexpr ffn_unit_cost kUnitCost[3] = {
+    {{{4.8, 4.4}, {5.2, 4.7}, {5.5, 6.0}}, {{8.6, 7.9}, {11.4, 8.3}, {20.0, 23.0}}, 13.2, 0.95},
+    {{{2.9, 2.7}, {2.9, 3.5}, {3.1, 4.9}}, {{6.9, 5.9}, {9.1, 5.8}, {16.5, 16.7}}, 17.4, 0.95},
+    {{{5.1, 5.8}, {4.6, 7.0}, {5.4, 8.2}}, {{5.1, 20.2}, {12.1, 22.2}, {14.0, 29.3}}, 11.5, 1.03}};
+
+// Whether a small batch's weights are streamed.  Asked by every forward: nothing is allocated, nothing
+// kept and nothing added up over the experts.
+bool streamed(const craft_layer_plan &lp, int32_t rank, int64_t T, int32_t k, int32_t H, int32_t I, int src, int32_t cus) {
+    const double scale = tokens_per_load(lp, T, k);
+    if (scale <= 0.0) return false;
+    // passes by their rows, slots by theirs
+    int64_t passes[3] = {0, 0, 0}, slots[3] = {0, 0, 0};
+    double most = 0.0;
     for (int32_t p = lp.rank_slot_off[rank]; p < lp.rank_slot_off[rank + 1]; ++p) {
-        const int32_t e = lp.slot_expert[p];
-        // a slot expected to see a fraction of a row is counted with one: it costs a tile per
-        // column block as soon as a single token reaches it
-        const double est = (double)(lp.expert_load[e] / lp.copies[e]) * (double)T * k / total;
-        rows.push_back(est >= 0.2 ? std::max(1.0, est) : 0.0);
+        const double r = expected_rows(lp, p, scale);
+        if (r <= 0.0) continue;
+        most = std::max(most, r);
+        if (most > 2.0 * kStreamRows) return false;
+        const double rem = r > (double)kStreamRows ? r - kStreamRows : r;
+        passes[2] += r > (double)kStreamRows ? 1 : 0;
+        passes[rem <= 16.0 ? 0 : rem <= 32.0 ? 1 : 2] += 1;
+        slots[r <= 32.0 ? 0 : r <= (double)kColdRows ? 1 : 2] += 1;
     }
+    const int64_t all = passes[0] + passes[1] + passes[2];
+    if (all == 0) return true;
+    const int64_t groups[2] = {(I + 15) / 16, (H + 31) / 32}, nt[2] = {(I + 127) / 128, (H + 255) / 256};
+    // (packed, and row-major with more than one pass: tiles fill the CUs from here on)
+    if ((src != kSrcRowMajor || most > (double)kStreamRows) && all * 2 * nt[0] > cus) return false;
+    const ffn_unit_cost &cost = kUnitCost[src];
+    auto rounds = [](double items, double at_once) {           // half way between whole rounds and an even share
+        const double n = items / at_once;
+        return 0.5 * (std::ceil(n) + n);
+    };
+    double stream_t = cost.rest, tile_t = cost.rest;
+    for (int g = 0; g < 2; ++g) {
+        const double K = (g == 0 ? H : I) * 1e-3;
+        double unit_us = 0.0, tile_us = 0.0;
+        int64_t tiles = 0;
+        for (int c = 0; c < 3; ++c) {
+            // (cold slots of packed weights have half-width tiles)
+            const int64_t n = slots[c] * nt[g] * (src != kSrcRowMajor && c < 2 ? 2 : 1);
+            tiles += n;
+            tile_us += (double)n * (cost.tile[c][0] + cost.tile[c][1] * K);
+            unit_us += (double)passes[c] * (cost.unit[c][0] + cost.unit[c][1] * K);
+        }
+        stream_t += rounds((double)(all * groups[g]), 2.0 * cus) * unit_us / (double)all;
+        tile_t += rounds((double)tiles, (double)cus) * tile_us / (double)tiles;
+    }
+    return stream_t < cost.gain * tile_t;
+}
+
+tile_choice choose_tiles(const craft_layer_plan &lp, int32_t rank, int64_t T, int32_t k, int32_t H, int32_t I, int32_t cus) {
+    tile_choice best{{kFragsPacked, kFragsPacked}, {false, false}};
+    const double scale = tokens_per_load(lp, T, k);
+    if (scale <= 0.0) return best;
+    std::vector<double> rows;
+    for (int32_t p = lp.rank_slot_off[rank]; p < lp.rank_slot_off[rank + 1]; ++p) rows.push_back(expected_rows(lp, p, scale));
     std::sort(rows.begin(), rows.end(), std::greater<double>());
-    // Small batches are streamed (ffn_stream.hip) where that is faster, on MI355X:
-    //   - few slots, less than a half-width tile per CU between them, up to two passes of 64 rows:
-    //     the tiles leave CUs without work (H = 7168, I = 2048, us a forward, streamed / tiles: two
-    //     slots of 10 rows 51 / 76, of 57 59 / 90, of 76 87 / 134; of 153 rows 120 / 105)
-    //   - more slots, row-major weights, a single pass: 94 / 113 with eight live slots of up to 48
-    //     rows at H = 4096, I = 1536, 134 / 129 with up to 72.  Packed tiles are as fast: 80 / 72.
-    int64_t passes = 0;
-    for (double r : rows) passes += (int64_t)std::ceil(r / kStreamRows);
-    const double most = rows.empty() ? 0.0 : rows[0];
-    best.stream = most <= 2.0 * kStreamRows && passes * 2 * ((I + 127) / 128) <= cus;
-    best.stream_rowmajor = best.stream || most <= (double)kStreamRows;
     for (int kind = 0; kind < 2; ++kind) {
         const int64_t K = kind == 0 ? H : I, N = kind == 0 ? I : H;
         const int64_t nt = kind == 0 ? (N + 127) / 128 : (N + 255) / 256;
@@ -224,11 +280,24 @@ tile_choice choose_tiles(const craft_plan_t *plan, int32_t layer, int32_t rank, 
     return best;
 }
 
-// The choice for (layer, rank, T, k, H, I) is made once and kept with the plan: later forwards
-// of the same shape find it by walking a short insert-only list, without a lock.
+// How the packed weights' tiles are cut for (layer, rank, T, k, H, I) is chosen once and kept with
+// the plan: later forwards of the same shape find it by walking a short insert-only list, without a
+// lock.  Row-major and streamed batches have no cut to choose.
 tile_choice tile_choice_of(const craft_plan_t *plan, int32_t layer, int32_t rank, const craft_fwd_args *a,
                            bool packed, bool may_stream) {
     if (a->dtype != CRAFT_BF16) return {{kFragsF32, kFragsF32}, {false, false}};
+    const craft_layer_plan &lp = plan->layers[layer];
+    const int32_t rows_arg[2] = {a->tile_rows_gateup, a->tile_rows_down};
+    const int32_t riders_arg[2] = {a->riders_gateup, a->riders_down};
+    const bool told = rows_arg[0] || rows_arg[1] || riders_arg[0] || riders_arg[1];
+    const bool w8 = packed && a->weight_format == CRAFT_W_E4M3;
+    // the streaming kernels address x and a weight matrix by 32-bit byte offsets (the packed
+    // kernels' sizes are checked with the other arguments)
+    const int64_t limit = (int64_t)1 << 32;
+    if (may_stream && !(packed && told) && a->T * (int64_t)a->H * 2 < limit && (int64_t)a->I * a->H * 2 < limit &&
+        streamed(lp, rank, a->T, a->k, a->H, a->I, !packed ? kSrcRowMajor : w8 ? kSrcE4M3 : kSrcPacked, cached_num_cu()))
+        return {{kStreamRows / 32, kStreamRows / 32}, {false, false}, true};
+    if (!packed) return {{kFragsBf16, kFragsBf16}, {false, false}};
     craft_rank_state &rs = plan->state(layer, rank);
     auto find = [&]() -> const craft_tile_choice * {
         for (const craft_tile_choice *t = rs.tiles.load(std::memory_order_acquire); t; t = t->next)
@@ -240,24 +309,14 @@ tile_choice tile_choice_of(const craft_plan_t *plan, int32_t layer, int32_t rank
         std::lock_guard<std::mutex> lk(rs.mu);
         hit = find();
         if (!hit) {
-            const tile_choice c = choose_tiles(plan, layer, rank, a->T, a->k, a->H, a->I, cached_num_cu());
+            const tile_choice c = choose_tiles(lp, rank, a->T, a->k, a->H, a->I, cached_num_cu());
             craft_tile_choice *n = new craft_tile_choice{a->T, a->k, a->H, a->I, {c.frags[0], c.frags[1]},
-                                                         {c.riders[0], c.riders[1]}, c.stream, c.stream_rowmajor,
-                                                         rs.tiles.load(std::memory_order_relaxed)};
+                                                         {c.riders[0], c.riders[1]}, rs.tiles.load(std::memory_order_relaxed)};
             rs.tiles.store(n, std::memory_order_release);
             hit = n;
         }
     }
     tile_choice c{{hit->frags[0], hit->frags[1]}, {hit->riders[0], hit->riders[1]}, false};
-    const int32_t rows_arg[2] = {a->tile_rows_gateup, a->tile_rows_down};
-    const int32_t riders_arg[2] = {a->riders_gateup, a->riders_down};
-    const bool told = rows_arg[0] || rows_arg[1] || riders_arg[0] || riders_arg[1];
-    // the streaming kernels address x and a weight matrix by 32-bit byte offsets (the packed
-    // kernels' sizes are checked with the other arguments)
-    const int64_t limit = (int64_t)1 << 32;
-    if (may_stream && (packed ? hit->stream && !told : hit->stream_rowmajor) && a->T * (int64_t)a->H * 2 < limit && (int64_t)a->I * a->H * 2 < limit)
-        return {{kStreamRows / 32, kStreamRows / 32}, {false, false}, true};
-    if (!packed) return {{kFragsBf16, kFragsBf16}, {false, false}};
     // the caller's own heights: riders wherever such tiles can carry them, unless told
     for (int kind = 0; kind < 2; ++kind) {
         if (rows_arg[kind]) { c.frags[kind] = rows_arg[kind] / 32; c.riders[kind] = true; }

@@ -19,6 +19,8 @@ struct craft_layer_plan {
     std::vector<int32_t> rank_slot_off;  // [D+1]
     std::vector<int64_t> rank_load;      // [D]
     std::vector<int64_t> expert_load;    // [E] profiled load summed over batches
+    std::vector<double> slot_load;       // [S] a slot's share of its expert's, whole
+    double total_load = 0.0;             // of all experts
     int64_t est_max_rank_load = 0;
     double est_balancedness = 1.0;
 };
@@ -39,7 +41,6 @@ struct craft_tile_choice {
     int32_t k, H, I;
     int32_t frags[2];
     bool riders[2];
-    bool stream, stream_rowmajor;
     craft_tile_choice *next;
 };
 

@@ -381,6 +381,8 @@ craft_status craft_plan(const craft_plan_params *pp, craft_plan_t **out) {
             }
             lp.rank_load = pl.load;
             lp.expert_load.assign(ws.begin() + (size_t)l * E, ws.begin() + (size_t)(l + 1) * E);
+            for (int64_t v : lp.expert_load) lp.total_load += (double)v;
+            for (int32_t e : lp.slot_expert) lp.slot_load.push_back((double)(lp.expert_load[e] / lp.copies[e]));
             int64_t mx = 0, sum = 0;
             for (int64_t v : pl.load) { mx = std::max(mx, v); sum += v; }
             lp.est_max_rank_load = mx;

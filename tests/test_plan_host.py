@@ -261,6 +261,43 @@ def test_ffn_tile_heights_query():
     assert query(9) == -1
 
 
+# One rank that holds `slots` experts with `rows` tokens each; us streamed / tiled where it was measured.
+STREAM_CASES = [
+    ("bf16", 7168, 2048, 2, 14, True),          # 53 / 74
+    ("bf16", 7168, 2048, 1, 126, True),         # 62 / 144
+    ("bf16", 7168, 2048, 3, 44, False),         # 98 / 85
+    ("bf16", 7168, 2048, 8, 62, False),         # 193 / 137
+    ("bf16", 4096, 1536, 2, 62, True),          # 45 / 60
+    ("bf16", 4096, 1536, 8, 44, False),         # 96 / 72
+    ("bf16", 2048, 768, 4, 28, True),           # 29 / 39
+    ("bf16", 2048, 768, 16, 62, False),         # 68 / 56
+    ("e4m3", 7168, 2048, 3, 14, True),          # 56 / 72
+    ("e4m3", 7168, 2048, 6, 14, True),          # 81 / 87
+    ("e4m3", 7168, 2048, 4, 62, False),         # 92 / 76
+    ("e4m3", 7168, 2048, 8, 62, False),         # 152 / 97
+    ("rowmajor", 7168, 2048, 4, 62, True),      # 137 / 163
+    ("rowmajor", 7168, 2048, 8, 62, False),     # 235 / 188
+    ("rowmajor", 7168, 2048, 16, 44, False),    # 454 / 273
+    ("rowmajor", 4096, 1536, 8, 14, True),      # 84 / 95
+    ("rowmajor", 4096, 1536, 16, 44, False),    # 207 / 143
+    ("rowmajor", 2048, 768, 10, 28, True),      # 50 / 61
+]
+
+
+@pytest.mark.parametrize("weights,H,I,slots,rows,streamed", STREAM_CASES)
+def test_small_batches_are_streamed_where_that_is_faster(weights, H, I, slots, rows, streamed):
+    lib = binding.lib()
+    plan = binding.Plan(np.full((1, 1, slots), rows, dtype=np.int64), 1, 0)
+    a = binding.FwdArgs()
+    a.dtype, a.T, a.H, a.I, a.k = 1, slots * rows, H, I, 1
+    if weights != "rowmajor":
+        a.w_gateup_packed = a.w_down_packed = 0x1000
+        a.weight_format = binding.CRAFT_W_E4M3 if weights == "e4m3" else binding.CRAFT_W_BF16
+    gu, dn = ctypes.c_int32(), ctypes.c_int32()
+    assert lib.craft_moe_rank_forward_tiles(plan._h, 0, 0, ctypes.byref(a), gu, dn, None, None) == 0
+    assert ((gu.value, dn.value) == (64, 64)) == streamed
+
+
 def test_gate_workspace_query_and_forward_workspace_with_own_gate():
     # host-side sizes only; no device work
     lib = binding.lib()
