@@ -7,7 +7,6 @@
 #include <cstring>
 #include <memory>
 #include <mutex>
-#include <queue>
 #include <vector>
 
 #include "kernels.h"
@@ -120,10 +119,12 @@ int cached_num_cu() {
 // CU) plus a part per fragment.  The constants are fitted to tile timings on MI355X under
 // full load; replayed against measured sweeps of the height on three workloads the model
 // picks the fastest or second-fastest height each time.
+// Returns as soon as the launch is known to take `limit` or longer (with some such time).
 double ffn_makespan(const std::vector<double> &slot_rows, int32_t frags, int64_t nt,
-                    double fixed_us, double frag_us, bool riders, double rider_us, int32_t cus) {
+                    double fixed_us, double frag_us, bool riders, double rider_us, int32_t cus, double limit) {
     // the tile list as the kernel walks it: busy slots first (rows sorted, busiest first)
     std::vector<double> cost;
+    cost.reserve(2048);
     int64_t ncold = 0, ncold2 = 0;
     for (double r : slot_rows) {
         const int64_t F = (int64_t)((r + 31.0) / 32.0);
@@ -146,13 +147,28 @@ double ffn_makespan(const std::vector<double> &slot_rows, int32_t frags, int64_t
     const int64_t left1 = carried <= units2 ? (ncold - ncold2) * 2 * nt : units - carried;
     for (int64_t i = 0; i < left2 * 2 * nt; ++i) cost.push_back(4.0 + 0.5 * (fixed_us + frag_us * 2.0));
     for (int64_t i = 0; i < left1; ++i) cost.push_back(4.0 + 0.5 * (fixed_us + frag_us));
-    std::priority_queue<double, std::vector<double>, std::greater<double>> free_at;
-    for (int32_t i = 0; i < cus; ++i) free_at.push(0.0);
+    double work = 0.0;
+    for (double c : cost) work += c;
+    // no launch beats an even share (less a hair for the sums of the CUs, added in another order)
+    if (work / cus * (1.0 - 1e-9) >= limit) return limit;
+    // a heap of the times at which the CUs become free, the earliest on top; the first tiles find
+    // every CU free
+    const size_t at_once = std::min(cost.size(), (size_t)cus);
+    std::vector<double> free_at(cost.begin(), cost.begin() + at_once);
     double end = 0.0;
-    for (double c : cost) {
-        const double t = free_at.top() + c;
-        free_at.pop();
-        free_at.push(t);
+    for (double t : free_at) end = std::max(end, t);
+    if (cost.size() == at_once) return end;
+    std::make_heap(free_at.begin(), free_at.end(), std::greater<double>());
+    for (size_t k = at_once; k < cost.size() && end < limit; ++k) {
+        const double t = free_at[0] + cost[k];
+        size_t i = 0;
+        for (size_t j = 1; j < at_once; j = 2 * i + 1) {
+            if (j + 1 < at_once && free_at[j + 1] < free_at[j]) ++j;
+            if (free_at[j] >= t) break;
+            free_at[i] = free_at[j];
+            i = j;
+        }
+        free_at[i] = t;
         end = std::max(end, t);
     }
     return end;
@@ -258,14 +274,20 @@ tile_choice choose_tiles(const craft_layer_plan &lp, int32_t rank, int64_t T, in
         // time; over many rounds the tallest tile (most reuse per weight fragment, fewest
         // fixed costs) wins by itself, and there the model is not trusted to say otherwise.
         int64_t tall_tiles = 0;
+        std::vector<int32_t> busy;                 // fragments of the busy slots
         for (double r : rows)
-            if (r > (double)kColdRows) tall_tiles += (((int64_t)((r + 31.0) / 32.0) + kFragsPacked - 1) / kFragsPacked) * nt;
+            if (r > (double)kColdRows) {
+                busy.push_back((int32_t)((r + 31.0) / 32.0));
+                tall_tiles += ((busy.back() + kFragsPacked - 1) / kFragsPacked) * nt;
+            }
         if (tall_tiles > 2 * (int64_t)cus) continue;
         double best_t = 0.0;
         auto consider = [&](int32_t frags) {
             for (int riders = 0; riders < (tile_height(frags) <= kRiderHostFrags ? 2 : 1); ++riders) {
-                const double t = ffn_makespan(rows, frags, nt, fixed_us, frag_us, riders != 0, rider_us, cus);
-                if (frags == kFragsPacked || t < best_t * 0.97) {       // a change has to earn it
+                const bool first = frags == kFragsPacked;
+                const double limit = first ? 1e30 : best_t * 0.97;      // a change has to earn it
+                const double t = ffn_makespan(rows, frags, nt, fixed_us, frag_us, riders != 0, rider_us, cus, limit);
+                if (t < limit) {
                     best_t = t;
                     best.frags[kind] = frags;
                     best.riders[kind] = riders != 0;
@@ -273,9 +295,20 @@ tile_choice choose_tiles(const craft_layer_plan &lp, int32_t rank, int64_t T, in
             }
         };
         // whole fragments with a remainder, or shared evenly, in steps that also reach the counts of
-        // row-tiles between those of two whole heights
+        // row-tiles between those of two whole heights; an even cut with the same row-tiles as the
+        // one before it (fewer are never smaller: the totals tell) is not played through again
         for (int32_t f = kFragsPacked; f >= 4; --f) consider(f);
-        for (int32_t f10 = 10 * kFragsPacked; f10 >= 40; f10 -= 2) consider(-f10);
+        int64_t last_tiles = -1;
+        bool last_carries = false;
+        for (int32_t f10 = 10 * kFragsPacked; f10 >= 40; f10 -= 2) {
+            int64_t n = 0;
+            for (int32_t F : busy) n += row_tiles(F, -f10);
+            const bool carries = tile_height(-f10) <= kRiderHostFrags;
+            if (n == last_tiles && carries == last_carries) continue;
+            last_tiles = n;
+            last_carries = carries;
+            consider(-f10);
+        }
     }
     return best;
 }

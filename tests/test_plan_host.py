@@ -1,6 +1,7 @@
 """Host logic of the library: craft_plan and its accessors against the CPU checker's
 independently written planner (bit-exact), plus argument checking.  No GPU needed."""
 import ctypes
+import time
 
 import numpy as np
 import pytest
@@ -259,6 +260,33 @@ def test_ffn_tile_heights_query():
     assert query() == 0
     assert (gu.value, dn.value, rgu.value, rdn.value) == (32, 32, 0, 0)
     assert query(9) == -1
+
+
+def test_tile_choice_for_a_new_batch_size_is_quick():
+    # host time of the first forward of a shape, the least of many: packed tiles play their cuts through
+    # (0.15 ms; with every one of them to its end 0.6 to 1.4 ms), row-major and streamed batches have no
+    # choice to make (0.002 ms; they took as long)
+    lib = binding.lib()
+    g = np.random.default_rng(3)
+    W = g.multinomial(8 * 4096, synth.popularity(128, 1.0, 2, 0), size=(4, 1)).astype(np.int64)
+    plan = binding.Plan(W, 8, 8)
+    a = binding.FwdArgs()
+    a.dtype, a.H, a.I, a.k = 1, 4096, 1536, 8
+
+    def least(first, calls=60):
+        best = 1.0
+        for T in range(first, first + calls):
+            a.T = T
+            t = time.perf_counter()
+            assert lib.craft_moe_rank_forward_tiles(plan._h, 0, 0, ctypes.byref(a), None, None, None, None) == 0
+            best = min(best, time.perf_counter() - t)
+        return best
+
+    rowmajor = max(least(64), least(1700), least(4096))
+    a.w_gateup_packed = a.w_down_packed = 0x1000
+    packed = least(4096)
+    print(f"  a new batch size: row-major {rowmajor * 1e6:.1f} us, packed {packed * 1e6:.0f} us")
+    assert packed < 450e-6 and rowmajor < 50e-6
 
 
 # One rank that holds `slots` experts with `rows` tokens each; us streamed / tiled where it was measured.
