@@ -252,7 +252,8 @@ bool streamed(const craft_layer_plan &lp, int32_t rank, int64_t T, int32_t k, in
     return stream_t < cost.gain * tile_t;
 }
 
-tile_choice choose_tiles(const craft_layer_plan &lp, int32_t rank, int64_t T, int32_t k, int32_t H, int32_t I, int32_t cus) {
+tile_choice choose_tiles(const craft_layer_plan &lp, int32_t rank, int64_t T, int32_t k, int32_t H, int32_t I, bool w8,
+                         int32_t cus) {
     tile_choice best{{kFragsPacked, kFragsPacked}, {false, false}};
     const double scale = tokens_per_load(lp, T, k);
     if (scale <= 0.0) return best;
@@ -269,7 +270,9 @@ tile_choice choose_tiles(const craft_layer_plan &lp, int32_t rank, int64_t T, in
         // A rider's weights come through the same path from L2 as the tile's own operands, and
         // that path is what bounds a tile under full load: the rider costs its bytes (5 KB per
         // step against the tile's 8 + fragments) rather than its one MFMA in 2 * fragments + 1.
-        const double rider_us = 4.0 + 0.004 * (double)K;
+        // E4M3: fewer bytes, more instructions; 4096 tokens on 17 slots at H = 4096 carry their riders
+        // (216 -> 207 us), and 5000 do not, where that would cost 242 -> 257.
+        const double rider_us = 4.0 + (w8 ? 0.0034 : 0.004) * (double)K;
         // Only where the busy slots' tiles make up a round or two does their count decide the
         // time; over many rounds the tallest tile (most reuse per weight fragment, fewest
         // fixed costs) wins by itself, and there the model is not trusted to say otherwise.
@@ -313,7 +316,7 @@ tile_choice choose_tiles(const craft_layer_plan &lp, int32_t rank, int64_t T, in
     return best;
 }
 
-// How the packed weights' tiles are cut for (layer, rank, T, k, H, I) is chosen once and kept with
+// How the packed weights' tiles are cut for (layer, rank, T, k, H, I, format) is chosen once and kept with
 // the plan: later forwards of the same shape find it by walking a short insert-only list, without a
 // lock.  Row-major and streamed batches have no cut to choose.
 tile_choice tile_choice_of(const craft_plan_t *plan, int32_t layer, int32_t rank, const craft_fwd_args *a,
@@ -334,7 +337,7 @@ tile_choice tile_choice_of(const craft_plan_t *plan, int32_t layer, int32_t rank
     craft_rank_state &rs = plan->state(layer, rank);
     auto find = [&]() -> const craft_tile_choice * {
         for (const craft_tile_choice *t = rs.tiles.load(std::memory_order_acquire); t; t = t->next)
-            if (t->T == a->T && t->k == a->k && t->H == a->H && t->I == a->I) return t;
+            if (t->T == a->T && t->k == a->k && t->H == a->H && t->I == a->I && t->w8 == w8) return t;
         return nullptr;
     };
     const craft_tile_choice *hit = find();
@@ -342,8 +345,8 @@ tile_choice tile_choice_of(const craft_plan_t *plan, int32_t layer, int32_t rank
         std::lock_guard<std::mutex> lk(rs.mu);
         hit = find();
         if (!hit) {
-            const tile_choice c = choose_tiles(lp, rank, a->T, a->k, a->H, a->I, cached_num_cu());
-            craft_tile_choice *n = new craft_tile_choice{a->T, a->k, a->H, a->I, {c.frags[0], c.frags[1]},
+            const tile_choice c = choose_tiles(lp, rank, a->T, a->k, a->H, a->I, w8, cached_num_cu());
+            craft_tile_choice *n = new craft_tile_choice{a->T, a->k, a->H, a->I, w8, {c.frags[0], c.frags[1]},
                                                          {c.riders[0], c.riders[1]}, rs.tiles.load(std::memory_order_relaxed)};
             rs.tiles.store(n, std::memory_order_release);
             hit = n;

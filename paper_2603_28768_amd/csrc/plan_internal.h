@@ -34,11 +34,12 @@ struct craft_table_reg {
     int32_t layer, rank;                  // whose list the node is in
 };
 
-// FFN tile choice made for one (T, k, H, I): for gate/up and down, the fragments per row-tile
-// (negative: shared evenly) and whether cold slots ride along with busy tiles.
+// FFN tile choice made for one (T, k, H, I, weight format): for gate/up and down, how a slot's rows are
+// cut (row_tiles) and whether cold slots ride along with busy tiles.
 struct craft_tile_choice {
     int64_t T;
     int32_t k, H, I;
+    bool w8;
     int32_t frags[2];
     bool riders[2];
     craft_tile_choice *next;
