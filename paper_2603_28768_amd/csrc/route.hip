@@ -4,8 +4,8 @@
 // tokens at once and every cross-lane step is a row-local DPP move (quad permutes and
 // row mirrors), not an LDS permute.  A lane holds the scores of experts 4*lane..4*lane+3,
 // +64, +128, ... (16-byte loads; a token's row is read as contiguous 256-byte pieces).
-// Up to 16 picks are made at once (see the kernel); otherwise, or where too many scores tie for
-// that, each of the k picks is an arg-max over (score, expert id): first inside the lane in
+// Up to 14 picks are made at once where that pays (see the kernel); otherwise, or where too many scores
+// tie for that, each of the k picks is an arg-max over (score, expert id): first inside the lane in
 // ascending expert order, then a four-step butterfly over the row.  Scores are compared
 // raw, never their exponentials, and equal scores resolve to the lower expert id.
 //
@@ -178,9 +178,14 @@ __global__ __launch_bounds__(kThreads) void route_kernel(RouteArgs a) {
         // Few of the row's scores can be among its k best: the k-th largest of the 16 lanes' maxima
         // is a bound that k of them reach, and a dozen or so reach in all.  Those are gathered
         // through LDS, one or two to a lane, and each finds its place by being compared with
-        // every other (k = 8: T = 32768, E = 256 20.6 -> 14.2 us, T = 16384, E = 384 15.9 -> 9.0, against k arg-max
-        // rounds).
-        const bool few = NQ <= 8 && a.k <= 16;     // more than 512 scores: no registers for it
+        // every other.  Not for few picks, which the rounds make sooner, the fewer scores a lane has;
+        // not where fewer lanes than picks have a score, or from 14 picks on (15 of one chunk): there
+        // some row of nearly every wave has more than 32 above its bound, and the rounds come on top.
+        // T = 131072, against k arg-max rounds: E = 64, k = 4 17.8 / 15.8 us, k = 5 0.99 of their time,
+        // k = 8 0.74; E = 128, k = 2 1.36, 4 1.00, 8 0.64, 13 0.72; E = 256, k = 2 1.07, 3 0.96, 8 0.54;
+        // E = 384, k = 1 0.97, 8 0.54, 14 1.05.
+        constexpr int kFewest = NQ == 1 ? 5 : NQ == 2 ? 4 : NQ <= 4 ? 3 : NQ <= 6 ? 2 : 1, kMost = NQ == 1 ? 14 : 13;
+        const bool few = NQ <= 8 && a.k >= kFewest && a.k <= kMost && 4 * a.k <= a.E + 3;   // (more than 512 scores: no registers)
         int n_cand = 0;
         float bound = kGone;
         if (few) {
@@ -252,11 +257,27 @@ __global__ __launch_bounds__(kThreads) void route_kernel(RouteArgs a) {
                     // strictly greater, so equal scores keep the lower id
                     float bv = v[0][0];
                     int bi = sub * 4;
+                    if (NQ == 2) {
+                        // as a tournament: a shorter chain (64 picks of 128 scores, 4096 tokens: 20.2 -> 19.4 us);
+                        // more scores would take registers that cost waves
+                        float tv[8];
+                        int ti[8];
 #pragma unroll
-                    for (int q = 0; q < NQ; ++q)
+                        for (int i = 0; i < 8; ++i) { tv[i] = v[i / 4 < NQ ? i / 4 : 0][i % 4]; ti[i] = i / 4 * 64 + sub * 4 + i % 4; }
 #pragma unroll
-                        for (int c = 0; c < 4; ++c)
-                            if (v[q][c] > bv) { bv = v[q][c]; bi = q * 64 + sub * 4 + c; }
+                        for (int width = 1; width < 8; width *= 2)
+#pragma unroll
+                            for (int i = 0; i + width < 8; i += 2 * width)
+                                if (tv[i + width] > tv[i]) { tv[i] = tv[i + width]; ti[i] = ti[i + width]; }
+                        bv = tv[0];
+                        bi = ti[0];
+                    } else {
+#pragma unroll
+                        for (int q = 0; q < NQ; ++q)
+#pragma unroll
+                            for (int c = 0; c < 4; ++c)
+                                if (v[q][c] > bv) { bv = v[q][c]; bi = q * 64 + sub * 4 + c; }
+                    }
                     argmax_step<kXor1>(bv, bi);
                     argmax_step<kXor2>(bv, bi);
                     argmax_step<kHalfMirror>(bv, bi);

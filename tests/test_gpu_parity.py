@@ -40,6 +40,49 @@ def test_route_parity(torch_cuda, T, E, k, quantum, renorm):
     assert np.allclose(_np(w), rw, rtol=1e-5, atol=1e-30)
 
 
+@pytest.mark.parametrize("E,ks", [(16, (1, 4, 5, 16)), (64, (4, 5, 14, 15)), (100, (3, 4, 13, 14)), (256, (2, 3, 13, 14)),
+                                  (384, (1, 2, 13, 14)), (512, (1, 13, 14)), (23, (5, 6, 7))])
+def test_route_on_both_sides_of_its_rule(torch_cuda, E, ks):
+    # fewest and most picks that are gathered at once, and more picks than lanes with a score
+    torch = torch_cuda
+    g = np.random.default_rng(E)
+    l = (g.standard_normal((500, E)) * 2).astype(np.float32)
+    dev = torch.from_numpy(l).cuda()
+    for k in ks:
+        for renorm in (True, False):
+            ids, w = binding.route_topk(dev, k, renorm)
+            rid, rw = oracle.route(l, k, renorm)
+            assert np.array_equal(_np(ids), rid)
+            assert np.allclose(_np(w), rw, rtol=1e-5, atol=1e-30)
+
+
+@pytest.mark.parametrize("E,k,most", [(8, 2, 0.82), (64, 2, 0.82), (128, 2, 0.94), (32, 12, 2.1)])
+def test_route_gathers_only_where_that_is_sooner(torch_cuda, E, k, most):
+    # time against 8 picks of 64 scores, which are gathered (62 us): gathered too, one or two picks took as
+    # long (1.00, 0.99, 1.07; by rounds 0.68, 0.66, 0.83), and for more picks than lanes with a score
+    # gathering came on top of the rounds (2.26; rounds alone 1.96)
+    torch = torch_cuda
+    T = 1 << 19
+
+    def least(E, k):
+        l = torch.randn((T, E), device="cuda:0")
+        out = []
+        for _ in range(8):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            binding.route_topk(l, k)
+            a.record()
+            for _ in range(20):
+                binding.route_topk(l, k)
+            b.record()
+            torch.cuda.synchronize()
+            out.append(a.elapsed_time(b) * 50)
+        return min(out)
+
+    us, eight = least(E, k), least(64, 8)
+    print(f"  E={E} k={k}: {us:.1f} us, E=64 k=8: {eight:.1f} us, {us / eight:.2f}", flush=True)
+    assert us <= most * eight
+
+
 def test_route_reads_scores_that_are_not_16_byte_aligned(torch_cuda):
     # E % 4 == 0 lets the kernel read rows 16 bytes at a time, but only from a 16-byte aligned
     # base: a score matrix that starts 4 bytes into an allocation is read score by score
