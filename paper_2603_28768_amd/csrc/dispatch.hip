@@ -4,9 +4,11 @@
 // The i-th assignment (in flat token-major order) that names expert e goes to that
 // expert's copy i mod c_e, and is the (i div c_e)-th row of that copy's slot.  i is
 // assembled from two parts: the assignment's rank inside its 32-token block (recorded by
-// the routing kernel) and the number of assignments to e in all earlier blocks, which
-// scan_kernel produces as an exclusive prefix over blocks.  No result depends on the
-// order in which atomics retire, so indices are reproducible bit for bit.
+// the routing kernel) and the number of assignments to e in all earlier blocks.  The latter is an
+// exclusive prefix over blocks, either from scan_kernel, which also leaves the slots' offsets, for
+// dispatch_kernel; or put together by every workgroup of dispatch_direct_kernel for itself, from
+// the counts of a few blocks or prefix_kernel's totals of chunks of them (see direct_dispatch for which).
+// No result depends on the order in which atomics retire, so indices are reproducible bit for bit.
 #include <algorithm>
 
 #include "kernels.h"
@@ -327,12 +329,11 @@ __global__ __launch_bounds__(64 * kDirectWaves) void prefix_kernel(int32_t *hist
 // and needs no other workgroup's results.  In a batch of up to kSmallBlocks blocks a chunk is a
 // single block, whose counts the routing kernel has left: no other launch at all (T = 256, E = 384:
 // 14.3 -> 8.7 us for the two).  In a larger one prefix_kernel runs in front (T = 16384, E = 384:
-// scan 14.9 and dispatch 5.4 us -> 4.8 and 8.3; T = 32768, E = 256: 17.9 and 8.5 -> 5.2 and 12.9; T =
-// 4096, E = 128: 6.7 and 5.6 -> 4.9 and 7.9).  A workgroup handles one block of 32 tokens, a few
-// neighbouring ones in a large batch.  COPY, for the small-batch FFN: the token rows bound for this
-// rank are copied into fragment order on the way, by sa.slices workgroups per block that take a
-// share of the columns each (the first one writes dest / src).  The last workgroup builds the
-// tile tables.
+// scan 14.9 and dispatch 5.4 us -> 4.8 and 8.3; T = 32768, E = 256: 17.9 and 8.5 -> 5.2 and 12.9).
+// A workgroup handles one block of 32 tokens, a few neighbouring ones in a large batch.  COPY, for the
+// small-batch FFN: the token rows bound for this rank are copied into fragment order on the way, by
+// sa.slices workgroups per block that take a share of the columns each (the first one writes
+// dest / src).  The last workgroup builds the tile tables.
 constexpr int kDirectThreads = 512;
 constexpr int kDirectSlots = 2048;
 template <bool COPY>
@@ -478,9 +479,19 @@ __global__ __launch_bounds__(kDirectThreads) void dispatch_direct_kernel(DirectD
 
 }  // namespace
 
-// (up to 16 chunks: every workgroup reads all of their totals)
-bool direct_dispatch(int64_t T, int32_t S) { return T > 0 && T <= 16ll * kDirectChunk * kTokPerBlock && S <= kDirectSlots; }
-bool small_dispatch(int64_t T, int32_t S) { return direct_dispatch(T, S) && T <= (int64_t)kSmallBlocks * kTokPerBlock; }
+bool small_dispatch(int64_t T, int32_t S) { return T > 0 && T <= (int64_t)kSmallBlocks * kTokPerBlock && S <= kDirectSlots; }
+// Up to 16 chunks: every workgroup reads all of their totals.  But where one workgroup has little to
+// scan (one or two groups of 64 experts, up to a chunk of blocks between them) the scan and the plain
+// dispatch are sooner than a second launch in front of the direct kernel.  Together, scanned / direct,
+// us in a forward: E = 64 and 64 slots, T = 2048 9.0 / 11.1, 8192 11.3 / 13.0; E = 64 and 512 slots,
+// T = 4096 11.0 / 14.1; E = 128 and 144 slots, T = 2048 12.1 / 12.7, 8192 16.0 / 15.6; E = 128 and 800
+// slots, T = 2048 11.4 / 12.7; E = 192 even; E = 256, T = 2048 14.4 / 12.3.
+bool direct_dispatch(int64_t T, int32_t E, int32_t S) {
+    if (small_dispatch(T, S)) return true;
+    const int64_t groups = (E + 63) / 64, blocks = (T + kTokPerBlock - 1) / kTokPerBlock;
+    if (groups <= 2 && blocks * groups <= kScanChunk) return false;
+    return T > 0 && T <= 16ll * kDirectChunk * kTokPerBlock && S <= kDirectSlots;
+}
 
 hipError_t launch_prefix(int32_t *hist, int32_t *chunk_tot, int32_t NB, int32_t E, hipStream_t s) {
     if (NB <= kSmallBlocks) return hipSuccess;

@@ -165,7 +165,7 @@ struct DirectDispatchArgs {
     int32_t ntot, chunk_blocks, slices, span;
     bool local;               // the blocks' prefixes inside their chunk come on top
 };
-bool direct_dispatch(int64_t T, int32_t S);
+bool direct_dispatch(int64_t T, int32_t E, int32_t S);
 bool small_dispatch(int64_t T, int32_t S);
 hipError_t launch_prefix(int32_t *hist, int32_t *chunk_tot, int32_t NB, int32_t E, hipStream_t s);
 hipError_t launch_dispatch_direct(DirectDispatchArgs a, const int32_t *chunk_tot, hipStream_t s);

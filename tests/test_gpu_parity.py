@@ -629,16 +629,26 @@ def test_rank_with_more_slots_than_the_tile_tables_in_lds(torch_cuda):
 
 
 @pytest.mark.parametrize("T,E,k,D,slots", [
-    (3000, 160, 4, 4, 6),        # three expert groups share the waves five each; 19 blocks per wave
-    (4100, 128, 8, 8, 16),       # two groups, 17 blocks per wave: one more than the registers keep
-    (8192, 384, 8, 8, 24),       # six groups, 128 blocks per wave, four waves idle
-    (2000, 1024, 2, 16, 32),     # a wave per group, every block of the batch
-    (8200, 72, 4, 2, 5),         # one block more than a chunk: two workgroups per group, ragged group
-    (20000, 200, 3, 4, 9),       # three chunks of four groups
+    # prefixes over chunks of 128 blocks, every workgroup derives the slots
+    (3000, 160, 4, 4, 6),        # one chunk, three expert groups, a short last block
+    (4100, 128, 8, 8, 16),       # two groups, one block more than a chunk
+    (8192, 384, 8, 8, 24),       # six groups, two whole chunks
+    (2000, 1024, 2, 16, 32),     # the most experts
+    (8200, 72, 4, 2, 5),         # a third chunk of one block, ragged group
+    (20000, 200, 3, 4, 9),       # five chunks of four groups, two blocks to a workgroup
     (1024, 40, 2, 2, 3),         # the largest batch dispatched from the blocks' counts alone
-    (1025, 40, 2, 2, 3),         # the smallest with prefixes over chunks of blocks
+    (8193, 64, 2, 2, 3),         # one group, the smallest batch that is not scanned
     (16385, 48, 2, 2, 3),        # two blocks to a workgroup, the last one alone
-    (65600, 16, 1, 2, 2)])       # more chunks than every workgroup reads: the scan in front
+    # the scan, by a single workgroup
+    (1025, 40, 2, 2, 3),         # the smallest batch, ragged group
+    (8192, 64, 3, 4, 20),        # one group, the whole chunk
+    (4096, 128, 8, 8, 16),       # two groups, half a chunk: the largest batch of two
+    (3000, 1024, 2, 64, 1100),   # more slots than a dispatch workgroup keeps; a wave per group
+    (8192, 130, 2, 64, 2000),    # the same, three groups, the whole chunk
+    # the scan, by one workgroup per chunk and group
+    (9000, 1024, 2, 64, 1100),   # sixteen groups, a ragged second chunk
+    (65600, 16, 1, 2, 2),        # more chunks than a dispatch workgroup reads: nine of one group
+    (66000, 200, 3, 4, 9)])      # nine of four groups
 def test_dispatch_over_block_and_expert_shapes(torch_cuda, T, E, k, D, slots):
     # how the per-block counts are dealt to the waves depends on the number of 32-token blocks
     # and of 64-expert groups: integer results against the checker on every rank, narrow FFN
