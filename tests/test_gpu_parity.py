@@ -180,6 +180,10 @@ GATE_TOL = 1e-4
     ("bf16", 129, 192, 60),          # the smallest batch past the thin tiles; as many slabs as stages
     ("bf16", 260, 456, 1000),        # four blocks of experts, the last one ragged
     ("bf16", 16500, 136, 150),       # two fragments of tokens without a workspace, ragged slab
+    ("bf16", 8, 7168, 256),          # thin tiles, the contraction split eight ways
+    ("bf16", 100, 1000, 100),        # thin, split, ragged slab, tokens and experts, two blocks of tokens
+    ("bf16", 128, 2056, 384),        # thin, the last split shorter than the rest
+    ("bf16", 17, 520, 40),           # thin, two splits of a ragged contraction
     ("f32", 50, 100, 12)])
 def test_router_logits_parity(torch_cuda, dtype, T, H, E):
     cfg = synth.scaled(synth.CONFIGS["qwen3"], dtype=dtype, T=T, H=H, E=E)
@@ -275,12 +279,48 @@ def test_forward_with_its_own_gating_network(torch_cuda, dtype, T, H, I, E, k, D
         assert err <= TOL[dtype] * np.abs(ref["out"]).max() + 1e-30
 
 
+@pytest.mark.parametrize("T,H,E,k,renorm", [
+    (8, 7168, 256, 8, True),         # the most parts, in one trip
+    (40, 4096, 128, 8, False),       # the parts are read a second time for the weights
+    (100, 1000, 130, 4, True),       # scores read one by one, four parts
+    (128, 2056, 100, 5, False),      # two chunks of 64 scores, ragged slab
+    (300, 2048, 384, 8, True),       # several trips of three parts
+    (129, 1024, 300, 14, False),     # several trips, arg-max rounds
+    (60, 1024, 66, 1, True)])
+def test_forward_adds_up_the_parts_of_a_split_gate(torch_cuda, T, H, E, k, renorm):
+    # the routing kernel adds the partial scores in the order the gate's own sum has: the same bits as
+    # the stand-alone scores handed in, and decisions and output as the checker takes them on those
+    torch = torch_cuda
+    cfg = synth.scaled(synth.CONFIGS["qwen3"], T=T, H=H, I=64, E=E, k=k, D=32, replica_slots=2, zipf_s=1.0, profile_batches=2)
+    print("split gate", cfg, renorm, flush=True)
+    case = Case(cfg)
+    Wr = synth.gate_weights(cfg)
+    Wrd = binding.to_device(Wr, "bf16")
+    own, x, _ = case.gpu_rank(case.heaviest, packed=True, w_router=Wrd)
+    given, _, _ = case.gpu_rank(case.heaviest, packed=True)
+    own.args.renormalize = given.args.renormalize = int(renorm)
+    ws = binding.router_logits_workspace(x, Wrd)
+    assert ws is not None and ws.numel() >= 2 * T * E * 4               # split
+    logits = binding.router_logits(x, Wrd, ws)
+    out_own, out_given = own(x).clone(), given(x, logits)
+    torch.cuda.synchronize()
+    for name in ("ids", "topk_w", "dest"):
+        assert torch.equal(own.debug[name], given.debug[name])
+    assert torch.equal(out_own, out_given)
+    ref = oracle.rank_forward(case.x, _np(logits), k, case.slot_expert, case.rank_slot_off, case.heaviest, case.weights_of,
+                              renorm, None)
+    assert np.array_equal(_np(own.debug["ids"]), ref["ids"])
+    assert np.allclose(_np(own.debug["topk_w"]), ref["w"], rtol=1e-5, atol=1e-30)
+    assert np.abs(_np(out_own).astype(np.float64) - ref["out"]).max() <= TOL["bf16"] * np.abs(ref["out"]).max() + 1e-30
+
+
 # --------------------------------------------------------------------- forward
 
 def _row_units(case: Case, rank: int, heights):
     """Row ranges [a, b) (positions in the rank's row block) of everything the packed FFN
-    schedules as a unit, for both ways a busy slot's fragments may be cut into row-tiles of the
-    given heights (full tiles and a remainder, or shared evenly): the first and the last 32-row
+    schedules as a unit, for every way a busy slot's fragments may be cut into row-tiles of the
+    given heights (full tiles and a remainder, or shared evenly between the tiles that a height in
+    fifths of a fragment up to the given one asks for): the first and the last 32-row
     fragment of every row-tile of every slot with more than 64 rows, and every 32-row fragment
     of the slots with at most 64 rows (a tile of their own or a rider on a busy tile)."""
     p_lo, p_hi = case.rank_slot_off[rank], case.rank_slot_off[rank + 1]
@@ -296,8 +336,10 @@ def _row_units(case: Case, rank: int, heights):
             continue
         for h in heights:
             f = h // 32
-            m = (F + f - 1) // f
-            for cut in ([min(i * f, F) for i in range(m + 1)], [i * F // m for i in range(m + 1)]):
+            cuts = [[min(i * f, F) for i in range((F + f - 1) // f + 1)]]
+            for m in {-(-10 * F // tenths) for tenths in range(max(40, 10 * f - 8), 10 * f + 1, 2)}:
+                cuts.append([i * F // m for i in range(m + 1)])
+            for cut in cuts:
                 for f0, f1 in zip(cut[:-1], cut[1:]):
                     units.append((a + 32 * f0, a + min(32 * f0 + 32, n)))
                     units.append((a + 32 * (f1 - 1), a + min(32 * f1, n)))
@@ -703,6 +745,17 @@ def test_block_ordered_tile_list_with_ragged_bands(torch_cuda):
         row_tiles = [(int(r) + height - 1) // height for r in rows if r > 64]
         assert sum(row_tiles) * nt > 2 * 256 and any(m % 8 for m in row_tiles) and nt % 8
     print(f"  slot rows {rows.tolist()}, row-tiles of {rg}/{rd} rows", flush=True)
+    _check_rank(torch_cuda, case, 0, packed=True, cover=True)
+
+
+def test_packed_tiles_of_a_height_between_whole_fragments(torch_cuda):
+    # six slots of some 63 fragments, three column tiles: the down GEMM takes twelve row-tiles a slot (even
+    # heights of five or six whole fragments give thirteen or eleven), every token compared
+    cfg = synth.scaled(synth.CONFIGS["qwen3"], T=12000, H=520, I=264, E=6, k=1, D=1, replica_slots=0, zipf_s=0.0,
+                       profile_batches=2)
+    case = Case(cfg)
+    fwd, _, _ = case.gpu_rank(0, packed=True)
+    assert fwd.tile_choice() == (160, 192, 0, 0)
     _check_rank(torch_cuda, case, 0, packed=True, cover=True)
 
 
