@@ -668,7 +668,7 @@ craft_status forward_on(const craft_plan_t *plan, int32_t layer, int32_t rank, c
         ScopedEvent ev(CRAFT_K_GATE, s);
         float *own = reinterpret_cast<float *>(ws + L.gate_logits);
         RouterArgs ga{a->dtype, a->x, a->w_router, a->T, a->H, E, own, cached_num_cu(),
-                      L.gate_ws_bytes ? reinterpret_cast<float *>(ws + L.gate_ws) : nullptr, 1, E <= 512};
+                      L.gate_ws_bytes ? reinterpret_cast<float *>(ws + L.gate_ws) : nullptr, 1, E <= 384};
         if (launch_router_logits(ga, s) != hipSuccess) return CRAFT_EHIP;
         // a split gate's partial scores are added by the routing kernel
         nparts = ga.keep_parts && L.gate_ws_bytes ? (int)(L.gate_ws_bytes / ((size_t)a->T * E * sizeof(float))) : 1;

@@ -103,7 +103,7 @@ struct RouteArgs {
     uint8_t *lrank;     // [T][k] rank of the assignment among same-expert ones of its block; may be null
     int32_t *hist;      // [NB][E] per-block expert counts; may be null
     int32_t *ctrl;      // control words to clear; may be null
-    int32_t nparts;     // > 1: a score is the sum of this many partial scores, [nparts][T][E] at `logits` (E <= 512)
+    int32_t nparts;     // > 1: a score is the sum of this many partial scores, [nparts][T][E] at `logits` (E <= 384)
 };
 hipError_t launch_route(const RouteArgs &a, hipStream_t s);
 

@@ -148,7 +148,7 @@ __global__ __launch_bounds__(kThreads) void route_kernel(RouteArgs a) {
             load_row(row, v);
             // the gate's partial scores, added in ascending order of the split; a few parts are
             // requested together, one by one each would cost a round trip
-            constexpr int G = NQ <= 4 ? 7 : NQ <= 6 ? 3 : 1;
+            constexpr int G = NQ <= 4 ? 7 : 3;
             if (PARTS)
                 for (int z0 = 1; z0 < a.nparts; z0 += G) {
                     float f[G][NQ][4];
@@ -353,9 +353,9 @@ hipError_t launch_route(const RouteArgs &a, hipStream_t s) {
     const int64_t nb = (a.T + kTokPerBlock - 1) / kTokPerBlock;
     dim3 grid((unsigned)nb), block(kThreads);
     const int nq = (a.E + 63) / 64;
-    if (nq > 8 && a.nparts > 1) return hipErrorInvalidValue;
+    if (nq > 6 && a.nparts > 1) return hipErrorInvalidValue;    // (a gate of so many experts is never split)
     auto go = [&](auto n) {
-        if (n.value <= 8 && a.nparts > 1) hipLaunchKernelGGL((route_kernel<(n.value <= 8 ? n.value : 8), true>), grid, block, 0, s, a);
+        if (n.value <= 6 && a.nparts > 1) hipLaunchKernelGGL((route_kernel<(n.value <= 6 ? n.value : 6), true>), grid, block, 0, s, a);
         else hipLaunchKernelGGL((route_kernel<n.value, false>), grid, block, 0, s, a);
     };
     if (nq <= 1) go(std::integral_constant<int, 1>{});

@@ -190,8 +190,11 @@ hipError_t launch_bf16(const RouterArgs &a, int nxf, hipStream_t s) {
 
 // Tile height (32-token fragments per workgroup) and split of the contraction for a shape.
 // Without a workspace: short tiles, as many as there are CUs if possible.  With one: the
-// tallest tile the registers allow, and as many splits as bring the workgroups up to the CU
-// count (at most 8, at least 4 slabs each).
+// tallest tile, and as many splits as bring the workgroups up to the CU count (at most 8, at least 4
+// slabs each).  Workgroups are counted in blocks of up to 384 experts, not the 256 of a tile, and more
+// than 384 experts are never split: 257 to 384 get twice the workgroups this aims at (T = 16384, E = 384:
+// 512, two rounds), more get short tiles.  No shape is slower for it than with the tiles of 512
+// experts that the count was made for.
 void router_logits_shape(int64_t T, int32_t H, int32_t E, int32_t num_cu, bool workspace, int *nxf, int *nsplit) {
     const int nb = E > 512 ? 4 : (E + 127) / 128;
     *nsplit = 1;
