@@ -360,9 +360,10 @@ craft_status craft_moe_rank_forward(const craft_plan_t *plan, int32_t layer, int
  * device memory; the first forward of a new (T, k, H, I) on a (layer, rank) notes its tile
  * choice in the plan (a few bytes of host memory), and the first call on a device looks up
  * the array's address there (make that call outside a capture).
- *   CRAFT_EINFEASIBLE when craft_moe_rank_forward_workspace() for these arguments exceeds
- *   CRAFT_STATIC_SCRATCH_BYTES (checked on the host before anything is launched: lower
- *   max_rows or T); the other errors as craft_moe_rank_forward.
+ *   CRAFT_EINFEASIBLE when the workspace of these arguments exceeds CRAFT_STATIC_SCRATCH_BYTES
+ *   (checked on the host before anything is launched: lower max_rows or T; a small batch that would
+ *   only not fit for its weights to be streamed is tiled); the other errors as
+ *   craft_moe_rank_forward.
  * All calls on one GPU share that GPU's array and the array keeps the last call's contents:
  * forwards through this entry point must be ordered on one stream (calls that overlap on
  * one GPU race), and craft_moe_rank_forward_result has no workspace pointer to read here
@@ -375,12 +376,12 @@ craft_status craft_moe_rank_forward_static(const craft_plan_t *plan, int32_t lay
 /* How forwards with these arguments cut the two grouped GEMMs into tiles: the most rows a
  * row-tile gets (a multiple of 32), and whether the slots with few rows are carried along by
  * the tiles of the busy slots (1) or get tiles of their own (0).  With packed weights both
- * are chosen per (plan, layer, rank, T, k, H, I) from the loads the plan was made from, by
- * playing the launch through against a cost model, so that the tiles of the busy slots fill
- * the CUs in whole rounds; the choice is kept in the plan.  64 rows in both: a small batch whose
- * weights are streamed, with at most 64 rows of a slot against one pass over them (not with
- * tuning knobs set, and only where the workspace is of the size
- * craft_moe_rank_forward_workspace names for it).  Any output pointer may be NULL.
+ * are chosen per (plan, layer, rank, T, k, H, I, weight_format) from the loads the plan was made
+ * from, by playing the launch through against a cost model, so that the tiles of the busy slots
+ * fill the CUs in whole rounds; the choice is kept in the plan.  64 rows in both: a small batch whose
+ * weights are streamed, packed or row-major, with at most 64 rows of a slot against one pass over
+ * them, because that is expected to be faster than tiles (packed: not with tuning knobs set; and only
+ * where the workspace is of the size craft_moe_rank_forward_workspace names for it).  Any output pointer may be NULL.
  * Host-side, no device work. */
 craft_status craft_moe_rank_forward_tiles(const craft_plan_t *plan, int32_t layer, int32_t rank,
                                           const craft_fwd_args *args, int32_t *rows_gateup,

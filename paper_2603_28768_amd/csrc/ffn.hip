@@ -18,10 +18,12 @@
 // the weight rows of a tile are 128 gate and the 128 matching up rows, 16 of one followed by 16 of
 // the other, so that gate and up of one output meet in the same lane and element of two
 // accumulators: SwiGLU is applied in registers.  The gate/up GEMM reads its rows straight from x
-// through the dispatch permutation (no staged copy).  What bounds it is what a CU pulls out of its
-// L2, 48 KiB per slab of a tall tile in 1.4 us: taller tiles move less but come out in fewer
-// rounds.  1777 tokens on 17 slots, H = 4096, I = 1536: gate/up 190 -> 117 us, down 84 -> 63 (before: 128 x
-// 128 tiles through registers, one slab ahead).
+// through the dispatch permutation (no staged copy).  A slab of a tall tile, 48 KiB, takes 1.4 us, three
+// times its matrix instructions; which of the latency of loads that miss the L2 and the issue of reads
+// and requests holds it there has not been taken apart (a CU reads three times as fast out of its L2
+// in a plain loop).  Taller tiles move less but come out in fewer rounds.  1777 tokens on 17 slots,
+// H = 4096, I = 1536: gate/up 190 -> 117 us, down 84 -> 63 (before: 128 x 128 tiles through registers, one
+// slab ahead).
 //
 // fp32 path: units of 16 columns and 32 rows from the same tile list (small configurations).
 #include <type_traits>

@@ -112,10 +112,6 @@ static __device__ __forceinline__ int64_t first_tile(int64_t total) {
     return b / 8 < run ? (b % 8) * run + b / 8 : total;
 }
 
-static __device__ __forceinline__ uint32_t bf16_rne(float f) {
-    const uint32_t u = __float_as_uint(f);
-    return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
-}
 static __device__ __forceinline__ float silu(float g) { return g / (1.0f + __expf(-g)); }
 // The same with the hardware reciprocal (1 ulp) instead of a correctly rounded division: the
 // result is rounded to bf16 right after.

@@ -146,8 +146,9 @@ struct DispatchArgs {
 };
 hipError_t launch_dispatch(const DispatchArgs &a, hipStream_t s);
 
-// Without the scan: see dispatch_direct_kernel.  Batches of at most kSmallBlocks 32-token blocks
-// need no other launch, larger ones launch_prefix over chunks of kDirectChunk blocks.
+// Without the scan: see dispatch_direct_kernel, and direct_dispatch for where.  Batches of at most
+// kSmallBlocks 32-token blocks need no other launch, larger ones launch_prefix over chunks of
+// kDirectChunk blocks.
 constexpr int kSmallBlocks = 32;
 constexpr int kDirectChunk = kScanChunk / 2;   // the totals take the room of the scan's chunk_tot and chunk_base
 struct DirectDispatchArgs {

@@ -685,10 +685,7 @@ def test_rank_with_more_slots_than_the_tile_tables_in_lds(torch_cuda):
     (1025, 40, 2, 2, 3),         # the smallest batch, ragged group
     (8192, 64, 3, 4, 20),        # one group, the whole chunk
     (4096, 128, 8, 8, 16),       # two groups, half a chunk: the largest batch of two
-    (3000, 1024, 2, 64, 1100),   # more slots than a dispatch workgroup keeps; a wave per group
-    (8192, 130, 2, 64, 2000),    # the same, three groups, the whole chunk
     # the scan, by one workgroup per chunk and group
-    (9000, 1024, 2, 64, 1100),   # sixteen groups, a ragged second chunk
     (65600, 16, 1, 2, 2),        # more chunks than a dispatch workgroup reads: nine of one group
     (66000, 200, 3, 4, 9)])      # nine of four groups
 def test_dispatch_over_block_and_expert_shapes(torch_cuda, T, E, k, D, slots):
@@ -701,6 +698,21 @@ def test_dispatch_over_block_and_expert_shapes(torch_cuda, T, E, k, D, slots):
     toks = list(range(0, T, max(1, T // 16)))
     for g in (0, D - 1):
         _check_rank(torch_cuda, case, g, tokens=toks, packed=True)
+
+
+@pytest.mark.parametrize("T,E,k,D,slots", [
+    (3000, 1024, 2, 64, 1100),   # a wave per group of experts
+    (8192, 130, 2, 64, 2000),    # three groups, the whole chunk
+    (9000, 1024, 2, 64, 1100)])  # one workgroup per chunk and group, a ragged second chunk
+def test_dispatch_of_more_slots_than_a_workgroup_keeps(torch_cuda, T, E, k, D, slots):
+    # scanned, whatever the batch; the plan is the library's (its checker is slow at so many replicas)
+    cfg = synth.scaled(synth.CONFIGS["qwen3"], T=T, H=64, I=32, E=E, k=k, D=D, replica_slots=slots, zipf_s=1.0)
+    pop = synth.layer_popularity(cfg, 0)
+    plan = binding.Plan(np.maximum(1, pop * 1e6).astype(np.int64)[None, None], D, slots)
+    case = Case(cfg, plan=plan, pop=pop)
+    assert len(case.slot_expert) > 2048
+    for g in (0, D - 1):
+        _check_rank(torch_cuda, case, g, tokens=list(range(0, T, T // 16)), packed=True)
 
 
 @pytest.mark.parametrize("w8", [False, True])
