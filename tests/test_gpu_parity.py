@@ -670,6 +670,16 @@ def test_rank_with_more_slots_than_the_tile_tables_in_lds(torch_cuda):
     _check_rank(torch_cuda, case, 0, packed=False)
 
 
+@pytest.mark.parametrize("T", [90, 1100, 2100])       # few blocks, prefixes in front, scanned
+@pytest.mark.parametrize("slots", [1, 63, 64, 65])
+def test_tile_tables_of_a_wave_of_slots(torch_cuda, T, slots):
+    # a slot per lane up to 64 of them; slots of equal rows and, with 90 tokens, without any
+    torch = torch_cuda
+    cfg = synth.scaled(synth.CONFIGS["qwen3"], T=T, H=64, I=32, E=slots, k=min(2, slots), D=1, replica_slots=0,
+                       zipf_s=1.3, profile_batches=2)
+    _check_rank(torch, Case(cfg), 0, packed=True)
+
+
 @pytest.mark.parametrize("T,E,k,D,slots", [
     # prefixes over chunks of 128 blocks, every workgroup derives the slots
     (3000, 160, 4, 4, 6),        # one chunk, three expert groups, a short last block
