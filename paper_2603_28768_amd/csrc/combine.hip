@@ -1,8 +1,13 @@
 // Gather-weighted combine: the last step of the MoE layer of Sec. 2.1, each token's sum of
-// its experts' outputs scaled by the routing weights.  One 64-lane wavefront per token; a lane owns 16-byte column chunks of the
-// row.  Only assignments whose dispatched position falls inside this rank's row range
+// its experts' outputs scaled by the routing weights.  A 64-lane wavefront takes a piece of a token's row, 2 KiB; a lane owns
+// 16-byte column chunks of it.  Only assignments whose dispatched position falls inside this rank's row range
 // contribute, added in ascending j with fp32 accumulation; there are no atomics, so the
 // result does not depend on scheduling.  Tokens with no assignment on the rank get zeros.
+//
+// A large batch is bound by HBM (mostly zero rows to write), a small one by its chain of round trips on
+// the few CUs that have a wave.  With whole rows per wave (8 KiB a round) a forward took, us, whole / in
+// pieces: 8 tokens of H = 7168 53.1 / 51.3, 250 46.6 / 44.4, 64 of H = 4096 66.4 / 65.2, 1024 151.4 / 150.8;
+// large batches too, 8192 of H = 7168 233.5 / 231.6, 32768 783 / 780.
 #include <hip/hip_bf16.h>
 
 #include "kernels.h"
@@ -47,11 +52,15 @@ template <> struct Chunk<__hip_bfloat16> {
     }
 };
 
+// A wave takes 64 U chunks of one token's row, one request round; the `parts` waves of a row sit in
+// neighbouring workgroups.
+constexpr int U = 2;
 template <typename T>
-__global__ __launch_bounds__(256) void combine_kernel(CombineArgs a) {
+__global__ __launch_bounds__(256) void combine_kernel(CombineArgs a, uint32_t parts) {
     constexpr int N = Chunk<T>::N;
     const int lane = threadIdx.x & 63;
-    const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const uint32_t tokens = blockIdx.x / parts, part = blockIdx.x - tokens * parts;
+    const int64_t t = (int64_t)tokens * 4 + (threadIdx.x >> 6);
     if (t >= a.T) return;
     const int32_t lo = a.slot_off[a.s_lo], hi = a.slot_off[a.s_hi];
     const bool dead = a.ctrl[CTRL_OVERFLOW] != 0;
@@ -65,82 +74,82 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a) {
     const unsigned long long live = __ballot(mine);
     const T *y = static_cast<const T *>(a.y);
     T *out = static_cast<T *>(a.out) + t * a.H;
-    // The chunk loop is uniform over the wave (shuffles need every lane); a lane past the end
-    // of the row only skips its loads and its store.  A lane owns U chunks of the row and the
-    // rows of up to G assignments are requested together before any of them is added (in
+    // A lane past the end of the row only skips its loads and its store (shuffles need every lane).
+    // The rows of up to G assignments are requested together before any of them is added (in
     // ascending j, as always): what a wave takes is a chain of memory latencies, one per round
     // of requests, and a token of the busiest rank has several of its experts there.
-    constexpr int U = 8, G = 4;
-    for (int base = 0; base < a.H; base += 64 * N * U) {
-        int c0[U];
-        bool inside[U];
-        float acc[U][N];
+    constexpr int G = 4;
+    int c0[U];
+    bool inside[U];
+    float acc[U][N];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            c0[u] = base + (u * 64 + lane) * N;
-            inside[u] = c0[u] < a.H;
+    for (int u = 0; u < U; ++u) {
+        c0[u] = ((int)part * U * 64 + u * 64 + lane) * N;
+        inside[u] = c0[u] < a.H;
 #pragma unroll
-            for (int i = 0; i < N; ++i) acc[u][i] = 0.0f;
-        }
-        unsigned long long m = live;
-        while (m) {
-            const T *row[G];
-            float wv[G];
-            int n = 0;
+        for (int i = 0; i < N; ++i) acc[u][i] = 0.0f;
+    }
+    unsigned long long m = live;
+    while (m) {
+        const T *row[G];
+        float wv[G];
+        int n = 0;
 #pragma unroll
-            for (int g = 0; g < G; ++g) {
-                row[g] = y;
-                wv[g] = 0.0f;
-                if (m) {
-                    const int j = __ffsll((long long)m) - 1;
-                    m &= m - 1;
-                    row[g] = y + (int64_t)(__shfl(d, j, 64) - lo) * a.H;
-                    wv[g] = __shfl(wj, j, 64);
-                    n = g + 1;
-                }
+        for (int g = 0; g < G; ++g) {
+            row[g] = y;
+            wv[g] = 0.0f;
+            if (m) {
+                const int j = __ffsll((long long)m) - 1;
+                m &= m - 1;
+                row[g] = y + (int64_t)(__shfl(d, j, 64) - lo) * a.H;
+                wv[g] = __shfl(wj, j, 64);
+                n = g + 1;
             }
-            uint4 raw[G][U];
-#pragma unroll
-            for (int g = 0; g < G; ++g)
-                if (g < n) {
-#pragma unroll
-                    for (int u = 0; u < U; ++u)
-                        raw[g][u] = inside[u] ? *reinterpret_cast<const uint4 *>(row[g] + c0[u])
-                                              : make_uint4(0, 0, 0, 0);
-                }
-#pragma unroll
-            for (int g = 0; g < G; ++g)
-                if (g < n) {
-#pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        float v[N];
-                        Chunk<T>::unpack(raw[g][u], v);
-#pragma unroll
-                        for (int i = 0; i < N; ++i) acc[u][i] += wv[g] * v[i];
-                    }
-                }
         }
+        uint4 raw[G][U];
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (inside[u]) {
-                // written once and not read again by this launch: a streaming store
-                typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-                const uint4 q = Chunk<T>::pack(acc[u]);
-                const u32x4 v = {q.x, q.y, q.z, q.w};
-                __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(out + c0[u]));
+        for (int g = 0; g < G; ++g)
+            if (g < n) {
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    raw[g][u] = inside[u] ? *reinterpret_cast<const uint4 *>(row[g] + c0[u])
+                                          : make_uint4(0, 0, 0, 0);
+            }
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+            if (g < n) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    float v[N];
+                    Chunk<T>::unpack(raw[g][u], v);
+#pragma unroll
+                    for (int i = 0; i < N; ++i) acc[u][i] += wv[g] * v[i];
+                }
             }
     }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (inside[u]) {
+            // written once and not read again by this launch: a streaming store
+            typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+            const uint4 q = Chunk<T>::pack(acc[u]);
+            const u32x4 v = {q.x, q.y, q.z, q.w};
+            __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(out + c0[u]));
+        }
+}
+
+template <typename T>
+void launch_rows(const CombineArgs &a, hipStream_t s) {
+    const uint32_t parts = (uint32_t)((a.H + 64 * Chunk<T>::N * U - 1) / (64 * Chunk<T>::N * U));
+    hipLaunchKernelGGL(combine_kernel<T>, dim3((unsigned)((a.T + 3) / 4) * parts), dim3(256), 0, s, a, parts);
 }
 
 }  // namespace
 
 hipError_t launch_combine(const CombineArgs &a, hipStream_t s) {
     if (a.T == 0) return hipSuccess;
-    const unsigned blocks = (unsigned)((a.T + 3) / 4);
-    if (a.dtype == CRAFT_F32)
-        hipLaunchKernelGGL(combine_kernel<float>, dim3(blocks), dim3(256), 0, s, a);
-    else
-        hipLaunchKernelGGL(combine_kernel<__hip_bfloat16>, dim3(blocks), dim3(256), 0, s, a);
+    if (a.dtype == CRAFT_F32) launch_rows<float>(a, s);
+    else launch_rows<__hip_bfloat16>(a, s);
     return hipGetLastError();
 }
 

@@ -680,6 +680,18 @@ def test_tile_tables_of_a_wave_of_slots(torch_cuda, T, slots):
     _check_rank(torch, Case(cfg), 0, packed=True)
 
 
+@pytest.mark.parametrize("dtype,H", [("bf16", 1016), ("bf16", 1024), ("bf16", 1032), ("bf16", 2056), ("f32", 508), ("f32", 512),
+                                     ("f32", 516)])
+def test_combine_of_rows_in_pieces(torch_cuda, dtype, H):
+    # a wave takes 1024 (fp32: 512) columns of a row; a number of tokens that is no multiple of four
+    torch = torch_cuda
+    cfg = synth.scaled(synth.CONFIGS["qwen3"], dtype=dtype, T=201, H=H, I=40, E=12, k=6, D=2, replica_slots=1,
+                       zipf_s=0.8, profile_batches=2)
+    case = Case(cfg)
+    for rank in range(2):
+        _check_rank(torch, case, rank)
+
+
 @pytest.mark.parametrize("T,E,k,D,slots", [
     # prefixes over chunks of 128 blocks, every workgroup derives the slots
     (3000, 160, 4, 4, 6),        # one chunk, three expert groups, a short last block
