@@ -11,7 +11,7 @@
 // No result depends on the order in which atomics retire, so indices are reproducible bit for bit.
 #include <algorithm>
 
-#include "kernels.h"
+#include "route_block.h"
 
 namespace craft {
 namespace {
@@ -388,11 +388,22 @@ __global__ __launch_bounds__(64 * kDirectWaves) void prefix_kernel(int32_t *hist
 // small-batch FFN: the token rows bound for this rank are copied into fragment order on the way, by
 // sa.slices workgroups per block that take a share of the columns each (the first one writes
 // dest / src).  The last workgroup builds the tile tables.
+//
+// NQ > 0, a batch of a single block: the workgroups route it as well, each for itself (the work of the
+// routing kernel, which has a single workgroup for such a batch, too), and nothing about ids, ranks and
+// counts goes through memory between two launches.  8 tokens with the gate's parts to add, E = 256: the two
+// launches 6.3 + 5 us, a forward 56.3 -> 53.8.
 constexpr int kDirectThreads = 512;
 constexpr int kDirectSlots = 2048;
-template <bool COPY>
-__global__ __launch_bounds__(kDirectThreads) void dispatch_direct_kernel(DirectDispatchArgs sa) {
+static_assert(kDirectThreads == kRouteThreads, "a workgroup routes its block itself");
+template <bool COPY, int NQ = 0, bool PARTS = false>
+__global__ __launch_bounds__(kDirectThreads) void dispatch_direct_kernel(DirectDispatchArgs sa, RouteArgs ra) {
     const DispatchArgs &a = sa.d;
+    constexpr bool ROUTE = NQ > 0;
+    __shared__ uint32_t mask[ROUTE ? kRouteMaxE : 1];
+    __shared__ uint64_t cand[ROUTE ? kTokPerBlock : 1][32];
+    int my_id[kMaxPickSlots];
+    const int tl = threadIdx.x >> 4, sub = threadIdx.x & 15;
     __shared__ int32_t cnt[1024], before[1024], ncopies[1024];
     __shared__ uint16_t first[1024], slots_of[kDirectSlots];
     __shared__ int32_t soff[kDirectSlots + 1];
@@ -409,7 +420,7 @@ __global__ __launch_bounds__(kDirectThreads) void dispatch_direct_kernel(DirectD
     // side, and a line that several XCDs write pieces of is written back by each of them.
     const int32_t spans = (int32_t)gridDim.x - 1;          // (with one slice: a multiple of 8)
     const int32_t turn = blockIdx.x / sa.slices, slice = blockIdx.x % sa.slices;
-    const int32_t b = (sa.slices > 1 ? turn : turn % 8 * (spans / 8) + turn / 8) * sa.span;
+    const int32_t b = ROUTE ? 0 : (sa.slices > 1 ? turn : turn % 8 * (spans / 8) + turn / 8) * sa.span;
     const bool writer = tables;                            // of what there is one of per batch
     const int32_t own = b / sa.chunk_blocks;               // (a span lies inside one chunk)
 
@@ -422,15 +433,35 @@ __global__ __launch_bounds__(kDirectThreads) void dispatch_direct_kernel(DirectD
 #pragma unroll
     for (int u = 0; u < kFirst; ++u) {
         const int32_t i = threadIdx.x + u * kDirectThreads;
-        const bool have = !tables && i < mine_n && as0 + i < A;
+        const bool have = !ROUTE && !tables && i < mine_n && as0 + i < A;
         e0[u] = have ? a.ids[as0 + i] : 0;
         rank0[u] = have ? (int32_t)a.lrank[as0 + i] : 0;
     }
     const int32_t ex0 = threadIdx.x < sa.S ? slot_expert[threadIdx.x] : 0, q0 = threadIdx.x < sa.S ? slot_copy[threadIdx.x] : 0;
     for (int32_t p = threadIdx.x; p < sa.S; p += kDirectThreads) slots_of[p] = (uint16_t)eslots[p];
     if (threadIdx.x == 0) list_len = 0;
+    if constexpr (ROUTE) {
+        for (int32_t e = threadIdx.x; e < a.E; e += kDirectThreads) {
+            ncopies[e] = copies[e];
+            first[e] = (uint16_t)efirst[e];
+            mask[e] = 0u;
+        }
+        if (writer && threadIdx.x < CTRL_WORDS) a.ctrl[threadIdx.x] = 0;
+        __syncthreads();
+        route_block<NQ, PARTS>(ra, tl, tl, writer, mask, cand, my_id);
+        __syncthreads();
+    }
     for (int32_t e = threadIdx.x; e < a.E; e += kDirectThreads) {
         int32_t total = 0, mine = 0;
+        if constexpr (ROUTE) {
+            cnt[e] = total = __popc(mask[e]);
+            before[e] = 0;
+            if (writer) {
+                sa.counts[e] = total;
+                if (sa.user_counts) sa.user_counts[e] = total;
+            }
+            continue;
+        }
         ncopies[e] = copies[e];
         first[e] = (uint16_t)efirst[e];
         // eight at a time, whatever their number: one by one each is a round trip (8 chunks of E = 384:
@@ -514,14 +545,21 @@ __global__ __launch_bounds__(kDirectThreads) void dispatch_direct_kernel(DirectD
             list[2 * at + 1] = stream_fragment(soff[p] - lo, p - a.s_lo, row) * 16 + (row & 15);
         }
     };
+    if constexpr (ROUTE) {
 #pragma unroll
-    for (int u = 0; u < kFirst; ++u) {
-        const int32_t i = threadIdx.x + u * kDirectThreads;
-        if (i < mine_n && as0 + i < A) place(i, e0[u], rank0[u]);
-    }
-    for (int32_t i = threadIdx.x + kFirst * kDirectThreads; i < mine_n && as0 + i < A; i += kDirectThreads) {
-        const int32_t e = a.ids[as0 + i];
-        place(i, e, (int32_t)a.lrank[as0 + i] + (sa.local ? a.base[(int64_t)(b + i / per_block) * a.E + e] : 0));
+        for (int s = 0; s < kMaxPickSlots; ++s)
+            if (tl < a.T && s * 16 + sub < a.k)
+                place(tl * a.k + s * 16 + sub, my_id[s], __popc(mask[my_id[s]] & ((1u << tl) - 1u)));
+    } else {
+#pragma unroll
+        for (int u = 0; u < kFirst; ++u) {
+            const int32_t i = threadIdx.x + u * kDirectThreads;
+            if (i < mine_n && as0 + i < A) place(i, e0[u], rank0[u]);
+        }
+        for (int32_t i = threadIdx.x + kFirst * kDirectThreads; i < mine_n && as0 + i < A; i += kDirectThreads) {
+            const int32_t e = a.ids[as0 + i];
+            place(i, e, (int32_t)a.lrank[as0 + i] + (sa.local ? a.base[(int64_t)(b + i / per_block) * a.E + e] : 0));
+        }
     }
     if (!COPY) return;
     __syncthreads();
@@ -560,7 +598,11 @@ hipError_t launch_prefix(int32_t *hist, int32_t *chunk_tot, int32_t NB, int32_t 
     return hipGetLastError();
 }
 
-hipError_t launch_dispatch_direct(DirectDispatchArgs a, const int32_t *chunk_tot, hipStream_t s) {
+// One block: more would be routed one after the other by every workgroup.  E: up to what the scores of a
+// lane fit registers beside the rest (and a gate's parts are added for).
+bool routed_dispatch(int64_t T, int32_t E, int32_t S) { return T <= kTokPerBlock && E <= 384 && small_dispatch(T, S); }
+
+hipError_t launch_dispatch_direct(DirectDispatchArgs a, const int32_t *chunk_tot, const RouteArgs *route, hipStream_t s) {
     const int32_t NB = (int32_t)((a.d.T + kTokPerBlock - 1) / kTokPerBlock);
     a.local = NB > kSmallBlocks;
     a.chunk_blocks = a.local ? kDirectChunk : 1;
@@ -573,8 +615,25 @@ hipError_t launch_dispatch_direct(DirectDispatchArgs a, const int32_t *chunk_tot
     while (a.local && a.span < 8 && NB / (a.span * 2) >= 256) a.span *= 2;
     const int32_t spans = (NB + a.span - 1) / a.span;
     const dim3 grid((unsigned)((a.slices > 1 ? spans * a.slices : (spans + 7) / 8 * 8) + 1)), block(kDirectThreads);
-    if (a.xpk) hipLaunchKernelGGL(dispatch_direct_kernel<true>, grid, block, 0, s, a);
-    else hipLaunchKernelGGL(dispatch_direct_kernel<false>, grid, block, 0, s, a);
+    if (route) {
+        const dim3 grid((unsigned)a.slices + 1);           // no workgroup without a share of the block
+        auto go = [&](auto nq) {
+            auto with = [&](auto copy) {
+                if (route->nparts > 1) hipLaunchKernelGGL((dispatch_direct_kernel<copy.value, nq.value, true>), grid, block, 0, s, a, *route);
+                else hipLaunchKernelGGL((dispatch_direct_kernel<copy.value, nq.value, false>), grid, block, 0, s, a, *route);
+            };
+            if (a.xpk) with(std::true_type{});
+            else with(std::false_type{});
+        };
+        const int nq = (route->E + 63) / 64;
+        if (nq <= 1) go(std::integral_constant<int, 1>{});
+        else if (nq <= 2) go(std::integral_constant<int, 2>{});
+        else if (nq <= 4) go(std::integral_constant<int, 4>{});
+        else go(std::integral_constant<int, 6>{});
+        return hipGetLastError();
+    }
+    if (a.xpk) hipLaunchKernelGGL(dispatch_direct_kernel<true>, grid, block, 0, s, a, RouteArgs{});
+    else hipLaunchKernelGGL(dispatch_direct_kernel<false>, grid, block, 0, s, a, RouteArgs{});
     return hipGetLastError();
 }
 

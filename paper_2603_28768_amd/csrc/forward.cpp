@@ -678,9 +678,10 @@ craft_status forward_on(const craft_plan_t *plan, int32_t layer, int32_t rank, c
     // same kernel when asked for, so route straight into them and alias the workspace views
     int32_t *ids_out = a->ids ? a->ids : ids;
     float *w_out = a->topk_w ? a->topk_w : w;
-    {
+    const RouteArgs ra{logits, a->T, E, a->k, a->renormalize ? 1 : 0, ids_out, w_out, lrank, hist, ctrl, nparts};
+    const bool routed = routed_dispatch(a->T, E, S);       // by the dispatch launch itself
+    if (!routed) {
         ScopedEvent ev(CRAFT_K_ROUTE, s);
-        RouteArgs ra{logits, a->T, E, a->k, a->renormalize ? 1 : 0, ids_out, w_out, lrank, hist, ctrl, nparts};
         if (launch_route(ra, s) != hipSuccess) return CRAFT_EHIP;
     }
     // 2 per-expert totals, slot offsets; 3 dispatch permutation (and, beside it, the tile tables of
@@ -697,7 +698,7 @@ craft_status forward_on(const craft_plan_t *plan, int32_t layer, int32_t rank, c
         ScopedEvent ev(CRAFT_K_DISPATCH, s);
         DirectDispatchArgs dd{da, craft_tables_layout(E, S), S, L.max_rows, counts, slot_cnt, slot_off, a->counts, a->slot_cnt,
                               a->slot_off, a->x, a->H, tiles.stream ? ws + L.xpk : nullptr, nullptr, 0, 0, 0, 0, false};
-        if (launch_dispatch_direct(dd, chunk_tot, s) != hipSuccess) return CRAFT_EHIP;
+        if (launch_dispatch_direct(dd, chunk_tot, routed ? &ra : nullptr, s) != hipSuccess) return CRAFT_EHIP;
     } else {
         {
             ScopedEvent ev(CRAFT_K_SCAN, s);

@@ -169,7 +169,9 @@ struct DirectDispatchArgs {
 bool direct_dispatch(int64_t T, int32_t E, int32_t S);
 bool small_dispatch(int64_t T, int32_t S);
 hipError_t launch_prefix(int32_t *hist, int32_t *chunk_tot, int32_t NB, int32_t E, hipStream_t s);
-hipError_t launch_dispatch_direct(DirectDispatchArgs a, const int32_t *chunk_tot, hipStream_t s);
+// route: a batch for which routed_dispatch holds is routed by the same launch; else null
+bool routed_dispatch(int64_t T, int32_t E, int32_t S);
+hipError_t launch_dispatch_direct(DirectDispatchArgs a, const int32_t *chunk_tot, const RouteArgs *route, hipStream_t s);
 
 struct FfnArgs {
     int32_t dtype;

@@ -670,6 +670,36 @@ def test_rank_with_more_slots_than_the_tile_tables_in_lds(torch_cuda):
     _check_rank(torch_cuda, case, 0, packed=False)
 
 
+@pytest.mark.parametrize("dtype,T,H,E,k,renorm", [
+    ("bf16", 1, 256, 8, 2, True),            # one token, one share of the columns
+    ("bf16", 31, 4096, 64, 6, False),        # one chunk of scores, sixteen shares; weights from all scores
+    ("bf16", 32, 520, 65, 4, True),          # scores read one by one
+    ("f32", 32, 64, 128, 20, True),          # no rows copied, picks in two places per lane
+    ("f32", 7, 100, 200, 8, False),
+    ("bf16", 32, 2048, 384, 64, True),       # most experts and most picks
+    ("bf16", 32, 256, 385, 8, True),         # more experts: routed by a launch of its own
+    ("bf16", 33, 256, 64, 8, True)])         # two blocks: the same
+def test_one_block_of_tokens_is_routed_by_the_dispatch(torch_cuda, dtype, T, H, E, k, renorm):
+    torch = torch_cuda
+    cfg = synth.scaled(synth.CONFIGS["qwen3"], dtype=dtype, T=T, H=H, I=64, E=E, k=k, D=3, replica_slots=3, zipf_s=1.0,
+                       profile_batches=2)
+    print("one block", cfg, renorm, flush=True)
+    case = Case(cfg)
+    fwd, x, logits = case.gpu_rank(case.heaviest, packed=dtype == "bf16")
+    fwd.args.renormalize = int(renorm)
+    ref = oracle.rank_forward(case.x, case.logits, k, case.slot_expert, case.rank_slot_off, case.heaviest, case.weights_of,
+                              renorm, None)
+    ids, w = binding.route_topk(logits, k, renormalize=renorm)      # the routing kernel's own
+    for _ in range(2):
+        out = fwd(x, logits)
+        torch.cuda.synchronize()
+        assert np.array_equal(_np(fwd.debug["ids"]), ref["ids"]) and torch.equal(fwd.debug["ids"], ids)
+        assert torch.equal(fwd.debug["topk_w"], w)
+        for name in ("dest", "src", "counts", "slot_cnt", "slot_off"):
+            assert np.array_equal(_np(fwd.debug[name]).reshape(-1), ref[name]), name
+        assert np.abs(_np(out).astype(np.float64) - ref["out"]).max() <= TOL[dtype] * np.abs(ref["out"]).max() + 1e-30
+
+
 @pytest.mark.parametrize("T", [90, 1100, 2100])       # few blocks, prefixes in front, scanned
 @pytest.mark.parametrize("slots", [1, 63, 64, 65])
 def test_tile_tables_of_a_wave_of_slots(torch_cuda, T, slots):
