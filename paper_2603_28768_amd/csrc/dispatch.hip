@@ -578,18 +578,11 @@ __global__ __launch_bounds__(kDirectThreads) void dispatch_direct_kernel(DirectD
 }  // namespace
 
 bool small_dispatch(int64_t T, int32_t S) { return T > 0 && T <= (int64_t)kSmallBlocks * kTokPerBlock && S <= kDirectSlots; }
-// Up to 16 chunks: every workgroup reads all of their totals.  But where one workgroup has little to
-// scan (one or two groups of 64 experts, up to a chunk of blocks between them) the scan and the plain
-// dispatch are sooner than a second launch in front of the direct kernel.  Together, scanned / direct,
-// us in a forward: E = 64 and 64 slots, T = 2048 9.0 / 11.1, 8192 11.3 / 13.0; E = 64 and 512 slots,
-// T = 4096 11.0 / 14.1; E = 128 and 144 slots, T = 2048 12.1 / 12.7, 8192 16.0 / 15.6; E = 128 and 800
-// slots, T = 2048 11.4 / 12.7; E = 192 even; E = 256, T = 2048 14.4 / 12.3.
-bool direct_dispatch(int64_t T, int32_t E, int32_t S) {
-    if (small_dispatch(T, S)) return true;
-    const int64_t groups = (E + 63) / 64, blocks = (T + kTokPerBlock - 1) / kTokPerBlock;
-    if (groups <= 2 && blocks * groups <= kScanChunk) return false;
-    return T > 0 && T <= 16ll * kDirectChunk * kTokPerBlock && S <= kDirectSlots;
-}
+// Up to 16 chunks: every workgroup reads all of their totals.  Few experts, where one workgroup has little
+// to scan, are no exception: a forward scanned / direct, us: E = 64, T = 2048 34.5 / 34.5, 4096 37.5 / 37.0,
+// 8192 41.5 / 41.4, with 512 slots 37.6 / 37.8; E = 100, T = 2048 36.9 / 35.9; E = 128, T = 2048 37.4 / 36.0,
+// with 800 slots 36.3 / 35.3, 8192 43.1 / 43.2; qwen3's layer, 1777 tokens 167.5 / 166.4, 4096 220.0 / 218.7.
+bool direct_dispatch(int64_t T, int32_t S) { return T > 0 && T <= 16ll * kDirectChunk * kTokPerBlock && S <= kDirectSlots; }
 
 hipError_t launch_prefix(int32_t *hist, int32_t *chunk_tot, int32_t NB, int32_t E, hipStream_t s) {
     if (NB <= kSmallBlocks) return hipSuccess;

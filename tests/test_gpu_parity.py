@@ -700,7 +700,7 @@ def test_one_block_of_tokens_is_routed_by_the_dispatch(torch_cuda, dtype, T, H, 
         assert np.abs(_np(out).astype(np.float64) - ref["out"]).max() <= TOL[dtype] * np.abs(ref["out"]).max() + 1e-30
 
 
-@pytest.mark.parametrize("T", [90, 1100, 2100])       # few blocks, prefixes in front, scanned
+@pytest.mark.parametrize("T", [90, 1100, 2100])       # few blocks; prefixes in front
 @pytest.mark.parametrize("slots", [1, 63, 64, 65])
 def test_tile_tables_of_a_wave_of_slots(torch_cuda, T, slots):
     # a slot per lane up to 64 of them; slots of equal rows and, with 90 tokens, without any
