@@ -10,6 +10,8 @@
 // large batches too, 8192 of H = 7168 233.5 / 231.6, 32768 783 / 780.
 #include <hip/hip_bf16.h>
 
+#include <algorithm>
+
 #include "kernels.h"
 
 namespace craft {
@@ -53,14 +55,14 @@ template <> struct Chunk<__hip_bfloat16> {
 };
 
 // A wave takes 64 U chunks of one token's row, one request round; the `parts` waves of a row sit in
-// neighbouring workgroups.
+// neighbouring workgroups.  `first`: the launch's first token.
 constexpr int U = 2;
 template <typename T>
-__global__ __launch_bounds__(256) void combine_kernel(CombineArgs a, uint32_t parts) {
+__global__ __launch_bounds__(256) void combine_kernel(CombineArgs a, uint32_t parts, int64_t first) {
     constexpr int N = Chunk<T>::N;
     const int lane = threadIdx.x & 63;
     const uint32_t tokens = blockIdx.x / parts, part = blockIdx.x - tokens * parts;
-    const int64_t t = (int64_t)tokens * 4 + (threadIdx.x >> 6);
+    const int64_t t = first + (int64_t)tokens * 4 + (threadIdx.x >> 6);
     if (t >= a.T) return;
     const int32_t lo = a.slot_off[a.s_lo], hi = a.slot_off[a.s_hi];
     const bool dead = a.ctrl[CTRL_OVERFLOW] != 0;
@@ -140,8 +142,13 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a, uint32_t pa
 
 template <typename T>
 void launch_rows(const CombineArgs &a, hipStream_t s) {
-    const uint32_t parts = (uint32_t)((a.H + 64 * Chunk<T>::N * U - 1) / (64 * Chunk<T>::N * U));
-    hipLaunchKernelGGL(combine_kernel<T>, dim3((unsigned)((a.T + 3) / 4) * parts), dim3(256), 0, s, a, parts);
+    constexpr int64_t kRow = 64 * Chunk<T>::N * U;
+    const int64_t parts = (a.H + kRow - 1) / kRow, groups = (a.T + 3) / 4;
+    // a launch has fewer than 2^32 threads (of one with more only the remainder runs, without an error)
+    const int64_t most = std::max<int64_t>(1, (1ll << 31) / 256 / parts);
+    for (int64_t g = 0; g < groups; g += most)
+        hipLaunchKernelGGL(combine_kernel<T>, dim3((unsigned)(std::min(most, groups - g) * parts)), dim3(256), 0, s, a,
+                           (uint32_t)parts, g * 4);
 }
 
 }  // namespace

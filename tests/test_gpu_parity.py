@@ -722,6 +722,39 @@ def test_combine_of_rows_in_pieces(torch_cuda, dtype, H):
         _check_rank(torch, case, rank)
 
 
+def test_combine_in_several_launches(torch_cuda):
+    # narrow rows, more tokens than the threads of one launch hold: every row of the result against a plain
+    # fp32 product
+    torch = torch_cuda
+    T, H, I, E = (1 << 26) + 5, 8, 16, 4
+    print("combine in launches", T, H, flush=True)
+    plan = binding.Plan(np.full((1, 1, E), 8, dtype=np.int64), E, 0)
+    lay = plan.layer(0)
+    e = int(lay["slot_expert"][lay["rank_slot_off"][1]])
+    g = torch.Generator(device="cuda:0").manual_seed(6)
+    x = torch.empty((T, H), device="cuda:0", dtype=torch.bfloat16)
+    for part in x.view(-1).split(1 << 26):
+        part.copy_(torch.randn(part.numel(), generator=g, device="cuda:0"))
+    w = [torch.randn(s, generator=g, device="cuda:0").bfloat16() * 0.5 for s in ((I, H), (I, H), (H, I))]
+    picked = torch.randint(0, E, (T,), generator=g, device="cuda:0")
+    logits = torch.zeros((T, E), device="cuda:0")
+    logits.scatter_(1, picked[:, None], 4.0)
+    rows = int((picked == e).sum())
+    fwd = binding.RankForward(plan, 0, 1, "bf16", T, H, I, 1, [w[0]], [w[1]], [w[2]], max_rows=rows)
+    fwd.out.fill_(float("nan"))
+    out = fwd(x, logits)
+    assert fwd.result() == (rows, 0)
+    biggest, worst = 0.0, 0.0
+    for t0 in range(0, T, 1 << 24):
+        t1 = min(T, t0 + (1 << 24))
+        xs = x[t0:t1].float()
+        act = (torch.nn.functional.silu(xs @ w[0].float().t()) * (xs @ w[1].float().t())).bfloat16().float()
+        ref = (act @ w[2].float().t()) * (picked[t0:t1] == e)[:, None]
+        worst = max(worst, float((out[t0:t1].float() - ref).abs().nan_to_num(float("inf")).max()))
+        biggest = max(biggest, float(ref.abs().max()))
+    assert worst <= TOL["bf16"] * biggest
+
+
 @pytest.mark.parametrize("T,E,k,D,slots", [
     # prefixes over chunks of 128 blocks, every workgroup derives the slots
     (3000, 160, 4, 4, 6),        # one chunk, three expert groups, a short last block

@@ -1,0 +1,124 @@
+"""What a forward launches, recorded in place of the launches: no device work.
+
+The library is loaded in a process of its own, behind a recorder that takes the place of the few HIP
+calls a forward makes."""
+import ctypes
+import json
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+RECORDER = r"""
+#include <stddef.h>
+#include <stdio.h>
+#include <string.h>
+typedef struct { unsigned x, y, z; } grid_t;
+static struct { const void *host; const char *name; } known[512];
+static struct { const char *name; unsigned long long groups, threads; } seen[256];
+static int n_known, n_seen;
+static grid_t grid, block;
+void **__hipRegisterFatBinary(void *b) { (void)b; static void *m; return &m; }
+void __hipUnregisterFatBinary(void **m) { (void)m; }
+void __hipRegisterVar(void **m, void *v, char *h, char *d, int e, size_t n, int c, int g) { (void)m; (void)v; (void)h; (void)d; (void)e; (void)n; (void)c; (void)g; }
+void __hipRegisterFunction(void **m, const void *f, char *d, const char *name, unsigned t, void *a, void *b, void *c, void *e, int *w) {
+    (void)m; (void)d; (void)t; (void)a; (void)b; (void)c; (void)e; (void)w;
+    known[n_known].host = f; known[n_known++].name = name;
+}
+int __hipPushCallConfiguration(grid_t g, grid_t b, size_t l, void *s) { (void)l; (void)s; grid = g; block = b; return 0; }
+int __hipPopCallConfiguration(grid_t *g, grid_t *b, size_t *l, void **s) { *g = grid; *b = block; *l = 0; *s = 0; return 0; }
+int hipLaunchKernel(const void *f, grid_t g, grid_t b, void **args, size_t l, void *s) {
+    (void)args; (void)l; (void)s;
+    const char *name = "?";
+    for (int i = 0; i < n_known; ++i) if (known[i].host == f) name = known[i].name;
+    if (n_seen < 256) {
+        seen[n_seen].name = name;
+        seen[n_seen].groups = (unsigned long long)g.x * g.y * g.z;
+        seen[n_seen++].threads = (unsigned long long)b.x * b.y * b.z;
+    }
+    return 0;
+}
+int hipGetLastError(void) { return 0; }
+int hipGetDevice(int *d) { *d = 0; return 0; }
+int hipGetDevicePropertiesR0600(void *p, int d) { (void)p; (void)d; return 1; }
+int hipMemcpyAsync(void *d, const void *s, size_t n, int k, void *q) { (void)d; (void)s; (void)n; (void)k; (void)q; return 0; }
+int recorded(void) { return n_seen; }
+const char *recorded_name(int i) { return seen[i].name; }
+unsigned long long recorded_groups(int i) { return seen[i].groups; }
+unsigned long long recorded_threads(int i) { return seen[i].threads; }
+void recorded_clear(void) { n_seen = 0; }
+"""
+
+
+def record(recorder_path, cases):
+    """The launches of each case's forward, [name, workgroups, threads of one]; runs in the child process."""
+    import numpy as np
+    import torch  # noqa: F401    (its own HIP calls are bound before the recorder comes)
+    sys.path.insert(0, os.path.dirname(HERE))
+    from paper_2603_28768_amd import binding
+    rec = ctypes.CDLL(recorder_path, mode=ctypes.RTLD_GLOBAL)
+    rec.recorded_name.restype = ctypes.c_char_p
+    rec.recorded_groups.restype = rec.recorded_threads.restype = ctypes.c_uint64
+    lib = binding.lib()
+    out = []
+    for c in cases:
+        D, E, k = c.get("D", 1), c["E"], c["k"]
+        plan = binding.Plan(np.arange(E, 2 * E, dtype=np.int64)[None, None], D, c.get("replicas", 0))
+        a = binding.FwdArgs()
+        a.dtype = binding.CRAFT_BF16 if c["dtype"] == "bf16" else binding.CRAFT_F32
+        a.T, a.H, a.I, a.k, a.renormalize, a.max_rows = c["T"], c["H"], c["I"], k, 1, c.get("max_rows", 0)
+        somewhere = 1 << 40                        # aligned, not null, never read
+        a.x = a.out = a.w_gate = a.w_up = a.w_down = a.workspace = a.tables = somewhere
+        if c.get("gate"):
+            a.w_router = somewhere
+        else:
+            a.logits = somewhere
+        if c.get("packed"):
+            a.w_gateup_packed = a.w_down_packed = somewhere
+            a.tile_rows_gateup = c.get("tile_rows", 0)
+        n = ctypes.c_size_t()
+        assert lib.craft_plan_tables_bytes(plan._h, 0, 0, ctypes.byref(n)) == 0
+        assert lib.craft_plan_tables_upload(plan._h, 0, 0, ctypes.c_void_p(somewhere), n.value, None) == 0
+        assert lib.craft_moe_rank_forward_workspace(plan._h, 0, 0, ctypes.byref(a), ctypes.byref(n)) == 0
+        a.workspace_bytes = n.value
+        rec.recorded_clear()
+        assert lib.craft_moe_rank_forward(plan._h, 0, 0, ctypes.byref(a), None) == 0
+        out.append([[rec.recorded_name(i).decode(), rec.recorded_groups(i), rec.recorded_threads(i)]
+                    for i in range(rec.recorded())])
+    return out
+
+
+@pytest.fixture(scope="module")
+def launches_of(tmp_path_factory):
+    where = tmp_path_factory.mktemp("recorder")
+    source, so = str(where / "recorder.c"), str(where / "librecorder.so")
+    with open(source, "w") as f:
+        f.write(RECORDER)
+    subprocess.check_call(["gcc", "-O1", "-fPIC", "-shared", source, "-o", so])
+
+    def ask(*cases):
+        res = subprocess.run([sys.executable, os.path.abspath(__file__), so, json.dumps(cases)],
+                             capture_output=True, text=True, timeout=600)
+        assert res.returncode == 0, (res.stdout + res.stderr)[-3000:]
+        return json.loads(res.stdout.splitlines()[-1])
+    return ask
+
+
+def test_combine_reaches_every_row_of_a_very_large_batch(launches_of):
+    # a launch has fewer than 2^32 threads: of one with more only the remainder would run.  Rows of one and
+    # of several pieces on both sides of that, and few rows of very many pieces
+    shapes = [("bf16", (1 << 25) - 4, 1024, 1), ("bf16", 1 << 25, 1032, 2), ("f32", 1 << 25, 516, 2), ("bf16", 1 << 24, 4096, 4),
+              ("bf16", (1 << 26) + 5, 8, 1), ("bf16", 1024, 1 << 26, 1 << 16), ("bf16", 4096, 7168, 7)]
+    found = launches_of(*[dict(dtype=dt, T=T, H=H, I=8, E=2, k=1, D=2, max_rows=64) for dt, T, H, _ in shapes])
+    for (dt, T, H, pieces), launches in zip(shapes, found):
+        combine = [l for l in launches if "combine" in l[0]]
+        assert all(groups * threads < 1 << 32 for _, groups, threads in launches), (dt, T, H, launches)
+        assert all(threads == 256 for _, _, threads in combine)
+        assert sum(groups for _, groups, _ in combine) == (T + 3) // 4 * pieces, (dt, T, H, combine)
+
+
+if __name__ == "__main__":
+    print(json.dumps(record(sys.argv[1], json.loads(sys.argv[2]))))
