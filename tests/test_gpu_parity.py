@@ -785,6 +785,18 @@ def test_dispatch_over_block_and_expert_shapes(torch_cuda, T, E, k, D, slots):
         _check_rank(torch_cuda, case, g, tokens=toks, packed=True)
 
 
+@pytest.mark.parametrize("T,E", [(64, 72), (96, 600), (128, 130), (160, 72), (225, 40), (256, 520), (290, 72), (420, 72), (1000, 72),
+                                 (32768, 72), (41000, 40), (53000, 72), (65536, 72)])
+def test_dispatch_over_numbers_of_totals(torch_cuda, T, E):
+    # counts of 2 to 32 blocks, or of 8 to 16 chunks of blocks, added in eights, a four and single ones;
+    # fewer and more experts than threads
+    cfg = synth.scaled(synth.CONFIGS["qwen3"], T=T, H=64, I=32, E=E, k=3, D=2, replica_slots=3, zipf_s=1.0, profile_batches=1)
+    print("numbers of totals", cfg, flush=True)
+    case = Case(cfg)
+    for g in (0, 1):
+        _check_rank(torch_cuda, case, g, tokens=list(range(0, T, max(1, T // 16))), packed=True)
+
+
 @pytest.mark.parametrize("T,E,k,D,slots", [
     (3000, 1024, 2, 64, 1100),   # a wave per group of experts
     (8192, 130, 2, 64, 2000),    # three groups, the whole chunk
