@@ -589,11 +589,17 @@ __global__ __launch_bounds__(kDirectThreads) void dispatch_direct_kernel(DirectD
 }  // namespace
 
 bool small_dispatch(int64_t T, int32_t S) { return T > 0 && T <= (int64_t)kSmallBlocks * kTokPerBlock && S <= kDirectSlots; }
-// Up to 16 chunks: every workgroup reads all of their totals.  Few experts, where one workgroup has little
-// to scan, are no exception: a forward scanned / direct, us: E = 64, T = 2048 34.5 / 34.5, 4096 37.5 / 37.0,
-// 8192 41.5 / 41.4, with 512 slots 37.6 / 37.8; E = 100, T = 2048 36.9 / 35.9; E = 128, T = 2048 37.4 / 36.0,
-// with 800 slots 36.3 / 35.3, 8192 43.1 / 43.2; qwen3's layer, 1777 tokens 167.5 / 166.4, 4096 220.0 / 218.7.
-bool direct_dispatch(int64_t T, int32_t S) { return T > 0 && T <= 16ll * kDirectChunk * kTokPerBlock && S <= kDirectSlots; }
+// Up to 16 chunks: every workgroup reads all of their totals.  But every workgroup also goes over all the
+// slots, 512 at a time, and where a single workgroup scans a batch quickly (one group of experts, one chunk
+// of blocks) four such passes in each are the dearer way.  A forward scanned / direct, us (mean of both
+// orders on one machine): E = 64, 1537 slots, T = 2048 27.5 / 28.1, 8192 38.0 / 39.2; 2044 slots, 4096 28.5 /
+// 29.3; 1536 slots, 2048 27.2 / 27.3, 4096 27.7 / 27.9; 513 slots, 2048 24.6 / 24.7; 512 slots, 2048 24.4 /
+// 23.8; 72 slots, 2048 33.3 / 32.9; E = 96, 1996 slots, 2048 29.9 / 29.4.
+bool direct_dispatch(int64_t T, int32_t E, int32_t S) {
+    if (small_dispatch(T, S)) return true;
+    if (E <= 64 && S > 3 * kDirectThreads && T <= (int64_t)kScanChunk * kTokPerBlock) return false;
+    return T > 0 && T <= 16ll * kDirectChunk * kTokPerBlock && S <= kDirectSlots;
+}
 
 hipError_t launch_prefix(int32_t *hist, int32_t *chunk_tot, int32_t NB, int32_t E, hipStream_t s) {
     if (NB <= kSmallBlocks) return hipSuccess;

@@ -690,7 +690,7 @@ craft_status forward_on(const craft_plan_t *plan, int32_t layer, int32_t rank, c
                     a->dest, a->src, slot_cnt, s_lo, s_hi, tiles.frags[0], tiles.frags[1],
                     tiles.riders[0] ? (a->I + 127) / 128 : 0, tiles.riders[1] ? (a->H + 255) / 256 : 0,
                     mt_start, order, ctrl};
-    if (direct_dispatch(a->T, S)) {
+    if (direct_dispatch(a->T, E, S)) {
         if (L.NB > kSmallBlocks) {
             ScopedEvent ev(CRAFT_K_SCAN, s);
             if (launch_prefix(hist, chunk_tot, (int32_t)L.NB, E, s) != hipSuccess) return CRAFT_EHIP;

@@ -166,7 +166,7 @@ struct DirectDispatchArgs {
     int32_t ntot, chunk_blocks, slices, span;
     bool local;               // the blocks' prefixes inside their chunk come on top
 };
-bool direct_dispatch(int64_t T, int32_t S);
+bool direct_dispatch(int64_t T, int32_t E, int32_t S);
 bool small_dispatch(int64_t T, int32_t S);
 hipError_t launch_prefix(int32_t *hist, int32_t *chunk_tot, int32_t NB, int32_t E, hipStream_t s);
 // route: a batch for which routed_dispatch holds is routed by the same launch; else null

@@ -67,6 +67,7 @@ def record(recorder_path, cases):
     for c in cases:
         D, E, k = c.get("D", 1), c["E"], c["k"]
         plan = binding.Plan(np.arange(E, 2 * E, dtype=np.int64)[None, None], D, c.get("replicas", 0))
+        assert plan.layer(0)["n_slots"] == E + c.get("replicas", 0)
         a = binding.FwdArgs()
         a.dtype = binding.CRAFT_BF16 if c["dtype"] == "bf16" else binding.CRAFT_F32
         a.T, a.H, a.I, a.k, a.renormalize, a.max_rows = c["T"], c["H"], c["I"], k, 1, c.get("max_rows", 0)
@@ -118,6 +119,25 @@ def test_combine_reaches_every_row_of_a_very_large_batch(launches_of):
         assert all(groups * threads < 1 << 32 for _, groups, threads in launches), (dt, T, H, launches)
         assert all(threads == 256 for _, _, threads in combine)
         assert sum(groups for _, groups, _ in combine) == (T + 3) // 4 * pieces, (dt, T, H, combine)
+
+
+DIRECT, SCAN = ["prefix_kernel", "dispatch_direct_kernel"], ["scan_kernel", "dispatch_kernel"]
+
+
+INDICES = [
+    (1024, 64, 2048, ["dispatch_direct_kernel"]), (1024, 64, 2049, SCAN),      # from the blocks' counts alone
+    (1025, 64, 72, DIRECT), (8192, 100, 104, DIRECT), (65536, 40, 48, DIRECT), (65537, 40, 48, SCAN),
+    (65536, 64, 2048, DIRECT), (65536, 64, 2049, SCAN),
+    # one group of experts and more than three passes over the slots: scanned by a single workgroup
+    (1025, 64, 1537, SCAN), (8192, 64, 2048, SCAN), (4096, 33, 2048, SCAN),
+    (8192, 64, 1536, DIRECT), (8193, 64, 1537, DIRECT), (4096, 65, 2048, DIRECT)]
+
+
+def test_which_launches_make_the_dispatch_indices(launches_of):
+    found = launches_of(*[dict(dtype="f32", T=T, H=64, I=32, E=E, k=2, D=64, replicas=slots - E) for T, E, slots, _ in INDICES])
+    for (T, E, slots, indices), launches in zip(INDICES, found):
+        names = [l[0] for l in launches if any(w in l[0] for w in ("prefix", "scan", "dispatch"))]
+        assert len(names) == len(indices) and all(i in n for i, n in zip(indices, names)), (T, E, slots, names)
 
 
 if __name__ == "__main__":
