@@ -279,6 +279,7 @@ def test_forward_with_its_own_gating_network(torch_cuda, dtype, T, H, I, E, k, D
         assert err <= TOL[dtype] * np.abs(ref["out"]).max() + 1e-30
 
 
+@pytest.mark.parametrize("tiled", [False, True])        # token rows copied by a small batch's dispatch, or not
 @pytest.mark.parametrize("T,H,E,k,renorm", [
     (8, 7168, 256, 8, True),         # the most parts, in one trip
     (40, 4096, 128, 8, False),       # the parts are read a second time for the weights
@@ -286,9 +287,15 @@ def test_forward_with_its_own_gating_network(torch_cuda, dtype, T, H, I, E, k, D
     (128, 2056, 100, 5, False),      # two chunks of 64 scores, ragged slab
     (300, 2048, 384, 8, True),       # several trips of three parts
     (129, 1024, 300, 14, False),     # several trips, arg-max rounds
-    (60, 1024, 66, 1, True)])
-def test_forward_adds_up_the_parts_of_a_split_gate(torch_cuda, T, H, E, k, renorm):
-    # the routing kernel adds the partial scores in the order the gate's own sum has: the same bits as
+    (60, 1024, 66, 1, True),
+    # up to 32 tokens: by the dispatch launch itself
+    (1, 1024, 64, 8, True), (32, 2048, 64, 20, False),       # up to 64 experts; picks in two places per lane
+    (32, 4096, 128, 8, False), (9, 1024, 100, 4, True),      # up to 128
+    (32, 1024, 130, 6, True), (32, 7168, 256, 8, False),     # up to 256; scores read one by one
+    (32, 4096, 384, 8, True), (31, 2048, 383, 20, False)])   # up to 384: several trips of three parts
+def test_forward_adds_up_the_parts_of_a_split_gate(torch_cuda, T, H, E, k, renorm, tiled):
+    # the partial scores are added in the order the gate's own sum has, by the routing kernel or, up to 32
+    # tokens, by the dispatch: the same bits as
     # the stand-alone scores handed in, and decisions and output as the checker takes them on those
     torch = torch_cuda
     cfg = synth.scaled(synth.CONFIGS["qwen3"], T=T, H=H, I=64, E=E, k=k, D=32, replica_slots=2, zipf_s=1.0, profile_batches=2)
@@ -299,6 +306,11 @@ def test_forward_adds_up_the_parts_of_a_split_gate(torch_cuda, T, H, E, k, renor
     own, x, _ = case.gpu_rank(case.heaviest, packed=True, w_router=Wrd)
     given, _, _ = case.gpu_rank(case.heaviest, packed=True)
     own.args.renormalize = given.args.renormalize = int(renorm)
+    if tiled:                                                           # the caller's own tile heights: never streamed
+        own.args.tile_rows_gateup = given.args.tile_rows_gateup = 128
+        assert own.tile_choice()[0] == 128
+    elif T <= 32:
+        assert own.tile_choice() == (64, 64, 0, 0)
     ws = binding.router_logits_workspace(x, Wrd)
     assert ws is not None and ws.numel() >= 2 * T * E * 4               # split
     logits = binding.router_logits(x, Wrd, ws)
@@ -764,15 +776,16 @@ def test_combine_in_several_launches(torch_cuda):
     (8200, 72, 4, 2, 5),         # a third chunk of one block, ragged group
     (20000, 200, 3, 4, 9),       # five chunks of four groups, two blocks to a workgroup
     (1024, 40, 2, 2, 3),         # the largest batch dispatched from the blocks' counts alone
-    (8193, 64, 2, 2, 3),         # one group, the smallest batch that is not scanned
+    (1025, 40, 2, 2, 3),         # the smallest with prefixes in front, ragged group
+    (4096, 128, 8, 8, 16),       # two groups, one whole chunk
+    (8192, 64, 3, 4, 20),        # one group, two whole chunks
+    (8193, 64, 2, 2, 3),         # one group, a third chunk of one token
     (16385, 48, 2, 2, 3),        # two blocks to a workgroup, the last one alone
-    # the scan, by a single workgroup
-    (1025, 40, 2, 2, 3),         # the smallest batch, ragged group
-    (8192, 64, 3, 4, 20),        # one group, the whole chunk
-    (4096, 128, 8, 8, 16),       # two groups, half a chunk: the largest batch of two
+    (65536, 48, 1, 2, 3),        # the most chunks that a workgroup reads
     # the scan, by one workgroup per chunk and group
-    (65600, 16, 1, 2, 2),        # more chunks than a dispatch workgroup reads: nine of one group
-    (66000, 200, 3, 4, 9)])      # nine of four groups
+    (65537, 48, 1, 2, 3),        # the smallest such batch: nine chunks of one ragged group, one token in the last
+    (65600, 16, 1, 2, 2),        # three blocks in the last
+    (66000, 200, 3, 4, 9)])      # four groups
 def test_dispatch_over_block_and_expert_shapes(torch_cuda, T, E, k, D, slots):
     # how the per-block counts are dealt to the waves depends on the number of 32-token blocks
     # and of 64-expert groups: integer results against the checker on every rank, narrow FFN
@@ -798,16 +811,22 @@ def test_dispatch_over_numbers_of_totals(torch_cuda, T, E):
 
 
 @pytest.mark.parametrize("T,E,k,D,slots", [
+    # more than a workgroup of the direct dispatch keeps: scanned, whatever the batch
     (3000, 1024, 2, 64, 1100),   # a wave per group of experts
     (8192, 130, 2, 64, 2000),    # three groups, the whole chunk
-    (9000, 1024, 2, 64, 1100)])  # one workgroup per chunk and group, a ragged second chunk
+    (9000, 1024, 2, 64, 1100),   # one workgroup per chunk and group, a ragged second chunk
+    (300, 64, 2, 64, 2000),      # one whole group, few blocks
+    (2000, 100, 2, 64, 2000),    # two groups, the second one ragged
+    # one group of experts and more than 1536: scanned by a single workgroup
+    (1025, 64, 2, 64, 1500),     # the smallest such batch
+    (8192, 40, 3, 64, 1600)])    # the largest, ragged group
 def test_dispatch_of_more_slots_than_a_workgroup_keeps(torch_cuda, T, E, k, D, slots):
-    # scanned, whatever the batch; the plan is the library's (its checker is slow at so many replicas)
+    # the plan is the library's (its checker is slow at so many replicas)
     cfg = synth.scaled(synth.CONFIGS["qwen3"], T=T, H=64, I=32, E=E, k=k, D=D, replica_slots=slots, zipf_s=1.0)
     pop = synth.layer_popularity(cfg, 0)
     plan = binding.Plan(np.maximum(1, pop * 1e6).astype(np.int64)[None, None], D, slots)
     case = Case(cfg, plan=plan, pop=pop)
-    assert len(case.slot_expert) > 2048
+    assert len(case.slot_expert) > (2048 if E > 64 or T <= 1024 else 1536)
     for g in (0, D - 1):
         _check_rank(torch_cuda, case, g, tokens=list(range(0, T, T // 16)), packed=True)
 

@@ -140,5 +140,34 @@ def test_which_launches_make_the_dispatch_indices(launches_of):
         assert len(names) == len(indices) and all(i in n for i, n in zip(indices, names)), (T, E, slots, names)
 
 
+# dtype, tokens, experts, gate, the caller's own tile heights -> instance of the routing dispatch: rows
+# copied, 64-expert groups up to, parts added; None: routed by a launch of its own
+ROUTED = [
+    ("bf16", 1, 8, False, False, (1, 1, 0)), ("bf16", 32, 64, True, False, (1, 1, 1)), ("bf16", 32, 65, False, True, (0, 2, 0)),
+    ("bf16", 32, 128, True, True, (0, 2, 1)), ("bf16", 8, 129, True, False, (1, 4, 1)), ("bf16", 32, 256, False, False, (1, 4, 0)),
+    ("bf16", 32, 257, True, True, (0, 6, 1)), ("bf16", 32, 384, True, False, (1, 6, 1)), ("f32", 32, 384, False, False, (0, 6, 0)),
+    ("f32", 32, 64, True, False, (0, 1, 0)),               # a gate that is not split
+    ("bf16", 33, 64, True, False, None), ("bf16", 32, 385, False, False, None), ("bf16", 32, 512, True, False, None)]
+
+
+def test_which_batches_are_routed_by_the_dispatch(launches_of):
+    found = launches_of(*[dict(dtype=dt, T=T, H=2048, I=64, E=E, k=4, D=min(E, 32), gate=gate, packed=dt == "bf16",
+                               tile_rows=128 if tiled else 0) for dt, T, E, gate, tiled, _ in ROUTED])
+    for (dt, T, E, gate, tiled, instance), launches in zip(ROUTED, found):
+        names = [l[0] for l in launches]
+        routed = [n for n in names if "12route_kernel" in n]
+        dispatch, = [n for n in names if "dispatch_direct_kernel" in n]
+        assert len(routed) == (instance is None), names
+        if instance is not None:
+            assert "Lb%dELi%dELb%dE" % instance in dispatch, (dt, T, E, gate, tiled, dispatch)
+        else:
+            assert "Li0E" in dispatch
+
+
+def test_a_batch_of_more_than_2048_slots_is_routed_by_a_launch_of_its_own(launches_of):
+    many, few = launches_of(*[dict(dtype="f32", T=32, H=64, I=32, E=64, k=4, D=64, replicas=r) for r in (1985, 1984)])
+    assert any("12route_kernel" in l[0] for l in many) and not any("12route_kernel" in l[0] for l in few)
+
+
 if __name__ == "__main__":
     print(json.dumps(record(sys.argv[1], json.loads(sys.argv[2]))))
