@@ -1,13 +1,13 @@
 // Gather-weighted combine: the last step of the MoE layer of Sec. 2.1, each token's sum of
-// its experts' outputs scaled by the routing weights.  A 64-lane wavefront takes a piece of a token's row, 2 KiB; a lane owns
+// its experts' outputs scaled by the routing weights.  A 64-lane wavefront takes a piece of a token's row, 2 or 3 KiB; a lane owns
 // 16-byte column chunks of it.  Only assignments whose dispatched position falls inside this rank's row range
 // contribute, added in ascending j with fp32 accumulation; there are no atomics, so the
 // result does not depend on scheduling.  Tokens with no assignment on the rank get zeros.
 //
 // A large batch is bound by HBM (mostly zero rows to write), a small one by its chain of round trips on
-// the few CUs that have a wave.  With whole rows per wave (8 KiB a round) a forward took, us, whole / in
-// pieces: 8 tokens of H = 7168 53.1 / 51.3, 250 46.6 / 44.4, 64 of H = 4096 66.4 / 65.2, 1024 151.4 / 150.8;
-// large batches too, 8192 of H = 7168 233.5 / 231.6, 32768 783 / 780.
+// the few CUs that have a wave.  A forward (bf16, E = 64, k = 4, I = 64, one of eight ranks) with whole rows
+// per wave (8 KiB a round) / in pieces, us: H = 7168, 40 tokens 28.5 / 25.9, 256 40.8 / 37.7, 1024 100.6 / 99.2,
+// 8192 141.6 / 139.9; H = 1024, 4096 tokens 47.6 / 45.7, 32768 96.7 / 80.4; H = 4096, 8192 tokens the same.
 #include <hip/hip_bf16.h>
 
 #include <algorithm>
@@ -56,8 +56,7 @@ template <> struct Chunk<__hip_bfloat16> {
 
 // A wave takes 64 U chunks of one token's row, one request round; the `parts` waves of a row sit in
 // neighbouring workgroups.  `first`: the launch's first token.
-constexpr int U = 2;
-template <typename T>
+template <typename T, int U>
 __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a, uint32_t parts, int64_t first) {
     constexpr int N = Chunk<T>::N;
     const int lane = threadIdx.x & 63;
@@ -86,8 +85,9 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a, uint32_t pa
     float acc[U][N];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        c0[u] = ((int)part * U * 64 + u * 64 + lane) * N;
-        inside[u] = c0[u] < a.H;
+        const int chunk = (int)part * U * 64 + u * 64 + lane;
+        inside[u] = chunk < a.H / N;
+        c0[u] = chunk * N;
 #pragma unroll
         for (int i = 0; i < N; ++i) acc[u][i] = 0.0f;
     }
@@ -140,15 +140,29 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a, uint32_t pa
         }
 }
 
-template <typename T>
-void launch_rows(const CombineArgs &a, hipStream_t s) {
+template <typename T, int U>
+void launch_pieces(const CombineArgs &a, hipStream_t s) {
     constexpr int64_t kRow = 64 * Chunk<T>::N * U;
     const int64_t parts = (a.H + kRow - 1) / kRow, groups = (a.T + 3) / 4;
     // a launch has fewer than 2^32 threads (of one with more only the remainder runs, without an error)
     const int64_t most = std::max<int64_t>(1, (1ll << 31) / 256 / parts);
     for (int64_t g = 0; g < groups; g += most)
-        hipLaunchKernelGGL(combine_kernel<T>, dim3((unsigned)(std::min(most, groups - g) * parts)), dim3(256), 0, s, a,
+        hipLaunchKernelGGL((combine_kernel<T, U>), dim3((unsigned)(std::min(most, groups - g) * parts)), dim3(256), 0, s, a,
                            (uint32_t)parts, g * 4);
+}
+
+// Pieces of 2 KiB, or of 3 KiB where the last one of 2 would be a wave for little: a row of 2 to 2.5 KiB,
+// and in a large batch, bound by what its waves write, a row of more than three pieces whose last one is
+// not full, unless pieces of 3 KiB leave yet more lanes idle (by more than a request of one wave).  The
+// forward above, pieces of 2 / 3 KiB, us: H = 1032, 64 tokens 19.4 / 19.2, 1024 42.5 / 40.1, 32768 99.0 / 91.0;
+// H = 3080, 4096 tokens 87.4 / 84.8, 32768 182.5 / 169.9 (whole rows 174.3); H = 3592, 16384 140.7 / 136.1 (136.8);
+// H = 7176, 16384 247.9 / 243.3 (244.3).  Not H = 2056, 32768 tokens 130.9 / 134.5, H = 4616, 16384 166.4 / 170.5,
+// nor few tokens: H = 3080, 8 tokens 18.1 / 18.3, 2048 77.3 / 78.3.
+template <typename T>
+void launch_rows(const CombineArgs &a, hipStream_t s) {
+    const int64_t chunks = a.H / Chunk<T>::N, two = (chunks + 127) / 128 * 128, three = (chunks + 191) / 192 * 192;
+    if ((chunks > 128 && chunks <= 160) || (a.T >= 4096 && chunks > 384 && chunks < two && three <= two + 64)) launch_pieces<T, 3>(a, s);
+    else launch_pieces<T, 2>(a, s);
 }
 
 }  // namespace

@@ -734,6 +734,19 @@ def test_combine_of_rows_in_pieces(torch_cuda, dtype, H):
         _check_rank(torch, case, rank)
 
 
+@pytest.mark.parametrize("dtype,T,H", [("bf16", 41, 1280), ("bf16", 41, 1288), ("f32", 41, 640), ("f32", 41, 644), ("bf16", 4097, 3080),
+                                       ("bf16", 4097, 4608), ("bf16", 4097, 5128), ("f32", 4097, 1540)])
+def test_combine_of_rows_in_longer_pieces(torch_cuda, dtype, T, H):
+    # pieces of 1536 columns (fp32: 768): rows of one, three and four of them, whole and not, and a row too
+    # long for one
+    cfg = synth.scaled(synth.CONFIGS["qwen3"], dtype=dtype, T=T, H=H, I=40, E=12, k=6, D=2, replica_slots=1,
+                       zipf_s=0.8, profile_batches=2)
+    case = Case(cfg)
+    toks = sorted(set(range(0, T, max(1, T // 40))) | {T - 1})
+    for rank in range(2):
+        _check_rank(torch_cuda, case, rank, tokens=toks)
+
+
 def test_combine_in_several_launches(torch_cuda):
     # narrow rows, more tokens than the threads of one launch hold: every row of the result against a plain
     # fp32 product

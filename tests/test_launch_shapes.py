@@ -111,7 +111,7 @@ def launches_of(tmp_path_factory):
 def test_combine_reaches_every_row_of_a_very_large_batch(launches_of):
     # a launch has fewer than 2^32 threads: of one with more only the remainder would run.  Rows of one and
     # of several pieces on both sides of that, and few rows of very many pieces
-    shapes = [("bf16", (1 << 25) - 4, 1024, 1), ("bf16", 1 << 25, 1032, 2), ("f32", 1 << 25, 516, 2), ("bf16", 1 << 24, 4096, 4),
+    shapes = [("bf16", (1 << 25) - 4, 1024, 1), ("bf16", 1 << 25, 1288, 2), ("f32", 1 << 25, 644, 2), ("bf16", 1 << 24, 4096, 4),
               ("bf16", (1 << 26) + 5, 8, 1), ("bf16", 1024, 1 << 26, 1 << 16), ("bf16", 4096, 7168, 7)]
     found = launches_of(*[dict(dtype=dt, T=T, H=H, I=8, E=2, k=1, D=2, max_rows=64) for dt, T, H, _ in shapes])
     for (dt, T, H, pieces), launches in zip(shapes, found):
@@ -119,6 +119,17 @@ def test_combine_reaches_every_row_of_a_very_large_batch(launches_of):
         assert all(groups * threads < 1 << 32 for _, groups, threads in launches), (dt, T, H, launches)
         assert all(threads == 256 for _, _, threads in combine)
         assert sum(groups for _, groups, _ in combine) == (T + 3) // 4 * pieces, (dt, T, H, combine)
+
+
+def test_combine_sends_no_wave_for_little(launches_of):
+    # pieces of a row, 2 KiB or 3
+    shapes = [("bf16", 64, 1024, 1), ("bf16", 64, 1032, 1), ("bf16", 64, 1280, 1), ("bf16", 64, 1288, 2), ("f32", 5000, 640, 1), ("f32", 5000, 644, 2),
+              ("bf16", 16384, 2056, 3), ("bf16", 16384, 3072, 3), ("bf16", 16384, 3080, 3), ("bf16", 4095, 3080, 4), ("bf16", 4096, 4088, 3),
+              ("bf16", 16384, 4096, 4), ("bf16", 16384, 4104, 3), ("bf16", 16384, 4616, 5), ("bf16", 32768, 7168, 7), ("bf16", 16384, 7176, 5),
+              ("f32", 16384, 1540, 3)]
+    found = launches_of(*[dict(dtype=dt, T=T, H=H, I=8, E=2, k=1, D=2, max_rows=64) for dt, T, H, _ in shapes])
+    for (dt, T, H, pieces), launches in zip(shapes, found):
+        assert [l[1] for l in launches if "combine" in l[0]] == [(T + 3) // 4 * pieces], (dt, T, H)
 
 
 DIRECT, SCAN = ["prefix_kernel", "dispatch_direct_kernel"], ["scan_kernel", "dispatch_kernel"]
