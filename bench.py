@@ -290,7 +290,7 @@ def copy_calibration(args):
 # over the workload's launches), scaled by what the same counters read for a plain 256 MiB copy
 # (x2.0 and x1.0).  A figure belongs to the kernel as it was when the counters were taken: it
 # is reported only while the sources that shape that kernel still hash to the recorded value.
-TRAFFIC_SOURCES = ["ffn_packed.hip", "ffn_common.h", "kernels.h", "dispatch.hip", "forward.cpp"]
+TRAFFIC_SOURCES = ["ffn_packed.hip", "ffn_common.h", "kernels.h", "dispatch.hip", "route_block.h", "forward.cpp"]
 _SHA = "da11b72b984ea0f2fe117747317d940ad70fbc12395322f0241e03199f32eda2"
 TRAFFIC = {
     "qwen3": dict(fetch_kib=287180.3, write_kib=13510.0, fetch_scale=2.0, write_scale=1.0, mfma_util=0.415, mfma_busy_of_peak_clock=0.382, l2_to_cu_mb=1296.4, l2_hit=0.549, sources_sha256=_SHA),

@@ -403,8 +403,10 @@ craft_status craft_moe_rank_forward_result(const void *workspace, int64_t *rows,
  * summed milliseconds and the number of launches per kernel, and rewinds the pool.
  */
 enum {
-    CRAFT_K_ROUTE = 0,     /* top-k + per-block ranks (up to 32 tokens: part of CRAFT_K_DISPATCH) */
-    CRAFT_K_SCAN = 1,      /* per-expert scan, slot offsets */
+    CRAFT_K_ROUTE = 0,     /* top-k + per-block ranks (part of CRAFT_K_DISPATCH for up to 32 tokens,
+                            * 384 experts and 2048 slots of all ranks together) */
+    CRAFT_K_SCAN = 1,      /* per-expert prefixes over token blocks (and slot offsets, where no
+                            * dispatch workgroup derives them) */
     CRAFT_K_DISPATCH = 2,  /* dest / src, tile tables of the GEMMs */
     CRAFT_K_GATEUP = 3,    /* grouped gate/up GEMM + SwiGLU (gathers its rows) */
     CRAFT_K_DOWN = 4,      /* grouped down GEMM */

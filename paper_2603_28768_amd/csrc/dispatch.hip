@@ -190,13 +190,10 @@ __device__ __forceinline__ int32_t rider_units(int64_t nt, int32_t cut, int32_t 
     return (int32_t)carried;
 }
 
-// What the grouped GEMMs need beyond the slot offsets: the rank's slots ordered by rows, the
-// row-tile prefixes of both GEMMs over that order and the rider units.  None of it is needed
-// for the dispatch indices, so it is built by one extra workgroup of the dispatch launch
-// while the others write dest / src, instead of at the end of the scan's serial tail.
-// Up to 64 slots: one wave, a slot per lane, and not a barrier (the general form below waits at two dozen).
-// The tables are what a dispatch launch of a small batch ends with: 8 tokens on 9 slots 3.2 -> 1.7 us, the
-// launch 6.4 -> 4.9; 256 tokens of an fp32 layer 7.7 -> 5.6 with the totals' requests sent together.
+// The tables of build_tile_tables for up to 64 slots: one wave, a slot per lane, and not a barrier (the
+// general form waits at two dozen).  They are what the dispatch launch of a small batch ends with.  A
+// forward with the general form / this, us: 8 tokens on 3 slots 16.1 / 14.5, on 17 17.9 / 16.3, on 34 18.5 /
+// 17.5, on 64 19.4 / 19.3; 4096 tokens on 17 slots 39.2 / 37.6; 256 tokens of the tiny fp32 layer 23.6 / 21.9.
 template <typename ROWS>
 __device__ void build_tile_tables_wave(const DispatchArgs &a, bool ovf, const ROWS &rows_of) {
     const int32_t nslots = a.s_hi - a.s_lo, lane = threadIdx.x;
@@ -241,6 +238,10 @@ __device__ void build_tile_tables_wave(const DispatchArgs &a, bool ovf, const RO
     }
 }
 
+// What the grouped GEMMs need beyond the slot offsets: the rank's slots ordered by rows, the
+// row-tile prefixes of both GEMMs over that order and the rider units.  None of it is needed
+// for the dispatch indices, so it is built by one extra workgroup of the dispatch launch
+// while the others write dest / src, instead of at the end of the scan's serial tail.
 template <int kTableThreads, typename ROWS>
 __device__ void build_tile_tables(const DispatchArgs &a, bool ovf, const ROWS &rows_of) {
     __shared__ int32_t rank_slot_rows[1024];
@@ -381,9 +382,9 @@ __global__ __launch_bounds__(64 * kDirectWaves) void prefix_kernel(int32_t *hist
 // Dispatch without a serial step in front of it.  Every workgroup derives what it needs for itself
 // -- the experts' counts from the totals of the chunks of blocks, the rows and offsets of the slots --
 // and needs no other workgroup's results.  In a batch of up to kSmallBlocks blocks a chunk is a
-// single block, whose counts the routing kernel has left: no other launch at all (T = 256, E = 384:
-// 14.3 -> 8.7 us for the two).  In a larger one prefix_kernel runs in front (T = 16384, E = 384:
-// scan 14.9 and dispatch 5.4 us -> 4.8 and 8.3; T = 32768, E = 256: 17.9 and 8.5 -> 5.2 and 12.9).
+// single block, whose counts the routing kernel has left: no other launch at all.  In a larger one
+// prefix_kernel runs in front (a forward scanned / direct, us: E = 256, 8192 tokens 44.1 / 39.0, 32768 65.5 /
+// 56.4, 65536 85.1 / 71.6; E = 384, 16384 58.1 / 48.3; E = 1024, 65536 223.6 / 183.7).
 // A workgroup handles one block of 32 tokens, a few neighbouring ones in a large batch.  COPY, for the
 // small-batch FFN: the token rows bound for this rank are copied into fragment order on the way, by
 // sa.slices workgroups per block that take a share of the columns each (the first one writes
@@ -391,8 +392,9 @@ __global__ __launch_bounds__(64 * kDirectWaves) void prefix_kernel(int32_t *hist
 //
 // NQ > 0, a batch of a single block: the workgroups route it as well, each for itself (the work of the
 // routing kernel, which has a single workgroup for such a batch, too), and nothing about ids, ranks and
-// counts goes through memory between two launches.  8 tokens with the gate's parts to add, E = 256: the two
-// launches 6.3 + 5 us, a forward 56.3 -> 53.8.
+// counts goes through memory between two launches.  A forward with a routing launch / without, us: 8 tokens,
+// E = 256, k = 8 22.0 / 20.0, with a gate's parts to add 34.9 / 32.0; 32 tokens, E = 384, k = 8 34.9 / 33.2, with
+// parts 45.1 / 42.9; k = 64, where the arg-max rounds are most of it, 101.6 / 99.6 and with parts 157.1 / 155.8.
 constexpr int kDirectThreads = 512;
 constexpr int kDirectSlots = 2048;
 static_assert(kDirectThreads == kRouteThreads, "a workgroup routes its block itself");
@@ -609,7 +611,9 @@ hipError_t launch_prefix(int32_t *hist, int32_t *chunk_tot, int32_t NB, int32_t 
 }
 
 // One block: more would be routed one after the other by every workgroup.  E: up to what the scores of a
-// lane fit registers beside the rest (and a gate's parts are added for).
+// lane fit registers beside the rest (and a gate's parts are added for).  Any number of picks and parts:
+// over 137 forwards of 1, 8 and 32 tokens, E = 8 to 384, k = 1 to 64 it takes 0.79 to 1.00 of the time (one
+// of them 0.97 and 1.02 in two runs).
 bool routed_dispatch(int64_t T, int32_t E, int32_t S) { return T <= kTokPerBlock && E <= 384 && small_dispatch(T, S); }
 
 hipError_t launch_dispatch_direct(DirectDispatchArgs a, const int32_t *chunk_tot, const RouteArgs *route, hipStream_t s) {
