@@ -136,12 +136,14 @@ template <bool W8> struct WFrag { typedef bf16x8_t type; };
 template <> struct WFrag<true> { typedef u32x2_t type; };
 
 static __device__ __forceinline__ bf16x8_t widen(bf16x8_t w) { return w; }
+// Two neighbouring codes (the lower or upper half of a word) to a pair of bf16: one instruction,
+// exact for every code (the scale is 1).  Through fp32 it takes two.
+template <bool UPPER> static __device__ __forceinline__ uint32_t widen_pair(uint32_t codes) {
+    return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(codes, 1.0f, UPPER));
+}
+typedef unsigned int wide_t __attribute__((ext_vector_type(4)));       // eight bf16 values, a pair per word
 static __device__ __forceinline__ bf16x8_t widen(u32x2_t w) {
-    // two codes per conversion (bytes 0,1 / 2,3 of a word), then pairs of fp32 to bf16
-    const f32x2_t a = __builtin_amdgcn_cvt_pk_f32_fp8(w[0], false), b = __builtin_amdgcn_cvt_pk_f32_fp8(w[0], true);
-    const f32x2_t c = __builtin_amdgcn_cvt_pk_f32_fp8(w[1], false), d = __builtin_amdgcn_cvt_pk_f32_fp8(w[1], true);
-    typedef unsigned int u32x4v __attribute__((ext_vector_type(4)));
-    const u32x4v r = {bf16_pair(a[0], a[1]), bf16_pair(b[0], b[1]), bf16_pair(c[0], c[1]), bf16_pair(d[0], d[1])};
+    const wide_t r = {widen_pair<false>(w[0]), widen_pair<true>(w[0]), widen_pair<false>(w[1]), widen_pair<true>(w[1])};
     return __builtin_bit_cast(bf16x8_t, r);
 }
 

@@ -83,6 +83,20 @@ template <> __device__ __forceinline__ u32x2_t zero_fragment<true>() {
     const u32x2_t z = {0u, 0u};
     return z;
 }
+// 8-bit weights are widened once per step and held for both halves of it: the fragments of the tile's
+// own step, then the rider's, one instruction for two codes, a quarter of a fragment behind an MFMA.
+// (bf16 weights need no such copy: one placeholder that nothing touches.)  A forward of 16384 tokens at
+// H = 7168, I = 2048 whose GEMMs widened every fragment in front of each half's first use of it,
+// through fp32: 263 us, so 255.
+constexpr int wide_fragments(int ngt, bool w8, bool rider) { return w8 ? 2 * ngt + (rider ? 2 : 0) : 1; }
+static __device__ __forceinline__ void widen_quarter(wide_t &to, u32x2_t from, int c) {
+    to[c] = c & 1 ? widen_pair<true>(from[c >> 1]) : widen_pair<false>(from[c >> 1]);
+}
+static __device__ __forceinline__ void widen_quarter(wide_t &, bf16x8_t, int) {}
+template <bool W8, typename F> static __device__ __forceinline__ bf16x8_t operand(const F &w, const wide_t &wide) {
+    if constexpr (W8) return __builtin_bit_cast(bf16x8_t, wide);
+    else return w;
+}
 // The lane's index inside its wave, counted afresh from the execution mask: with the wave's
 // index kept in a scalar register no vector register has to carry the thread index through
 // the contraction loops (it was spilled there, and its reload at the start of the epilogue
@@ -143,6 +157,7 @@ template <int NXF, int NGT, int R, int RR, int PW, int HI, int STAGE, bool W8, b
 __device__ __forceinline__ void packed_half(uint32_t xnext, Streams &sm,
                                             typename WFrag<W8>::type (&wq)[NGT][PW][2],
                                             typename WFrag<W8>::type (&wr)[RIDER ? rider_ring(NXF, W8) : 1][2],
+                                            wide_t (&wide)[wide_fragments(NGT, W8, RIDER)],
                                             const bf16x8_t (&XC)[NXF + RIDER], bf16x8_t (&XN)[NXF + RIDER],
                                             f32x4_t (&acc)[NGT][2][2 * NXF], f32x4_t (&accr)[1][2][2], uint32_t dma_lds,
                                             const uint32_t (&xp)[NXF + RIDER], uint32_t koff) {
@@ -177,16 +192,31 @@ __device__ __forceinline__ void packed_half(uint32_t xnext, Streams &sm,
             }
         }
     };
+    // 8-bit weights: which quarter of which fragment is widened behind MFMA g of fragment f
+    constexpr int W = 2 * NGT;
+    constexpr int PER = NXF > 4 ? 1 : NXF > 1 ? (3 + NXF - 1) / (NXF - 1) : 4;     // quarters per MFMA, none behind a fragment's last
+    auto widen_some = [&](int f, int g) __attribute__((always_inline)) {
+#pragma unroll
+        for (int c = g * PER; c < (g + 1) * PER && c < 4; ++c) {
+            if (HI && f > 0) {
+                constexpr int RN = (R + 1) % PW;
+                widen_quarter(wide[W8 && f > 0 ? f - 1 : 0], wq[(f > 0 ? f - 1 : 0) >> 1][RN][(f - 1) & 1], c);
+            }
+            if (!HI && f == 0) widen_quarter(wide[W8 ? W - 1 : 0], wq[NGT - 1][R][1], c);
+            if (!HI && RIDER && (f == 1 || f == 2)) widen_quarter(wide[W8 && RIDER ? W + f - 1 : 0], wr[RR % RING_R][(f - 1) & 1], c);
+        }
+    };
 #pragma unroll
     for (int n = 0; n < NGT; ++n) {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const bf16x8_t wf = widen(wq[n][R][h]);
+            const bf16x8_t wf = operand<W8>(wq[n][R][h], wide[W8 ? 2 * n + h : 0]);
 #pragma unroll
             for (int g = 0; g < NXF; ++g) {
-                if (g == 0) mfma16<W8>(wf, XC[g], acc[n][h][HI * NXF + g]);
+                if (g == 0 && !HI) mfma16<W8>(wf, XC[g], acc[n][h][HI * NXF + g]);
                 else mfma16<false>(wf, XC[g], acc[n][h][HI * NXF + g]);
                 after((2 * n + h) * NXF + g);
+                if constexpr (W8) widen_some(2 * n + h, g);
                 if (HI && g == NXF - 1) wq[n][R][h] = wload<ONCE, F>(wcur + (2 * n + h) * 64 * (int)sizeof(F), sm.wl);
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -195,7 +225,7 @@ __device__ __forceinline__ void packed_half(uint32_t xnext, Streams &sm,
     if (RIDER) {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            mfma16<W8>(widen(wr[RR % RING_R][h]), XC[NXA - 1], accr[0][h][HI]);
+            mfma16<W8 && !HI>(operand<W8>(wr[RR % RING_R][h], wide[W8 ? W + h : 0]), XC[NXA - 1], accr[0][h][HI]);
             after(2 * NGT * NXF + h);
             if (HI) wr[RR % RING_R][h] = wload<true, F>(wrcur + h * 64 * (int)sizeof(F), sm.wlr);
             __builtin_amdgcn_sched_barrier(0);
@@ -217,6 +247,7 @@ __device__ __forceinline__ void packed_slab(int ks, int last_slab, int K, uint32
                                             Streams &sm, const uint32_t (&xp)[NXF + RIDER],
                                             typename WFrag<W8>::type (&wq)[NGT][PW][2],
                                             typename WFrag<W8>::type (&wr)[RIDER ? rider_ring(NXF, W8) : 1][2],
+                                            wide_t (&wide)[wide_fragments(NGT, W8, RIDER)],
                                             bf16x8_t (&X0)[NXF + RIDER],
                                             bf16x8_t (&X1)[NXF + RIDER], f32x4_t (&acc)[NGT][2][2 * NXF],
                                             f32x4_t (&accr)[1][2][2]) {
@@ -228,12 +259,12 @@ __device__ __forceinline__ void packed_slab(int ks, int last_slab, int K, uint32
     const uint32_t dma_lds = lds_wave + (uint32_t)((U + 2) % kStages * XSTAGEB);
     const uint32_t cur = lds0 + U * XSTAGEB, nxt = lds0 + (U + 1) % kStages * XSTAGEB;
     const uint32_t fo1 = fo0 ^ 64u;                // the same fragment of the slab's second step
-    packed_half<NXF, NGT, (U * 2 + 0) % PW, U * 2 + 0, PW, 0, 0, W8, RIDER, ONCE>(cur + fo0, sm, wq, wr, X0, X1, acc, accr, dma_lds, xp, koff);
-    packed_half<NXF, NGT, (U * 2 + 0) % PW, U * 2 + 0, PW, 1, -1, W8, RIDER, ONCE>(cur + fo1, sm, wq, wr, X1, X0, acc, accr, dma_lds, xp, koff);
-    packed_half<NXF, NGT, (U * 2 + 1) % PW, U * 2 + 1, PW, 0, -1, W8, RIDER, ONCE>(cur + fo1, sm, wq, wr, X0, X1, acc, accr, dma_lds, xp, koff);
+    packed_half<NXF, NGT, (U * 2 + 0) % PW, U * 2 + 0, PW, 0, 0, W8, RIDER, ONCE>(cur + fo0, sm, wq, wr, wide, X0, X1, acc, accr, dma_lds, xp, koff);
+    packed_half<NXF, NGT, (U * 2 + 0) % PW, U * 2 + 0, PW, 1, -1, W8, RIDER, ONCE>(cur + fo1, sm, wq, wr, wide, X1, X0, acc, accr, dma_lds, xp, koff);
+    packed_half<NXF, NGT, (U * 2 + 1) % PW, U * 2 + 1, PW, 0, -1, W8, RIDER, ONCE>(cur + fo1, sm, wq, wr, wide, X0, X1, acc, accr, dma_lds, xp, koff);
     dma_wait<3 * V + NXA>();
     __syncthreads();
-    packed_half<NXF, NGT, (U * 2 + 1) % PW, U * 2 + 1, PW, 1, -1, W8, RIDER, ONCE>(nxt + fo0, sm, wq, wr, X1, X0, acc, accr, dma_lds, xp, koff);
+    packed_half<NXF, NGT, (U * 2 + 1) % PW, U * 2 + 1, PW, 1, -1, W8, RIDER, ONCE>(nxt + fo0, sm, wq, wr, wide, X1, X0, acc, accr, dma_lds, xp, koff);
 }
 
 // Epilogue of 2 NF accumulator fragments of 16 rows x NGT column groups, which are the rows of
@@ -457,12 +488,18 @@ __device__ __forceinline__ int32_t packed_tile(const FfnArgs &a, const Tile &t, 
     for (int g = 0; g < NXF; ++g) x0[g] = *reinterpret_cast<const bf16x8_t *>(smem + fo0 + g * 16 * XROWB);
     if (RIDER) x0[NXA - 1] = *reinterpret_cast<const bf16x8_t *>(smem + fo0 + 32 * NXF * XROWB);
 
+    // and, of 8-bit weights, all of its fragments but the last, which its own lower half widens
+    wide_t wide[wide_fragments(NGT, W8, RIDER)];
+    if constexpr (W8)
+#pragma unroll
+        for (int f = 0; f < 2 * NGT - 1; ++f) wide[f] = __builtin_bit_cast(wide_t, widen(wq[f >> 1][0][f & 1]));
+
     const int last_slab = nk4 * 4 - 1;
     for (int ks = 0; ks <= last_slab; ks += 4) {
-        packed_slab<NXF, NGT, 0, PW, W8, RIDER, ONCE>(ks + 0, last_slab, K, kcb, lds0, lds_wave, fo0, sm, xp, wq, wr, x0, x1, acc, accr);
-        packed_slab<NXF, NGT, 1, PW, W8, RIDER, ONCE>(ks + 1, last_slab, K, kcb, lds0, lds_wave, fo0, sm, xp, wq, wr, x0, x1, acc, accr);
-        packed_slab<NXF, NGT, 2, PW, W8, RIDER, ONCE>(ks + 2, last_slab, K, kcb, lds0, lds_wave, fo0, sm, xp, wq, wr, x0, x1, acc, accr);
-        packed_slab<NXF, NGT, 3, PW, W8, RIDER, ONCE>(ks + 3, last_slab, K, kcb, lds0, lds_wave, fo0, sm, xp, wq, wr, x0, x1, acc, accr);
+        packed_slab<NXF, NGT, 0, PW, W8, RIDER, ONCE>(ks + 0, last_slab, K, kcb, lds0, lds_wave, fo0, sm, xp, wq, wr, wide, x0, x1, acc, accr);
+        packed_slab<NXF, NGT, 1, PW, W8, RIDER, ONCE>(ks + 1, last_slab, K, kcb, lds0, lds_wave, fo0, sm, xp, wq, wr, wide, x0, x1, acc, accr);
+        packed_slab<NXF, NGT, 2, PW, W8, RIDER, ONCE>(ks + 2, last_slab, K, kcb, lds0, lds_wave, fo0, sm, xp, wq, wr, wide, x0, x1, acc, accr);
+        packed_slab<NXF, NGT, 3, PW, W8, RIDER, ONCE>(ks + 3, last_slab, K, kcb, lds0, lds_wave, fo0, sm, xp, wq, wr, wide, x0, x1, acc, accr);
     }
     // the last slabs have requested rows past the end of the contraction (the last slab again):
     // nothing may still be on its way into LDS when the tile, and perhaps the workgroup, ends
