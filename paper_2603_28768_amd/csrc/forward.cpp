@@ -28,9 +28,8 @@ struct Layout {
 int cached_num_cu();
 
 size_t gate_workspace_bytes(int32_t dtype, int64_t T, int32_t H, int32_t E) {
-    int nxf = 1, nsplit = 1;
-    if (dtype == CRAFT_BF16 && T > 0) router_logits_shape(T, H, E, cached_num_cu(), true, &nxf, &nsplit);
-    return nsplit > 1 ? (size_t)nsplit * (size_t)T * (size_t)E * sizeof(float) : 0;
+    const int nparts = dtype == CRAFT_BF16 && T > 0 ? router_logits_shape(T, H, E, cached_num_cu(), true).nparts : 1;
+    return nparts > 1 ? (size_t)nparts * (size_t)T * (size_t)E * sizeof(float) : 0;
 }
 
 Layout make_layout(int64_t T, int32_t k, int32_t E, int32_t S, int32_t nslots, int32_t H, int32_t I,
@@ -671,7 +670,7 @@ craft_status forward_on(const craft_plan_t *plan, int32_t layer, int32_t rank, c
                       L.gate_ws_bytes ? reinterpret_cast<float *>(ws + L.gate_ws) : nullptr, 1, E <= 384};
         if (launch_router_logits(ga, s) != hipSuccess) return CRAFT_EHIP;
         // a split gate's partial scores are added by the routing kernel
-        nparts = ga.keep_parts && L.gate_ws_bytes ? (int)(L.gate_ws_bytes / ((size_t)a->T * E * sizeof(float))) : 1;
+        nparts = ga.keep_parts && L.gate_ws_bytes ? router_logits_shape(a->T, a->H, E, cached_num_cu(), true).nsplit : 1;
         logits = nparts > 1 ? ga.part : own;
     }
     // 1 route (+ per-block ranks and counts); user copies of ids / weights are written by the

@@ -88,11 +88,18 @@ struct RouterArgs {
     float *logits;            // [T][E]
     int32_t num_cu;
     float *part;              // [nsplit][T][E] partial scores when the contraction is split; may be null
-    int32_t nsplit;           // set by the launcher
+    int32_t nsplit;           // set by the launcher: workgroups per tile
     bool keep_parts;          // with a split contraction: leave the sums to the reader of `part`
+    int32_t nparts = 1;       // set by the launcher: parts of the contraction that are summed by themselves, a multiple of nsplit
+    int32_t eblocks = 1;      // set by the launcher: blocks of experts
 };
 hipError_t launch_router_logits(const RouterArgs &a, hipStream_t s);
-void router_logits_shape(int64_t T, int32_t H, int32_t E, int32_t num_cu, bool workspace, int *nxf, int *nsplit);
+struct RouterShape {
+    int tokens;               // 32-token fragments of a tile
+    int experts;              // most experts of a tile
+    int nparts, nsplit;       // as in RouterArgs
+};
+RouterShape router_logits_shape(int64_t T, int32_t H, int32_t E, int32_t num_cu, bool workspace);
 
 struct RouteArgs {
     const float *logits;

@@ -25,15 +25,28 @@ constexpr int kNtLds = 3 * 12 * 32 * 128;          // three stages of 256 + 128 
 template <int FA, int FB> constexpr int nt_stages() { return nt_stage_bytes<FA, FB>() * 4 <= kNtLds ? 4 : 3; }
 template <int FA, int FB> constexpr int nt_lds_bytes() { return nt_stages<FA, FB>() * nt_stage_bytes<FA, FB>(); }
 
+// Before an accumulator is read: more idle cycles than a matrix instruction takes to be read, then
+// every accumulator passes through a statement ordered behind them.
+template <int FA, int FB> static __device__ __forceinline__ void nt_settle(f32x4_t (&acc)[FA][FB]) {
+    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+#pragma unroll
+    for (int f = 0; f < FA; ++f)
+#pragma unroll
+        for (int g = 0; g < FB; ++g) asm volatile("" : "+a"(acc[f][g]));
+}
+
 // Rows of this many elements: 256 of them stay inside a 32-bit byte offset.
 constexpr int kNtRowLimit = 1 << 23;
 // abase, bbase: wave-uniform; aoff, boff: the byte offset of a row (0 .. 32 FA - 1, 32 FB - 1) from them.  K: elements
 // per row, a multiple of 8, less than kNtRowLimit.  acc[f][g] += A fragment wa FA + f x B fragment wb FB + g, where wave w of
 // the workgroup is (wa, wb) = (w >> 1, w & 1); element v of lane l is row 4 (l >> 4) + v of A's fragment
 // and row l & 15 of B's.  kbeg, kend: the slabs to take.  Ends with a barrier and nothing in flight.
-template <int FA, int FB, typename AOFF, typename BOFF>
+// `after_slab` runs behind every slab.
+struct NothingAfter { __device__ __forceinline__ void operator()(int) const {} };
+template <int FA, int FB, typename AOFF, typename BOFF, typename AFTER = NothingAfter>
 static __device__ __forceinline__ void nt_tile(unsigned char *smem, ubase_t abase, const AOFF &aoff_of, ubase_t bbase,
-                                               const BOFF &boff_of, int K, int kbeg, int kend, f32x4_t (&acc)[FA][FB]) {
+                                               const BOFF &boff_of, int K, int kbeg, int kend, f32x4_t (&acc)[FA][FB],
+                                               const AFTER &after_slab = AFTER{}) {
     constexpr int STAGEB = nt_stage_bytes<FA, FB>(), S = nt_stages<FA, FB>();
     const int lane = threadIdx.x & 63, q = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -141,6 +154,7 @@ static __device__ __forceinline__ void nt_tile(unsigned char *smem, ubase_t abas
         dma_wait<(S - 3) * NR + (NR + 1) / 2>();
         __syncthreads();
         half(set1, with, there, 0, koff, s2);
+        after_slab(ks);
         s = s1;
     }
     for (; ks < kend; ++ks) {
@@ -152,16 +166,11 @@ static __device__ __forceinline__ void nt_tile(unsigned char *smem, ubase_t abas
         __syncthreads();
         if (ks == last) cut(1, ks * 64 + 32);
         half(set1, without, there, 0, 0u, 0);      // after the last slab: read and not used
+        after_slab(ks);
         s = s1;
     }
     __syncthreads();                               // the stages may be filled again
-    // more idle cycles than a matrix instruction takes to be read, then every accumulator passes
-    // through a statement ordered behind them
-    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
-#pragma unroll
-    for (int f = 0; f < FA; ++f)
-#pragma unroll
-        for (int g = 0; g < FB; ++g) asm volatile("" : "+a"(acc[f][g]));
+    nt_settle(acc);
 }
 
 // The same product for rows of A that are not 16-byte aligned, which loads into LDS ask for, and, with

@@ -6,14 +6,16 @@
 //
 // A skinny GEMM: few output columns (E = 128 .. 384), so the tokens' activations are what
 // has to cross HBM (once) and the gate's weights are re-read from L2 by every workgroup.
-// bf16: 32, 64 or 128 tokens against up to 256 experts per workgroup (nt_tile.h), the experts as the
+// bf16: 32, 64 or 128 tokens against 64 to 256 experts per workgroup (nt_tile.h), the experts as the
 // matrix instruction's row operand, so that a lane holds four neighbouring experts of a token:
-// 16-byte stores.  Every workgroup pulls the whole gate out of L2, so T H 2 (1 + E / tokens per
-// workgroup) bytes move from L2 into the CUs; taller workgroups move less but there are only
-// T / 128 of them, so with a workspace the contraction is split over up to 8 workgroups per tile:
-// each writes its partial scores and a second kernel (or the routing kernel) adds them in ascending
-// order of the split (a fixed order: the result does not depend on scheduling).
+// 16-byte stores.  Every workgroup pulls its experts' rows out of L2, so T H 2 (E / experts + E / tokens per
+// workgroup) bytes move from L2 into the CUs; large tiles move less but there are few of them, so with a
+// workspace the contraction is summed in up to 8 parts per tile, by one workgroup after one another or by
+// several: those write their partial scores and a second kernel (or the routing kernel) adds them in
+// ascending order of the split (a fixed order: the result does not depend on scheduling).
 // fp32: one thread per score, a plain chain of fused multiply-adds (small configurations).
+#include <algorithm>
+
 #include "nt_tile.h"
 
 namespace craft {
@@ -28,16 +30,20 @@ constexpr int GK = 64;                  // contraction slab
 typedef unsigned int gu32x4_t __attribute__((ext_vector_type(4)));
 typedef const gu32x4_t __attribute__((address_space(1))) *gchunk_t;
 
-template <int FA, int FB>
+// PARTED: a workgroup takes several parts of the contraction.
+template <int FA, int FB, bool PARTED>
 __global__ __launch_bounds__(kNtThreads) void router_logits_bf16_kernel(RouterArgs a) {
     __shared__ __attribute__((aligned(16))) unsigned char gate_smem[nt_lds_bytes<FA, FB>()];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int64_t t0 = (int64_t)blockIdx.x * (FB * 32);
-    const int e0 = blockIdx.y * (FA * 32);
+    // workgroups go round the XCDs: the blocks of experts of one tile of tokens meet in one L2
+    const int tile = (int)blockIdx.x / (8 * a.eblocks) * 8 + (int)blockIdx.x % 8, eblock = (int)blockIdx.x / 8 % a.eblocks;
+    const int64_t t0 = (int64_t)tile * (FB * 32);
+    const int e0 = eblock * (FA * 32);
+    if (t0 >= a.T) return;
     // this workgroup's share of the contraction (may be empty)
-    const int nk = (a.H + GK - 1) / GK, per = (nk + a.nsplit - 1) / a.nsplit;
-    const int kbeg = min(nk, (int)blockIdx.z * per), kend = min(nk, kbeg + per);
+    const int nk = (a.H + GK - 1) / GK, per = (nk + a.nparts - 1) / a.nparts, share = per * (a.nparts / a.nsplit);
+    const int kbeg = min(nk, (int)blockIdx.z * share), kend = min(nk, kbeg + share);
     float *dst = a.nsplit > 1 ? a.part + (int64_t)blockIdx.z * a.T * a.E : a.logits;
     // rows past the end are clamped into the matrix (their results are not stored)
     auto eoff = [&](int i) { return (uint32_t)min(i, a.E - 1 - e0) * (uint32_t)a.H * 2u; };
@@ -47,8 +53,35 @@ __global__ __launch_bounds__(kNtThreads) void router_logits_bf16_kernel(RouterAr
     for (int f = 0; f < FA; ++f)
 #pragma unroll
         for (int g = 0; g < FB; ++g) acc[f][g] = (f32x4_t)(0.0f);
-    nt_tile<FA, FB>(gate_smem, uniform_base(static_cast<ubase_t>(a.w) + (int64_t)e0 * a.H * 2), eoff,
-                    uniform_base(static_cast<ubase_t>(a.x) + t0 * a.H * 2), toff, a.H, kbeg, kend, acc);
+    const ubase_t wbase = uniform_base(static_cast<ubase_t>(a.w) + (int64_t)e0 * a.H * 2), xbase = uniform_base(static_cast<ubase_t>(a.x) + t0 * a.H * 2);
+    if constexpr (PARTED) {
+        // each part starts from zero, like one of a workgroup of its own
+        f32x4_t sum[FA][FB];
+#pragma unroll
+        for (int f = 0; f < FA; ++f)
+#pragma unroll
+            for (int g = 0; g < FB; ++g) sum[f][g] = (f32x4_t)(0.0f);
+        int cut = kbeg + per - 1;
+        nt_tile<FA, FB>(gate_smem, wbase, eoff, xbase, toff, a.H, kbeg, kend, acc, [&](int ks) __attribute__((always_inline)) {
+            if (ks != cut || ks == kend - 1) return;
+            cut += per;
+            nt_settle(acc);
+#pragma unroll
+            for (int f = 0; f < FA; ++f)
+#pragma unroll
+                for (int g = 0; g < FB; ++g) {
+                    sum[f][g] += acc[f][g];
+                    acc[f][g] = (f32x4_t)(0.0f);
+                    asm volatile("s_nop 1" : "+a"(acc[f][g]));  // a matrix instruction reads it two cycles later at the earliest
+                }
+        });
+#pragma unroll
+        for (int f = 0; f < FA; ++f)
+#pragma unroll
+            for (int g = 0; g < FB; ++g) acc[f][g] = sum[f][g] + acc[f][g];
+    } else {
+        nt_tile<FA, FB>(gate_smem, wbase, eoff, xbase, toff, a.H, kbeg, kend, acc);
+    }
     const bool whole = (a.E & 3) == 0 && (reinterpret_cast<uintptr_t>(dst) & 15) == 0;
 #pragma unroll
     for (int g = 0; g < FB; ++g) {
@@ -177,8 +210,11 @@ void launch_reduce(const RouterArgs &a, int nsplit, int64_t n, hipStream_t s) {
 }
 template <int FA, int FB>
 hipError_t launch_bf16(const RouterArgs &a, hipStream_t s) {
-    const dim3 grid((unsigned)((a.T + FB * 32 - 1) / (FB * 32)), (unsigned)((a.E + FA * 32 - 1) / (FA * 32)), (unsigned)a.nsplit);
-    hipLaunchKernelGGL((router_logits_bf16_kernel<FA, FB>), grid, dim3(kNtThreads), 0, s, a);
+    RouterArgs b = a;
+    b.eblocks = (a.E + FA * 32 - 1) / (FA * 32);
+    const dim3 grid((unsigned)((a.T + FB * 32 * 8 - 1) / (FB * 32 * 8) * 8 * b.eblocks), 1, (unsigned)a.nsplit);
+    if (a.nparts > a.nsplit) hipLaunchKernelGGL((router_logits_bf16_kernel<FA, FB, true>), grid, dim3(kNtThreads), 0, s, b);
+    else hipLaunchKernelGGL((router_logits_bf16_kernel<FA, FB, false>), grid, dim3(kNtThreads), 0, s, b);
     return hipGetLastError();
 }
 template <int FA>
@@ -188,26 +224,69 @@ hipError_t launch_bf16(const RouterArgs &a, int nxf, hipStream_t s) {
 
 }  // namespace
 
-// Tile height (32-token fragments per workgroup) and split of the contraction for a shape.
-// Without a workspace: short tiles, as many as there are CUs if possible.  With one: the
-// tallest tile, and as many splits as bring the workgroups up to the CU count (at most 8, at least 4
-// slabs each).  Workgroups are counted in blocks of up to 384 experts, not the 256 of a tile, and more
-// than 384 experts are never split: 257 to 384 get twice the workgroups this aims at (T = 16384, E = 384:
-// 512, two rounds), more get short tiles.  No shape is slower for it than with the tiles of 512
-// experts that the count was made for.
-void router_logits_shape(int64_t T, int32_t H, int32_t E, int32_t num_cu, bool workspace, int *nxf, int *nsplit) {
+namespace {
+
+// 16-row fragments of experts per wave, and blocks of experts, of tiles of up to `most` experts: blocks as
+// even as they come.
+int expert_blocks(int32_t E, int most) { return (E + most - 1) / most; }
+int expert_fragments(int32_t E, int most) {
+    const int rows = (E + expert_blocks(E, most) - 1) / expert_blocks(E, most);
+    return rows <= 64 ? 2 : rows <= 128 ? 4 : rows <= 192 ? 6 : 8;
+}
+// Expected us of a launch and what follows it: a slab takes a workgroup the longer of its matrix instructions
+// and of what it loads, more than one workgroup per CU share it, and parts in memory are written, read and
+// added by a launch of their own.  Fitted to 1700 calls over 123 shapes (below).
+double expected_us(const RouterShape &s, int64_t T, int32_t H, int32_t E, int32_t num_cu) {
+    const int fa = expert_fragments(E, s.experts), nk = (H + GK - 1) / GK;
+    const double wgs = (double)((T + 32 * s.tokens - 1) / (32 * s.tokens)) * expert_blocks(E, s.experts) * s.nsplit;
+    const double slabs = (double)((nk + s.nparts - 1) / s.nparts) * (s.nparts / s.nsplit);
+    double slab = std::max(0.0357 * fa * s.tokens, 0.0643 * (fa + s.tokens) + 0.021);
+    if (wgs > num_cu) slab *= 1.37;
+    const double load = std::max((wgs > num_cu ? wgs / num_cu : 1.0) * (10.5 + slabs * slab), (double)T * H * 2e-6 / 11.9);
+    const double mb = (double)T * E * 4e-6;
+    return (load + (s.nsplit > 1 ? s.nsplit * mb * 0.66 + 4.75 : mb * 0.33)) * (s.nsplit == 1 && s.nparts > 2 ? 1.10 : 1.0);
+}
+
+}  // namespace
+
+// The tile and the split of the contraction for a shape.  Without a workspace: short tiles, as many as
+// there are CUs if possible.  With one, the contraction is summed in as many parts as bring tall tiles of
+// all experts up to the CU count (at most 8, at least 4 slabs each; counted in blocks of up to 384 experts,
+// more than 384 are never split), which is what the workspace is sized for; how many of those parts one
+// workgroup takes after another, and how large the tiles are, follows expected_us: tall tiles of 256
+// experts, a workgroup per part, unless another way takes less than 0.84 of their time.  Every other part
+// left to another workgroup is a copy of the scores to write, read and add.  us a call, tall tiles with a
+// workgroup per part / this: H = 7168, E = 256, 512 tokens 21.4 / 13.3, 2048 23.7 / 17.5, 8192 47.9 / 47.5; E = 384, 4096
+// 50.3 / 40.0, 16384 127 / 109; H = 2880, E = 256, 4096 22.7 / 14.9, 8192 30.3 / 23.6.  Over 270 shapes of
+// H = 1024 to 7168, E = 64 to 384 and 150 to 16384 tokens scores and top-k together take 0.94 of the time in the
+// mean, from 0.62 to 1.03 (H = 7168, E = 256, 12000 tokens 77.6 / 80.3).
+RouterShape router_logits_shape(int64_t T, int32_t H, int32_t E, int32_t num_cu, bool workspace) {
     const int nb = E > 512 ? 4 : (E + 127) / 128;
-    *nsplit = 1;
+    RouterShape s{1, 256, 1, 1};
     if (!workspace || nb > 3) {
-        *nxf = nb <= 3 && (T + 63) / 64 >= (int64_t)num_cu ? 2 : 1;
-        return;
+        s.tokens = nb <= 3 && (T + 63) / 64 >= (int64_t)num_cu ? 2 : 1;
+        return s;
     }
-    *nxf = 4;
+    s.tokens = 4;
     const int64_t tiles = (T + 127) / 128 * ((E + nb * 128 - 1) / (nb * 128));
     const int nk = (H + GK - 1) / GK;
-    int sp = 1;
-    while (sp < 8 && tiles * sp * 2 <= num_cu && nk / (sp * 2) >= 4) sp *= 2;
-    *nsplit = sp;
+    while (s.nparts < 8 && tiles * s.nparts * 2 <= num_cu && nk / (s.nparts * 2) >= 4) s.nparts *= 2;
+    s.nsplit = s.nparts;
+    if (T <= kThinBatch || H >= kNtRowLimit || s.nparts == 1) return s;
+    RouterShape best = s;
+    double best_us = expected_us(s, T, H, E, num_cu) * 0.84;
+    for (int tokens = 1; tokens <= 4; tokens *= 2)
+        for (int experts = 64; experts <= 256; experts += 64) {
+            if (experts > 64 && expert_blocks(E, experts) == expert_blocks(E, experts - 64)) continue;
+            const int64_t wgs = (T + 32 * tokens - 1) / (32 * tokens) * expert_blocks(E, experts);
+            for (int nsplit = 1; nsplit <= s.nparts; nsplit *= 2) {
+                if (wgs * nsplit < num_cu / 4 || wgs * nsplit > 4 * num_cu) continue;
+                const RouterShape c{tokens, experts, s.nparts, nsplit};
+                const double us = expected_us(c, T, H, E, num_cu);
+                if (us < best_us) { best_us = us; best = c; }
+            }
+        }
+    return best;
 }
 
 hipError_t launch_router_logits(const RouterArgs &a, hipStream_t s) {
@@ -217,20 +296,20 @@ hipError_t launch_router_logits(const RouterArgs &a, hipStream_t s) {
         hipLaunchKernelGGL(router_logits_f32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a);
         return hipGetLastError();
     }
-    int nxf, nsplit;
-    router_logits_shape(a.T, a.H, a.E, a.num_cu, a.part != nullptr, &nxf, &nsplit);
+    const RouterShape shape = router_logits_shape(a.T, a.H, a.E, a.num_cu, a.part != nullptr);
+    const int nxf = shape.tokens, nsplit = shape.nsplit;
     RouterArgs b = a;
     b.nsplit = nsplit;
+    b.nparts = shape.nparts;
     hipError_t err;
     if (a.T <= kThinBatch || a.H >= kNtRowLimit) {         // (thin tiles take rows of any length)
         const dim3 grid((unsigned)((a.E + 15) / 16), (unsigned)((a.T + kThinTokens - 1) / kThinTokens), (unsigned)nsplit);
         hipLaunchKernelGGL(router_thin_kernel, grid, dim3(64 * kThinWaves), 0, s, b);
         err = hipGetLastError();
     } else {
-        // blocks of up to 256 experts, as even as they come
-        const int blocks = (a.E + 255) / 256, rows = (a.E + blocks - 1) / blocks;
-        err = rows <= 64 ? launch_bf16<2>(b, nxf, s) : rows <= 128 ? launch_bf16<4>(b, nxf, s)
-              : rows <= 192 ? launch_bf16<6>(b, nxf, s) : launch_bf16<8>(b, nxf, s);
+        const int fa = expert_fragments(a.E, shape.experts);
+        err = fa == 2 ? launch_bf16<2>(b, nxf, s) : fa == 4 ? launch_bf16<4>(b, nxf, s) : fa == 6 ? launch_bf16<6>(b, nxf, s)
+                                                                                                  : launch_bf16<8>(b, nxf, s);
     }
     if (err != hipSuccess || nsplit == 1 || a.keep_parts) return err;
     const int64_t n = a.T * a.E;

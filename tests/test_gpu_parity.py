@@ -208,6 +208,31 @@ def test_router_logits_parity(torch_cuda, dtype, T, H, E):
         assert np.array_equal(_np(binding.router_logits(xd, Wd, workspace)), _np(binding.router_logits(xd, Wd, workspace)))
 
 
+@pytest.mark.parametrize("T,H,E", [
+    (600, 1000, 250),                # tiles of 32 tokens x 64 experts, four parts after one another; ragged slab, last block of experts
+    (3000, 1032, 130),               # 64 x 64, three blocks of experts, a tile of tokens past a multiple of eight
+    (2049, 520, 200),                # two parts of five and four slabs, the last tile one token
+    (2100, 584, 384),                # the most experts that are split
+    (600, 2056, 380),                # two parts in each of four workgroups
+    (5000, 1096, 321)])              # 64 x 128, four parts of five slabs and fewer
+def test_router_logits_of_several_parts_in_a_workgroup(torch_cuda, T, H, E):
+    cfg = synth.scaled(synth.CONFIGS["qwen3"], T=T, H=H, E=E)
+    x, W = synth.activations(cfg), synth.gate_weights(cfg)
+    xd, Wd = binding.to_device(x, "bf16"), binding.to_device(W, "bf16")
+    want = oracle.router_logits(x, W)
+    ws = binding.router_logits_workspace(xd, Wd)
+    got = _np(binding.router_logits(xd, Wd, ws))
+    err = np.abs(got.astype(np.float64) - want).max()
+    print(f"  gate T={T} H={H} E={E}: max|ref|={np.abs(want).max():.3g} max|err|={err:.3g}", flush=True)
+    assert err <= GATE_TOL * np.abs(want).max()
+    assert np.array_equal(got, _np(binding.router_logits(xd, Wd, ws)))
+    # a gate of unit rows copies columns of x, whichever part they are in
+    U = np.zeros((E, H), dtype=np.float32)
+    at = np.arange(E) * 7 % H
+    U[np.arange(E), at] = 1.0
+    assert np.array_equal(_np(binding.router_logits(xd, binding.to_device(U, "bf16"), ws)), x[:, at])
+
+
 def test_router_logits_empty_and_rejected(torch_cuda):
     torch = torch_cuda
     x = torch.zeros((0, 64), dtype=torch.bfloat16, device="cuda:0")
