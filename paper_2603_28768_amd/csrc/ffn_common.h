@@ -43,15 +43,31 @@ struct TileTables {
     int32_t mt_start[kMaxSlots + 1];
     int32_t order[kMaxSlots];
     int32_t slot_off[kMaxSlots + 1];      // offsets of the rank's slots, busiest-first order undone
+    int32_t ctrl[CTRL_WORDS];             // the control words (the counters among them as the launch finds them)
 };
 static __device__ __forceinline__ void load_tile_tables(const FfnArgs &a, const int32_t *mt_start,
                                                         TileTables &tt) {
+    // no branch around a load: everything travels in one round trip
+    const int32_t word = a.ctrl[min((int)threadIdx.x, CTRL_WORDS - 1)];
     for (int i = threadIdx.x; i <= a.nslots; i += blockDim.x) {
-        tt.mt_start[i] = mt_start[i];
-        tt.slot_off[i] = a.slot_off[a.s_lo + i];
-        if (i < a.nslots) tt.order[i] = a.order[i];
+        const int last = min(i, a.nslots - 1);
+        const int32_t start = mt_start[i], off = a.slot_off[a.s_lo + i], slot = a.order[last];
+        tt.mt_start[i] = start;
+        tt.slot_off[i] = off;
+        tt.order[last] = slot;
     }
+    if (threadIdx.x < CTRL_WORDS) tt.ctrl[threadIdx.x] = word;
     __syncthreads();
+}
+// A control word, an entry of the first table and the rank's first row, from the copy where there is one.
+static __device__ __forceinline__ int32_t ctrl_word(const FfnArgs &a, const TileTables &tt, bool small, int i) {
+    return __builtin_amdgcn_readfirstlane(small ? tt.ctrl[i] : a.ctrl[i]);
+}
+static __device__ __forceinline__ int32_t tiles_before(const int32_t *mt_start, const TileTables &tt, bool small, int32_t p) {
+    return __builtin_amdgcn_readfirstlane(small ? tt.mt_start[p] : mt_start[p]);
+}
+static __device__ __forceinline__ int32_t first_row(const FfnArgs &a, const TileTables &tt, bool small) {
+    return __builtin_amdgcn_readfirstlane(small ? tt.slot_off[0] : a.slot_off[a.s_lo]);
 }
 // MT, ORD, OFF: the three tables, in global memory or in a workgroup's LDS copy
 // fmax > 0: row-tiles of fmax fragments and a remainder; fmax < 0: shared evenly

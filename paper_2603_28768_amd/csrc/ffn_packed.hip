@@ -540,6 +540,10 @@ __global__ __launch_bounds__(256, 1) void ffn_packed_kernel(FfnArgs a) {
     const int32_t *mt_start = a.mt_start + (GATEUP ? 0 : a.nslots + 1);
     const bool small = a.nslots <= TileTables::kMaxSlots;
     if (small) load_tile_tables(a, mt_start, tt);
+    const int32_t hot = ctrl_word(a, tt, small, CTRL_HOT_SLOTS), live = ctrl_word(a, tt, small, CTRL_LIVE_SLOTS);
+    const int32_t cold2 = ctrl_word(a, tt, small, CTRL_COLD2_SLOTS);
+    const int64_t carried = ctrl_word(a, tt, small, GATEUP ? CTRL_RIDERS_GATEUP : CTRL_RIDERS_DOWN);
+    const int32_t lo_pos = first_row(a, tt, small);
     const int K = GATEUP ? a.H : a.I;
     const int N = GATEUP ? a.I : a.H;
     constexpr int GC = GATEUP ? 16 : 32;           // output columns per weight group
@@ -552,15 +556,11 @@ __global__ __launch_bounds__(256, 1) void ffn_packed_kernel(FfnArgs a) {
     // cold slots' units as tiles of their own (one row-tile, 2 nt half-width column tiles per
     // slot).  Units are counted over the cold slots in list order: a two-fragment slot has
     // 4 nt (fragment-major), a one-fragment slot 2 nt.
-    const int32_t hot = a.ctrl[CTRL_HOT_SLOTS], live = a.ctrl[CTRL_LIVE_SLOTS];
-    const int32_t cold2 = a.ctrl[CTRL_COLD2_SLOTS];
-    const int64_t carried = a.ctrl[GATEUP ? CTRL_RIDERS_GATEUP : CTRL_RIDERS_DOWN];
     const int64_t units2 = (int64_t)cold2 * 4 * nt;
-    const int64_t hot_tiles = (int64_t)mt_start[hot] * nt;
+    const int64_t hot_tiles = (int64_t)tiles_before(mt_start, tt, small, hot) * nt;
     const int64_t cold_tiles = carried <= units2 ? (int64_t)(live - hot) * 2 * nt - carried / 2
                                                  : (int64_t)(live - hot - cold2) * 2 * nt - (carried - units2);
     const int64_t total = hot_tiles + cold_tiles;
-    const int32_t lo_pos = a.slot_off[a.s_lo];
     const int32_t fmax = GATEUP ? a.frags_gu : a.frags_dn;
     // A launch of more than two rounds of busy tiles lists a slot's tiles block by block
     // (ffn_common.h); a shorter one column by column, which packs its end best.

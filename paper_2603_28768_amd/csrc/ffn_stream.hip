@@ -216,13 +216,15 @@ __global__ __launch_bounds__(kThreads, 2) void ffn_stream_kernel(FfnArgs a) {
     const bool small = a.nslots <= StreamTables::kMaxSlots;
     if (small) {
         for (int i = threadIdx.x; i <= a.nslots; i += kThreads) {
-            tt.mt_start[i] = mt_start[i];
-            tt.slot_off[i] = a.slot_off[a.s_lo + i];
-            if (i < a.nslots) {
-                tt.order[i] = a.order[i];
-                tt.w[0][i] = w0[i];
-                tt.w[1][i] = w1[i];
-            }
+            // (no branch around a load)
+            const int last = min(i, a.nslots - 1);
+            const int32_t start = mt_start[i], off = a.slot_off[a.s_lo + i], slot = a.order[last];
+            const void *p0 = w0[last], *p1 = w1[last];
+            tt.mt_start[i] = start;
+            tt.slot_off[i] = off;
+            tt.order[last] = slot;
+            tt.w[0][last] = p0;
+            tt.w[1][last] = p1;
         }
         __syncthreads();
     }
