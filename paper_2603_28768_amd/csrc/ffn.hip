@@ -23,7 +23,10 @@
 // and requests holds it there has not been taken apart (a CU reads three times as fast out of its L2
 // in a plain loop).  Taller tiles move less but come out in fewer rounds.  1777 tokens on 17 slots,
 // H = 4096, I = 1536: gate/up 190 -> 117 us, down 84 -> 63 (before: 128 x 128 tiles through registers, one
-// slab ahead).
+// slab ahead).  A cold slot's tile is bound by what one CU gets out of HBM, about 42 GB/s whatever it has in
+// flight: 256 weight rows of 4096 elements take it 50 us.  Where there is more than a round of tiles the cold
+// slots therefore get 64 weight rows a tile; a forward of those 1777 tokens 195 -> 178 us, 1100 tokens 183 -> 158,
+// of 4767 on slots of H = 5120, I = 2048 430 -> 406; without a cold slot the same within 2 %.  With 128 rows a tile 183.
 //
 // fp32 path: units of 16 columns and 32 rows from the same tile list (small configurations).
 #include <type_traits>
@@ -40,10 +43,10 @@ template <bool GATEUP> static __device__ __forceinline__ int weight_row(int r) {
     return GATEUP ? (r >> 5) * 16 + (r & 15) : r;
 }
 
-template <bool GATEUP, int FB, bool FAR>
+// 32 FA weight rows: FA = 8, or 2 for a tile of a quarter of the width
+template <bool GATEUP, int FA, int FB, bool FAR>
 __device__ __forceinline__ int32_t bf16_tile(const FfnArgs &a, const Tile &t, unsigned char *smem, int K, int N, int32_t lo_pos,
                                              int32_t *counter) {
-    constexpr int FA = 8;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     // chunks of 32 rows of A: the first two waves fetch gate rows, the others up rows
@@ -92,6 +95,9 @@ __device__ __forceinline__ int32_t bf16_tile(const FfnArgs &a, const Tile &t, un
     return claimed;
 }
 
+// The tile list: the busy slots' tiles, then those of the cold slots, one row-tile each, at a quarter of
+// the width (so that the launch does not end with a tile that streams 256 weight rows through one CU);
+// or, where every slot's tiles make up a single round, all of them at full width.
 template <bool GATEUP, bool FAR>
 __global__ __launch_bounds__(kNtThreads, 1) void ffn_bf16_kernel(FfnArgs a) {
     __shared__ __attribute__((aligned(16))) unsigned char ffn_smem[kNtLds];
@@ -100,27 +106,53 @@ __global__ __launch_bounds__(kNtThreads, 1) void ffn_bf16_kernel(FfnArgs a) {
     const int32_t *mt_start = a.mt_start + (GATEUP ? 0 : a.nslots + 1);
     const bool small = a.nslots <= TileTables::kMaxSlots;
     if (small) load_tile_tables(a, mt_start, tt);
+    const int32_t hot = ctrl_word(a, tt, small, CTRL_HOT_SLOTS), live = ctrl_word(a, tt, small, CTRL_LIVE_SLOTS);
+    const int32_t lo_pos = first_row(a, tt, small);
     const int K = GATEUP ? a.H : a.I;              // contraction length
     const int N = GATEUP ? a.I : a.H;              // output columns
     constexpr int BN = GATEUP ? 128 : 256;         // output columns per tile
     const int nt = (N + BN - 1) / BN;
-    const int64_t total = (int64_t)mt_start[a.nslots] * nt;
-    const int32_t lo_pos = a.slot_off[a.s_lo];
-    const int32_t fmax = GATEUP ? a.frags_gu : a.frags_dn;
+    const int64_t all = (int64_t)tiles_before(mt_start, tt, small, a.nslots) * nt;
+    const bool one_round = all <= (int64_t)gridDim.x;
+    const int64_t wide = one_round ? all : (int64_t)tiles_before(mt_start, tt, small, hot) * nt;
+    const int64_t total = wide + (one_round ? 0 : (int64_t)(live - hot) * 4 * nt);
     int32_t *const counter = a.ctrl + (GATEUP ? CTRL_WORK_GATEUP : CTRL_WORK_DOWN);
+    auto next = [&](int32_t claimed) {
+        if (threadIdx.x == 0) next_item = (int64_t)gridDim.x + claimed;
+        __syncthreads();
+        return next_item;                          // (written again only after the next tile's barriers)
+    };
     int64_t w = first_tile(total);                 // first tile by position, the rest on demand
-    while (w < total) {
+    const int32_t fmax = GATEUP ? a.frags_gu : a.frags_dn;
+    while (w < wide) {
         Tile t = small ? decode_tile(a, tt, w, nt, BN, fmax) : decode_tile(a, mt_start, w, nt, BN, fmax);
         t.slot = __builtin_amdgcn_readfirstlane(t.slot);
         t.n0 = __builtin_amdgcn_readfirstlane(t.n0);
         t.rows = __builtin_amdgcn_readfirstlane(t.rows);
         int32_t claimed;
-        if (t.rows <= 32) claimed = bf16_tile<GATEUP, 1, FAR>(a, t, ffn_smem, K, N, lo_pos, counter);
-        else if (t.rows <= 64) claimed = bf16_tile<GATEUP, 2, FAR>(a, t, ffn_smem, K, N, lo_pos, counter);
-        else claimed = bf16_tile<GATEUP, 4, FAR>(a, t, ffn_smem, K, N, lo_pos, counter);
-        if (threadIdx.x == 0) next_item = (int64_t)gridDim.x + claimed;
-        __syncthreads();
-        w = next_item;                             // (written again only after the next tile's barriers)
+        if (t.rows <= 32) claimed = bf16_tile<GATEUP, 8, 1, FAR>(a, t, ffn_smem, K, N, lo_pos, counter);
+        else if (t.rows <= 64) claimed = bf16_tile<GATEUP, 8, 2, FAR>(a, t, ffn_smem, K, N, lo_pos, counter);
+        else claimed = bf16_tile<GATEUP, 8, 4, FAR>(a, t, ffn_smem, K, N, lo_pos, counter);
+        w = next(claimed);
+    }
+    while (w < total) {
+        const int64_t u = w - wide;
+        const int32_t pos = hot + (int32_t)(u / (4 * nt));
+        Tile t;
+        t.slot = __builtin_amdgcn_readfirstlane(small ? tt.order[pos] : a.order[pos]);
+        t.pos0 = small ? tt.slot_off[t.slot] : a.slot_off[a.s_lo + t.slot];
+        t.rows = __builtin_amdgcn_readfirstlane((small ? tt.slot_off[t.slot + 1] : a.slot_off[a.s_lo + t.slot + 1]) - t.pos0);
+        t.m0 = 0;
+        t.n0 = __builtin_amdgcn_readfirstlane((int32_t)(u % (4 * nt)) * (BN / 4));
+        int32_t claimed = 0;
+        if (t.n0 < N) {
+            if (t.rows <= 32) claimed = bf16_tile<GATEUP, 2, 1, FAR>(a, t, ffn_smem, K, N, lo_pos, counter);
+            else claimed = bf16_tile<GATEUP, 2, 2, FAR>(a, t, ffn_smem, K, N, lo_pos, counter);
+        } else {                                   // the last quarters may lie past the matrix
+            if (threadIdx.x == 0) claimed = (int32_t)atomicInc(reinterpret_cast<unsigned int *>(counter), 0xffffffffu);
+            __syncthreads();                       // next_item has been read by all
+        }
+        w = next(claimed);
     }
 }
 
@@ -233,8 +265,8 @@ __global__ __launch_bounds__(64 * kF32Waves) void ffn_f32_kernel(FfnArgs a) {
     const int32_t fmax = GATEUP ? a.frags_gu : a.frags_dn;
     const bool small = a.nslots <= TileTables::kMaxSlots;
     if (small) load_tile_tables(a, mt_start, tt);
-    const int64_t total = (int64_t)(small ? tt.mt_start[a.nslots] : mt_start[a.nslots]) * nt;
-    const int32_t lo_pos = small ? tt.slot_off[0] : a.slot_off[a.s_lo];
+    const int64_t total = (int64_t)tiles_before(mt_start, tt, small, a.nslots) * nt;
+    const int32_t lo_pos = first_row(a, tt, small);
     for (int64_t w = blockIdx.x; w < total; w += gridDim.x) {
         const Tile t = small ? decode_tile(a, tt, w, nt, FN, fmax) : decode_tile(a, mt_start, w, nt, FN, fmax);
         if (t.rows <= 16) f32_unit<GATEUP, 1>(a, t, K, N, lo_pos, part);
@@ -249,7 +281,7 @@ hipError_t launch_ffn(const FfnArgs &a, hipStream_t s) {
     if (a.dtype == CRAFT_BF16) {
         const int bn = GATEUP ? 128 : 256;
         const int64_t nt = (N + bn - 1) / bn;
-        const int64_t bound = (a.max_rows / (kFragsBf16 * 32) + a.nslots) * nt;     // most tiles any batch can have
+        const int64_t bound = (a.max_rows / (kFragsBf16 * 32) + 4 * a.nslots) * nt; // most tiles any batch can have
         int64_t grid = std::min<int64_t>(bound, (int64_t)a.num_cu);
         grid = std::max<int64_t>(8, (grid + 7) / 8 * 8);
         // token rows are fetched at 32-bit offsets where x allows it

@@ -5,7 +5,7 @@
 // Both operands travel from global memory straight into LDS (dma_chunk) in 64-wide slabs of 128
 // bytes per row, unpadded, the eight 16-byte pieces of row r in the order piece ^ (r & 7) so that the
 // fragment reads (16 rows at one contraction offset) hit every bank once.  Three stages, four where
-// they fit: while one slab is multiplied the next is on its way or landed and the ones after it are
+// they fit, five or six of the small tiles': while one slab is multiplied the next is on its way or landed and the ones after it are
 // requested, up to 96 KiB in flight per CU.  The fragments of the next 32-wide step are read while the present
 // one is multiplied, across the slab's barrier too: the barrier stands in front of a slab's second
 // step, by when every wave has read all of the slab (its reads are complete at the barrier) and the
@@ -22,7 +22,10 @@ constexpr int kNtThreads = 256;
 // FA, FB: 16-row fragments of A and B per wave
 template <int FA, int FB> constexpr int nt_stage_bytes() { return (FA + FB) * 32 * 128; }
 constexpr int kNtLds = 3 * 12 * 32 * 128;          // three stages of 256 + 128 rows
-template <int FA, int FB> constexpr int nt_stages() { return nt_stage_bytes<FA, FB>() * 4 <= kNtLds ? 4 : 3; }
+template <int FA, int FB> constexpr int nt_stages() {
+    constexpr int bytes = nt_stage_bytes<FA, FB>();
+    return bytes <= 12 << 10 ? 6 : bytes <= 16 << 10 ? 5 : bytes * 4 <= kNtLds ? 4 : 3;
+}
 template <int FA, int FB> constexpr int nt_lds_bytes() { return nt_stages<FA, FB>() * nt_stage_bytes<FA, FB>(); }
 
 // Before an accumulator is read: more idle cycles than a matrix instruction takes to be read, then

@@ -958,6 +958,19 @@ def test_rowmajor_tiles_of_every_height(torch_cuda, H, I):
     _check_rank(torch_cuda, case, 0, packed=False)
 
 
+@pytest.mark.parametrize("H,I,E", [
+    (1608, 776, 40),                 # the last quarters of a tile's columns ragged or past the matrix
+    (1792, 896, 40),                 # whole tiles
+    (1544, 776, 300)])               # more slots than the tile tables in LDS
+def test_rowmajor_cold_slots_of_more_than_a_round(torch_cuda, H, I, E):
+    cfg = synth.scaled(synth.CONFIGS["qwen3"], T=1100, H=H, I=I, E=E, k=2, D=1, replica_slots=0, zipf_s=1.0, profile_batches=2)
+    case = Case(cfg)
+    rows = case.slot_cnt
+    assert (rows > 128).any() and ((rows > 32) & (rows <= 64)).any() and ((rows > 0) & (rows <= 32)).any()
+    assert min((I + 127) // 128, (H + 255) // 256) * (rows > 0).sum() > 256
+    _check_rank(torch_cuda, case, 0, packed=False)
+
+
 @pytest.mark.parametrize("dtype,T,H,I,E", [("bf16", 1100, 200, 72, 24), ("bf16", 40, 200, 72, 6), ("f32", 300, 52, 36, 8)])
 def test_rowmajor_weights_at_any_element(torch_cuda, dtype, T, H, I, E):
     # contiguous views that start one element into an allocation: the same bits as aligned weights
