@@ -254,12 +254,12 @@ double expected_us(const RouterShape &s, int64_t T, int32_t H, int32_t E, int32_
 // all experts up to the CU count (at most 8, at least 4 slabs each; counted in blocks of up to 384 experts,
 // more than 384 are never split), which is what the workspace is sized for; how many of those parts one
 // workgroup takes after another, and how large the tiles are, follows expected_us: tall tiles of 256
-// experts, a workgroup per part, unless another way takes less than 0.84 of their time.  Every other part
+// experts, a workgroup per part, unless another way takes less than 0.82 of their time.  Every other part
 // left to another workgroup is a copy of the scores to write, read and add.  us a call, tall tiles with a
 // workgroup per part / this: H = 7168, E = 256, 512 tokens 21.4 / 13.3, 2048 23.7 / 17.5, 8192 47.9 / 47.5; E = 384, 4096
 // 50.3 / 40.0, 16384 127 / 109; H = 2880, E = 256, 4096 22.7 / 14.9, 8192 30.3 / 23.6.  Over 270 shapes of
 // H = 1024 to 7168, E = 64 to 384 and 150 to 16384 tokens scores and top-k together take 0.94 of the time in the
-// mean, from 0.62 to 1.03 (H = 7168, E = 256, 12000 tokens 77.6 / 80.3).
+// mean, from 0.62 to 1.03.
 RouterShape router_logits_shape(int64_t T, int32_t H, int32_t E, int32_t num_cu, bool workspace) {
     const int nb = E > 512 ? 4 : (E + 127) / 128;
     RouterShape s{1, 256, 1, 1};
@@ -274,7 +274,7 @@ RouterShape router_logits_shape(int64_t T, int32_t H, int32_t E, int32_t num_cu,
     s.nsplit = s.nparts;
     if (T <= kThinBatch || H >= kNtRowLimit || s.nparts == 1) return s;
     RouterShape best = s;
-    double best_us = expected_us(s, T, H, E, num_cu) * 0.84;
+    double best_us = expected_us(s, T, H, E, num_cu) * 0.82;
     for (int tokens = 1; tokens <= 4; tokens *= 2)
         for (int experts = 64; experts <= 256; experts += 64) {
             if (experts > 64 && expert_blocks(E, experts) == expert_blocks(E, experts - 64)) continue;
