@@ -87,7 +87,7 @@ template <> __device__ __forceinline__ u32x2_t zero_fragment<true>() {
 // own step, then the rider's, one instruction for two codes, a quarter of a fragment behind an MFMA.
 // (bf16 weights need no such copy: one placeholder that nothing touches.)  A forward of 16384 tokens at
 // H = 7168, I = 2048 whose GEMMs widened every fragment in front of each half's first use of it,
-// through fp32: 263 us, so 255.
+// through fp32: 263 us, so 251 (255 with the last fragment's share behind the reads from LDS).
 constexpr int wide_fragments(int ngt, bool w8, bool rider) { return w8 ? 2 * ngt + (rider ? 2 : 0) : 1; }
 static __device__ __forceinline__ void widen_quarter(wide_t &to, u32x2_t from, int c) {
     to[c] = c & 1 ? widen_pair<true>(from[c >> 1]) : widen_pair<false>(from[c >> 1]);
@@ -202,8 +202,9 @@ __device__ __forceinline__ void packed_half(uint32_t xnext, Streams &sm,
                 constexpr int RN = (R + 1) % PW;
                 widen_quarter(wide[W8 && f > 0 ? f - 1 : 0], wq[(f > 0 ? f - 1 : 0) >> 1][RN][(f - 1) & 1], c);
             }
-            if (!HI && f == 0) widen_quarter(wide[W8 ? W - 1 : 0], wq[NGT - 1][R][1], c);
-            if (!HI && RIDER && (f == 1 || f == 2)) widen_quarter(wide[W8 && RIDER ? W + f - 1 : 0], wr[RR % RING_R][(f - 1) & 1], c);
+            // (behind the first fragment's matrix instructions go the reads from LDS)
+            if (!HI && f == (W > 2 ? 1 : 0)) widen_quarter(wide[W8 ? W - 1 : 0], wq[NGT - 1][R][1], c);
+            if (!HI && RIDER && f < 2) widen_quarter(wide[W8 && RIDER ? W + f : 0], wr[RR % RING_R][f & 1], c);
         }
     };
 #pragma unroll
