@@ -106,16 +106,17 @@ __global__ __launch_bounds__(kNtThreads, 1) void ffn_bf16_kernel(FfnArgs a) {
     const int32_t *mt_start = a.mt_start + (GATEUP ? 0 : a.nslots + 1);
     const bool small = a.nslots <= TileTables::kMaxSlots;
     if (small) load_tile_tables(a, mt_start, tt);
-    const int32_t hot = ctrl_word(a, tt, small, CTRL_HOT_SLOTS), live = ctrl_word(a, tt, small, CTRL_LIVE_SLOTS);
     const int32_t lo_pos = first_row(a, tt, small);
     const int K = GATEUP ? a.H : a.I;              // contraction length
     const int N = GATEUP ? a.I : a.H;              // output columns
     constexpr int BN = GATEUP ? 128 : 256;         // output columns per tile
     const int nt = (N + BN - 1) / BN;
-    const int64_t all = (int64_t)tiles_before(mt_start, tt, small, a.nslots) * nt;
-    const bool one_round = all <= (int64_t)gridDim.x;
-    const int64_t wide = one_round ? all : (int64_t)tiles_before(mt_start, tt, small, hot) * nt;
-    const int64_t total = wide + (one_round ? 0 : (int64_t)(live - hot) * 4 * nt);
+    int64_t wide = (int64_t)tiles_before(mt_start, tt, small, a.nslots) * nt, total = wide;
+    if (wide > (int64_t)gridDim.x) {
+        const int32_t hot = ctrl_word(a, tt, small, CTRL_HOT_SLOTS);
+        wide = (int64_t)tiles_before(mt_start, tt, small, hot) * nt;
+        total = wide + (int64_t)(ctrl_word(a, tt, small, CTRL_LIVE_SLOTS) - hot) * 4 * nt;
+    }
     int32_t *const counter = a.ctrl + (GATEUP ? CTRL_WORK_GATEUP : CTRL_WORK_DOWN);
     auto next = [&](int32_t claimed) {
         if (threadIdx.x == 0) next_item = (int64_t)gridDim.x + claimed;
@@ -135,9 +136,9 @@ __global__ __launch_bounds__(kNtThreads, 1) void ffn_bf16_kernel(FfnArgs a) {
         else claimed = bf16_tile<GATEUP, 8, 4, FAR>(a, t, ffn_smem, K, N, lo_pos, counter);
         w = next(claimed);
     }
-    while (w < total) {
+    while (__builtin_expect(w < total, 0)) {       // (out of the way of the others' code, which is fetched first)
         const int64_t u = w - wide;
-        const int32_t pos = hot + (int32_t)(u / (4 * nt));
+        const int32_t pos = ctrl_word(a, tt, small, CTRL_HOT_SLOTS) + (int32_t)(u / (4 * nt));
         Tile t;
         t.slot = __builtin_amdgcn_readfirstlane(small ? tt.order[pos] : a.order[pos]);
         t.pos0 = small ? tt.slot_off[t.slot] : a.slot_off[a.s_lo + t.slot];
