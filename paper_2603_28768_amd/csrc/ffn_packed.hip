@@ -31,10 +31,11 @@
 //     hand over four data registers per lane, which the MFMAs' own operand fetches leave no
 //     room for), one barrier per slab.  The contraction loop has no branch around a memory
 //     operation, so the in-order load counter lets all of that stay in flight.
-//   * Under full load a CU gets about 45 GB/s out of L2 whatever it asks for, and a 16-wide
-//     piece of the contraction moves 8 KB of weights plus 1 KB per 32 rows into it: at
-//     256 x 256 the tile needs those bytes about as fast as the MFMAs consume them, below that
-//     it is bound by them.
+//   * What a CU gets from beyond its L2 is about 42 GB/s whatever it has in flight (a cold slot's tile),
+//     95-120 out of L2.  A tile of five fragments or more is not bound by either: it issues its matrix
+//     instructions in 0.86 of the cycles of a slab (1280 of 1480; 2048 of 2380 at eight fragments) at the
+//     1.5-1.85 GHz that the chip's power leaves; with every operand out of L1 a launch takes 0.88 of its
+//     time.
 //   * Weight fragments that a single tile reads (a cold slot's, a rider's, a busy slot's with
 //     one row-tile) are requested with streaming loads, so that the L2 keeps the activation
 //     rows and the weights that several tiles share.
