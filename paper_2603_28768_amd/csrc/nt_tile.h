@@ -40,7 +40,8 @@ template <int FA, int FB> static __device__ __forceinline__ void nt_settle(f32x4
 
 // Rows of this many elements: 256 of them stay inside a 32-bit byte offset.
 constexpr int kNtRowLimit = 1 << 23;
-// abase, bbase: wave-uniform; aoff, boff: the byte offset of a row (0 .. 32 FA - 1, 32 FB - 1) from them.  K: elements
+// abase, bbase: wave-uniform; aoff, boff: the byte offset of a row (0 .. 32 FA - 1, 32 FB - 1) from them, B's also
+// told which chunk of 32 rows it is in (row 32 chunk + threadIdx.x / 8, always).  K: elements
 // per row, a multiple of 8, less than kNtRowLimit.  acc[f][g] += A fragment wa FA + f x B fragment wb FB + g, where wave w of
 // the workgroup is (wa, wb) = (w >> 1, w & 1); element v of lane l is row 4 (l >> 4) + v of A's fragment
 // and row l & 15 of B's.  kbeg, kend: the slabs to take.  Ends with a barrier and nothing in flight.
@@ -60,12 +61,12 @@ static __device__ __forceinline__ void nt_tile(unsigned char *smem, ubase_t abas
     const uint32_t fa0 = fo + (uint32_t)((wave >> 1) * FA * 16 * 128), fb0 = fo + (uint32_t)((FA * 32 + (wave & 1) * FB * 16) * 128);
     if (kbeg >= kend) return;
     uint32_t aoff[FA];
-    decltype(boff_of(0)) boff[FB];                 // 32 or 64 bits
+    decltype(boff_of(0, 0)) boff[FB];              // 32 or 64 bits
     const int lr = (int)threadIdx.x >> 3;          // this lane's row of a 32-row chunk
 #pragma unroll
     for (int i = 0; i < FA; ++i) aoff[i] = (uint32_t)aoff_of(32 * i + lr);
 #pragma unroll
-    for (int i = 0; i < FB; ++i) boff[i] = boff_of(32 * i + lr);
+    for (int i = 0; i < FB; ++i) boff[i] = boff_of(i, 32 * i + lr);
     typedef const bf16x8_t __attribute__((address_space(3))) *lds_frag_t;
     constexpr int NR = FA + FB;                    // requests per slab and fragments per step
     // where this lane reads slab ks; pieces past the rows are read from inside them (zeroed below)
@@ -194,11 +195,11 @@ static __device__ __forceinline__ void nt_tile_unaligned(unsigned char *smem, ub
     constexpr int STAGEB = nt_stage_bytes<FA, FB>();
     const int c = lane & 7, place = lr * 128 + (c ^ (lr & 7)) * 16;
     off_t aoff[FA];
-    decltype(boff_of(0)) boff[FB];
+    decltype(boff_of(0, 0)) boff[FB];
 #pragma unroll
     for (int i = 0; i < FA; ++i) aoff[i] = (off_t)aoff_of(32 * i + lr);
 #pragma unroll
-    for (int i = 0; i < FB; ++i) boff[i] = boff_of(32 * i + lr);
+    for (int i = 0; i < FB; ++i) boff[i] = boff_of(i, 32 * i + lr);
     u16x8_t av[FA], bv[FB];
     // (past the rows or the last slab: read from inside the rows, replaced by zeros on the way into
     // LDS or not used; no branch around a request, the waits count them)

@@ -47,7 +47,7 @@ __global__ __launch_bounds__(kNtThreads) void router_logits_bf16_kernel(RouterAr
     float *dst = a.nsplit > 1 ? a.part + (int64_t)blockIdx.z * a.T * a.E : a.logits;
     // rows past the end are clamped into the matrix (their results are not stored)
     auto eoff = [&](int i) { return (uint32_t)min(i, a.E - 1 - e0) * (uint32_t)a.H * 2u; };
-    auto toff = [&](int i) { return (uint32_t)min((int64_t)i, a.T - 1 - t0) * (uint32_t)a.H * 2u; };
+    auto toff = [&](int, int i) { return (uint32_t)min((int64_t)i, a.T - 1 - t0) * (uint32_t)a.H * 2u; };
     f32x4_t acc[FA][FB];
 #pragma unroll
     for (int f = 0; f < FA; ++f)
