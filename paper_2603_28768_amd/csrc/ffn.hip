@@ -24,8 +24,8 @@
 // in a plain loop).  Taller tiles move less but come out in fewer rounds.  1777 tokens on 17 slots,
 // H = 4096, I = 1536: gate/up 190 -> 117 us, down 84 -> 63 (before: 128 x 128 tiles through registers, one
 // slab ahead).  A cold slot's tile is bound by what one CU gets out of HBM, about 42 GB/s whatever it has in
-// flight: 256 weight rows of 4096 elements take it 50 us.  Where there is more than a round of tiles the cold
-// slots therefore get 64 weight rows a tile; a forward of those 1777 tokens 195 -> 178 us, 1100 tokens 183 -> 158,
+// flight: 256 weight rows of 4096 elements take it 50 us.  Where a launch would end with them the cold
+// slots therefore get 64 weight rows a tile (below); a forward of those 1777 tokens 195 -> 178 us, 1100 tokens 183 -> 158,
 // of 4767 on slots of H = 5120, I = 2048 430 -> 406; without a cold slot the same within 2 %.  With 128 rows a tile 183.
 //
 // fp32 path: units of 16 columns and 32 rows from the same tile list (small configurations).
@@ -105,8 +105,14 @@ __device__ __forceinline__ int32_t bf16_tile(const FfnArgs &a, const Tile &t, un
 }
 
 // The tile list: the busy slots' tiles, then those of the cold slots, one row-tile each, at a quarter of
-// the width (so that the launch does not end with a tile that streams 256 weight rows through one CU);
-// or, where every slot's tiles make up a single round, all of them at full width.
+// the width, so that the launch does not end with a tile that streams 256 weight rows through one CU.  All
+// stay at full width where every tile is in a single round, and where quarters are no gain: where the cold
+// tiles find room beside the last round of the busy ones (276 + 120 tiles of K = 4096 on 256 CUs: a quarter as
+// wide +8.8 us of a forward of 224), and where they are many and short, so that a small tile's fixed part
+// counts (640 + 592 of K = 512: +8.8 us of 230).  264 launches of 300 drawn batches: quarters everywhere cost
+// more than 1 % of the forward in 40 of them, by this rule in 4 (the worst 228 + 36 of K = 1408, 4 %), which
+// keeps 96 % of what they save.
+constexpr int kQuarterLength = 1024;               // contraction from which on a whole round of cold tiles may be quartered
 template <bool GATEUP, bool FAR>
 __global__ __launch_bounds__(kNtThreads, 1) void ffn_bf16_kernel(FfnArgs a) {
     __shared__ __attribute__((aligned(16))) unsigned char ffn_smem[kNtLds];
@@ -123,8 +129,12 @@ __global__ __launch_bounds__(kNtThreads, 1) void ffn_bf16_kernel(FfnArgs a) {
     int64_t wide = (int64_t)tiles_before(mt_start, tt, small, a.nslots) * nt, total = wide;
     if (wide > (int64_t)gridDim.x) {
         const int32_t hot = ctrl_word(a, tt, small, CTRL_HOT_SLOTS);
-        wide = (int64_t)tiles_before(mt_start, tt, small, hot) * nt;
-        total = wide + (int64_t)(ctrl_word(a, tt, small, CTRL_LIVE_SLOTS) - hot) * 4 * nt;
+        const int64_t busy = (int64_t)tiles_before(mt_start, tt, small, hot) * nt, cold = wide - busy, over = busy % gridDim.x;
+        const int64_t room = over ? (int64_t)gridDim.x - over : 0;     // CUs without a tile of the last round of busy ones
+        if (cold > room && cold * kQuarterLength <= (int64_t)gridDim.x * K) {
+            wide = busy;
+            total = busy + 4 * cold;
+        }
     }
     int32_t *const counter = a.ctrl + (GATEUP ? CTRL_WORK_GATEUP : CTRL_WORK_DOWN);
     auto next = [&](int32_t claimed) {

@@ -958,16 +958,28 @@ def test_rowmajor_tiles_of_every_height(torch_cuda, H, I):
     _check_rank(torch_cuda, case, 0, packed=False)
 
 
-@pytest.mark.parametrize("H,I,E", [
-    (1608, 776, 40),                 # the last quarters of a tile's columns ragged or past the matrix
-    (1792, 896, 40),                 # whole tiles
-    (1544, 776, 300)])               # more slots than the tile tables in LDS
-def test_rowmajor_cold_slots_of_more_than_a_round(torch_cuda, H, I, E):
+def _narrow_tiles(rows, K, N, gateup, num_cu=256):
+    # the rule of ffn_bf16_kernel: whether the cold slots' tiles are a quarter as wide
+    nt = -(-N // (128 if gateup else 256))
+    busy, cold = sum(-(-r // 128) for r in rows if r > 64) * nt, sum(0 < r <= 64 for r in rows) * nt
+    room = -busy % num_cu
+    return busy + cold > num_cu and cold > room and cold * 1024 <= num_cu * K
+
+
+@pytest.mark.parametrize("H,I,E,narrow", [
+    (1608, 776, 40, (True, False)),  # the last quarters of gate/up's columns ragged or past the matrix; down many and short
+    (1608, 1032, 40, (True, True)),  # and of down's
+    (1792, 896, 40, (True, True)),   # whole tiles
+    (1544, 776, 300, (True, False)),            # more slots than the tile tables in LDS
+    (1544, 1288, 300, (False, True)),           # gate/up many and short
+    (1288, 1736, 12, (False, False))])          # gate/up's cold tiles fit beside the last round of busy ones
+def test_rowmajor_cold_slots_of_more_than_a_round(torch_cuda, H, I, E, narrow):
     cfg = synth.scaled(synth.CONFIGS["qwen3"], T=1100, H=H, I=I, E=E, k=2, D=1, replica_slots=0, zipf_s=1.0, profile_batches=2)
     case = Case(cfg)
     rows = case.slot_cnt
     assert (rows > 128).any() and ((rows > 32) & (rows <= 64)).any() and ((rows > 0) & (rows <= 32)).any()
-    assert min((I + 127) // 128, (H + 255) // 256) * (rows > 0).sum() > 256
+    assert (I + 127) // 128 * sum(max(1, -(-r // 128)) for r in rows if r > 0) > 256
+    assert (_narrow_tiles(rows, H, I, True), _narrow_tiles(rows, I, H, False)) == narrow
     _check_rank(torch_cuda, case, 0, packed=False)
 
 
