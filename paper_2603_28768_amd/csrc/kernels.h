@@ -90,8 +90,12 @@ struct RouterArgs {
     float *part;              // [nsplit][T][E] partial scores when the contraction is split; may be null
     int32_t nsplit;           // set by the launcher: workgroups per tile
     bool keep_parts;          // with a split contraction: leave the sums to the reader of `part`
-    int32_t nparts = 1;       // set by the launcher: parts of the contraction that are summed by themselves, a multiple of nsplit
-    int32_t eblocks = 1;      // set by the launcher: blocks of experts
+    // set by the launcher, so that no workgroup divides in front of its first request
+    int32_t nparts = 1;       // parts of the contraction that are summed by themselves, a multiple of nsplit
+    int32_t per = 0;          // slabs of a part
+    int32_t share = 0;        // slabs of a workgroup
+    int32_t eblocks = 1;      // blocks of experts
+    uint32_t eblocks_inv = 0; // 2^32 / eblocks, rounded up
 };
 hipError_t launch_router_logits(const RouterArgs &a, hipStream_t s);
 struct RouterShape {

@@ -37,13 +37,14 @@ __global__ __launch_bounds__(kNtThreads) void router_logits_bf16_kernel(RouterAr
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     // workgroups go round the XCDs: the blocks of experts of one tile of tokens meet in one L2
-    const int tile = (int)blockIdx.x / (8 * a.eblocks) * 8 + (int)blockIdx.x % 8, eblock = (int)blockIdx.x / 8 % a.eblocks;
+    const uint32_t eight = blockIdx.x >> 3, group = a.eblocks == 1 ? eight : __umulhi(eight, a.eblocks_inv);
+    const int tile = (int)(group * 8 + (blockIdx.x & 7)), eblock = (int)(eight - group * (uint32_t)a.eblocks);
     const int64_t t0 = (int64_t)tile * (FB * 32);
     const int e0 = eblock * (FA * 32);
     if (t0 >= a.T) return;
     // this workgroup's share of the contraction (may be empty)
-    const int nk = (a.H + GK - 1) / GK, per = (nk + a.nparts - 1) / a.nparts, share = per * (a.nparts / a.nsplit);
-    const int kbeg = min(nk, (int)blockIdx.z * share), kend = min(nk, kbeg + share);
+    const int nk = (a.H + GK - 1) / GK;
+    const int kbeg = min(nk, (int)blockIdx.z * a.share), kend = min(nk, kbeg + a.share);
     float *dst = a.nsplit > 1 ? a.part + (int64_t)blockIdx.z * a.T * a.E : a.logits;
     // rows past the end are clamped into the matrix (their results are not stored)
     auto eoff = [&](int i) { return (uint32_t)min(i, a.E - 1 - e0) * (uint32_t)a.H * 2u; };
@@ -61,10 +62,10 @@ __global__ __launch_bounds__(kNtThreads) void router_logits_bf16_kernel(RouterAr
         for (int f = 0; f < FA; ++f)
 #pragma unroll
             for (int g = 0; g < FB; ++g) sum[f][g] = (f32x4_t)(0.0f);
-        int cut = kbeg + per - 1;
+        int cut = kbeg + a.per - 1;
         nt_tile<FA, FB>(gate_smem, wbase, eoff, xbase, toff, a.H, kbeg, kend, acc, [&](int ks) __attribute__((always_inline)) {
             if (ks != cut || ks == kend - 1) return;
-            cut += per;
+            cut += a.per;
             nt_settle(acc);
 #pragma unroll
             for (int f = 0; f < FA; ++f)
@@ -166,8 +167,8 @@ __global__ __launch_bounds__(64 * kThinWaves) void router_thin_kernel(RouterArgs
     __shared__ f32x4_t sums[kThinWaves * (kThinTokens / 16) * 64];
     const int64_t t0 = (int64_t)blockIdx.y * kThinTokens;
     const int e0 = blockIdx.x * 16;
-    const int nk = (a.H + GK - 1) / GK, per = (nk + a.nsplit - 1) / a.nsplit;
-    const int kbeg = min(nk, (int)blockIdx.z * per), kend = min(nk, kbeg + per);
+    const int nk = (a.H + GK - 1) / GK;
+    const int kbeg = min(nk, (int)blockIdx.z * a.share), kend = min(nk, kbeg + a.share);
     float *dst = a.nsplit > 1 ? a.part + (int64_t)blockIdx.z * a.T * a.E : a.logits;
     const int64_t tokens = a.T - t0;
     if (tokens <= 16) thin_tile<1>(a, t0, e0, kbeg, kend, dst, sums);
@@ -212,6 +213,7 @@ template <int FA, int FB>
 hipError_t launch_bf16(const RouterArgs &a, hipStream_t s) {
     RouterArgs b = a;
     b.eblocks = (a.E + FA * 32 - 1) / (FA * 32);
+    b.eblocks_inv = (uint32_t)((((uint64_t)1 << 32) + b.eblocks - 1) / b.eblocks);     // (exact for fewer than 2^32 / eblocks eights)
     const dim3 grid((unsigned)((a.T + FB * 32 * 8 - 1) / (FB * 32 * 8) * 8 * b.eblocks), 1, (unsigned)a.nsplit);
     if (a.nparts > a.nsplit) hipLaunchKernelGGL((router_logits_bf16_kernel<FA, FB, true>), grid, dim3(kNtThreads), 0, s, b);
     else hipLaunchKernelGGL((router_logits_bf16_kernel<FA, FB, false>), grid, dim3(kNtThreads), 0, s, b);
@@ -301,6 +303,9 @@ hipError_t launch_router_logits(const RouterArgs &a, hipStream_t s) {
     RouterArgs b = a;
     b.nsplit = nsplit;
     b.nparts = shape.nparts;
+    const int nk = (a.H + GK - 1) / GK;
+    b.per = (nk + b.nparts - 1) / b.nparts;
+    b.share = b.per * (b.nparts / b.nsplit);
     hipError_t err;
     if (a.T <= kThinBatch || a.H >= kNtRowLimit) {         // (thin tiles take rows of any length)
         const dim3 grid((unsigned)((a.E + 15) / 16), (unsigned)((a.T + kThinTokens - 1) / kThinTokens), (unsigned)nsplit);
