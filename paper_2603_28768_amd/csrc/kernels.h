@@ -95,7 +95,8 @@ struct RouterArgs {
     int32_t per = 0;          // slabs of a part
     int32_t share = 0;        // slabs of a workgroup
     int32_t eblocks = 1;      // blocks of experts
-    uint32_t eblocks_inv = 0; // 2^32 / eblocks, rounded up
+    int32_t tiles = 0;        // tiles of tokens
+    uint32_t eblocks_inv = 0, tiles_inv = 0;       // 2^32 / eblocks, 2^32 / tiles, rounded up
 };
 hipError_t launch_router_logits(const RouterArgs &a, hipStream_t s);
 struct RouterShape {

@@ -36,16 +36,26 @@ __global__ __launch_bounds__(kNtThreads) void router_logits_bf16_kernel(RouterAr
     __shared__ __attribute__((aligned(16))) unsigned char gate_smem[nt_lds_bytes<FA, FB>()];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    // workgroups go round the XCDs: the blocks of experts of one tile of tokens meet in one L2
-    const uint32_t eight = blockIdx.x >> 3, group = a.eblocks == 1 ? eight : __umulhi(eight, a.eblocks_inv);
-    const int tile = (int)(group * 8 + (blockIdx.x & 7)), eblock = (int)(eight - group * (uint32_t)a.eblocks);
+    // Workgroups go round the XCDs: (tile of tokens, split) by (tile, split), so that a few tiles reach all of
+    // them, and the blocks of experts of one, which read the same activations, one behind the other in one L2.
+    // (With the splits of a tile in one L2, 2 tiles of 150 tokens kept to two XCDs: H = 2048, E = 160 9.8 us, so 9.0.)
+    uint32_t tile = blockIdx.x, split = blockIdx.z, eblock = 0;
+    if (a.eblocks > 1) {
+        const uint32_t eight = blockIdx.x >> 3, group = __umulhi(eight, a.eblocks_inv);
+        eblock = eight - group * (uint32_t)a.eblocks;
+        tile = group * 8 + (blockIdx.x & 7);
+        if (a.nsplit > 1) {
+            split = __umulhi(tile, a.tiles_inv);
+            tile -= split * (uint32_t)a.tiles;
+        }
+    }
     const int64_t t0 = (int64_t)tile * (FB * 32);
-    const int e0 = eblock * (FA * 32);
-    if (t0 >= a.T) return;
+    const int e0 = (int)eblock * (FA * 32);
+    if (t0 >= a.T || split >= (uint32_t)a.nsplit) return;          // (the last eight are not all there)
     // this workgroup's share of the contraction (may be empty)
     const int nk = (a.H + GK - 1) / GK;
-    const int kbeg = min(nk, (int)blockIdx.z * a.share), kend = min(nk, kbeg + a.share);
-    float *dst = a.nsplit > 1 ? a.part + (int64_t)blockIdx.z * a.T * a.E : a.logits;
+    const int kbeg = min(nk, (int)split * a.share), kend = min(nk, kbeg + a.share);
+    float *dst = a.nsplit > 1 ? a.part + (int64_t)split * a.T * a.E : a.logits;
     // rows past the end are clamped into the matrix (their results are not stored)
     auto eoff = [&](int i) { return (uint32_t)min(i, a.E - 1 - e0) * (uint32_t)a.H * 2u; };
     auto toff = [&](int, int i) { return (uint32_t)min((int64_t)i, a.T - 1 - t0) * (uint32_t)a.H * 2u; };
@@ -213,8 +223,18 @@ template <int FA, int FB>
 hipError_t launch_bf16(const RouterArgs &a, hipStream_t s) {
     RouterArgs b = a;
     b.eblocks = (a.E + FA * 32 - 1) / (FA * 32);
-    b.eblocks_inv = (uint32_t)((((uint64_t)1 << 32) + b.eblocks - 1) / b.eblocks);     // (exact for fewer than 2^32 / eblocks eights)
-    const dim3 grid((unsigned)((a.T + FB * 32 * 8 - 1) / (FB * 32 * 8) * 8 * b.eblocks), 1, (unsigned)a.nsplit);
+    const int64_t tiles = (a.T + FB * 32 - 1) / (FB * 32), units = tiles * a.nsplit;
+    dim3 grid((unsigned)tiles, 1, (unsigned)a.nsplit);
+    if (b.eblocks > 1) {
+        // the quotients by these are exact: fewer than 2^21 eights by up to 16 blocks, and a split launch has two
+        // tiles or more and fewer than 4 num_cu + 8 units
+        static_assert(kThinBatch >= 32 * 4, "tiles_inv of one tile");
+        auto inverse = [](int64_t n) { return (uint32_t)((((uint64_t)1 << 32) + (uint64_t)n - 1) / (uint64_t)n); };
+        b.tiles = (int32_t)tiles;
+        b.eblocks_inv = inverse(b.eblocks);
+        b.tiles_inv = inverse(tiles);
+        grid = dim3((unsigned)((units + 7) / 8 * 8 * b.eblocks), 1, 1);
+    }
     if (a.nparts > a.nsplit) hipLaunchKernelGGL((router_logits_bf16_kernel<FA, FB, true>), grid, dim3(kNtThreads), 0, s, b);
     else hipLaunchKernelGGL((router_logits_bf16_kernel<FA, FB, false>), grid, dim3(kNtThreads), 0, s, b);
     return hipGetLastError();
