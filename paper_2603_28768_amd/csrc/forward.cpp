@@ -28,7 +28,7 @@ struct Layout {
 int cached_num_cu();
 
 size_t gate_workspace_bytes(int32_t dtype, int64_t T, int32_t H, int32_t E) {
-    const int nparts = dtype == CRAFT_BF16 && T > 0 ? router_logits_shape(T, H, E, cached_num_cu(), true).nparts : 1;
+    const int nparts = dtype == CRAFT_BF16 && T > 0 ? router_logits_parts(T, H, E, cached_num_cu()) : 1;
     return nparts > 1 ? (size_t)nparts * (size_t)T * (size_t)E * sizeof(float) : 0;
 }
 
@@ -668,9 +668,8 @@ craft_status forward_on(const craft_plan_t *plan, int32_t layer, int32_t rank, c
         float *own = reinterpret_cast<float *>(ws + L.gate_logits);
         RouterArgs ga{a->dtype, a->x, a->w_router, a->T, a->H, E, own, cached_num_cu(),
                       L.gate_ws_bytes ? reinterpret_cast<float *>(ws + L.gate_ws) : nullptr, 1, E <= 384};
-        if (launch_router_logits(ga, s) != hipSuccess) return CRAFT_EHIP;
+        if (launch_router_logits(ga, s, &nparts) != hipSuccess) return CRAFT_EHIP;
         // a split gate's partial scores are added by the routing kernel
-        nparts = ga.keep_parts && L.gate_ws_bytes ? router_logits_shape(a->T, a->H, E, cached_num_cu(), true).nsplit : 1;
         logits = nparts > 1 ? ga.part : own;
     }
     // 1 route (+ per-block ranks and counts); user copies of ids / weights are written by the

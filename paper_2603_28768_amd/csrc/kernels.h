@@ -98,7 +98,10 @@ struct RouterArgs {
     int32_t tiles = 0;        // tiles of tokens
     uint32_t eblocks_inv = 0, tiles_inv = 0;       // 2^32 / eblocks, 2^32 / tiles, rounded up
 };
-hipError_t launch_router_logits(const RouterArgs &a, hipStream_t s);
+// nsplit: if not null, the copies of the scores left in `part` with keep_parts (1: none, they are in `logits`)
+hipError_t launch_router_logits(const RouterArgs &a, hipStream_t s, int *nsplit = nullptr);
+// Parts the contraction is summed in with a workspace, which is sized for them.
+int router_logits_parts(int64_t T, int32_t H, int32_t E, int32_t num_cu);
 struct RouterShape {
     int tokens;               // 32-token fragments of a tile
     int experts;              // most experts of a tile

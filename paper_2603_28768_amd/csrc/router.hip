@@ -271,29 +271,35 @@ double expected_us(const RouterShape &s, int64_t T, int32_t H, int32_t E, int32_
 
 }  // namespace
 
+// With a workspace the contraction is summed in as many parts as bring tall tiles of all experts up to the CU
+// count (at most 8, at least 4 slabs each; more than 384 experts are never split).  Asked by every call and
+// every forward for the size of the workspace, which the tile choice below (0.3 us of host time) does not change.
+int router_logits_parts(int64_t T, int32_t H, int32_t E, int32_t num_cu) {
+    if (E > 384) return 1;
+    const int64_t tiles = (T + 127) / 128;
+    const int nk = (H + GK - 1) / GK;
+    int parts = 1;
+    while (parts < 8 && tiles * parts * 2 <= num_cu && nk / (parts * 2) >= 4) parts *= 2;
+    return parts;
+}
+
 // The tile and the split of the contraction for a shape.  Without a workspace: short tiles, as many as
-// there are CUs if possible.  With one, the contraction is summed in as many parts as bring tall tiles of
-// all experts up to the CU count (at most 8, at least 4 slabs each; counted in blocks of up to 384 experts,
-// more than 384 are never split), which is what the workspace is sized for; how many of those parts one
-// workgroup takes after another, and how large the tiles are, follows expected_us: tall tiles of 256
-// experts, a workgroup per part, unless another way takes less than 0.82 of their time.  Every other part
-// left to another workgroup is a copy of the scores to write, read and add.  us a call, tall tiles with a
+// there are CUs if possible.  With one: how many of the parts one workgroup takes after another, and how
+// large the tiles are, follows expected_us: tall tiles of 256 experts, a workgroup per part, unless another
+// way takes less than 0.82 of their time.  Every other part left to another workgroup is a copy of the scores
+// to write, read and add.  us a call, tall tiles with a
 // workgroup per part / this: H = 7168, E = 256, 512 tokens 21.4 / 13.3, 2048 23.7 / 17.5, 8192 47.9 / 47.5; E = 384, 4096
 // 50.3 / 40.0, 16384 127 / 109; H = 2880, E = 256, 4096 22.7 / 14.9, 8192 30.3 / 23.6.  Over 270 shapes of
 // H = 1024 to 7168, E = 64 to 384 and 150 to 16384 tokens scores and top-k together take 0.94 of the time in the
 // mean, from 0.62 to 1.03.
 RouterShape router_logits_shape(int64_t T, int32_t H, int32_t E, int32_t num_cu, bool workspace) {
-    const int nb = E > 512 ? 4 : (E + 127) / 128;
     RouterShape s{1, 256, 1, 1};
-    if (!workspace || nb > 3) {
-        s.tokens = nb <= 3 && (T + 63) / 64 >= (int64_t)num_cu ? 2 : 1;
+    if (!workspace || E > 384) {
+        s.tokens = E <= 384 && (T + 63) / 64 >= (int64_t)num_cu ? 2 : 1;
         return s;
     }
     s.tokens = 4;
-    const int64_t tiles = (T + 127) / 128 * ((E + nb * 128 - 1) / (nb * 128));
-    const int nk = (H + GK - 1) / GK;
-    while (s.nparts < 8 && tiles * s.nparts * 2 <= num_cu && nk / (s.nparts * 2) >= 4) s.nparts *= 2;
-    s.nsplit = s.nparts;
+    s.nparts = s.nsplit = router_logits_parts(T, H, E, num_cu);
     if (T <= kThinBatch || H >= kNtRowLimit || s.nparts == 1) return s;
     RouterShape best = s;
     double best_us = expected_us(s, T, H, E, num_cu) * 0.82;
@@ -311,7 +317,8 @@ RouterShape router_logits_shape(int64_t T, int32_t H, int32_t E, int32_t num_cu,
     return best;
 }
 
-hipError_t launch_router_logits(const RouterArgs &a, hipStream_t s) {
+hipError_t launch_router_logits(const RouterArgs &a, hipStream_t s, int *nsplit_out) {
+    if (nsplit_out) *nsplit_out = 1;
     if (a.T == 0) return hipSuccess;
     if (a.dtype == CRAFT_F32) {
         const int64_t n = a.T * a.E;
@@ -320,6 +327,7 @@ hipError_t launch_router_logits(const RouterArgs &a, hipStream_t s) {
     }
     const RouterShape shape = router_logits_shape(a.T, a.H, a.E, a.num_cu, a.part != nullptr);
     const int nxf = shape.tokens, nsplit = shape.nsplit;
+    if (nsplit_out && a.keep_parts) *nsplit_out = nsplit;
     RouterArgs b = a;
     b.nsplit = nsplit;
     b.nparts = shape.nparts;
