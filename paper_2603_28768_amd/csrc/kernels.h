@@ -94,7 +94,7 @@ struct RouterArgs {
     int32_t nparts = 1;       // parts of the contraction that are summed by themselves, a multiple of nsplit
     int32_t per = 0;          // slabs of a part
     int32_t share = 0;        // slabs of a workgroup
-    int32_t eblocks = 1;      // blocks of experts
+    int32_t eblocks = 0;      // blocks of experts, where those of a tile are to meet in one XCD; 0: numbered by the grid
     int32_t tiles = 0;        // tiles of tokens
     uint32_t eblocks_inv = 0, tiles_inv = 0;       // 2^32 / eblocks, 2^32 / tiles, rounded up
 };

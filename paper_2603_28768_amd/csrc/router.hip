@@ -37,10 +37,11 @@ __global__ __launch_bounds__(kNtThreads) void router_logits_bf16_kernel(RouterAr
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     // Workgroups go round the XCDs: (tile of tokens, split) by (tile, split), so that a few tiles reach all of
-    // them, and the blocks of experts of one, which read the same activations, one behind the other in one L2.
-    // (With the splits of a tile in one L2, 2 tiles of 150 tokens kept to two XCDs: H = 2048, E = 160 9.8 us, so 9.0.)
-    uint32_t tile = blockIdx.x, split = blockIdx.z, eblock = 0;
-    if (a.eblocks > 1) {
+    // them, and the blocks of experts of one, which read the same activations, one behind the other in one L2
+    // (launch_bf16 says when).  (With the splits of a tile in one L2, 2 tiles of 150 tokens kept to two XCDs:
+    // H = 2048, E = 160 9.8 us, so 9.0.)
+    uint32_t tile = blockIdx.x, split = blockIdx.z, eblock = blockIdx.y;
+    if (a.eblocks != 0) {
         const uint32_t eight = blockIdx.x >> 3, group = __umulhi(eight, a.eblocks_inv);
         eblock = eight - group * (uint32_t)a.eblocks;
         tile = group * 8 + (blockIdx.x & 7);
@@ -222,18 +223,28 @@ void launch_reduce(const RouterArgs &a, int nsplit, int64_t n, hipStream_t s) {
 template <int FA, int FB>
 hipError_t launch_bf16(const RouterArgs &a, hipStream_t s) {
     RouterArgs b = a;
-    b.eblocks = (a.E + FA * 32 - 1) / (FA * 32);
     const int64_t tiles = (a.T + FB * 32 - 1) / (FB * 32), units = tiles * a.nsplit;
-    dim3 grid((unsigned)tiles, 1, (unsigned)a.nsplit);
-    if (b.eblocks > 1) {
+    const int eblocks = (a.E + FA * 32 - 1) / (FA * 32);
+    dim3 grid((unsigned)tiles, (unsigned)eblocks, (unsigned)a.nsplit);
+    // The blocks of experts of a tile meet in one L2 unless some XCD would get a round of workgroups more for
+    // it (10266 tokens of H = 4096, E = 300, 81 tiles x 3 blocks: 62.9 us, one block after another 43.2; 2280 of
+    // H = 7168, E = 130 17.7 / 23.7).  A contraction in one part comes out in several rounds of workgroups: there
+    // one block follows another, whose rows then stay in L2, as long as the memory-side cache holds the activations
+    // for the next block (E = 384, 19060 tokens of H = 1024 38.9 / 32.8, 18555 of 5120 149 / 136, 32764 of 6144 241 / 272).
+    constexpr int fit = (160 << 10) / nt_lds_bytes<FA, FB>();      // workgroups a CU has LDS for
+    const int at_once = fit * (a.num_cu > 8 ? a.num_cu / 8 : 1);   // and an XCD
+    const bool meet = eblocks > 1 && (a.nparts > 1 ? ((units + 7) / 8 * eblocks + at_once - 1) / at_once <= (units * eblocks + 8 * at_once - 1) / (8 * at_once)
+                                                   : a.T * a.H * 2 > ((int64_t)220 << 20));
+    if (meet) {
         // the quotients by these are exact: fewer than 2^21 eights by up to 16 blocks, and a split launch has two
         // tiles or more and fewer than 4 num_cu + 8 units
         static_assert(kThinBatch >= 32 * 4, "tiles_inv of one tile");
         auto inverse = [](int64_t n) { return (uint32_t)((((uint64_t)1 << 32) + (uint64_t)n - 1) / (uint64_t)n); };
+        b.eblocks = eblocks;
         b.tiles = (int32_t)tiles;
-        b.eblocks_inv = inverse(b.eblocks);
+        b.eblocks_inv = inverse(eblocks);
         b.tiles_inv = inverse(tiles);
-        grid = dim3((unsigned)((units + 7) / 8 * 8 * b.eblocks), 1, 1);
+        grid = dim3((unsigned)((units + 7) / 8 * 8 * eblocks), 1, 1);
     }
     if (a.nparts > a.nsplit) hipLaunchKernelGGL((router_logits_bf16_kernel<FA, FB, true>), grid, dim3(kNtThreads), 0, s, b);
     else hipLaunchKernelGGL((router_logits_bf16_kernel<FA, FB, false>), grid, dim3(kNtThreads), 0, s, b);

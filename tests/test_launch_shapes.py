@@ -140,6 +140,17 @@ def test_a_gate_of_few_tiles_starts_no_other_workgroups(launches_of):
         assert [l[1] for l in launches if "router_logits" in l[0]] == [groups], (T, E, H, launches)
 
 
+def test_the_blocks_of_experts_of_a_gate_in_one_part_meet_only_past_the_cache(launches_of):
+    # tiles of 64 tokens x 256 experts in one part: by the grid (tiles x blocks) while 220 MiB hold the
+    # activations, padded to eight tiles beyond
+    most = (220 << 20) // (2 * 4096)
+    shapes = [(most, 384, 4096, (most + 63) // 64 * 2), (most + 1, 384, 4096, ((most + 64) // 64 + 7) // 8 * 8 * 2),
+              (16401, 300, 1024, 257 * 2)]
+    found = launches_of(*[dict(dtype="bf16", T=T, H=H, I=64, E=E, k=4, D=32, gate=True) for T, E, H, _ in shapes])
+    for (T, E, H, groups), launches in zip(shapes, found):
+        assert [l[1] for l in launches if "router_logits" in l[0]] == [groups], (T, E, H, launches)
+
+
 DIRECT, SCAN = ["prefix_kernel", "dispatch_direct_kernel"], ["scan_kernel", "dispatch_kernel"]
 
 
