@@ -22,10 +22,8 @@ constexpr int kNtThreads = 256;
 // FA, FB: 16-row fragments of A and B per wave
 template <int FA, int FB> constexpr int nt_stage_bytes() { return (FA + FB) * 32 * 128; }
 constexpr int kNtLds = 3 * 12 * 32 * 128;          // three stages of 256 + 128 rows
-template <int FA, int FB> constexpr int nt_stages() {
-    constexpr int bytes = nt_stage_bytes<FA, FB>();
-    return bytes <= 12 << 10 ? 6 : bytes <= 16 << 10 ? 5 : bytes * 4 <= kNtLds ? 4 : 3;
-}
+constexpr int nt_stages_of(int bytes) { return bytes <= 12 << 10 ? 6 : bytes <= 16 << 10 ? 5 : bytes * 4 <= kNtLds ? 4 : 3; }
+template <int FA, int FB> constexpr int nt_stages() { return nt_stages_of(nt_stage_bytes<FA, FB>()); }
 template <int FA, int FB> constexpr int nt_lds_bytes() { return nt_stages<FA, FB>() * nt_stage_bytes<FA, FB>(); }
 
 // Before an accumulator is read: more idle cycles than a matrix instruction takes to be read, then

@@ -22,9 +22,9 @@ namespace craft {
 namespace {
 
 // Tokens up to which the gate is read by thin tiles: few tall ones leave CUs without work (8 tokens:
-// 23 us for scores of E = 256, H = 7168, thin 4.4).  From there on it depends on E, thin / tall with the
-// sum of the parts at 192 tokens: E = 256 16.5 / 19.4, E = 128 14.4 / 13.5, E = 384 21.4 / 16.6; at 1024
-// tokens 45 / 22.
+// 23 us for scores of E = 256, H = 7168, thin 4.4).  Past it the small ones of the tiles below are the faster
+// ones at every shape tried (129 tokens, H = 7168, us thin / tiles: E = 64 9.8 / 9.2, E = 256 14.7 / 7.3, E = 384
+// 15.8 / 7.7); where below it they begin to be has not been measured.
 constexpr int kThinBatch = 128;
 constexpr int GK = 64;                  // contraction slab
 typedef unsigned int gu32x4_t __attribute__((ext_vector_type(4)));
@@ -226,11 +226,12 @@ hipError_t launch_bf16(const RouterArgs &a, hipStream_t s) {
     const int64_t tiles = (a.T + FB * 32 - 1) / (FB * 32), units = tiles * a.nsplit;
     const int eblocks = (a.E + FA * 32 - 1) / (FA * 32);
     dim3 grid((unsigned)tiles, (unsigned)eblocks, (unsigned)a.nsplit);
-    // The blocks of experts of a tile meet in one L2 unless some XCD would get a round of workgroups more for
-    // it (10266 tokens of H = 4096, E = 300, 81 tiles x 3 blocks: 62.9 us, one block after another 43.2; 2280 of
-    // H = 7168, E = 130 17.7 / 23.7).  A contraction in one part comes out in several rounds of workgroups: there
+    // The blocks of experts of a tile meet in one L2 (2280 tokens of H = 7168, E = 130: 17.7 us a call, one block
+    // after another 23.7) unless some XCD would get a round of workgroups more for it (10266 of H = 4096, E = 300, 81
+    // tiles x 3 blocks: 62.9, so 43.2).  A contraction in one part comes out in several rounds of workgroups: there
     // one block follows another, whose rows then stay in L2, as long as the memory-side cache holds the activations
-    // for the next block (E = 384, 19060 tokens of H = 1024 38.9 / 32.8, 18555 of 5120 149 / 136, 32764 of 6144 241 / 272).
+    // for the next block (E = 384, us meeting / one after another: 19060 tokens of H = 1024 38.9 / 32.8, 18555 of 5120
+    // 149 / 136, 32764 of 6144 241 / 272).
     constexpr int fit = (160 << 10) / nt_lds_bytes<FA, FB>();      // workgroups a CU has LDS for
     const int at_once = fit * (a.num_cu > 8 ? a.num_cu / 8 : 1);   // and an XCD
     const bool meet = eblocks > 1 && (a.nparts > 1 ? ((units + 7) / 8 * eblocks + at_once - 1) / at_once <= (units * eblocks + 8 * at_once - 1) / (8 * at_once)
@@ -266,18 +267,20 @@ int expert_fragments(int32_t E, int most) {
     const int rows = (E + expert_blocks(E, most) - 1) / expert_blocks(E, most);
     return rows <= 64 ? 2 : rows <= 128 ? 4 : rows <= 192 ? 6 : 8;
 }
-// Expected us of a launch and what follows it: a slab takes a workgroup the longer of its matrix instructions
-// and of what it loads, more than one workgroup per CU share it, and parts in memory are written, read and
-// added by a launch of their own.  Fitted to 1700 calls over 123 shapes (below).
+// Expected us of a launch and of the one that adds its parts.  A CU takes as many workgroups at a time as it has
+// LDS for, each bound by what it loads (more so with three stages of LDS than with more) and slowed down by the
+// others; parts in memory are written, read and added.  Fitted to 1030 shapes (H = 512 to 8192, E = 48 to 384,
+// 129 to 16384 tokens; every tile and split of each, timed without host time between the calls): off by 16 %
+// (rms), on 350 others as well.
 double expected_us(const RouterShape &s, int64_t T, int32_t H, int32_t E, int32_t num_cu) {
     const int fa = expert_fragments(E, s.experts), nk = (H + GK - 1) / GK;
-    const double wgs = (double)((T + 32 * s.tokens - 1) / (32 * s.tokens)) * expert_blocks(E, s.experts) * s.nsplit;
+    const int stage = (fa + s.tokens) * 32 * 128, stages = nt_stages_of(stage), fit = (160 << 10) / (stages * stage);
+    const int64_t wgs = (T + 32 * s.tokens - 1) / (32 * s.tokens) * expert_blocks(E, s.experts) * s.nsplit, per_cu = (wgs + num_cu - 1) / num_cu;
     const double slabs = (double)((nk + s.nparts - 1) / s.nparts) * (s.nparts / s.nsplit);
-    double slab = std::max(0.0357 * fa * s.tokens, 0.0643 * (fa + s.tokens) + 0.021);
-    if (wgs > num_cu) slab *= 1.37;
-    const double load = std::max((wgs > num_cu ? wgs / num_cu : 1.0) * (10.5 + slabs * slab), (double)T * H * 2e-6 / 11.9);
-    const double mb = (double)T * E * 4e-6;
-    return (load + (s.nsplit > 1 ? s.nsplit * mb * 0.66 + 4.75 : mb * 0.33)) * (s.nsplit == 1 && s.nparts > 2 ? 1.10 : 1.0);
+    const double slab = 0.061 * (fa + s.tokens) * (stages == 3 ? 1.115 : 1.0);
+    auto at_once = [&](int64_t n) { return n > 0 ? 3.1 + slabs * slab * (0.27 + 0.73 * (double)n) : 0.0; };
+    const double load = (double)(per_cu / fit) * at_once(fit) + at_once(per_cu % fit), mb = (double)T * E * 4e-6;
+    return (load + (s.nsplit > 1 ? s.nsplit * mb * 0.51 + 2.1 : mb * 0.1)) * (s.nparts > s.nsplit ? 1.026 : 1.0);
 }
 
 }  // namespace
@@ -296,13 +299,13 @@ int router_logits_parts(int64_t T, int32_t H, int32_t E, int32_t num_cu) {
 
 // The tile and the split of the contraction for a shape.  Without a workspace: short tiles, as many as
 // there are CUs if possible.  With one: how many of the parts one workgroup takes after another, and how
-// large the tiles are, follows expected_us: tall tiles of 256 experts, a workgroup per part, unless another
-// way takes less than 0.82 of their time.  Every other part left to another workgroup is a copy of the scores
-// to write, read and add.  us a call, tall tiles with a
-// workgroup per part / this: H = 7168, E = 256, 512 tokens 21.4 / 13.3, 2048 23.7 / 17.5, 8192 47.9 / 47.5; E = 384, 4096
-// 50.3 / 40.0, 16384 127 / 109; H = 2880, E = 256, 4096 22.7 / 14.9, 8192 30.3 / 23.6.  Over 270 shapes of
-// H = 1024 to 7168, E = 64 to 384 and 150 to 16384 tokens scores and top-k together take 0.94 of the time in the
-// mean, from 0.62 to 1.03.
+// large the tiles are, follows expected_us: tall tiles of 256 experts, a workgroup per part, unless another way
+// is expected to take less than 0.95 of their time.  Every other part left to another workgroup is a copy of the
+// scores to write, read and add.  us a call, tall tiles with a workgroup per part / this: H = 7168, E = 256, 600 tokens
+// 19.7 / 12.0, 2048 22.4 / 17.3; E = 384, 4096 49.2 / 40.0, 16384 129 / 112; H = 2880, E = 256, 4096 23.1 / 14.9, 8192
+// 30.9 / 24.6.  Over 300 shapes (H = 1024 to 7168, E = 64 to 384, 150 to 16384 tokens) it takes 0.74 of the time of tall
+// tiles in the mean, from 0.40 to 1.06 (8192 tokens of H = 4096, E = 128: 24.1 / 25.4), over 500 drawn ones 0.77, up to
+// 1.13 (8703 of H = 4880, E = 256: 56.7 / 64.2).
 RouterShape router_logits_shape(int64_t T, int32_t H, int32_t E, int32_t num_cu, bool workspace) {
     RouterShape s{1, 256, 1, 1};
     if (!workspace || E > 384) {
@@ -313,7 +316,7 @@ RouterShape router_logits_shape(int64_t T, int32_t H, int32_t E, int32_t num_cu,
     s.nparts = s.nsplit = router_logits_parts(T, H, E, num_cu);
     if (T <= kThinBatch || H >= kNtRowLimit || s.nparts == 1) return s;
     RouterShape best = s;
-    double best_us = expected_us(s, T, H, E, num_cu) * 0.82;
+    double best_us = expected_us(s, T, H, E, num_cu) * 0.95;
     for (int tokens = 1; tokens <= 4; tokens *= 2)
         for (int experts = 64; experts <= 256; experts += 64) {
             if (experts > 64 && expert_blocks(E, experts) == expert_blocks(E, experts - 64)) continue;
