@@ -211,6 +211,10 @@ __global__ __launch_bounds__(256) void router_logits_f32_kernel(RouterArgs a) {
     a.logits[o] = s;
 }
 
+// Tiles whose workgroups may take several parts.  The others were never or hardly ever the ones expected to be
+// fastest (5 million shapes of H = 8 to 16384), and the largest keeps 380 registers for the sums.
+constexpr bool parted_tile(int fa, int tokens) { return fa == 2 || (fa <= 6 && tokens >= 2); }
+
 template <typename V>
 void launch_reduce(const RouterArgs &a, int nsplit, int64_t n, hipStream_t s) {
     const dim3 grid((unsigned)((n + 255) / 256)), block(256);
@@ -247,8 +251,12 @@ hipError_t launch_bf16(const RouterArgs &a, hipStream_t s) {
         b.tiles_inv = inverse(tiles);
         grid = dim3((unsigned)((units + 7) / 8 * 8 * eblocks), 1, 1);
     }
-    if (a.nparts > a.nsplit) hipLaunchKernelGGL((router_logits_bf16_kernel<FA, FB, true>), grid, dim3(kNtThreads), 0, s, b);
-    else hipLaunchKernelGGL((router_logits_bf16_kernel<FA, FB, false>), grid, dim3(kNtThreads), 0, s, b);
+    if constexpr (parted_tile(FA, FB))
+        if (a.nparts > a.nsplit) {
+            hipLaunchKernelGGL((router_logits_bf16_kernel<FA, FB, true>), grid, dim3(kNtThreads), 0, s, b);
+            return hipGetLastError();
+        }
+    hipLaunchKernelGGL((router_logits_bf16_kernel<FA, FB, false>), grid, dim3(kNtThreads), 0, s, b);
     return hipGetLastError();
 }
 template <int FA>
@@ -323,6 +331,7 @@ RouterShape router_logits_shape(int64_t T, int32_t H, int32_t E, int32_t num_cu,
             const int64_t wgs = (T + 32 * tokens - 1) / (32 * tokens) * expert_blocks(E, experts);
             for (int nsplit = 1; nsplit <= s.nparts; nsplit *= 2) {
                 if (wgs * nsplit < num_cu / 4 || wgs * nsplit > 4 * num_cu) continue;
+                if (nsplit < s.nparts && !parted_tile(expert_fragments(E, experts), tokens)) continue;
                 const RouterShape c{tokens, experts, s.nparts, nsplit};
                 const double us = expected_us(c, T, H, E, num_cu);
                 if (us < best_us) { best_us = us; best = c; }
