@@ -10,6 +10,25 @@ from oracle import plan_oracle as po
 from paper_2603_28768_amd import binding, synth
 
 
+# Gates of more than 128 tokens with a workspace, on 256 CUs: (T, H, E) -> the tile (16-row fragments of
+# experts per wave, 32-token fragments), blocks of experts, parts the contraction is summed in, workgroups
+# that share them.  Ragged slabs, tokens and experts nearly everywhere.
+GATE_SHAPES = [
+    # all parts in one workgroup
+    ((1010, 456, 65), (2, 1), 2, 2, 1), ((600, 1000, 250), (2, 1), 4, 4, 1), ((2027, 472, 33), (2, 1), 1, 2, 1),
+    ((3000, 1032, 130), (2, 2), 3, 4, 1), ((2049, 520, 200), (2, 2), 4, 2, 1), ((2100, 584, 384), (2, 2), 6, 2, 1),
+    ((9200, 520, 129), (2, 4), 3, 2, 1), ((5000, 1096, 321), (4, 2), 3, 4, 1), ((8200, 464, 195), (4, 4), 2, 2, 1),
+    ((12300, 456, 130), (6, 2), 1, 2, 1), ((13000, 464, 261), (6, 4), 2, 2, 1),
+    # several workgroups with several parts each
+    ((643, 2000, 129), (2, 1), 3, 8, 4), ((1896, 2008, 44), (2, 1), 1, 8, 4), ((600, 2056, 380), (2, 2), 6, 8, 4),
+    ((2065, 2568, 129), (2, 4), 3, 8, 4), ((1384, 2056, 132), (4, 2), 2, 8, 4), ((2068, 2592, 194), (4, 4), 2, 8, 4),
+    ((1633, 2584, 260), (6, 2), 2, 8, 4), ((3299, 2568, 257), (6, 4), 2, 8, 4), ((2048, 7168, 256), (4, 2), 2, 8, 4),
+    # a workgroup per part
+    ((487, 456, 65), (2, 1), 2, 2, 2), ((521, 2056, 65), (2, 2), 2, 8, 8), ((1033, 3096, 129), (2, 4), 3, 8, 8),
+    ((680, 2056, 130), (4, 2), 2, 8, 8), ((132, 488, 66), (4, 4), 1, 2, 2), ((806, 2600, 257), (6, 2), 2, 8, 8),
+    ((131, 456, 261), (6, 4), 2, 2, 2), ((134, 456, 199), (8, 4), 1, 2, 2)]
+
+
 class Case:
     def __init__(self, cfg: synth.LayerConfig, plan=None, layer: int = 0, pop=None, w8: bool = False):
         """Without `plan`: a one-layer plan is made from this config's profiling batches.

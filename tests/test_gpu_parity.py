@@ -9,7 +9,7 @@ import pytest
 import oracle
 from paper_2603_28768_amd import binding, synth
 
-from cases import Case
+from cases import GATE_SHAPES, Case
 
 pytestmark = pytest.mark.gpu
 
@@ -208,14 +208,8 @@ def test_router_logits_parity(torch_cuda, dtype, T, H, E):
         assert np.array_equal(_np(binding.router_logits(xd, Wd, workspace)), _np(binding.router_logits(xd, Wd, workspace)))
 
 
-@pytest.mark.parametrize("T,H,E", [
-    (600, 1000, 250),                # tiles of 32 tokens x 64 experts, four parts after one another; ragged slab, last block of experts
-    (3000, 1032, 130),               # 64 x 64, three blocks of experts, a tile of tokens past a multiple of eight
-    (2049, 520, 200),                # two parts of five and four slabs, the last tile one token
-    (2100, 584, 384),                # the most experts that are split
-    (600, 2056, 380),                # two parts in each of four workgroups
-    (5000, 1096, 321)])              # 64 x 128, four parts of five slabs and fewer
-def test_router_logits_of_several_parts_in_a_workgroup(torch_cuda, T, H, E):
+@pytest.mark.parametrize("T,H,E", [shape for shape, *_ in GATE_SHAPES])      # (test_launch_shapes.py pins their tiles and splits)
+def test_router_logits_of_every_tile_and_split(torch_cuda, T, H, E):
     cfg = synth.scaled(synth.CONFIGS["qwen3"], T=T, H=H, E=E)
     x, W = synth.activations(cfg), synth.gate_weights(cfg)
     xd, Wd = binding.to_device(x, "bf16"), binding.to_device(W, "bf16")
@@ -231,6 +225,20 @@ def test_router_logits_of_several_parts_in_a_workgroup(torch_cuda, T, H, E):
     at = np.arange(E) * 7 % H
     U[np.arange(E), at] = 1.0
     assert np.array_equal(_np(binding.router_logits(xd, binding.to_device(U, "bf16"), ws)), x[:, at])
+
+
+def test_router_logits_of_activations_past_the_memory_side_cache(torch_cuda):
+    # one part, two blocks of experts that meet in one L2: a last eight of tiles that is not all there.  A gate of
+    # unit rows copies columns of x
+    torch = torch_cuda
+    T, H, E = 16500, 7168, 300
+    assert T * H * 2 > 220 << 20
+    x = torch.randn(T, H, device="cuda:0").bfloat16()
+    at = torch.arange(E, device="cuda:0") * 23 % H
+    U = torch.zeros(E, H, dtype=torch.bfloat16, device="cuda:0")
+    U[torch.arange(E, device="cuda:0"), at] = 1.0
+    assert binding.router_logits_workspace(x, U) is None
+    assert torch.equal(binding.router_logits(x, U), x[:, at].float())
 
 
 def test_router_logits_empty_and_rejected(torch_cuda):
@@ -312,6 +320,9 @@ def test_forward_with_its_own_gating_network(torch_cuda, dtype, T, H, I, E, k, D
     (128, 2056, 100, 5, False),      # two chunks of 64 scores, ragged slab
     (300, 2048, 384, 8, True),       # several trips of three parts
     (129, 1024, 300, 14, False),     # several trips, arg-max rounds
+    (1010, 456, 65, 4, False),       # two parts in one workgroup: nothing left to add
+    (643, 2000, 129, 8, True), (600, 2056, 380, 6, False),   # four copies of eight parts
+    (9200, 520, 129, 4, True),
     (60, 1024, 66, 1, True),
     # up to 32 tokens: by the dispatch launch itself
     (1, 1024, 64, 8, True), (32, 2048, 64, 20, False),       # up to 64 experts; picks in two places per lane

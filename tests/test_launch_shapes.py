@@ -140,6 +140,20 @@ def test_a_gate_of_few_tiles_starts_no_other_workgroups(launches_of):
         assert [l[1] for l in launches if "router_logits" in l[0]] == [groups], (T, E, H, launches)
 
 
+def test_every_gate_shape_takes_the_way_it_stands_for(launches_of):
+    from cases import GATE_SHAPES
+    from paper_2603_28768_amd import binding
+    found = launches_of(*[dict(dtype="bf16", T=T, H=H, I=64, E=E, k=4, D=32, gate=True) for (T, H, E), *_ in GATE_SHAPES])
+    for ((T, H, E), (fa, fb), blocks, nparts, nsplit), launches in zip(GATE_SHAPES, found):
+        (name, groups, _), = [l for l in launches if "router_" in l[0]]
+        assert "router_logits_bf16_kernelILi%dELi%dELb%dE" % (fa, fb, nsplit < nparts) in name, (T, H, E, name)
+        units = -(-T // (32 * fb)) * nsplit
+        assert groups in (units * blocks, -(-units // 8) * 8 * blocks), (T, H, E, groups)
+        n = ctypes.c_size_t()
+        assert binding.lib().craft_router_logits_workspace(1, T, H, E, ctypes.byref(n)) == 0 and n.value == nparts * T * E * 4
+    assert len({(tile, nsplit < nparts) for _, tile, _, nparts, nsplit in GATE_SHAPES}) == 15     # all there are
+
+
 def test_the_blocks_of_experts_of_a_gate_in_one_part_meet_only_past_the_cache(launches_of):
     # tiles of 64 tokens x 256 experts in one part: by the grid (tiles x blocks) while 220 MiB hold the
     # activations, padded to eight tiles beyond
