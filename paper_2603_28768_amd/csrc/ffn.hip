@@ -109,10 +109,9 @@ __device__ __forceinline__ int32_t bf16_tile(const FfnArgs &a, const Tile &t, un
 // stay at full width where every tile is in a single round, and where quarters are no gain: where the cold
 // tiles find room beside the last round of the busy ones (276 + 120 tiles of K = 4096 on 256 CUs: a quarter as
 // wide +8.8 us of a forward of 224), and where they are many and short, so that a small tile's fixed part
-// counts (640 + 592 of K = 512: +8.8 us of 230).  264 launches of 300 drawn batches: quarters everywhere cost
+// counts (640 + 592 of K = 512: +8.8 us of 230): narrow_cold_tiles.  264 launches of 300 drawn batches: quarters everywhere cost
 // more than 1 % of the forward in 40 of them, by this rule in 4 (the worst 228 + 36 of K = 1408, 4 %), which
 // keeps 96 % of what they save.
-constexpr int kQuarterLength = 1024;               // contraction from which on a whole round of cold tiles may be quartered
 template <bool GATEUP, bool FAR>
 __global__ __launch_bounds__(kNtThreads, 1) void ffn_bf16_kernel(FfnArgs a) {
     __shared__ __attribute__((aligned(16))) unsigned char ffn_smem[kNtLds];
@@ -129,9 +128,8 @@ __global__ __launch_bounds__(kNtThreads, 1) void ffn_bf16_kernel(FfnArgs a) {
     int64_t wide = (int64_t)tiles_before(mt_start, tt, small, a.nslots) * nt, total = wide;
     if (wide > (int64_t)gridDim.x) {
         const int32_t hot = ctrl_word(a, tt, small, CTRL_HOT_SLOTS);
-        const int64_t busy = (int64_t)tiles_before(mt_start, tt, small, hot) * nt, cold = wide - busy, over = busy % gridDim.x;
-        const int64_t room = over ? (int64_t)gridDim.x - over : 0;     // CUs without a tile of the last round of busy ones
-        if (cold > room && cold * kQuarterLength <= (int64_t)gridDim.x * K) {
+        const int64_t busy = (int64_t)tiles_before(mt_start, tt, small, hot) * nt, cold = wide - busy;
+        if (narrow_cold_tiles(busy, cold, gridDim.x, K)) {
             wide = busy;
             total = busy + 4 * cold;
         }

@@ -79,6 +79,14 @@ __host__ __device__ inline int32_t row_tiles(int32_t F, int32_t frags) {
 // most fragments of a row-tile
 __host__ __device__ inline int32_t tile_height(int32_t frags) { return frags > 0 ? frags : (9 - frags) / 10; }
 
+// Row-major bf16 FFN: whether the cold slots' tiles of a launch (`cold` at full width behind `busy` ones, contraction
+// K) are a quarter as wide; ffn.hip says why, the choice of streaming asks the same for the loads it expects.
+constexpr int kNarrowLength = 1024;                // contraction from which on a whole round of cold tiles may be
+static inline __host__ __device__ bool narrow_cold_tiles(int64_t busy, int64_t cold, int64_t cus, int64_t K) {
+    const int64_t over = busy % cus, room = over ? cus - over : 0;     // CUs without a tile of the last round of busy ones
+    return busy + cold > cus && cold > room && cold * kNarrowLength <= cus * K;
+}
+
 struct RouterArgs {
     int32_t dtype;
     const void *x;            // [T][H]

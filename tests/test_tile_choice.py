@@ -74,6 +74,7 @@ STREAM_CASES = [
     ("rowmajor", 4096, 1536, 8, 14, True),      # 84 / 95
     ("rowmajor", 4096, 1536, 16, 44, False),    # 207 / 143
     ("rowmajor", 2048, 768, 10, 28, True),      # 50 / 61
+    ("rowmajor", 2880, 1536, 22, 5, False),     # 152 / 130 (narrow tiles)
 ]
 
 
