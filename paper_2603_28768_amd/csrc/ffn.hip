@@ -299,7 +299,9 @@ hipError_t launch_ffn(const FfnArgs &a, hipStream_t s) {
     if (a.dtype == CRAFT_BF16) {
         const int bn = GATEUP ? 128 : 256;
         const int64_t nt = (N + bn - 1) / bn;
-        const int64_t bound = (a.max_rows / (kFragsBf16 * 32) + 4 * a.nslots) * nt; // most tiles any batch can have
+        // most tiles of full width that any batch can have: cold slots get narrow ones only in a launch of more than
+        // a round of wide tiles, whose grid is every CU
+        const int64_t bound = (a.max_rows / (kFragsBf16 * 32) + a.nslots) * nt;
         int64_t grid = std::min<int64_t>(bound, (int64_t)a.num_cu);
         grid = std::max<int64_t>(8, (grid + 7) / 8 * 8);
         // token rows are fetched at 32-bit offsets where x allows it
