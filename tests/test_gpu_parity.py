@@ -994,12 +994,16 @@ def test_rowmajor_cold_slots_of_more_than_a_round(torch_cuda, H, I, E, narrow):
     _check_rank(torch_cuda, case, 0, packed=False)
 
 
-@pytest.mark.parametrize("dtype,T,H,I,E", [("bf16", 1100, 200, 72, 24), ("bf16", 40, 200, 72, 6), ("f32", 300, 52, 36, 8)])
+@pytest.mark.parametrize("dtype,T,H,I,E", [
+    ("bf16", 1100, 200, 72, 24), ("bf16", 40, 200, 72, 6), ("f32", 300, 52, 36, 8),
+    ("bf16", 1100, 1608, 1032, 40)])                        # narrow tiles for the cold slots, in both GEMMs
 def test_rowmajor_weights_at_any_element(torch_cuda, dtype, T, H, I, E):
     # contiguous views that start one element into an allocation: the same bits as aligned weights
     torch = torch_cuda
     cfg = synth.scaled(synth.CONFIGS["qwen3"], dtype=dtype, T=T, H=H, I=I, E=E, k=2, D=1, replica_slots=0, zipf_s=1.2, profile_batches=2)
     case = Case(cfg)
+    narrow = (_narrow_tiles(case.slot_cnt, H, I, True), _narrow_tiles(case.slot_cnt, I, H, False))
+    assert dtype == "f32" or narrow == (E == 40, E == 40)
     fwd, x, logits = case.gpu_rank(0)
     want = _np(fwd(x, logits).clone())
 
@@ -1125,6 +1129,57 @@ def test_quantize_and_pack_in_one_pass_is_the_two_steps(torch_cuda, H, I, scale)
         assert np.array_equal(codes.cpu().numpy()[finite], want_c[finite])
     assert torch.equal(pgu, want_gu)
     assert torch.equal(pdn, want_dn)
+
+
+@pytest.mark.parametrize("rows,tile_rows", [
+    ([16, 40, 3, 5, 1, 30], 0),                                         # streamed
+    *[([700, 300, 41, 20, 150, 260, 33, 9], r) for r in (128, 160, 192, 224, 256)]])        # tiles of every height, riders where they can be
+def test_every_e4m3_code_through_the_gemms(torch_cuda, rows, tile_rows):
+    # tokens and gate are chosen so that an output is 64 times one code: of the up matrix (experts 0, 2, 4 ..) or of the
+    # down matrix.  The fifth and sixth also hold a NaN, which reaches everything that is multiplied by its row
+    torch = torch_cuda
+    H = I = 512
+    E, T, dev = len(rows), sum(rows), "cuda:0"
+    finite = torch.tensor([c for c in range(256) if c & 0x7F != 0x7F], dtype=torch.uint8, device=dev)
+    value = finite.view(torch.float8_e4m3fn).float()
+    n = torch.arange(512, device=dev)
+    codes = finite[(n[:, None] + n[None, :]) % 254].contiguous()
+    one = torch.zeros((512, 512), dtype=torch.uint8, device=dev)
+    one[n, n] = 0x38                                                    # 1.0
+    gate = torch.full((512, 512), 0x38, dtype=torch.uint8, device=dev)
+    ones, g64 = torch.ones(512, device=dev), torch.full((512,), 64.0, device=dev)
+    plan = binding.Plan(np.array(rows, dtype=np.int64)[None, None], 1, 0)
+    lib, ptr, keep = binding.lib(), binding._dev, []
+
+    def expert(e):
+        up, down = (codes.clone(), one.clone()) if e % 2 == 0 else (one.clone(), codes.clone())
+        if e == 4:
+            up[5, 9] = 0x7F
+        if e == 5:
+            down[7, 11] = 0xFF
+        m = torch.zeros((512, 512), dtype=torch.bfloat16, device=dev)
+        gu, dn = binding.pack_weights_e4m3(m, m, m)                     # (buffers of the right size)
+        assert lib.craft_pack_weights_e4m3(H, I, ptr(gate), ptr(up), ptr(down), ptr(g64), ptr(ones), ptr(ones), ptr(gu), ptr(dn),
+                                           binding._stream_ptr()) == 0
+        keep.append((up, down))
+        return m, (gu, dn)
+    ex = [expert(int(e)) for e in plan.layer(0)["slot_expert"]]
+    fwd = binding.RankForward(plan, 0, 0, "bf16", T, H, I, 1, *[[m for m, _ in ex]] * 3, packed=[p for _, p in ex],
+                              weight_format=binding.CRAFT_W_E4M3)
+    fwd.args.tile_rows_gateup = fwd.args.tile_rows_down = tile_rows
+    fwd.args.riders_gateup = fwd.args.riders_down = 1 if tile_rows else 0
+    assert fwd.tile_choice()[:2] == ((tile_rows, tile_rows) if tile_rows else (64, 64))
+    expert_of = torch.from_numpy(np.random.default_rng(1).permutation(np.repeat(np.arange(E), rows))).to(dev)
+    logits = torch.where(n[None, :E] == expert_of[:, None], 5.0, -5.0).contiguous()
+    h = torch.arange(T, device=dev) * 7 % H
+    x = torch.zeros((T, H), dtype=torch.bfloat16, device=dev)
+    x[torch.arange(T, device=dev), h] = 1.0
+    out = fwd(x, logits).float()
+    want = 64.0 * value[(n[None, :] + h[:, None]) % 254]
+    want[expert_of == 4] = float("nan")
+    want[expert_of == 5, 7] = float("nan")
+    assert torch.equal(torch.isnan(out), torch.isnan(want))
+    assert torch.equal(torch.nan_to_num(out, nan=0.0), torch.nan_to_num(want, nan=0.0))
 
 
 @pytest.mark.parametrize("e4m3,I", [(False, (1 << 24) + 16), (True, (1 << 25) + 16)])
