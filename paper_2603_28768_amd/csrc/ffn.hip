@@ -18,10 +18,10 @@
 // the weight rows of a tile are 128 gate and the 128 matching up rows, 16 of one followed by 16 of
 // the other, so that gate and up of one output meet in the same lane and element of two
 // accumulators: SwiGLU is applied in registers.  The gate/up GEMM reads its rows straight from x
-// through the dispatch permutation (no staged copy).  A slab of a tall tile, 48 KiB, takes 1.4 us, three
-// times its matrix instructions; which of the latency of loads that miss the L2 and the issue of reads
-// and requests holds it there has not been taken apart (a CU reads three times as fast out of its L2
-// in a plain loop).  Taller tiles move less but come out in fewer rounds.  1777 tokens on 17 slots,
+// through the dispatch permutation (no staged copy).  A slab of a tall tile, 48 KiB, takes 0.87 us in a
+// launch of one slot and one round (2304 rows, I = 1536: gate/up 105.3 us at H = 7168, 23.2 at 1024), twice its
+// matrix instructions; which of the latency of loads that miss the L2 and the issue of reads and requests holds
+// it there has not been taken apart (a CU reads three times as fast out of its L2 in a plain loop).  Taller tiles move less but come out in fewer rounds.  1777 tokens on 17 slots,
 // H = 4096, I = 1536: gate/up 190 -> 117 us, down 84 -> 63 (before: 128 x 128 tiles through registers, one
 // slab ahead).  A cold slot's tile is bound by what one CU gets out of HBM, about 42 GB/s whatever it has in
 // flight: 256 weight rows of 4096 elements take it 50 us.  Where a launch would end with them the cold

@@ -146,8 +146,8 @@ static __device__ __forceinline__ uint32_t bf16_pair(float lo, float hi) {
 // A packed stream holds a multiple of kPackGroups column groups (whole full-width tiles).
 constexpr int kPackGroups = 8;
 typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
-// A weight fragment as it sits in registers: 8 bf16 values, or 8 E4M3 codes that are widened
-// (exactly) right in front of the MFMAs that use them.
+// A weight fragment as it sits in registers: 8 bf16 values, or 8 E4M3 codes that are widened (exactly): by the
+// streaming kernel in front of the MFMA that uses them, by the packed tiles once per step, behind other MFMAs.
 template <bool W8> struct WFrag { typedef bf16x8_t type; };
 template <> struct WFrag<true> { typedef u32x2_t type; };
 
