@@ -291,12 +291,12 @@ def copy_calibration(args):
 # (x2.0 and x1.0).  A figure belongs to the kernel as it was when the counters were taken: it
 # is reported only while the sources that shape that kernel still hash to the recorded value.
 TRAFFIC_SOURCES = ["ffn_packed.hip", "ffn_common.h", "kernels.h", "dispatch.hip", "route_block.h", "forward.cpp"]
-_SHA = "9d68887d203b9d49ee399374db03cb06f286e883ed36a759c9e38cd59fa2ee04"
+_SHA = "7bbd3bae238f649ab3609ae528dc69169b25930a511b0dc5a41aa92cc49de438"
 TRAFFIC = {
-    "qwen3": dict(fetch_kib=285405.2, write_kib=13510.0, fetch_scale=2.0, write_scale=1.0, mfma_util=0.419, mfma_busy_of_peak_clock=0.381, l2_to_cu_mb=1296.5, l2_hit=0.552, sources_sha256=_SHA),
-    "dsv3": dict(fetch_kib=194113.6, write_kib=10241.0, fetch_scale=2.0, write_scale=1.0, mfma_util=0.54, mfma_busy_of_peak_clock=0.464, l2_to_cu_mb=1545.1, l2_hit=0.741, sources_sha256=_SHA),
-    "kimi": dict(fetch_kib=171306.1, write_kib=10827.0, fetch_scale=2.0, write_scale=1.0, mfma_util=0.531, mfma_busy_of_peak_clock=0.472, l2_to_cu_mb=1413.5, l2_hit=0.749, sources_sha256=_SHA),
-    "stack": dict(fetch_kib=1009433.5, write_kib=75816.1, fetch_scale=2.0, write_scale=1.0, mfma_util=0.722, mfma_busy_of_peak_clock=0.559, l2_to_cu_mb=8925.2, l2_hit=0.762, sources_sha256=_SHA),
+    "qwen3": dict(fetch_kib=285812.0, write_kib=13510.0, fetch_scale=2.0, write_scale=1.0, mfma_util=0.421, mfma_busy_of_peak_clock=0.385, l2_to_cu_mb=1296.5, l2_hit=0.552, sources_sha256=_SHA),
+    "dsv3": dict(fetch_kib=195643.9, write_kib=10241.0, fetch_scale=2.0, write_scale=1.0, mfma_util=0.559, mfma_busy_of_peak_clock=0.483, l2_to_cu_mb=1545.1, l2_hit=0.74, sources_sha256=_SHA),
+    "kimi": dict(fetch_kib=172092.2, write_kib=10827.0, fetch_scale=2.0, write_scale=1.0, mfma_util=0.526, mfma_busy_of_peak_clock=0.469, l2_to_cu_mb=1413.5, l2_hit=0.749, sources_sha256=_SHA),
+    "stack": dict(fetch_kib=1212773.4, write_kib=75816.2, fetch_scale=2.0, write_scale=1.0, mfma_util=0.717, mfma_busy_of_peak_clock=0.569, l2_to_cu_mb=8925.2, l2_hit=0.732, sources_sha256=_SHA),
 }
 
 
